@@ -90,8 +90,9 @@ typedef struct {
  * it is distributed as the renormalised distribution on the kept set.  regret, logprob, entropy
  * and the state update are as without a filter (logprob and entropy refer to the unfiltered
  * distribution; the regret of a kept token does not depend on the renormalisation).  At most
- * one of the two may be active (ESPO_EINVAL otherwise).  A filtered step reads the row more than
- * once (the later passes mostly from the caches) and runs as its own kernel instantiation.
+ * one of the two may be active (ESPO_EINVAL otherwise).  A filtered step runs a kernel of its own, which
+ * reads the row once like the plain one; only a row whose kept set has thousands of tokens, or whose
+ * largest logits tie by the hundred, is read again.
  */
 
 /*
@@ -190,9 +191,8 @@ typedef enum {
  *               a leaner instantiation of the kernel runs (about 8 % faster at B = 512).
  *               logprob and entropy are fp32 sums whose order of summation follows the
  *               launch layout (how many wavefronts stream a row), which the library picks
- *               from B and from whether the draw is filtered: the same row can differ in
- *               the last bits between a batch below 256 rows and a larger one, and
- *               between a filtered and a plain draw.  Tokens, regret, z, alive and
+ *               from B: the same row can differ in
+ *               the last bits between a batch below 256 rows and a larger one.  Tokens, regret, z, alive and
  *               stop_step do not depend on the layout.
  *   entropy     device, [B] fp32 out, may be NULL (then nothing is spent on it: the
  *               pass with the entropy does two more vector operations per logit).

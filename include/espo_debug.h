@@ -19,8 +19,8 @@ extern "C" {
  *                       margin.  A scale >= 1 multiplies that margin (1 = what espo_step uses; a
  *                       huge value sends every row through the double-precision search).  The
  *                       sampled token does not depend on it.  ESPO_EINVAL below 1 or for NaN.
- *   waves               wavefronts per workgroup: 4, 8 or 16, or 0 for the library's choice (16; 8 for a
- *                       filtered draw).
+ *   waves               wavefronts per workgroup: 4, 8 or 16, or 0 for the library's choice (16; 8 from
+ *                       256 rows on).
  *   chunks              workgroups a row is split over, or 0 for the library's choice (1).  With
  *                       more than one, every workgroup streams a run of 512-index tiles of its row,
  *                       finds the exact winner of that run and leaves it in the workspace with the

@@ -4,13 +4,16 @@ from __future__ import annotations
 import os
 import subprocess
 import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_HERE, "csrc")
 LIB = os.path.join(_HERE, "libespo.so")
-SOURCES = ["espo_api.hip", "espo_step.hip", "espo_advantages.hip", "espo_batch_stats.hip", "espo_whiten.hip"]
+# translation units: source and its own flags (the step kernels take most of the time, so each logit type is one)
+SOURCES = [("espo_step.hip", []), ("espo_step.hip", ["-DESPO_STEP_F32"]), ("espo_advantages.hip", []), ("espo_whiten.hip", []),
+           ("espo_batch_stats.hip", []), ("espo_api.hip", [])]
 # packed-fp32 VALU forms are switched off for every device translation unit
-HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
                "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
                # device code never produces or consumes NaN; this drops the re-quieting of every fmax operand
                "-Xarch_device", "-fno-honor-nans", "-Xarch_device", "-Wno-nan-infinity-disabled"]
@@ -19,13 +22,21 @@ HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
 def build_library(verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     with tempfile.TemporaryDirectory() as tmp:
+        def run(cmd):
+            return subprocess.run(cmd, cwd=tmp, capture_output=True, text=True)
+
+        objs = [os.path.join(tmp, f"{i}.o") for i in range(len(SOURCES))]
+        cmds = [[hipcc, *HIPCC_FLAGS, *flags, "-c", os.path.join(CSRC, src), "-o", obj] for (src, flags), obj in zip(SOURCES, objs)]
+        with ThreadPoolExecutor(len(cmds)) as pool:
+            results = list(pool.map(run, cmds))
         out = os.path.join(tmp, "libespo.so")
-        cmd = [hipcc, *HIPCC_FLAGS, "-o", out, *[os.path.join(CSRC, s) for s in SOURCES]]
-        res = subprocess.run(cmd, cwd=tmp, capture_output=True, text=True)
-        if verbose or res.returncode != 0:
-            # the host pass does not know the device-only feature flag; that notice is noise
-            print("\n".join(l for l in (res.stdout + res.stderr).splitlines() if "packed-fp32-ops" not in l))
-        if res.returncode != 0:
+        if all(r.returncode == 0 for r in results):
+            results.append(run([hipcc, "--offload-arch=gfx950", "-shared", "-o", out, *objs]))
+        for res in results:
+            if verbose or res.returncode != 0:
+                # the host pass does not know the device-only feature flag; that notice is noise
+                print("\n".join(l for l in (res.stdout + res.stderr).splitlines() if "packed-fp32-ops" not in l))
+        if any(r.returncode != 0 for r in results):
             raise RuntimeError("hipcc failed building libespo.so")
         os.replace(out, LIB)
     return LIB

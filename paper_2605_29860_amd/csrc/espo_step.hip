@@ -22,14 +22,15 @@
 // Pruning only ever discards indices that provably cannot attain the maximum, so the
 // token equals the exhaustive double-precision argmax with lowest-index tie-break.
 //
-// Two optional features are template parameters, so that the plain step pays nothing for them:
-// the entropy of the sampling distribution (one more accumulator in phase 1) and filtered
-// draws (top-p / top-k: a table of block maxima in phase 1, and after phase 2 the search for
-// the edge of the kept set, see the comment at `if constexpr (Filter)`).
+// The entropy of the sampling distribution (one more accumulator in phase 1) is a template
+// parameter, so that the plain step pays nothing for it.  Filtered draws (top-p / top-k) have a
+// kernel of their own, which streams the row the same way but collects its largest logits
+// instead of bounding its blocks (see "filtered draws" below).
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "../../include/espo.h"
@@ -320,6 +321,30 @@ __device__ __forceinline__ ChainOut scalar_chain(const StepArgs& a, int row, flo
   return ChainOut{g, zn, a.stop_enabled && stop};
 }
 
+// What one lane does at the end of a row: the scalar chain on the sampled logit, then the row's outputs.
+template <int DT, bool Entropy, bool Sum>
+__device__ __forceinline__ void finish_row(const StepArgs& a, int row, const void* rowp, int32_t tok, float x_a, float m,
+                                           float S, float Sw, float z_prev, float value) {
+  if (tok < 0) { tok = 0; x_a = elem_at<DT>(rowp, 0); }  // row of -inf only: unspecified, stay in range
+  const ChainOut c = scalar_chain(a, row, m, x_a, z_prev, value);
+  a.tokens[row] = tok;
+  a.regret[row] = c.g;
+  a.z[row] = c.z;
+  if (Sum && a.logprob) a.logprob[row] = -c.g - flog(S);
+  if constexpr (Entropy)  // H = ln S - E_pi[y - y_max] >= 0; rounding can leave S a few ulp below 1
+    a.entropy[row] = fmaxf(flog(S) - kLn2 * Sw / S, 0.0f);
+  if (a.eos_id >= 0 && tok == a.eos_id) {
+    a.alive[row] = 0;  // natural end
+  } else if (c.stop) {
+    if (a.simulate) {  // bookkeeping only: the first stop step is recorded, decoding goes on
+      if (a.stop_step[row] < 0) a.stop_step[row] = a.step;
+    } else {
+      a.alive[row] = 0;  // absorbing failure (Eq. failure_reward): the trajectory ends here
+      a.stop_step[row] = a.step;
+    }
+  }
+}
+
 // ---------------------------------------------------------------- shared memory
 // Blocks are named by their index q in the row everywhere (survivor lists, top_q, visq); the
 // per-block tables only cover the workgroup's chunk and are reached through the accessors, which
@@ -389,7 +414,7 @@ __device__ __forceinline__ StepShared carve(unsigned char* base, int nslots, int
 }
 
 // Dynamic LDS of a workgroup of `waves` wavefronts whose chunk has `ntiles` tiles (what carve() lays out).
-size_t step_lds_bytes(int dt, int ntiles, bool filter, int waves) {
+[[maybe_unused]] size_t step_lds_bytes(int dt, int ntiles, bool filter, int waves) {
   const size_t esz = dt == ESPO_BF16 ? 2 : 4;
   const size_t nslots = (size_t)ntiles * kGroups, slots = (size_t)waves * kGroups;
   return 2 * (size_t)waves * 8 + slots * kDrawBlock * esz + slots * 4 + 14 * (size_t)waves * 4 + 16 + 2 * kCandCap * 4 +
@@ -523,17 +548,17 @@ struct Best {
 
 __device__ __forceinline__ Best no_best() { return Best{kNegInf, 0.0f, 0.0f, kNegInf, -1}; }
 
-// Scores index v (logit x) in fp32 and offers it to the lane's state.  An index is scored at
-// most once in this search, so a lane never meets the same index twice.
-__device__ __forceinline__ void score_element(const StepArgs& a, const StepShared& sh, int row, int32_t v, float x,
-                                              bool valid, Best& st) {
+// Scores index v (logit x) in fp32 and offers it to the lane's state, with `wb` the random word of its
+// block.  An index is scored at most once in a search, so a lane never meets the same index twice.
+// `v_named` is what the state calls the index (the index itself, or the index with a flag on top).
+__device__ __forceinline__ void score_drawn(const StepArgs& a, int row, int32_t v, int32_t v_named, float x, uint32_t wb,
+                                            bool valid, Best& st) {
   const int32_t q = v >> 6;
   const int32_t first = q * kDrawBlock;
   const int32_t n = a.V - first < kDrawBlock ? a.V - first : kDrawBlock;
   // the index's own word depends on nothing else here: its ten rounds overlap the loads
   const Philox4 p = philox4x32_10((uint32_t)(v >> 2), (uint32_t)a.step, (uint32_t)row, kTagElem, a.key0, a.key1);
   const uint32_t w = (v & 3) == 0 ? p.w[0] : (v & 3) == 1 ? p.w[1] : (v & 3) == 2 ? p.w[2] : p.w[3];
-  const uint32_t wb = sh.word(q);
   const float nlb = neg_log_uniform<float>(wb);
   const float M = flog((float)n) - flog(nlb);                 // M_q = ln n - ln(-ln u)
   const float emM = nlb * __builtin_amdgcn_rcpf((float)n);    // exp(-M_q) = (-ln u) / n
@@ -546,14 +571,19 @@ __device__ __forceinline__ void score_element(const StepArgs& a, const StepShare
   const float y = x * a.inv_tau;
   const float sc = y + G;
   const float e = score_margin(a, y);
-  if (valid && x > sh.floor) {  // masked (-inf) and filtered entries never win
+  if (valid) {
     if (sc > st.s) {
       st.hi2 = fmaxf(st.hi2, st.s + st.e);
-      st.s = sc; st.e = e; st.x = x; st.v = v;
+      st.s = sc; st.e = e; st.x = x; st.v = v_named;
     } else {
       st.hi2 = fmaxf(st.hi2, sc + e);
     }
   }
+}
+
+__device__ __forceinline__ void score_element(const StepArgs& a, const StepShared& sh, int row, int32_t v, float x,
+                                              bool valid, Best& st) {
+  score_drawn(a, row, v, v, x, sh.word(v >> 6), valid && x > sh.floor, st);  // masked (-inf) and filtered entries never win
 }
 
 // This lane's element of block q: from LDS if a lane group kept the block, else from the row.
@@ -792,13 +822,9 @@ __device__ __forceinline__ bool row_is_done(const uint8_t* alive, int row) {
 }
 
 template <int DT, bool Entropy, bool Filter, bool Sum, int W>
-// Registers: 64 per lane for 16 waves (two workgroups on a compute unit); workgroups of 8 waves get up
-// to 80 (three of them fit, in registers and in LDS) and use 75 without spilling; a filtered draw gets 128.
-__global__ __launch_bounds__(W * kWave, Filter ? 4 : W == 8 ? 6 : 8) void espo_step_kernel(StepArgs a) {
+__device__ __forceinline__ void step_row(const StepArgs& a, unsigned char* smem_raw) {
   static_assert(Sum || (!Entropy && !Filter), "entropy and filtered draws need the softmax sum");
-  static_assert(!Filter || W == 8, "a filtered draw looks at the whole row: one workgroup of 8 waves per row");
   constexpr int kStepWaves = W, kStepThreads = W * kWave, kSlots = W * kGroups;
-  extern __shared__ __align__(16) unsigned char smem_raw[];
   const int tid = threadIdx.x;
   // workgroup row * nch + c owns chunk c of the row: tiles [tile0, tile1)
   const unsigned unit = blockIdx.x;
@@ -879,7 +905,6 @@ __global__ __launch_bounds__(W * kWave, Filter ? 4 : W == 8 ? 6 : 8) void espo_s
   float sum = 0.0f;
   float sumw = 0.0f;         // entropy output: sum_v 2^t_v t_v with t_v = x_v k2 + nrk (see below)
   float mx = kNegInf;        // largest logit this lane group has seen
-  float mx_odd = kNegInf;    // filtered draws keep it apart for the odd tiles: twice as many values to choose a floor from
   float top_ub = kNegInf;    // largest block bound this lane group has seen, and its block
   int top_q = -1;
   char* const my_raw = (char*)sh.top_raw + ((size_t)(wave * kGroups + grp) * kDrawBlock + (lane & 7) * 8) * elem_bytes<DT>();
@@ -950,8 +975,7 @@ __global__ __launch_bounds__(W * kWave, Filter ? 4 : W == 8 ? 6 : 8) void espo_s
     const float ub = fmaf(bm, a.inv_tau, mu[0]);
     mu[1] = ub;  // the 8 lanes of the group store the same value
     if constexpr (Filter) bmx_lane[(size_t)i * (kStepWaves * kGroups)] = bm;
-    if (Filter && (i & 1)) mx_odd = fmaxf(mx_odd, bm);
-    else mx = fmaxf(mx, bm);
+    mx = fmaxf(mx, bm);
     if (ub > top_ub) {  // keep the data of the block with the group's largest bound
       top_ub = ub;
       top_q = t * kGroups + grp;
@@ -978,8 +1002,6 @@ __global__ __launch_bounds__(W * kWave, Filter ? 4 : W == 8 ? 6 : 8) void espo_s
       if (i0 + d < my_tiles) iteration(std::false_type{}, d, i0 + d);  // wave-uniform
   }
   // The wave's largest logit, and the block with its largest bound (lowest block among equals).
-  const float mx_even = mx;
-  if constexpr (Filter) mx = fmaxf(mx, mx_odd);
   const float mw = wave_max(mx);
   const float ubw = wave_max(top_ub);
   const int q_own = (int)wave_min_u32(top_q >= 0 && top_ub == ubw ? (uint32_t)top_q : 0xffffffffu);  // -1 if none
@@ -1036,11 +1058,6 @@ __global__ __launch_bounds__(W * kWave, Filter ? 4 : W == 8 ? 6 : 8) void espo_s
       e_a = fmaf(fabsf(s_a), 1.2e-7f, 1e-30f);
     }
   };
-  // the largest float below x (x finite or +inf): a floor that lets x itself through
-  const auto next_below = [](float x) {
-    const int32_t bits = __builtin_bit_cast(int32_t, x);
-    return x == 0.0f ? -1.401298464e-45f : __builtin_bit_cast(float, bits + (x > 0.0f ? -1 : 1));
-  };
   if constexpr (!Filter) {
     search(sh, softmax_sum);
   } else {
@@ -1052,86 +1069,44 @@ __global__ __launch_bounds__(W * kWave, Filter ? 4 : W == 8 ? 6 : 8) void espo_s
   }
 
   if constexpr (Filter) {
-    // Filtered draw (top-p as in the evaluation set-up of Section 5, or top-k).  The kept set is
-    // {v : the mass (the number) of strictly larger logits is below p (k)}, an upper set in the
-    // logit, so the filtered draw is the argmax of y + G over it.  What is needed is the mass
-    // (number) of the logits above a given floor, and those logits themselves when they are few.
-    // A table of the blocks' largest logits, filled while streaming, names the blocks that hold
-    // any; up to two thirds of the row's blocks are read again block by block, more of them by one
-    // more pass over the row.  First a floor that leaves about 64 blocks above it is tried: on rows
-    // like a language model's the kept set lies above it.  If it does not (a flat row, some hundred
-    // kept logits), a floor that leaves several hundred blocks is tried.  The smallest kept logit is
-    // then read off the collected logits (the smallest whose strictly larger ones hold less than p,
-    // number fewer than k) and one search above that edge gives the token; the unfiltered winner is
-    // not needed then and is not searched for.  Sums within 1e-5 of p times the softmax sum are not
-    // trusted in fp32: the search then runs above the smallest logit that may be kept, and its winner
-    // stands if it is kept for sure.  Otherwise (still flatter rows, or a winner in doubt) the winner
-    // is tested by measuring the mass above it, in double over the whole row and in the oracle's
-    // arithmetic where fp32 cannot tell, and while it is not kept the search is repeated above it;
-    // that floor rises strictly, so the loop ends.
-    // A workgroup of 8 waves with 128 registers per lane runs this instantiation, two of them on a
-    // compute unit: with 64 registers the stages below spill, and every reload is a trip to a memory
-    // system whose queues are full of the other rows' streaming (measured: 53 us per launch with 16
-    // waves and 64 registers, 46 us this way, B = 512, V = 152064, top-p 0.7 at temperature 0.6).
+    // The general search of a filtered draw, for the rows that filtered_row hands on (ties that fill its lists, a
+    // kept set of thousands of logits, a winner whose membership fp32 cannot tell).  The kept set is
+    // {v : the mass (the number) of strictly larger logits is below p (k)}, an upper set in the logit, so the
+    // winner of the unfiltered search is the token if it is kept, and otherwise the search is repeated above it:
+    // whether it is kept follows from the mass (number) of the logits above its own.  The floor rises strictly, so
+    // the loop ends, after 1/p rounds on average.  A table of the blocks' largest logits, filled while streaming,
+    // names the blocks that hold any; up to two thirds of the row's blocks are read again block by block, more of
+    // them by one more pass over the row.  Sums within 1e-5 of p times the softmax sum are formed again in double
+    // over the whole row, in the oracle's arithmetic.
     const auto nothing = [] {};
     const bool by_count = a.top_k > 0;
     const float nrk_row = -m * a.k2;
     const float total = wave_sum(lane < kStepWaves ? sh.sum[lane] : 0.0f);  // S, as the last step forms it
     const float want = a.top_p * total;
-    // The collected logits use both candidate areas as one array; their 2^t are formed again where needed.
-    constexpr int kKeptCap = 2 * kCandCap;
-    float* const kept_x = (float*)sh.cand_v;
-    static_assert(kCandCap % 4 == 0, "cand_x follows cand_v without a gap");
     float mass = 0.0f, count = 0.0f;
-    int ncand = 0;
 
-    // mass and number of the logits above floor_x; the logits themselves in kept_x if they fit
-    auto measure = [&](float floor_x) {
+    auto measure = [&](float floor_x) {  // mass and number of the logits above floor_x
       __syncthreads();  // whatever used the scratch before is over in every wave
-      if (tid == 0) {
-        *sh.nsurv = 0;
-        *sh.ncand = 0;
-      }
+      if (tid == 0) *sh.nsurv = 0;
       __syncthreads();
       for (int b = tid; b < nslots; b += kStepThreads)  // blocks that hold a logit above the floor
         if (sh.bmx[b] > floor_x) sh.surv(atomicAdd(sh.nsurv, 1)) = b;
       __syncthreads();
       const int nabove = *sh.nsurv;
       float acc_m = 0.0f, acc_n = 0.0f;
-      constexpr int kVisit = 8, kLoads = 4, kGroupRead = 1536;  // beyond that many blocks (two thirds of this row's) the whole row is streamed
-      if (nabove <= 16 * kStepWaves) {
-        // The usual case: one block per wave visit, one index per lane, eight loads in flight.  Most of
-        // these blocks are their lane group's best, which phase 1 kept in LDS: no trip to memory, whose
-        // queues are full of the other rows' streaming.
-#pragma unroll 1
-        for (int base = wave; base < nabove; base += kVisit * kStepWaves) {
-          float xs[kVisit];
-          int32_t ns[kVisit];
+      auto add = [&](const Raw<DT>& raw, int32_t v0, bool valid) {
+        float x[8];
+        unpack<DT>(raw, x);
 #pragma unroll
-          for (int u = 0; u < kVisit; ++u) {
-            const int k = base + u * kStepWaves;
-            xs[u] = kNegInf;
-            ns[u] = 0;
-            if (k < nabove) {
-              const int q = __builtin_amdgcn_readfirstlane(sh.surv(k));
-              ns[u] = a.V - q * kDrawBlock < kDrawBlock ? a.V - q * kDrawBlock : kDrawBlock;
-              xs[u] = block_elem<DT, W>(a, sh, rowp, q);
-            }
-          }
-#pragma unroll
-          for (int u = 0; u < kVisit; ++u) {
-            if (lane < ns[u] && xs[u] > floor_x) {
-              acc_m += __builtin_amdgcn_exp2f(fmaf(xs[u], a.k2, nrk_row));
-              acc_n += 1.0f;  // counts stay exact in fp32: V < 2^24
-              const int c = atomicAdd(sh.ncand, 1);
-              if (c < kKeptCap) kept_x[c] = xs[u];
-            }
-          }
+        for (int u = 0; u < 8; ++u) {
+          const bool above = valid && v0 + u < a.V && x[u] > floor_x;
+          acc_m += above ? __builtin_amdgcn_exp2f(fmaf(x[u], a.k2, nrk_row)) : 0.0f;
+          acc_n += above ? 1.0f : 0.0f;  // counts stay exact in fp32: V < 2^24
         }
-      } else if (nabove <= kGroupRead) {
-        // The listed blocks only, laid out as in phase 1: a lane group of 8 lanes per block, 16 bytes
-        // per lane, so one load of a wave covers 8 blocks and the workgroup 256 per trip to memory (eight
-        // loads in flight instead of four: 8 us slower on every row, with spills).
+      };
+      constexpr int kLoads = 4, kDeep = 6;
+      if (3 * nabove <= 2 * nslots) {
+        // the listed blocks only, laid out as in phase 1: a lane group of 8 lanes per block, 16 bytes per lane
         const uint32_t sub = (uint32_t)(lane & 7) * 8u;
 #pragma unroll 1
         for (int base = wave * kGroups; base < nabove; base += kLoads * kStepWaves * kGroups) {
@@ -1141,43 +1116,14 @@ __global__ __launch_bounds__(W * kWave, Filter ? 4 : W == 8 ? 6 : 8) void espo_s
           for (int j = 0; j < kLoads; ++j) {
             const int k = base + j * kStepWaves * kGroups + grp;
             qs[j] = k < nabove ? sh.surv(k) : -1;
-            // a group without a block reads block 0 and drops it; a ragged last block is masked below
+            // a group without a block reads block 0 and drops it; a ragged last block is masked
             const uint32_t e0 = (uint32_t)(qs[j] < 0 ? 0 : qs[j]) * kDrawBlock + sub;
             raw[j] = load_raw<DT>(rowp, e0 < last_group ? e0 : last_group, (uint32_t)a.V);
           }
-          uint64_t mine = 0;  // which of this lane's elements are above the floor
 #pragma unroll
-          for (int j = 0; j < kLoads; ++j) {
-            float x[8];
-            unpack<DT>(raw[j], x);
-            const int32_t v0 = qs[j] * kDrawBlock + (int32_t)sub;
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-              const bool above = qs[j] >= 0 && v0 + u < a.V && x[u] > floor_x;
-              const float e = __builtin_amdgcn_exp2f(fmaf(x[u], a.k2, nrk_row));
-              acc_m += above ? e : 0.0f;
-              acc_n += above ? 1.0f : 0.0f;  // counts stay exact in fp32: V < 2^24
-              mine |= above ? 1ull << (j * 8 + u) : 0ull;
-            }
-          }
-          // one counter update per lane that has any; its logits take consecutive entries
-          int c = mine != 0 ? atomicAdd(sh.ncand, (int)__builtin_popcountll(mine)) : 0;
-#pragma unroll
-          for (int j = 0; j < kLoads; ++j) {
-            if (((mine >> (j * 8)) & 0xffull) == 0) continue;
-            float x[8];
-            unpack<DT>(raw[j], x);
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-              if ((mine >> (j * 8 + u)) & 1ull) {
-                if (c < kKeptCap) kept_x[c] = x[u];
-                ++c;
-              }
-            }
-          }
+          for (int j = 0; j < kLoads; ++j) add(raw[j], qs[j] * kDrawBlock + (int32_t)sub, qs[j] >= 0);
         }
-      } else {  // many blocks: stream the row once more, six loads in flight per lane
-        constexpr int kDeep = 6;
+      } else {
 #pragma unroll 1
         for (int i0 = 0; i0 < my_tiles; i0 += kDeep) {
           Raw<DT> raw[kDeep];
@@ -1185,29 +1131,8 @@ __global__ __launch_bounds__(W * kWave, Filter ? 4 : W == 8 ? 6 : 8) void espo_s
           for (int d = 0; d < kDeep; ++d)
             if (i0 + d < my_tiles) raw[d] = load_tile((i0 + d) * kStepWaves + wave);
 #pragma unroll
-          for (int d = 0; d < kDeep; ++d) {
-            if (i0 + d < my_tiles) {
-              float x[8];
-              unpack<DT>(raw[d], x);
-              const int32_t e0 = ((i0 + d) * kStepWaves + wave) * kTile + (int32_t)lane_off;
-              const bool room = *sh.ncand <= kKeptCap;  // once the buffer has overflowed nothing more is kept
-#pragma unroll
-              for (int u = 0; u < 8; ++u) {
-                const bool above = e0 + u < a.V && x[u] > floor_x;
-                const float e = __builtin_amdgcn_exp2f(fmaf(x[u], a.k2, nrk_row));
-                acc_m += above ? e : 0.0f;
-                acc_n += above ? 1.0f : 0.0f;
-                const uint64_t who = __builtin_amdgcn_ballot_w64(above);
-                if (who != 0 && room) {  // one counter update per wave, the lanes take consecutive entries
-                  int base = 0;
-                  if (lane == (int)__builtin_ctzll(who)) base = atomicAdd(sh.ncand, (int)__builtin_popcountll(who));
-                  base = __builtin_amdgcn_readlane(base, (int)__builtin_ctzll(who));
-                  const int c = base + (int)__builtin_popcountll(who & ((1ull << lane) - 1ull));
-                  if (above && c < kKeptCap) kept_x[c] = x[u];
-                }
-              }
-            }
-          }
+          for (int d = 0; d < kDeep; ++d)
+            if (i0 + d < my_tiles) add(raw[d], ((i0 + d) * kStepWaves + wave) * kTile + (int32_t)lane_off, true);
         }
       }
       acc_m = wave_sum(acc_m);
@@ -1223,232 +1148,13 @@ __global__ __launch_bounds__(W * kWave, Filter ? 4 : W == 8 ? 6 : 8) void espo_s
         mass += (float)sh.res_s[w];
         count += sh.fres[w];
       }
-      ncand = *sh.ncand;
     };
 
-    // The smallest kept logit among the collected ones (all logits above floor_x, which lies below the
-    // kept set): the smallest candidate whose strictly larger candidates hold less than p (number
-    // fewer than k).  False if a sum is too close to p to tell in fp32, or if the method at hand
-    // does not fit.  A few hundred candidates are compared all with all.  More of them are first
-    // binned by their distance from the row's largest logit (256 bins of equal width down to the
-    // floor): the bins' weights, summed from the top, name the one bin in which
-    // the edge lies, and only that bin's candidates are compared with each other.  Weights are
-    // integers there (2^t in units of 2^-31 of the measured mass, or 1 for top-k), so the sums do
-    // not depend on the order in which the candidates arrive.
-    constexpr int kPairwise = 256, kBins = 256, kMembers = 256;
-    auto kept_edge = [&](float floor_x, float& edge_sure, float& edge_maybe) {
-      // this thread's candidate if it is kept for sure / if it may be kept, else +inf
-      float mine_sure = __builtin_huge_valf(), mine_maybe = __builtin_huge_valf();
-      const float slack = by_count ? 0.0f : 1e-5f * total;  // what an fp32 sum may be off by
-      const bool binned = ncand > kPairwise && nslots >= kBins + 2 * kMembers && (by_count || mass > 0.0f) && floor_x > kNegInf;
-      if (!binned) {
-        if (ncand > kCandCap) return false;
-        float* const cand_e = kept_x + kCandCap;  // the candidates' 2^t, in the half that their logits leave free
-        for (int c = tid; c < ncand; c += kStepThreads) cand_e[c] = __builtin_amdgcn_exp2f(fmaf(kept_x[c], a.k2, nrk_row));
-        __syncthreads();
-        for (int c = tid; c < ncand; c += kStepThreads) {  // at most one per thread
-          const float xc = kept_x[c];
-          float m_above = 0.0f, n_above = 0.0f;
-          // every thread reads the same entries (LDS broadcasts), four at a time and several
-          // reads in flight: one entry per dependent read would cost a microsecond per ten candidates
-          const int whole = ncand & ~3;
-#pragma unroll 4
-          for (int o = 0; o < whole; o += 4) {
-            const f32x4 xo = *(const f32x4*)(kept_x + o), eo = *(const f32x4*)(cand_e + o);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-              const bool larger = xo[u] > xc;
-              m_above += larger ? eo[u] : 0.0f;
-              n_above += larger ? 1.0f : 0.0f;
-            }
-          }
-          for (int o = whole; o < ncand; ++o) {
-            const bool larger = kept_x[o] > xc;
-            m_above += larger ? cand_e[o] : 0.0f;
-            n_above += larger ? 1.0f : 0.0f;
-          }
-          if (by_count ? n_above < (float)a.top_k : m_above < want - slack) mine_sure = xc;
-          if (by_count ? n_above < (float)a.top_k : m_above < want + slack) mine_maybe = xc;
-        }
-      } else {
-        // the survivor list of the measurement is over: its words hold the bins and the edge bin's members
-        uint32_t* const words = (uint32_t*)sh.mu;
-        auto bin_w = [&](int b) -> uint32_t& { return words[2 * b]; };
-        auto mem_x = [&](int i) -> float& { return ((float*)words)[2 * (kBins + i)]; };
-        auto mem_w = [&](int i) -> uint32_t& { return words[2 * (kBins + kMembers + i)]; };
-        const float per_logit = (float)kBins / (m - floor_x);  // bins of equal width between the floor and the row's largest logit
-        const float scale = by_count ? 1.0f : 2147483648.0f / (mass * 1.001f);
-        // what may be kept has less than `limit` above it, what is kept for sure less than `limit_sure`
-        const float limit_f = by_count ? (float)a.top_k : (want + slack) * scale;
-        const float limit_sure_f = by_count ? (float)a.top_k : (want - slack) * scale;
-        const uint32_t limit = limit_f < 1.0f ? 1u : limit_f < 4.0e9f ? (uint32_t)limit_f : 4000000000u;
-        const uint32_t limit_sure = limit_sure_f < 1.0f ? 1u : limit_sure_f < 4.0e9f ? (uint32_t)limit_sure_f : 4000000000u;
-        if (tid < kBins) bin_w(tid) = 0;
-        if (tid == 0) *sh.nsurv = 0;
-        __syncthreads();
-        float cx[kKeptCap / kStepThreads];
-        uint32_t cw[kKeptCap / kStepThreads];
-        int cb[kKeptCap / kStepThreads];
-#pragma unroll
-        for (int i = 0; i < kKeptCap / kStepThreads; ++i) {
-          const int c = tid + i * kStepThreads;
-          cb[i] = -1;
-          if (c < ncand) {
-            cx[i] = kept_x[c];
-            cw[i] = by_count ? 1u : (uint32_t)(__builtin_amdgcn_exp2f(fmaf(cx[i], a.k2, nrk_row)) * scale + 0.5f);
-            const int b = (int)((m - cx[i]) * per_logit);  // rounding is monotone: a larger logit never lands in a later bin
-            cb[i] = b < kBins ? b : kBins - 1;
-            atomicAdd(&bin_w(cb[i]), cw[i]);
-          }
-        }
-        __syncthreads();
-        // every wave for itself: the weight above each bin, and the last bins that have candidates and less
-        // than the two limits above them: the two edges lie in these bins or between them (nearly always one bin)
-        static_assert(kBins == 4 * kWave, "four bins per lane");
-        uint32_t h[4], above[4];
-        uint32_t lane_total = 0;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          h[u] = bin_w(4 * lane + u);
-          lane_total += h[u];
-        }
-        uint32_t incl = lane_total;
-#pragma unroll
-        for (int d = 1; d < kWave; d <<= 1) {
-          const uint32_t up = __shfl_up(incl, d);
-          if (lane >= d) incl += up;
-        }
-        above[0] = incl - lane_total;
-#pragma unroll
-        for (int u = 1; u < 4; ++u) above[u] = above[u - 1] + h[u - 1];
-        float best = -1.0f, best_sure = -1.0f;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          if (h[u] != 0 && above[u] < limit) best = (float)(4 * lane + u);
-          if (h[u] != 0 && above[u] < limit_sure) best_sure = (float)(4 * lane + u);
-        }
-        const int last_bin = (int)wave_max(best);        // the bin of the largest candidate at least: nothing is above it
-        const int edge_bin = (int)wave_max(best_sure);   // not after last_bin: its limit is the smaller one
-        const int u_sel = edge_bin & 3;
-        const uint32_t above_sel = u_sel == 0 ? above[0] : u_sel == 1 ? above[1] : u_sel == 2 ? above[2] : above[3];
-        const uint32_t above_edge_bin = __shfl(above_sel, edge_bin >> 2);
-#pragma unroll
-        for (int i = 0; i < kKeptCap / kStepThreads; ++i) {
-          if (cb[i] >= edge_bin && cb[i] <= last_bin) {
-            const int k = atomicAdd(sh.nsurv, 1);
-            if (k < kMembers) {
-              mem_x(k) = cx[i];
-              mem_w(k) = cw[i];
-            }
-          }
-        }
-        __syncthreads();
-        const int members = *sh.nsurv;
-        if (members > kMembers) return false;  // (uniform) a bin of ties, or of many close logits
-        // (the largest candidate of the next bin after last_bin that has any has the limit at least above
-        // it: it is not kept, nor is anything after it; everything before edge_bin is kept for sure)
-        if (tid < members) {
-          const float xc = mem_x(tid);
-          uint32_t w_above = above_edge_bin;
-#pragma unroll 4
-          for (int o = 0; o < members; ++o) w_above += mem_x(o) > xc ? mem_w(o) : 0u;
-          const float m_above = (float)w_above / scale;
-          if (by_count ? w_above < (uint32_t)a.top_k : m_above < want - slack) mine_sure = xc;
-          if (by_count ? w_above < (uint32_t)a.top_k : m_above < want + slack) mine_maybe = xc;
-        }
-      }
-      const float wave_sure = -wave_max(-mine_sure), wave_maybe = -wave_max(-mine_maybe);  // the wave's smallest ones
-      __syncthreads();  // the sums of the measurement have been read by everyone
-      if (lane == 0) {
-        sh.fres[wave] = wave_sure;
-        sh.fres[kStepWaves + wave] = wave_maybe;
-      }
-      __syncthreads();
-      edge_sure = __builtin_huge_valf();
-      edge_maybe = __builtin_huge_valf();
-      for (int w = 0; w < kStepWaves; ++w) {
-        edge_sure = fminf(edge_sure, sh.fres[w]);
-        edge_maybe = fminf(edge_maybe, sh.fres[kStepWaves + w]);
-      }
-      return edge_maybe < __builtin_huge_valf();
-    };
-
-    // The winner among everything that may be kept (the floor is the next float below that edge).  If
-    // its logit is kept for sure it is the token: leaving out the logits in doubt would not change the
-    // winner.  Else (seldom: the winner is one of the few logits whose sums are too close to p to
-    // tell in fp32) false, and the loop below tests that winner in double.
-    auto winner_above = [&](float edge_sure, float edge_maybe) {
-      StepShared kept_only = sh;
-      kept_only.floor = next_below(edge_maybe);
-      search(kept_only, nothing);
-      return tok < 0 || x_a >= edge_sure;
-    };
-
-    bool done = !(m > kNegInf);
-    float edge_known = kNegInf, edge_open = kNegInf;  // the edge of the kept set for sure, and the smallest logit that may be kept
-    bool have_edge = false;
-    if (!done && a.top_k == 1) {  // greedy decoding up to ties: the kept set is the row's largest logit
-      edge_known = edge_open = m;
-      have_edge = true;
-    } else if (!done) {
-      // a floor with about 64 blocks above it, the 64th largest of the 128 lane groups' largest logits
-      // (for top-k the (32 + k)-th: k logits have to lie above it).  Measured, 32 is 2 us faster on rows
-      // whose nucleus is a few dozen tokens and 10 to 30 us slower where it is a few hundred.  If the
-      // kept set turns out to reach below that floor (a flat row), the smallest of the 128 is tried:
-      // several hundred blocks lie above it, and a nucleus of some hundred tokens still does.
-      __syncthreads();
-      constexpr int kVals = 2 * kSlots;  // two values per lane group: its even and its odd tiles
-      if ((lane & 7) == 0) {
-        sh.cand_x[2 * (wave * kGroups + grp)] = mx_even;
-        sh.cand_x[2 * (wave * kGroups + grp) + 1] = mx_odd;
-      }
-      if (tid < kVals) sh.cand_v[tid] = 0;  // the ranks, summed from partial counts
-      __syncthreads();
-      const int trial_rank = by_count ? (a.top_k < kVals - 32 ? 31 + a.top_k : kVals - 1) : kVals / 2 - 1;
-      {
-        constexpr int kParts = kStepThreads / kVals, kOthers = kVals / kParts;  // threads per value, values each of them compares with
-        static_assert(kStepThreads % kVals == 0 && kVals % kParts == 0 && kOthers % 4 == 0, "the values are shared out evenly, four at a time");
-        const int j = tid & (kVals - 1), part = tid / kVals;
-        const float mine = sh.cand_x[j];
-        int r = 0;
-#pragma unroll
-        for (int q = 0; q < kOthers / 4; ++q) {
-          const f32x4 o4 = ((const f32x4*)sh.cand_x)[part * (kOthers / 4) + q];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const int o = part * kOthers + q * 4 + u;
-            r += (o4[u] > mine || (o4[u] == mine && o < j)) ? 1 : 0;
-          }
-        }
-        atomicAdd(&sh.cand_v[j], r);
-      }
-      __syncthreads();
-      if (tid < kVals) {  // -inf if fewer lane groups than that saw a finite logit
-        if (sh.cand_v[tid] == trial_rank) sh.fres[2 * kStepWaves] = sh.cand_x[tid];
-        if (sh.cand_v[tid] == kVals - 1) sh.fres[2 * kStepWaves + 1] = sh.cand_x[tid];
-      }
-      __syncthreads();
-      const float trials[2] = {sh.fres[2 * kStepWaves], sh.fres[2 * kStepWaves + 1]};
-#pragma unroll 1
-      for (int attempt = 0; attempt < 2; ++attempt) {
-        if (attempt == 1 && !(trials[1] < trials[0])) break;
-        const float trial = attempt == 0 ? trials[0] : trials[1];
-        measure(trial);
-        const bool below_edge = by_count ? count >= (float)a.top_k : mass - want > 1e-5f * total;
-        if (below_edge) {  // every kept logit has been seen; a lower floor could only add to them
-          if (ncand <= kKeptCap) have_edge = kept_edge(trial, edge_known, edge_open);
-          break;
-        }
-      }
-    }
-    if (have_edge) {  // the kept set is everything at or above the edge
-      done = winner_above(edge_known, edge_open);
-    } else if (!done) {
-      search(sh, nothing);  // the unfiltered winner, for the loop below
-    }
-    while (!done && tok >= 0) {
-      const float floor_x = x_a;
-      measure(floor_x);
+    StepShared above = sh;
+    while (m > kNegInf) {  // (a row without a finite logit has no winner)
+      search(above, nothing);
+      if (tok < 0) break;
+      measure(x_a);
       bool kept;
       if (by_count) {
         kept = count < (float)a.top_k;
@@ -1469,15 +1175,12 @@ __global__ __launch_bounds__(W * kWave, Filter ? 4 : W == 8 ? 6 : 8) void espo_s
             if (e0 + u < a.V && x[u] > kNegInf) {
               const double e = exp((double)x[u] * inv - y_max);
               ds += e;
-              if (x[u] > floor_x) dm += e;
+              if (x[u] > x_a) dm += e;
             }
           }
         }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-          dm += __shfl_xor(dm, off);
-          ds += __shfl_xor(ds, off);
-        }
+        dm = wave_sum_f64(dm);
+        ds = wave_sum_f64(ds);
         __syncthreads();
         if (lane == 0) {
           sh.res_s[wave] = dm;
@@ -1492,16 +1195,8 @@ __global__ __launch_bounds__(W * kWave, Filter ? 4 : W == 8 ? 6 : 8) void espo_s
         kept = dmass < (double)a.top_p * dtotal;
       }
       if (kept) break;
-      if (ncand <= kKeptCap) {  // every logit above the winner's is at hand
-        float edge, open_edge;
-        if (kept_edge(floor_x, edge, open_edge)) {
-          if (winner_above(edge, open_edge)) break;  // that winner is kept by construction
-          continue;                                  // or it is in doubt: tested next
-        }
-      }
-      StepShared above = sh;  // the bulk case, or a sum too close to tell: the next winner above the floor
-      above.floor = floor_x;
-      search(above, nothing);
+      above.floor = x_a;
+      __syncthreads();  // the sums have been read by everyone
     }
   }
 
@@ -1583,27 +1278,705 @@ __global__ __launch_bounds__(W * kWave, Filter ? 4 : W == 8 ? 6 : 8) void espo_s
       }
     }
   }
-  if (lane == 0) {
-    if (tok < 0) { tok = 0; x_a = elem_at<DT>(rowp, 0); }  // row of -inf only: unspecified, stay in range
-    const ChainOut c = scalar_chain(a, row, m, x_a, z_prev, value);
-    a.tokens[row] = tok;
-    a.regret[row] = c.g;
-    a.z[row] = c.z;
-    if (Sum && a.logprob) a.logprob[row] = -c.g - flog(S);
-    if constexpr (Entropy)  // H = ln S - E_pi[y - y_max] >= 0; rounding can leave S a few ulp below 1
-      a.entropy[row] = fmaxf(flog(S) - kLn2 * Sw / S, 0.0f);
-    if (a.eos_id >= 0 && tok == a.eos_id) {
-      a.alive[row] = 0;  // natural end
-    } else if (c.stop) {
-      if (a.simulate) {  // bookkeeping only: the first stop step is recorded, decoding goes on
-        if (a.stop_step[row] < 0) a.stop_step[row] = a.step;
-      } else {
-        a.alive[row] = 0;  // absorbing failure (Eq. failure_reward): the trajectory ends here
-        a.stop_step[row] = a.step;
+  if (lane == 0) finish_row<DT, Entropy, Sum>(a, row, rowp, tok, x_a, m, S, Sw, z_prev, value);
+}
+
+template <int DT, bool Entropy, bool Sum, int W>
+// Registers: 64 per lane for 16 waves (two workgroups on a compute unit); workgroups of 8 waves get up
+// to 80 (three of them fit, in registers and in LDS) and use 75 without spilling.
+__global__ __launch_bounds__(W * kWave, W == 8 ? 6 : 8) void espo_step_kernel(StepArgs a) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  step_row<DT, Entropy, false, Sum, W>(a, smem_raw);
+}
+
+// ---------------------------------------------------------------- filtered draws
+// The filtered token is the argmax of y + G over the kept set {x >= x*}, an upper set in the logit,
+// so neither a block's bound nor any index below x* is needed: what is needed is the row's largest
+// logits.  They are collected while the row streams.  A wave keeps the raw 16 (fp32: 32) bytes of
+// every lane whose 8 logits hold one above the wave's threshold, in an LDS list of its own (no
+// atomics, no barrier); when the list grows past kCompactAt the wave raises its threshold to about
+// the kKeep-th largest of the packs' maxima and drops the rest.  Every logit of the row above
+// T = the largest of the waves' thresholds is then in LDS, some 800 packs of a long row, and nothing
+// is read from memory again:
+//   1. row maximum m, T, softmax sum S;
+//   2. the logits above T are binned by value (256 bins of equal width), weights 2^t as integers in
+//      units of 2^-31 of S (1 for top-k), so the sums do not depend on their order;
+//   3. the bins' prefix sum tells whether the mass (number) above T exceeds p S (k) and names the bin
+//      with the edge of the kept set; logits in bins before it are kept, those in it are compared with
+//      each other;
+//   4. the kept logits are scored, one per thread, and the best one is the token.
+// Sums within 1e-5 of p S are not trusted: such a logit takes part in the search, and if it wins, or
+// if the kept set reaches below T, or a list does not hold what it has to, the row goes through the
+// general search of step_row from the start.
+// Bound by the streaming like the plain draw: B = 512, V = 152064 bf16, us per launch, against a
+// search for the edge that read the row's blocks again after a trial floor: top-p 0.7 at temperature
+// 0.6 / 0.8 / 1.0: 35.0 / 34.8 / 35.6 (44.1 / 48.7 / 67.3), top-k 50 at 1.0: 35.3 (48.8), the plain
+// draw at 1.0: 36.4.  B = 100, V = 50003, top-k 50: 13.6 (24.9).  What is left after the last tile is
+// five barriers, 7 to 8 us of a workgroup.  The lists' room is what two workgroups of 8 waves on a
+// compute unit leave (73 KB of LDS each); 16 waves are used below 256 rows (13.6 against 16.0 us there).
+constexpr int kKeptCap2 = 3072, kEdgeBins = 256, kEdgeMembers = 256;
+constexpr int32_t kInDoubt = 1 << 30;  // on top of an index whose membership of the kept set fp32 cannot tell
+
+template <int DT, int W>
+struct CollectLimits {  // packs of a wave's list: room, when it is compacted, what is kept then; tiles between two checks
+  static constexpr int kRoom = W == 8 ? (DT == ESPO_BF16 ? 448 : 256) : (DT == ESPO_BF16 ? 320 : 192);
+  static constexpr int kCheckTiles = W == 8 && DT == ESPO_BF16 ? 2 : 1;
+  static constexpr int kCompactAt = kRoom - kCheckTiles * kWave;
+  static constexpr int kKeep = (DT == ESPO_BF16 ? 160 : 112) * 8 / W, kKeepMin = kKeep / 2;
+};
+
+template <int DT, int W>
+struct FilterShared {
+  uint32_t* raw;     // [W][kRoom][words] the packs ...
+  uint16_t* id;      // [W][kRoom] ... and which 8 indices of the row each holds
+  uint16_t* kept;    // [kKeptCap2] logits kept for sure: pack * 8 + position
+  uint32_t* bins;    // [kEdgeBins]
+  float* mem_x;      // [kEdgeMembers] logits in the edge's bin, their weights, and where they are
+  uint32_t* mem_w;
+  uint16_t* mem_at;
+  float *m, *thr, *low, *least, *sum, *sumw;  // [W]
+  float* fres;       // [5][W]
+  double *res_s, *res_hi2;
+  float* res_e;
+  int* res_v;
+  float* res_x;
+  int *nkept, *nmem, *nover;
+};
+
+template <int DT, int W>
+__host__ __device__ constexpr size_t filter_lds_bytes() {
+  constexpr size_t packs = (size_t)W * CollectLimits<DT, W>::kRoom;
+  return packs * (DT == ESPO_BF16 ? 16 : 32) + packs * 2 + kKeptCap2 * 2 + kEdgeBins * 4 + kEdgeMembers * 10 +
+         W * (6 + 5 + 3) * 4 + W * 16 + 16;
+}
+
+template <int DT, int W>
+__device__ __forceinline__ FilterShared<DT, W> carve_filter(unsigned char* base) {
+  constexpr size_t packs = (size_t)W * CollectLimits<DT, W>::kRoom;
+  FilterShared<DT, W> f;
+  size_t off = 0;
+  auto take = [&](size_t bytes) { void* p = base + off; off += bytes; return p; };  // sizes are multiples of 16 down to `m`
+  f.raw = (uint32_t*)take(packs * (DT == ESPO_BF16 ? 16 : 32));
+  f.res_s = (double*)take(W * 8);
+  f.res_hi2 = (double*)take(W * 8);
+  f.bins = (uint32_t*)take(kEdgeBins * 4);
+  f.mem_x = (float*)take(kEdgeMembers * 4);
+  f.mem_w = (uint32_t*)take(kEdgeMembers * 4);
+  f.m = (float*)take(W * 4);
+  f.thr = (float*)take(W * 4);
+  f.low = (float*)take(W * 4);
+  f.least = (float*)take(W * 4);
+  f.sum = (float*)take(W * 4);
+  f.sumw = (float*)take(W * 4);
+  f.fres = (float*)take(5 * W * 4);
+  f.res_e = (float*)take(W * 4);
+  f.res_v = (int*)take(W * 4);
+  f.res_x = (float*)take(W * 4);
+  f.nkept = (int*)take(16);
+  f.nmem = f.nkept + 1;
+  f.nover = f.nkept + 2;
+  f.id = (uint16_t*)take(packs * 2);
+  f.kept = (uint16_t*)take(kKeptCap2 * 2);
+  f.mem_at = (uint16_t*)take(kEdgeMembers * 2);
+  return f;
+}
+
+template <int DT>
+__device__ __forceinline__ Raw<DT> pack_load(const uint32_t* raw) {
+  Raw<DT> r;
+#pragma unroll
+  for (int h = 0; h < Raw<DT>::kWords / 4; ++h) {
+    const u32x4 t = ((const u32x4*)raw)[h];
+    r.w[4 * h] = t.x; r.w[4 * h + 1] = t.y; r.w[4 * h + 2] = t.z; r.w[4 * h + 3] = t.w;
+  }
+  return r;
+}
+template <int DT>
+__device__ __forceinline__ void pack_store(uint32_t* raw, const Raw<DT>& r) {
+#pragma unroll
+  for (int h = 0; h < Raw<DT>::kWords / 4; ++h)
+    ((u32x4*)raw)[h] = u32x4{r.w[4 * h], r.w[4 * h + 1], r.w[4 * h + 2], r.w[4 * h + 3]};
+}
+
+// The lane's logits; those at or beyond V, which a ragged row's last pack holds, become -inf.
+template <int DT>
+__device__ __forceinline__ void pack_unpack(const Raw<DT>& r, int32_t v0, int32_t V, float x[8]) {
+  unpack<DT>(r, x);
+  if (v0 + 8 > V) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (v0 + j >= V) x[j] = kNegInf;
+  }
+}
+
+__device__ __forceinline__ float max8(const float x[8]) {
+  return fmaxf(fmaxf(fmaxf(fmaxf(fmaxf(x[0], x[1]), x[2]), fmaxf(fmaxf(x[3], x[4]), x[5])), x[6]), x[7]);
+}
+
+// Lanes below this one whose bit is set in `mask`.
+__device__ __forceinline__ int rank_below(uint64_t mask) {
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+
+// Raises a wave's threshold to a value that at most kKeep of the list's packs reach beyond and drops the
+// others.  (Packs that tie at the threshold are dropped as well: what is kept is everything above it.)
+template <int DT, int W>
+__device__ __forceinline__ void compact_list(uint32_t* raw, uint16_t* id, int32_t V, int& n, float& thr) {
+  using Lim = CollectLimits<DT, W>;
+  constexpr int kRounds = Lim::kRoom / kWave, kWords = Raw<DT>::kWords;
+  const int lane = threadIdx.x & (kWave - 1);
+  float pm[kRounds];
+  float top = kNegInf, bottom = kNegInf;  // bottom: of the negated maxima
+#pragma unroll
+  for (int r = 0; r < kRounds; ++r) {
+    const int i = r * kWave + lane;
+    pm[r] = kNegInf;
+    if (i < n) {
+      float x[8];
+      pack_unpack<DT>(pack_load<DT>(raw + i * kWords), (int32_t)id[i] * 8, V, x);
+      pm[r] = max8(x);
+      bottom = fmaxf(bottom, -pm[r]);
+    }
+    top = fmaxf(top, pm[r]);
+  }
+  float hi = wave_max(top), lo = -wave_max(bottom);  // none above hi; the search keeps at most kKeep above hi
+#pragma unroll 1
+  for (int it = 0; it < 12; ++it) {
+    const float mid = 0.5f * lo + 0.5f * hi;
+    int c = 0;
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) c += (int)__builtin_popcountll(__builtin_amdgcn_ballot_w64(pm[r] > mid));
+    if (c > Lim::kKeep) {
+      lo = mid;
+    } else {
+      hi = mid;
+      if (c >= Lim::kKeepMin) break;
+    }
+  }
+  thr = hi;
+  int kept = 0;
+#pragma unroll
+  for (int r = 0; r < kRounds; ++r) {  // in place: an entry never moves up, and a round reads before it writes
+    const bool keep = pm[r] > thr;
+    const uint64_t mask = __builtin_amdgcn_ballot_w64(keep);
+    if (keep) {
+      const int i = r * kWave + lane, to = kept + rank_below(mask);
+      const Raw<DT> p = pack_load<DT>(raw + i * kWords);
+      const uint16_t which = id[i];
+      pack_store<DT>(raw + to * kWords, p);
+      id[to] = which;
+    }
+    kept += (int)__builtin_popcountll(mask);
+  }
+  n = kept;
+}
+
+// The two forms of the collected logits, seen by one thread.  An entry is named by its place `at` in the list.
+template <int DT, int W>
+struct PackList {  // the wave's packs of 8, some 250 of them; each lane owns every 64th
+  static constexpr int kRoom = CollectLimits<DT, W>::kRoom, kRounds = kRoom / kWave;
+  const FilterShared<DT, W>& f;
+  int n;          // packs of this wave
+  int32_t V;
+  // of each of this lane's packs: the bin of its largest logit (kEdgeBins: none above T), and from bit 16 on
+  // which of its logits are above T (most packs in the list hold one)
+  uint32_t info[kRounds];
+  __device__ __forceinline__ uint32_t place(int r) const {
+    return (uint32_t)((threadIdx.x >> 6) * kRoom + r * kWave + (threadIdx.x & (kWave - 1))) * 8u;
+  }
+  __device__ __forceinline__ float logit(uint32_t at) const { return elem_at<DT>((const char*)f.raw, (int64_t)at); }
+  __device__ __forceinline__ int32_t index(uint32_t at) const { return (int32_t)f.id[at >> 3] * 8 + (int32_t)(at & 7u); }
+  template <typename Bin, typename Weight>
+  __device__ __forceinline__ void fill_bins(float bottom, Bin&& bin_of, Weight&& weight_of) {
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+      info[r] = kEdgeBins;
+      const int i = r * kWave + (int)(threadIdx.x & (kWave - 1));
+      if (i < n) {
+        float x[8];
+        const uint32_t at = place(r);
+        pack_unpack<DT>(pack_load<DT>(f.raw + (at >> 3) * Raw<DT>::kWords), index(at), V, x);
+        uint32_t over = 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) over |= x[j] > bottom ? 1u << j : 0u;
+        if (over != 0) info[r] = (uint32_t)bin_of(max8(x)) | (over << 16);
+        for (; over != 0; over &= over - 1) {
+          const float xo = logit(at + (uint32_t)__builtin_ctz(over));
+          atomicAdd(&f.bins[bin_of(xo)], weight_of(xo));
+        }
       }
     }
   }
+  // use(at, x, bin) for this thread's logits above T in bins up to last_bin
+  template <typename Bin, typename Use>
+  __device__ __forceinline__ void for_each(float, int last_bin, Bin&& bin_of, Use&& use) const {
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+      if ((int)(info[r] & 0xffffu) > last_bin) continue;
+      for (uint32_t over = info[r] >> 16; over != 0; over &= over - 1) {
+        const uint32_t at = place(r) + (uint32_t)__builtin_ctz(over);
+        const float x = logit(at);
+        const int b = bin_of(x);
+        if (b <= last_bin) use(at, x, b);
+      }
+    }
+  }
+};
+
+template <int DT, int W>
+struct LogitList {  // single logits with their indices, in the space of the packs
+  static constexpr int kBytes = CollectLimits<DT, W>::kRoom * (DT == ESPO_BF16 ? 16 : 32);  // of one wave
+  static constexpr int kRoom = kBytes / (DT == ESPO_BF16 ? 6 : 8) / 8 * 8;
+  const FilterShared<DT, W>& f;
+  int n;  // logits of this wave
+  __device__ __forceinline__ int32_t* index_area() const { return (int32_t*)f.raw; }                             // [W][kRoom]
+  __device__ __forceinline__ void* logit_area() const { return index_area() + W * kRoom; }            // [W][kRoom]
+  __device__ __forceinline__ float logit(uint32_t at) const { return elem_at<DT>(logit_area(), (int64_t)at); }
+  __device__ __forceinline__ int32_t index(uint32_t at) const { return index_area()[at]; }
+  __device__ __forceinline__ void put(int wave, int i, int32_t v, float x) const {
+    const int at = wave * kRoom + i;
+    index_area()[at] = v;
+    if constexpr (DT == ESPO_BF16) ((uint16_t*)logit_area())[at] = (uint16_t)(__builtin_bit_cast(uint32_t, x) >> 16);
+    else ((float*)logit_area())[at] = x;
+  }
+  template <typename Bin, typename Weight>
+  __device__ __forceinline__ void fill_bins(float, Bin&& bin_of, Weight&& weight_of) {
+    for (int i = threadIdx.x & (kWave - 1); i < n; i += kWave) {
+      const float x = logit((threadIdx.x >> 6) * kRoom + i);
+      atomicAdd(&f.bins[bin_of(x)], weight_of(x));
+    }
+  }
+  template <typename Bin, typename Use>
+  __device__ __forceinline__ void for_each(float, int last_bin, Bin&& bin_of, Use&& use) const {
+    for (int i = threadIdx.x & (kWave - 1); i < n; i += kWave) {
+      const uint32_t at = (threadIdx.x >> 6) * kRoom + i;
+      const float x = logit(at);
+      const int b = bin_of(x);
+      if (b <= last_bin) use(at, x, b);
+    }
+  }
+};
+
+enum DrawResult { kDrawn, kReachesBelow, kUndecided };
+
+// The draw from one of them: all logits of the row above `bottom` (< m) are in the list.  The same result in
+// every thread; f.bins and the two counters are zero and the list is complete when it is called.
+template <int DT, int W, typename List>
+__device__ __forceinline__ DrawResult draw_from_list(const StepArgs& a, const FilterShared<DT, W>& f, List& list, int row, float m,
+                                                     float S, float bottom, int32_t& tok, float& x_a) {
+  const int tid = threadIdx.x;
+  const int lane = tid & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool by_count = a.top_k > 0;
+  // ---------------------------------------------------------- bins
+  const float nrk_row = -m * a.k2;
+  const float want = a.top_p * S;
+  const float slack = by_count ? 0.0f : 1e-5f * S;  // what an fp32 sum may be off by
+  const float per_logit = (float)kEdgeBins / (m - bottom);
+  const float scale = by_count ? 1.0f : 2147483648.0f / (S * 1.001f);
+  auto bin_of = [&](float x) {  // rounding is monotone: a larger logit never lands in a later bin
+    return (int)min((uint32_t)(int)((m - x) * per_logit), (uint32_t)kEdgeBins - 1u);
+  };
+  auto weight_of = [&](float x) {
+    return by_count ? 1u : (uint32_t)(__builtin_amdgcn_exp2f(fmaf(x, a.k2, nrk_row)) * scale + 0.5f);
+  };
+  list.fill_bins(bottom, bin_of, weight_of);
+  __syncthreads();
+  // every wave for itself: the weight above each bin, and the last bins that have logits and less than the
+  // two limits above them: the two edges (kept for sure, may be kept) lie in these bins or between them
+  static_assert(kEdgeBins == 4 * kWave, "four bins per lane");
+  const float limit_f = by_count ? (float)a.top_k : (want + slack) * scale;
+  const float limit_sure_f = by_count ? (float)a.top_k : (want - slack) * scale;
+  const uint32_t limit = limit_f < 1.0f ? 1u : limit_f < 4.0e9f ? (uint32_t)limit_f : 4000000000u;
+  const uint32_t limit_sure = limit_sure_f < 1.0f ? 1u : limit_sure_f < 4.0e9f ? (uint32_t)limit_sure_f : 4000000000u;
+  const u32x4 h = ((const u32x4*)f.bins)[lane];
+  const uint32_t lane_total = h[0] + h[1] + h[2] + h[3];
+  uint32_t incl = lane_total;
+  incl += dpp_u32<kDppRowShr1, 0xf>(0u, incl);
+  incl += dpp_u32<kDppRowShr2, 0xf>(0u, incl);
+  incl += dpp_u32<kDppRowShr4, 0xf>(0u, incl);
+  incl += dpp_u32<kDppRowShr8, 0xf>(0u, incl);
+  incl += dpp_u32<kDppBcast15, 0xa>(0u, incl);
+  incl += dpp_u32<kDppBcast31, 0xc>(0u, incl);
+  const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
+  if (by_count ? total < (uint32_t)a.top_k : !((float)total / scale - want > slack)) return kReachesBelow;
+  uint32_t above[4];
+  above[0] = incl - lane_total;
+#pragma unroll
+  for (int u = 1; u < 4; ++u) above[u] = above[u - 1] + h[u - 1];
+  float best = -1.0f, best_sure = -1.0f;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    if (h[u] != 0 && above[u] < limit) best = (float)(4 * lane + u);
+    if (h[u] != 0 && above[u] < limit_sure) best_sure = (float)(4 * lane + u);
+  }
+  const int last_bin = (int)wave_max(best);       // the bin of the largest logit at least: nothing is above it
+  const int edge_bin = (int)wave_max(best_sure);  // not after last_bin: its limit is the smaller one
+  const int u_sel = edge_bin & 3;
+  const uint32_t above_sel = u_sel == 0 ? above[0] : u_sel == 1 ? above[1] : u_sel == 2 ? above[2] : above[3];
+  const uint32_t above_edge = (uint32_t)__builtin_amdgcn_readlane((int)above_sel, edge_bin >> 2);
+  // ---------------------------------------------------------- the kept logits, and the edge bin's members
+  list.for_each(bottom, last_bin, bin_of, [&](uint32_t at, float x, int b) {
+    if (b < edge_bin) {
+      const int c = atomicAdd(f.nkept, 1);
+      if (c < kKeptCap2) f.kept[c] = (uint16_t)at;
+    } else {
+      const int c = atomicAdd(f.nmem, 1);
+      if (c < kEdgeMembers) {
+        f.mem_x[c] = x;
+        f.mem_w[c] = weight_of(x);
+        f.mem_at[c] = (uint16_t)at;
+      }
+    }
+  });
+  __syncthreads();
+  const int nkept = *f.nkept, nmem = *f.nmem;
+  if (nkept > kKeptCap2 || nmem > kEdgeMembers) return kUndecided;
+  // ---------------------------------------------------------- scores
+  auto word_of = [&](int32_t v) {
+    const int q = v >> 6;
+    const Philox4 pb = philox4x32_10((uint32_t)(q >> 2), (uint32_t)a.step, (uint32_t)row, kTagBlock, a.key0, a.key1);
+    return (q & 3) == 0 ? pb.w[0] : (q & 3) == 1 ? pb.w[1] : (q & 3) == 2 ? pb.w[2] : pb.w[3];
+  };
+  bool take_member = false, sure_member = true;
+  const int my_member = W * kWave - 1 - tid;  // the other end of the workgroup from the kept logits, which are usually few
+  if (my_member < nmem) {  // (the largest logit of the bins after last_bin has the limit above it: not kept, nor is anything after it)
+    const float xc = f.mem_x[my_member];
+    uint32_t w_above = above_edge;
+#pragma unroll 4
+    for (int o = 0; o < nmem; ++o) w_above += f.mem_x[o] > xc ? f.mem_w[o] : 0u;
+    const float m_above = (float)w_above / scale;
+    sure_member = by_count ? w_above < (uint32_t)a.top_k : m_above < want - slack;
+    take_member = by_count ? w_above < (uint32_t)a.top_k : m_above < want + slack;
+  }
+  Best st = no_best();
+  // one loop for both: this thread's share of the kept logits, then its member of the edge bin
+#pragma unroll 1
+  for (int i = tid; i < nkept + W * kWave; i += W * kWave) {
+    const bool member = i >= nkept;
+    if (member ? !take_member : false) break;
+    const uint32_t at = member ? f.mem_at[my_member] : f.kept[i];
+    const int32_t v = list.index(at);
+    score_drawn(a, row, v, member && !sure_member ? v | kInDoubt : v, list.logit(at), word_of(v), true, st);
+    if (member) break;
+  }
+  const Best mine = wave_best(st);
+  if (lane == 0) {
+    f.fres[0 * W + wave] = mine.s;
+    f.fres[1 * W + wave] = mine.e;
+    f.fres[2 * W + wave] = mine.x;
+    f.fres[3 * W + wave] = mine.hi2;
+    f.fres[4 * W + wave] = __builtin_bit_cast(float, mine.v);
+  }
+  __syncthreads();
+  Best all = no_best();
+  if (lane < W) {
+    all.s = f.fres[0 * W + lane];
+    all.e = f.fres[1 * W + lane];
+    all.x = f.fres[2 * W + lane];
+    all.hi2 = f.fres[3 * W + lane];
+    all.v = __builtin_bit_cast(int32_t, f.fres[4 * W + lane]);
+  }
+  all = wave_best(all);
+  tok = all.v;
+  x_a = all.x;
+  if (!(all.s - all.e > all.hi2)) {
+    // the two best fp32 scores overlap within their margins: those that reach the winner's lower end, in double
+    const double lower = (double)all.s - (double)all.e;
+    Search<double> exact;
+    exact.init();
+#pragma unroll 1
+    for (int i = tid; i < nkept + W * kWave; i += W * kWave) {
+      const bool member = i >= nkept;
+      if (member ? !take_member : false) break;
+      const uint32_t at = member ? f.mem_at[my_member] : f.kept[i];
+      const int32_t v = list.index(at);
+      const BlockDraw<double> d = block_draw<double>(a, row, v >> 6);
+      Search<double> one;
+      one.init();
+      score_index<double>(a, row, v, list.logit(at), d, lower, kNegInf, one);
+      if (one.best.v >= 0 && member && !sure_member) one.best.v |= kInDoubt;
+      exact.merge(one);
+      if (member) break;
+    }
+    StepShared sh{};
+    sh.res_s = f.res_s; sh.res_hi2 = f.res_hi2; sh.res_e = f.res_e; sh.res_v = f.res_v; sh.res_x = f.res_x;
+    exact = combine_search<double, W>(sh, exact);
+    tok = exact.best.v;
+    x_a = exact.best.x;
+  }
+  return tok >= kInDoubt ? kUndecided : kDrawn;  // the winner may be one of the few logits whose sums are too close to p to tell
 }
+
+// The filtered draw of one row from its largest logits.  False (the same in every thread, nothing written): the
+// row needs the general search.
+template <int DT, bool Entropy, int W>
+__device__ __forceinline__ bool filtered_row(const StepArgs& a, unsigned char* smem_raw, int row) {
+  using Lim = CollectLimits<DT, W>;
+  constexpr int kWords = Raw<DT>::kWords;
+  const int tid = threadIdx.x;
+  const int lane = tid & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const FilterShared<DT, W> f = carve_filter<DT, W>(smem_raw);
+  const void* rowp = (const char*)a.logits + (size_t)row * (size_t)a.row_stride * elem_bytes<DT>();
+
+  // ------------------------------------------------------------ the row streams once, as in step_row
+  const int ntiles = a.ntiles;
+  const int my_tiles = wave < ntiles ? (ntiles - wave + W - 1) / W : 0;
+  const uint32_t last_group = (uint32_t)(a.V - 1) & ~7u;
+  const uint32_t lane_off = (uint32_t)lane * 8u;
+  const uint32_t lane_bytes = lane_off * (uint32_t)elem_bytes<DT>();
+  auto load_tile = [&](int t) {  // t is wave-uniform
+    if (t != ntiles - 1) return load_raw_inner<DT>((const char*)rowp + (size_t)t * kTile * elem_bytes<DT>(), lane_bytes);
+    const uint32_t e0 = (uint32_t)t * kTile + lane_off;  // last tile: may be ragged
+    return load_raw<DT>(rowp, e0 < last_group ? e0 : last_group, (uint32_t)a.V);
+  };
+  Raw<DT> ring[kRing];
+#pragma unroll
+  for (int d = 0; d < kRing; ++d) {  // issued by every wave, whether it has that many tiles or not
+    const uint32_t e0 = (uint32_t)(d * W + wave) * kTile + lane_off;
+    ring[d] = load_raw<DT>(rowp, e0 < last_group ? e0 : last_group, (uint32_t)a.V);
+  }
+  for (int b = tid; b < kEdgeBins; b += W * kWave) f.bins[b] = 0;
+  if (tid == 0) {
+    *f.nkept = 0;
+    *f.nmem = 0;
+  }
+
+  float nrk = 1e30f, lead = kNegInf, sum = 0.0f, sumw = 0.0f;  // the lane's softmax sum against its lazy reference
+  float mx = kNegInf;
+  uint32_t* const my_raw = f.raw + (size_t)wave * Lim::kRoom * kWords;
+  uint16_t* const my_id = f.id + (size_t)wave * Lim::kRoom;
+  int n = 0;                    // packs in this wave's list (wave-uniform)
+  float thr = kNegInf;          // every logit above it that the wave has seen is in the list
+  float low = __builtin_huge_valf();  // the smallest pack maximum this lane has put there
+  bool flooded = false;         // a compaction found most of the list tied at its threshold
+  int dry = 0;                  // passes since then that have left the list next to empty
+
+  auto iteration = [&](auto steady, int d, int i) {
+    constexpr bool Steady = decltype(steady)::value;
+    const int t = i * W + wave;
+    float x[8];
+    unpack<DT>(ring[d], x);
+    if (!Steady && (t + 1) * kTile > a.V) {  // ragged last tile: indices at or beyond V do not exist
+      const int32_t e0 = t * kTile + (int32_t)lane_off;
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        if (e0 + j >= a.V) x[j] = kNegInf;
+    }
+    const float gm = max8(x);
+    mx = fmaxf(mx, gm);
+    if (__builtin_amdgcn_ballot_w64(gm > lead) != 0) {  // rare after the first tile
+      asm volatile("" ::: "memory");  // keep this rare path out of the straight-line code
+      if (gm > lead) {  // move this lane's reference up to gm
+        const float nrk_new = -gm * a.k2;
+        const float shift = nrk_new - nrk;
+        const float g = __builtin_amdgcn_exp2f(shift);
+        if (Entropy) sumw = g * fmaf(shift, sum, sumw);
+        sum *= g;
+        nrk = nrk_new;
+        lead = gm + a.ref_lead;
+      }
+    }
+    if constexpr (!Entropy) {
+      float acc0 = __builtin_amdgcn_exp2f(fmaf(x[0], a.k2, nrk));
+      float acc1 = __builtin_amdgcn_exp2f(fmaf(x[1], a.k2, nrk));
+#pragma unroll
+      for (int j = 2; j < 8; j += 2) {
+        acc0 += __builtin_amdgcn_exp2f(fmaf(x[j], a.k2, nrk));
+        acc1 += __builtin_amdgcn_exp2f(fmaf(x[j + 1], a.k2, nrk));
+      }
+      sum += acc0 + acc1;
+    } else {  // t kept above -200: see step_row
+      float acc0 = 0.0f, acc1 = 0.0f, w0 = 0.0f, w1 = 0.0f;
+#pragma unroll
+      for (int j = 0; j < 8; j += 2) {
+        const float t0 = fmaxf(fmaf(x[j], a.k2, nrk), -200.0f), t1 = fmaxf(fmaf(x[j + 1], a.k2, nrk), -200.0f);
+        const float e0 = __builtin_amdgcn_exp2f(t0), e1 = __builtin_amdgcn_exp2f(t1);
+        acc0 += e0;
+        acc1 += e1;
+        w0 = fmaf(e0, t0, w0);
+        w1 = fmaf(e1, t1, w1);
+      }
+      sum += acc0 + acc1;
+      sumw += w0 + w1;
+    }
+    const bool in = gm > thr;
+    const uint64_t mask = __builtin_amdgcn_ballot_w64(in);
+    if (mask != 0) {
+      if (in) {
+        const int at = n + rank_below(mask);
+        pack_store<DT>(my_raw + at * kWords, ring[d]);
+        my_id[at] = (uint16_t)(t * kWave + lane);
+        low = fminf(low, gm);
+      }
+      n += (int)__builtin_popcountll(mask);
+    }
+    if (Steady)
+      ring[d] = load_raw_inner<DT>((const char*)rowp + (size_t)(t + kRing * W) * kTile * elem_bytes<DT>(), lane_bytes);
+    else if (i + kRing < my_tiles)
+      ring[d] = load_tile(t + kRing * W);
+    if ((d + 1) % Lim::kCheckTiles == 0 && n > Lim::kCompactAt) {
+      compact_list<DT, W>(my_raw, my_id, a.V, n, thr);
+      flooded = flooded || n < Lim::kKeepMin / 2;
+    }
+  };
+  const int steady_end = my_tiles > 2 * kRing ? ((my_tiles - kRing - 1) / kRing) * kRing : 0;
+  int i0 = 0;
+#pragma unroll 1
+  for (; i0 < steady_end; i0 += kRing) {
+#pragma unroll
+    for (int d = 0; d < kRing; ++d) iteration(std::true_type{}, d, i0 + d);
+    // Ties at the wave's largest logits: the kept set most likely reaches down to them, and they are not in the
+    // list.  Given up early, such a row costs the general search and a few tiles (76032 equal logits, B = 256: 29.1 us
+    // instead of 49.1, the general search alone 26.4).
+    if (flooded && n < Lim::kKeepMin / 4 && ++dry == 2) {
+      thr = __builtin_huge_valf();  // nothing is above it: the row is handed on
+      i0 = my_tiles;
+      break;
+    }
+  }
+#pragma unroll 1
+  for (; i0 < my_tiles; i0 += kRing) {
+#pragma unroll
+    for (int d = 0; d < kRing; ++d)
+      if (i0 + d < my_tiles) iteration(std::false_type{}, d, i0 + d);  // wave-uniform
+  }
+  const float mw = wave_max(mx), loww = -wave_max(-low), leastw = -wave_max(-mx);
+  if (lane == 0) {
+    f.least[wave] = leastw;
+    f.m[wave] = mw;
+    f.thr[wave] = thr;
+    f.low[wave] = loww;
+  }
+  float z_prev = 0.0f, value = 0.0f;  // wanted at the very end: fetched now, off the critical path
+  if (tid == 0) {
+    z_prev = a.z[row];
+    value = a.values[row];
+  }
+  __syncthreads();
+
+  // ------------------------------------------------------------ m, T and S
+  const float m = wave_max(lane < W ? f.m[lane] : kNegInf);
+  float bottom = wave_max(lane < W ? f.thr[lane] : kNegInf);  // every logit above it is in a list
+  if (!(bottom > kNegInf)) {  // no list was ever compacted: the smallest pack maximum leaves a logit of every pack above
+    const float lowest = -wave_max(lane < W ? -f.low[lane] : kNegInf);
+    const int32_t bits = __builtin_bit_cast(int32_t, lowest);
+    bottom = lowest == 0.0f ? -1.401298464e-45f : __builtin_bit_cast(float, bits + (lowest > 0.0f ? -1 : 1));
+  }
+  {
+    const float shift = -fmaf(m, a.k2, nrk);  // from this lane's reference to the row maximum
+    const float g = __builtin_amdgcn_exp2f(shift);
+    const float tot = wave_sum(sum > 0.0f ? sum * g : 0.0f);
+    if (lane == 0) f.sum[wave] = tot;
+    if constexpr (Entropy) {
+      const float totw = wave_sum(sum > 0.0f ? g * fmaf(shift, sum, sumw) : 0.0f);
+      if (lane == 0) f.sumw[wave] = totw;
+    }
+  }
+  __syncthreads();
+  const float S = wave_sum(lane < W ? f.sum[lane] : 0.0f);
+  int32_t tok = -1;
+  float x_a = 0.0f;
+  if (m > kNegInf) {
+    if (!(bottom < m)) return false;  // ties at the row's largest logit fill a list
+    PackList<DT, W> packs{f, n, a.V, {}};
+    DrawResult res = draw_from_list<DT, W>(a, f, packs, row, m, S, bottom, tok, x_a);
+    if (res == kReachesBelow) {
+      // A flat row: the row is read once more and its single logits above a lower floor are collected, the smallest
+      // of the lanes' largest logits.  (Of n lanes with V / n values each, about n ln n values of the row lie above the
+      // smallest maximum: 3200 with 8 waves, 7100 with 16, whatever V is.)
+      const float floor2 = -wave_max(lane < W ? -f.least[lane] : kNegInf);
+      if (!(floor2 < bottom && floor2 > kNegInf)) return false;
+      __syncthreads();  // the packs and the bins have been read by everyone
+      for (int b = tid; b < kEdgeBins; b += W * kWave) f.bins[b] = 0;
+      if (tid == 0) {
+        *f.nkept = 0;
+        *f.nmem = 0;
+        *f.nover = 0;
+      }
+      LogitList<DT, W> logits{f, 0};
+      constexpr int kDeep = 6;
+#pragma unroll 1
+      for (int i1 = 0; i1 < my_tiles; i1 += kDeep) {
+        Raw<DT> raw[kDeep];
+#pragma unroll
+        for (int d = 0; d < kDeep; ++d)
+          if (i1 + d < my_tiles) raw[d] = load_tile((i1 + d) * W + wave);
+#pragma unroll
+        for (int d = 0; d < kDeep; ++d) {
+          if (i1 + d < my_tiles) {
+            float x[8];
+            const int32_t v0 = ((i1 + d) * W + wave) * kTile + (int32_t)lane_off;
+            pack_unpack<DT>(raw[d], v0, a.V, x);
+            if (__builtin_amdgcn_ballot_w64(max8(x) > floor2) != 0) {
+#pragma unroll
+              for (int j = 0; j < 8; ++j) {
+                const uint64_t mask = __builtin_amdgcn_ballot_w64(x[j] > floor2);
+                if (mask != 0) {
+                  const int i = logits.n + rank_below(mask);
+                  if (x[j] > floor2 && i < LogitList<DT, W>::kRoom) logits.put(wave, i, v0 + j, x[j]);
+                  logits.n += (int)__builtin_popcountll(mask);
+                }
+              }
+            }
+          }
+        }
+      }
+      __syncthreads();  // the counters are zero
+      if (logits.n > LogitList<DT, W>::kRoom && lane == 0) *f.nover = 1;
+      __syncthreads();
+      if (*f.nover != 0) return false;
+      res = draw_from_list<DT, W>(a, f, logits, row, m, S, floor2, tok, x_a);
+    }
+    if (res != kDrawn) return false;
+  }
+
+  if (wave != 0) return true;
+  float Sw = 0.0f;
+  if constexpr (Entropy) Sw = wave_sum(lane < W ? f.sumw[lane] : 0.0f);
+  if (lane == 0) finish_row<DT, Entropy, true>(a, row, rowp, tok, x_a, m, S, Sw, z_prev, value);
+  return true;
+}
+
+template <int DT, bool Entropy, int W>
+// Registers: 107 per lane, two workgroups of 8 waves on a compute unit or one of 16.
+__global__ __launch_bounds__(W * kWave, 4) void espo_filtered_kernel(StepArgs a) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  const int row = (int)blockIdx.x;
+  if (!row_is_done(a.alive, row)) {
+    if (filtered_row<DT, Entropy, W>(a, smem_raw, row)) return;
+    __syncthreads();  // the general search uses the same shared memory
+  }
+  step_row<DT, Entropy, true, true, W>(a, smem_raw);
+}
+
+template <int DT, int W>
+const void* pick_kernel(bool sum, bool filter, bool entropy) {
+  if constexpr (W >= 8) {
+    if (filter) return entropy ? (const void*)espo_filtered_kernel<DT, true, W> : (const void*)espo_filtered_kernel<DT, false, W>;
+  }
+  if (!sum) return (const void*)espo_step_kernel<DT, false, false, W>;
+  return entropy ? (const void*)espo_step_kernel<DT, true, true, W> : (const void*)espo_step_kernel<DT, false, true, W>;
+}
+
+template <int DT>
+const void* pick_kernel(int waves, bool sum, bool filter, bool entropy) {
+  return waves == 16 ? pick_kernel<DT, 16>(sum, filter, entropy) : waves == 8 ? pick_kernel<DT, 8>(sum, filter, entropy)
+         : waves == 4 ? pick_kernel<DT, 4>(sum, filter, entropy) : nullptr;
+}
+
+}  // namespace
+
+// This file is compiled once per logit type (the kernels take most of the build's time): with ESPO_STEP_F32
+// defined for the fp32 kernels alone, without it for the bf16 kernels and everything below.
+#ifdef ESPO_STEP_F32
+const void* step_kernel_f32(int waves, bool sum, bool filter, bool entropy) { return pick_kernel<ESPO_F32>(waves, sum, filter, entropy); }
+#else
+const void* step_kernel_f32(int waves, bool sum, bool filter, bool entropy);
+const void* step_kernel_bf16(int waves, bool sum, bool filter, bool entropy) { return pick_kernel<ESPO_BF16>(waves, sum, filter, entropy); }
+
+namespace {
 
 // Measures what score_margin assumes about the hardware transcendentals: the largest relative
 // error of flog over every u(w) and over positive floats from 2^-26 to 64, and of fexp over
@@ -1678,25 +2051,24 @@ constexpr int64_t kEightWavesFrom = 256;
 StepPlan plan_step(int dt, int64_t B, int64_t V, bool filter, int waves, int chunks) {
   StepPlan p;
   const int ntiles = (int)((V + kTile - 1) / kTile);
-  p.waves = waves > 0 ? waves : filter || B >= kEightWavesFrom ? 8 : 16;
+  p.waves = waves > 0 ? waves : B >= kEightWavesFrom ? 8 : 16;
   int nch = filter || chunks <= 0 ? 1 : chunks;
   if (nch > ntiles) nch = ntiles;
   if (nch > kMaxChunks) nch = kMaxChunks;
   p.chunks = nch;
   p.grid = B * nch;
   const int ctiles = (ntiles + nch - 1) / nch;
-  p.lds = step_lds_bytes(dt, ctiles, filter, p.waves);
+  auto lds = [&](int w) {
+    const size_t tables = step_lds_bytes(dt, ctiles, filter, w);
+    if (!filter) return tables;
+    const size_t lists = dt == ESPO_BF16 ? (w == 8 ? filter_lds_bytes<ESPO_BF16, 8>() : filter_lds_bytes<ESPO_BF16, 16>())
+                                         : (w == 8 ? filter_lds_bytes<ESPO_F32, 8>() : filter_lds_bytes<ESPO_F32, 16>());
+    return std::max(tables, lists);
+  };
+  p.lds = lds(p.waves);
+  if (filter && waves <= 0 && p.lds > kMaxStepLds) p.lds = lds(p.waves = 8);  // the widest vocabularies: 8 waves need less
   p.workspace = nch > 1 ? step_workspace_layout(B, nch, nullptr) : 0;
   return p;
-}
-
-template <int DT, int W>
-void (*pick_kernel(bool sum, bool filter, bool entropy))(StepArgs) {
-  if constexpr (W == 8) {
-    if (filter) return entropy ? espo_step_kernel<DT, true, true, true, 8> : espo_step_kernel<DT, false, true, true, 8>;
-  }
-  if (!sum) return espo_step_kernel<DT, false, false, false, W>;
-  return entropy ? espo_step_kernel<DT, true, false, true, W> : espo_step_kernel<DT, false, false, true, W>;
 }
 
 int launch_step(const void* logits, int dt, int64_t B, int64_t V, int64_t row_stride, float temperature,
@@ -1752,28 +2124,22 @@ int launch_step(const void* logits, int dt, int64_t B, int64_t V, int64_t row_st
   // and so does a filtered draw (more passes over the row)
   const bool filter = (p.top_p > 0.0f && p.top_p < 1.0f) || p.top_k > 0;
   if (plan.lds > kMaxStepLds) return ESPO_ERANGE;
-  if (filter && (plan.waves != 8 || plan.chunks != 1)) return ESPO_EINVAL;
+  if (filter && (plan.waves < 8 || plan.chunks != 1)) return ESPO_EINVAL;
   if (plan.chunks > a.ntiles || plan.chunks > kMaxChunks || (int64_t)B * plan.chunks > 0x7fffffff) return ESPO_ERANGE;
   // and a step that is asked for neither log-probabilities nor either of these needs no softmax sum at all
   const bool sum = logprob != nullptr || entropy != nullptr || filter;
-  void (*kernel)(StepArgs) = nullptr;
   const bool ent = entropy != nullptr;
-  if (dt == ESPO_BF16)
-    kernel = plan.waves == 16 ? pick_kernel<ESPO_BF16, 16>(sum, filter, ent)
-             : plan.waves == 8 ? pick_kernel<ESPO_BF16, 8>(sum, filter, ent)
-             : plan.waves == 4 ? pick_kernel<ESPO_BF16, 4>(sum, filter, ent) : nullptr;
-  else
-    kernel = plan.waves == 16 ? pick_kernel<ESPO_F32, 16>(sum, filter, ent)
-             : plan.waves == 8 ? pick_kernel<ESPO_F32, 8>(sum, filter, ent)
-             : plan.waves == 4 ? pick_kernel<ESPO_F32, 4>(sum, filter, ent) : nullptr;
+  const void* const kernel = dt == ESPO_BF16 ? step_kernel_bf16(plan.waves, sum, filter, ent) : step_kernel_f32(plan.waves, sum, filter, ent);
   if (!kernel) return ESPO_EINVAL;
   if (plan.lds > 64 * 1024) {  // beyond the default limit the kernel has to be told (very large vocabularies)
-    if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxStepLds) != hipSuccess)
+    if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxStepLds) != hipSuccess)
       return ESPO_EHIP;
   }
   const dim3 grid((unsigned)plan.grid), block((unsigned)(plan.waves * kWave));
-  hipLaunchKernelGGL(kernel, grid, block, plan.lds, stream, a);
-  return hipGetLastError() == hipSuccess ? ESPO_OK : ESPO_EHIP;
+  void* args[] = {&a};
+  return hipLaunchKernel(kernel, grid, block, args, plan.lds, stream) == hipSuccess ? ESPO_OK : ESPO_EHIP;
 }
+
+#endif  // ESPO_STEP_F32
 
 }  // namespace espo

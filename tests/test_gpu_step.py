@@ -840,6 +840,40 @@ def test_top_p_at_the_edge_of_the_kept_set_is_decided_like_the_oracle():
                 H.compare_step(x.cuda(), tau, 99, step, torch.zeros(B, device="cuda"), gp, op, st)
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("order", ["ascending", "descending", "clustered", "tied"])
+def test_filtered_draws_whatever_order_the_logits_come_in(order, dtype):
+    _say(f"[case] filtered draws, largest logits {order} {dtype}")
+    # A wave collects its largest logits in a list whose threshold rises while the row streams.  Ascending rows
+    # raise it at every tile, descending ones fill it once, clustered ones put eight of the largest logits into each
+    # group of eight, and tied ones put 255 to 3100 equal logits at the edge of the kept set (what a bin's members,
+    # a list and the kept logits have room for, and one more).
+    B = 6
+    for V, tau, f in [(30011, 1.0, dict(top_k=1)), (30011, 1.0, dict(top_p=0.7)), (30011, 2.0, dict(top_p=0.9)), (30011, 1.0, dict(top_k=300)),
+                      (30011, 1.0, dict(top_k=3072)), (30011, 1.0, dict(top_k=3073)), (511, 1.0, dict(top_p=0.8)), (4096, 0.5, dict(top_k=40))]:
+        g = torch.Generator().manual_seed(V + int(10 * tau))
+        x = (torch.randn(B, V, generator=g) * 2.0).sort(dim=1, descending=order == "descending")[0]
+        if order == "clustered":                              # groups of eight neighbours, in random order
+            pad = (-V) % 8
+            y = torch.nn.functional.pad(x, (pad, 0), value=-9.0).view(B, -1, 8)
+            x = y[:, torch.randperm(y.shape[1], generator=g)].reshape(B, -1)[:, :V]
+        elif order == "tied":
+            for b, n in enumerate((255, 256, 257, 1025, 3071, 3100)):
+                n = min(n, V - 8)
+                x[b] = x[b].clamp(max=1.0)
+                x[b, torch.randperm(V, generator=g)[:n]] = 3.0
+                x[b, 5] = 4.0
+        stride = (V + 7) // 8 * 8
+        logits = torch.nn.functional.pad(x, (0, stride - V), value=1e4).to(dtype).cuda()
+        gp, op = H.params_pair(mu_g=1.0, var_g=2.0, beta=3.0, stop_enabled=0, **f)
+        st = H.GpuState(B)
+        for step in range(2):
+            try:
+                H.compare_step(logits, tau, 83, step, torch.zeros(B, device="cuda"), gp, op, st, V=V, entropy=step == 1)
+            except AssertionError as err:
+                raise AssertionError(f"V={V} tau={tau} {f} step {step}: {err}")
+
+
 # --------------------------------------------------------------------------- HIP graph capture
 def test_steps_captured_in_a_graph_replay_like_eager_launches():
     _say("[case] graph capture and replay")
