@@ -433,7 +433,7 @@ size_t espo_whiten_workspace_bytes(int64_t B, int64_t T);
  *
  * espo_whiten_from_ws is espo_whiten for an `adv` that one of the two has just written,
  * with the same B, T, lengths and workspace: mean and variance are merged from the rows' sums
- * (pairwise, in a fixed order, in double) instead of by a first pass over adv, so only the
+ * (in a fixed order, in double) instead of by a first pass over adv, so only the
  * rewrite remains.  The two ways of summing differ by rounding: mean and variance agree with
  * espo_whiten's to about 1e-14 relative, `out` to the last bit or one unit of it.
  *

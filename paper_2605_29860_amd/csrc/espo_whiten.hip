@@ -2,14 +2,25 @@
 // PPO applies to the GAE output before the clipped objective (the paper keeps the standard PPO
 // update, Section 3):  out = (A - mean) / sqrt(var + eps), mean and var over all A[b, t < L_b].
 //
-// Two launches over the same decomposition.  The batch is cut into items of 4096 consecutive
-// tokens of one row, numbered chunk position first so that a workgroup, which takes items
-// w, w + G, ..., sees every chunk position; every lane moves 16 bytes per item.  The first launch reduces each workgroup's items to (n, sum d, sum d^2) in double, with
-// d = A - shift and shift the first valid token of the batch: a shift that is itself a data
-// value keeps the one-pass variance free of cancellation however far the mean is from zero.
-// The second launch starts by adding the at most 512 partials in a fixed tree (every workgroup
-// gets the same bits whatever the scheduling), then rewrites its items.  Each element is normalised in
-// double and rounded to float once.  Positions at t >= L_b are neither read nor written.
+// Two launches over the same decomposition.  The batch is cut into items of 1024 positions of
+// one row, which start at 16-byte boundaries whatever the row length is and which a wave moves with
+// four 16-byte accesses per lane.  The first launch reduces each workgroup's items to
+// (n, sum d, sum d^2) in double, with d = A - shift and shift the first valid token of the batch: a
+// shift that is itself a data value keeps the one-pass variance free of cancellation however far
+// the mean is from zero.  The second launch adds the at most 512 partials in a fixed tree (every
+// workgroup gets the same bits whatever the scheduling) while its first items are on their way from
+// memory, then rewrites its items.  Each element is normalised in double and rounded to float once.
+// A batch of at most 16384 positions is one launch of one workgroup that keeps it in registers.
+// Positions at t >= L_b are neither read nor written.
+//
+// Bound by memory from some 10 MB on, below that by the two launches' latency (load lengths, load
+// tokens, reduce, store).  us per call, before -> now (before: items of 4096 positions and one
+// workgroup-wide access each, the sums merged before the first load, element-wise accesses for odd T):
+// B = 1024, T = 16384, lengths U[512, T]: 36.7 -> 27.2 (104 MB), from the rows' sums 23.9 -> 18.0 (69 MB,
+// 3.8 TB/s); B = 512, T = 8192: 18.1 -> 14.0; B = 4, T = 128: 9.8 -> 4.1.  The nontemporal accesses stay:
+// plain loads in the first launch take 3 us off the largest batch's second one, but leave the
+// next pass over other arrays 1.2 us slower on the B = 512 batch.  One workgroup against two launches:
+// 6.2 against 9.9 us for 8000 positions, 8.0 against 8.9 for 16384, so the line is there.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -23,13 +34,16 @@ namespace {
 
 constexpr int kWhThreads = 1024;
 constexpr int kWhWaves = kWhThreads / kWave;
-constexpr int kWhItem = kWhThreads * 4;  // tokens per item
-constexpr int kWhMaxGroups = 512;  // one workgroup per slot of the chip
+constexpr int kWhQuads = 4;                         // groups of four positions per lane and item
+constexpr int kWhItem = kWave * 4 * kWhQuads;       // positions per item: 1024
+constexpr int kWhUnroll = 2;                        // items of a wave whose loads are in flight together
+constexpr int kWhMaxGroups = 512;                   // one workgroup per slot of the chip
+constexpr int kWhSmallQuads = 4;                    // groups of four positions per lane of the one-workgroup form
+constexpr int64_t kWhSmall = (int64_t)kWhThreads * 4 * kWhSmallQuads;
+constexpr uint32_t kWhSkew = 389;                   // rows between a wave's items of neighbouring chunk positions
 
-struct WhPartial {
-  double s1, s2, shift;
-  long long n;
-};
+// Sums of some tokens about a shift of their own: the same fields as AdvRowStats.
+using Sums = AdvRowStats;
 
 struct WhArgs {
   const float* adv;
@@ -41,267 +55,333 @@ struct WhArgs {
   int shift_mean, ddof;
   float* out;
   double* stats;  // optional [3]: mean, var, n
-  WhPartial* part;
+  Sums* part;     // [groups]
 };
 
-// Sum over the workgroup in a fixed tree, returned to every thread.
-__device__ __forceinline__ double block_sum_all(double v, double* lds) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) v += shfl_down_f64(v, d);
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
-  __syncthreads();  // lds may still be read from the call before
-  if (lane == 0) lds[wave] = v;
-  __syncthreads();
-  double t = 0.0;
-  for (int w = 0; w < kWhWaves; ++w) t += lds[w];
-  return t;
+__device__ __forceinline__ double lane_f64(double v, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane), __builtin_amdgcn_readlane(__double2loint(v), lane));
 }
 
-// One pass of a workgroup over its items, four at a time with their loads issued together.
-// An item is (row, first token); `whole(g, t)` gets the four tokens of a lane that lies wholly
-// inside the trajectory, `single(x, t)` a token of a lane that the trajectory's end cuts.
-constexpr int kWhUnroll = 4;  // eight spill: three 64-bit offsets per item in flight
-template <bool VEC, typename Whole, typename Single, typename Count>
-__device__ __forceinline__ void for_items(const WhArgs& a, Whole&& whole, Single&& single, Count&& count) {
-  const int tid = threadIdx.x;
-  for (uint32_t it0 = blockIdx.x; it0 < (uint32_t)a.items; it0 += kWhUnroll * (uint32_t)a.groups) {
-    int64_t base[kWhUnroll], t[kWhUnroll], L[kWhUnroll];
-#pragma unroll
-    for (int u = 0; u < kWhUnroll; ++u) {
-      const uint32_t it = it0 + (uint32_t)u * (uint32_t)a.groups;
-      L[u] = 0;
-      base[u] = 0;
-      t[u] = 0;
-      if (it < (uint32_t)a.items) {
-        const uint32_t ch = it / (uint32_t)a.B, row = it - ch * (uint32_t)a.B;  // chunk-major: a workgroup sees every chunk position
-        const int64_t len = a.lengths[row];
-        L[u] = len < 0 ? 0 : (len > a.T ? a.T : len);
-        base[u] = (int64_t)row * a.T;
-        t[u] = (int64_t)ch * kWhItem + (VEC ? tid * 4 : tid);
-        const int64_t left = L[u] - (int64_t)ch * kWhItem;
-        count(left < 0 ? 0 : (left < kWhItem ? left : kWhItem));  // valid tokens of the item
-      }
-    }
-    if (VEC) {  // T % 4 == 0: every row is 16-byte aligned
-      f32x4 g[kWhUnroll];
-#pragma unroll
-      for (int u = 0; u < kWhUnroll; ++u)
-        if (t[u] + 4 <= L[u]) g[u] = __builtin_nontemporal_load((const f32x4*)(a.adv + base[u] + t[u]));
-#pragma unroll
-      for (int u = 0; u < kWhUnroll; ++u) {
-        if (t[u] + 4 <= L[u]) {
-          whole(g[u], base[u] + t[u]);
-        } else {
-          for (int j = 0; j < 4 && t[u] + j < L[u]; ++j) single(a.adv[base[u] + t[u] + j], base[u] + t[u] + j);
-        }
-      }
-    } else {
-#pragma unroll
-      for (int u = 0; u < kWhUnroll; ++u)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int64_t tt = t[u] + (int64_t)j * kWhThreads;
-          if (tt < L[u]) single(a.adv[base[u] + tt], base[u] + tt);
-        }
-    }
+// An item (uniform in the wave): where it starts in the flat array, a multiple of 4, and which of its positions
+// hold valid tokens of its row.
+struct Item {
+  int64_t start;
+  int32_t lo, hi;
+};
+
+// Items are numbered chunk position first, so the waves of a workgroup and their successive items see all chunk
+// positions; the rows are turned by kWhSkew from one chunk position to the next, so that the items a compute unit
+// gets come from different rows (without that, one that drew two long rows had all their chunks:
+// 18.6 against 18.0 us for the rewrite of a B = 1024, T = 16384 batch).
+__device__ __forceinline__ Item item_of(const WhArgs& a, uint32_t it) {
+  Item im{0, 0, 0};
+  if (it < (uint32_t)a.items) {
+    const uint32_t ch = it / (uint32_t)a.B, row = (it - ch * (uint32_t)a.B + ch * kWhSkew) % (uint32_t)a.B;
+    int64_t L = a.lengths[row];
+    L = L < 0 ? 0 : (L > a.T ? a.T : L);
+    const int64_t first = (int64_t)row * a.T, head = first & 3, off = (int64_t)ch * kWhItem;
+    im.start = first - head + off;
+    im.lo = ch == 0 ? (int32_t)head : 0;
+    const int64_t left = L + head - off;
+    im.hi = (int32_t)(left < 0 ? 0 : (left < kWhItem ? left : kWhItem));
+    if (L == 0) im.hi = 0;
   }
+  return im;
 }
 
-// From the batch's count, mean and sum of squared deviations to the rewrite of this workgroup's items.
-template <bool VEC>
-__device__ __forceinline__ void normalise_items(const WhArgs& a, double n, double mean, double ss) {
-  const int tid = threadIdx.x;
-  if (n == 0.0) {  // no valid token in the batch: nothing to write
-    if (a.stats && blockIdx.x == 0 && tid < 3) a.stats[tid] = 0.0;
-    return;
-  }
-  if (ss < 0.0) ss = 0.0;
-  const double denom = n - (double)a.ddof;
-  const double var = denom > 0.0 ? ss / denom : 0.0;
-  const double sd = sqrt(var + (double)a.eps);
-  const double rstd = sd > 0.0 ? 1.0 / sd : 0.0;  // a constant batch with eps = 0: every output is 0
-  const double sub = a.shift_mean ? mean : 0.0;
-  if (a.stats && blockIdx.x == 0 && tid == 0) {
-    a.stats[0] = mean;
-    a.stats[1] = var;
-    a.stats[2] = n;
-  }
-  for_items<VEC>(
-      a,
-      [&](const f32x4& g, int64_t at) {
-        f32x4 o;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) o[j] = rstd > 0.0 ? (float)(((double)g[j] - sub) * rstd) : 0.0f;
-        __builtin_nontemporal_store(o, (f32x4*)(a.out + at));
-      },
-      [&](float x, int64_t at) { a.out[at] = rstd > 0.0 ? (float)(((double)x - sub) * rstd) : 0.0f; }, [](int64_t) {});
+// Item k of this wave: the waves of one workgroup take items a whole grid apart.
+__device__ __forceinline__ uint32_t item_index(const WhArgs& a, int k) {
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  return ((uint32_t)k * kWhWaves + wave) * (uint32_t)a.groups + blockIdx.x;
 }
 
-template <bool VEC>
-__global__ __launch_bounds__(kWhThreads) void whiten_partial_kernel(WhArgs a) {
-  __shared__ double lds[kWhWaves];
-  const int tid = threadIdx.x;
-  // the shift: the first valid token of the batch (the same in every workgroup)
-  double shift = 0.0;
-  for (int64_t b = 0; b < a.B; ++b)
-    if (a.lengths[b] > 0) {
-      shift = (double)a.adv[b * a.T];
-      break;
+// This lane's four tokens at position t of an item, and which of them are valid (bit j).
+__device__ __forceinline__ uint32_t load_quad(const float* __restrict__ src, const Item& im, int t, f32x4& g) {
+  if (t >= im.lo && t + 4 <= im.hi) {
+    g = __builtin_nontemporal_load((const f32x4*)(src + im.start + t));
+    return 0xfu;
+  }
+  uint32_t in = 0;
+  g = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    if (t + j >= im.lo && t + j < im.hi) {
+      g[j] = src[im.start + t + j];
+      in |= 1u << j;
     }
-  long long n = 0;
+  return in;
+}
+
+__device__ __forceinline__ int quad_at(int q) { return q * kWave * 4 + (int)(threadIdx.x & (kWave - 1)) * 4; }
+
+// ---------------------------------------------------------------- sums
+// A lane's running sums about a shift that is the same in the whole batch.
+struct LaneSums {
   double s1 = 0.0, s2 = 0.0;
-  for_items<VEC>(
-      a,
-      [&](const f32x4& g, int64_t) {
+  int n = 0;  // tokens of the wave
+  __device__ __forceinline__ void add(const f32x4& g, uint32_t in, double shift) {
+    if (__builtin_amdgcn_ballot_w64(in != 0xfu) == 0) {
+      n += 4 * kWave;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const double d = (double)g[j] - shift;
-          s1 += d;
-          s2 += d * d;
-        }
-      },
-      [&](float x, int64_t) {
-        const double d = (double)x - shift;
+      for (int j = 0; j < 4; ++j) {
+        const double d = (double)g[j] - shift;
         s1 += d;
-        s2 += d * d;
-      },
-      [&](int64_t valid) { n += valid; });
-  const double t1 = block_sum_all(s1, lds);
-  const double t2 = block_sum_all(s2, lds);
-  if (tid == 0) a.part[blockIdx.x] = WhPartial{t1, t2, shift, n};
+        s2 = fma(d, d, s2);
+      }
+    } else if (__builtin_amdgcn_ballot_w64(in != 0) != 0) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        n += (int)__builtin_popcountll(__builtin_amdgcn_ballot_w64((in >> j) & 1u));
+        const double d = (in >> j) & 1u ? (double)g[j] - shift : 0.0;
+        s1 += d;
+        s2 = fma(d, d, s2);
+      }
+    }
+  }
+};
+
+// Sum over the first 16 lanes, returned to the wave.
+__device__ __forceinline__ double row_sum_f64(double v) {
+  v += dpp_f64<kDppRowShr1, 0xf>(v);
+  v += dpp_f64<kDppRowShr2, 0xf>(v);
+  v += dpp_f64<kDppRowShr4, 0xf>(v);
+  v += dpp_f64<kDppRowShr8, 0xf>(v);
+  return lane_f64(v, 15);
 }
 
-template <bool VEC>
-__global__ __launch_bounds__(kWhThreads) void whiten_apply_kernel(WhArgs a) {
-  __shared__ double lds[3 * kWhWaves];
-  const int tid = threadIdx.x;
-  const int lane = tid & (kWave - 1), wave = tid >> 6;
-  // combine the partials (all about the same shift): thread i holds partial i
-  WhPartial mine{0.0, 0.0, 0.0, 0};
-  if (tid < a.groups) mine = a.part[tid];
-  double v0 = (double)mine.n, v1 = mine.s1, v2 = mine.s2;  // counts are below 2^53: exact
+// Three sums over the workgroup in a fixed tree, the same in every thread; lds holds 3 * kWhWaves entries.
+__device__ __forceinline__ void block_sums(double v[3], double* lds) {
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
 #pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) {
-    v0 += shfl_down_f64(v0, d);
-    v1 += shfl_down_f64(v1, d);
-    v2 += shfl_down_f64(v2, d);
-  }
+  for (int i = 0; i < 3; ++i) v[i] = wave_sum_f64(v[i]);
   if (lane == 0) {
-    lds[wave] = v0;
-    lds[kWhWaves + wave] = v1;
-    lds[2 * kWhWaves + wave] = v2;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) lds[i * kWhWaves + wave] = v[i];
   }
   __syncthreads();
-  double n = 0.0, s1 = 0.0, s2 = 0.0;
-  for (int w = 0; w < kWhWaves; ++w) {  // fixed order: the same bits in every workgroup
-    n += lds[w];
-    s1 += lds[kWhWaves + w];
-    s2 += lds[2 * kWhWaves + w];
-  }
-  const double shift = a.part[0].shift;
-  const double md = n > 0.0 ? s1 / n : 0.0;
-  normalise_items<VEC>(a, n, shift + md, s2 - n * md * md);  // s2 - n md^2: the sum of squared deviations from the mean
+  static_assert(kWhWaves == 16, "one row of lanes holds the waves' sums");
+#pragma unroll
+  for (int i = 0; i < 3; ++i) v[i] = row_sum_f64(lane < kWhWaves ? lds[i * kWhWaves + lane] : 0.0);
 }
 
-// The same rewrite with the mean and variance combined from sums that the advantage pass left per row,
-// each about a shift of that row's own: every row gives (n, mean, sum of squared deviations), and two
-// such triples merge exactly (the pairwise update of Chan, Golub and LeVeque).  Thread i merges rows
-// i, i + 1024, ...; lanes and waves follow in a fixed tree, so every workgroup gets the same bits.
+// The first valid token of the batch, as its shift (0 without any).
+__device__ __forceinline__ double batch_shift(const WhArgs& a) {
+  for (int64_t b = 0; b < a.B; ++b)
+    if (a.lengths[b] > 0) return (double)a.adv[b * a.T];
+  return 0.0;
+}
+
+// What a set of sums amounts to: count, mean, and sum of squared deviations from it.
 struct Moments {
   double n, mean, m2;
 };
 
-__device__ __forceinline__ double shfl_lane0_f64(double v) {
-  return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)), __builtin_amdgcn_readfirstlane(__double2loint(v)));
-}
-
-__device__ __forceinline__ Moments merge(const Moments& x, const Moments& y) {
-  const double n = x.n + y.n;
-  if (n == 0.0) return Moments{0.0, 0.0, 0.0};
-  const double delta = y.mean - x.mean;
-  return Moments{n, x.mean + delta * (y.n / n), x.m2 + y.m2 + delta * delta * (x.n * (y.n / n))};
-}
-
-template <bool VEC>
-__global__ __launch_bounds__(kWhThreads) void whiten_apply_rows_kernel(WhArgs a, const AdvRowStats* __restrict__ rows) {
+__global__ __launch_bounds__(kWhThreads, 8) void whiten_partial_kernel(WhArgs a) {
   __shared__ double lds[3 * kWhWaves];
-  const int tid = threadIdx.x;
-  const int lane = tid & (kWave - 1), wave = tid >> 6;
-  Moments mine{0.0, 0.0, 0.0};
-  for (int64_t b = tid; b < a.B; b += kWhThreads) {
-    const AdvRowStats r = rows[b];
-    if (r.n > 0) {
-      const double n = (double)r.n, md = r.s1 / n;
-      const double m2 = r.s2 - n * md * md;
-      mine = merge(mine, Moments{n, r.shift + md, m2 > 0.0 ? m2 : 0.0});
+  const double shift = batch_shift(a);
+  LaneSums w;
+  for (int k = 0; item_index(a, k) < (uint32_t)a.items; k += kWhUnroll) {
+    f32x4 g[kWhUnroll][kWhQuads];
+    uint32_t in[kWhUnroll][kWhQuads];
+#pragma unroll
+    for (int u = 0; u < kWhUnroll; ++u) {
+      const Item im = item_of(a, item_index(a, k + u));
+#pragma unroll
+      for (int q = 0; q < kWhQuads; ++q) in[u][q] = load_quad(a.adv, im, quad_at(q), g[u][q]);
+    }
+#pragma unroll
+    for (int u = 0; u < kWhUnroll; ++u)
+#pragma unroll
+      for (int q = 0; q < kWhQuads; ++q) w.add(g[u][q], in[u][q], shift);
+  }
+  double v[3] = {w.s1, w.s2, (threadIdx.x & (kWave - 1)) == 0 ? (double)w.n : 0.0};
+  block_sums(v, lds);
+  if (threadIdx.x == 0) a.part[blockIdx.x] = Sums{v[0], v[1], shift, (long long)v[2]};
+}
+
+// ---------------------------------------------------------------- rewrite
+struct Scale {
+  double sub, rstd;
+};
+
+__device__ __forceinline__ Scale scale_of(const WhArgs& a, const Moments& m, bool report) {
+  const double denom = m.n - (double)a.ddof;
+  const double ss = m.m2 > 0.0 ? m.m2 : 0.0;
+  const double var = denom > 0.0 ? ss / denom : 0.0;
+  const double sd = sqrt(var + (double)a.eps);
+  if (report && a.stats) {
+    a.stats[0] = m.n > 0.0 ? m.mean : 0.0;
+    a.stats[1] = m.n > 0.0 ? var : 0.0;
+    a.stats[2] = m.n;
+  }
+  return Scale{a.shift_mean ? m.mean : 0.0, sd > 0.0 ? 1.0 / sd : 0.0};  // a constant batch with eps = 0: every output is 0
+}
+
+__device__ __forceinline__ float normalised(float x, const Scale& s) {
+  return s.rstd > 0.0 ? (float)(((double)x - s.sub) * s.rstd) : 0.0f;
+}
+
+__device__ __forceinline__ void store_quad(float* __restrict__ dst, const f32x4& g, uint32_t in, const Scale& s) {
+  if (in == 0xfu) {
+    __builtin_nontemporal_store(f32x4{normalised(g[0], s), normalised(g[1], s), normalised(g[2], s), normalised(g[3], s)}, (f32x4*)dst);
+    return;
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    if ((in >> j) & 1u) dst[j] = normalised(g[j], s);
+}
+
+// The moments of the batch from sums about a shift of each set's own, thread i taking sets i, i + 1024, ...; the
+// same bits in every workgroup.  Mean first, then the squared deviations from it (each set's about its own shift, moved to the
+// mean), so that nothing cancels however far the sets' levels are apart.  The sums on the way to the mean are about
+// one of the sets' shifts: a constant batch has its exact mean.
+__device__ __forceinline__ Moments moments_of_rows(const Sums* __restrict__ sets, int64_t count, Sums* lds, double* lds_m2) {
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+  Sums mine{0.0, 0.0, 0.0, 0};
+  double n = 0.0, s1 = 0.0, to = 0.0;
+  for (int64_t i = threadIdx.x; i < count; i += kWhThreads) {
+    mine = sets[i];
+    if (mine.n > 0) {
+      if (n == 0.0) to = mine.shift;
+      n += (double)mine.n;
+      s1 += fma((double)mine.n, mine.shift - to, mine.s1);
     }
   }
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) {
-    const Moments other{shfl_down_f64(mine.n, d), shfl_down_f64(mine.mean, d), shfl_down_f64(mine.m2, d)};
-    if (lane + d < kWave) mine = merge(mine, other);
-  }
-  if (lane == 0) {
-    lds[wave] = mine.n;
-    lds[kWhWaves + wave] = mine.mean;
-    lds[2 * kWhWaves + wave] = mine.m2;
+  {
+    const uint64_t who = __builtin_amdgcn_ballot_w64(n > 0.0);
+    const double wto = who != 0 ? lane_f64(to, (int)__builtin_ctzll(who)) : 0.0;
+    const double ws1 = wave_sum_f64(n > 0.0 ? fma(n, to - wto, s1) : 0.0), wn = wave_sum_f64(n);
+    if (lane == 0) lds[wave] = Sums{ws1, 0.0, wto, (long long)wn};
   }
   __syncthreads();
-  // the sixteen wave results, merged by the same tree in every wave
-  Moments all{0.0, 0.0, 0.0};
-  if (lane < kWhWaves) all = Moments{lds[lane], lds[kWhWaves + lane], lds[2 * kWhWaves + lane]};
-#pragma unroll
-  for (int d = kWhWaves / 2; d >= 1; d >>= 1) {
-    const Moments other{shfl_down_f64(all.n, d), shfl_down_f64(all.mean, d), shfl_down_f64(all.m2, d)};
-    if (lane + d < kWhWaves) all = merge(all, other);
+  Sums s{0.0, 0.0, 0.0, 0};
+  if (lane < kWhWaves) s = lds[lane];
+  const uint64_t who = __builtin_amdgcn_ballot_w64(s.n > 0);
+  to = who != 0 ? lane_f64(s.shift, (int)__builtin_ctzll(who)) : 0.0;
+  n = row_sum_f64((double)s.n);
+  s1 = row_sum_f64(s.n > 0 ? fma((double)s.n, s.shift - to, s.s1) : 0.0);
+  const double mean = n > 0.0 ? to + s1 / n : 0.0;
+  double m2 = 0.0;
+  auto deviations = [&](const Sums& x) {
+    const double d = x.shift - mean;
+    return x.n > 0 ? fma(d, fma((double)x.n, d, 2.0 * x.s1), x.s2) : 0.0;
+  };
+  if (count <= kWhThreads) {
+    m2 = deviations(mine);
+  } else {
+    for (int64_t i = threadIdx.x; i < count; i += kWhThreads) m2 += deviations(sets[i]);
   }
-  all = Moments{shfl_lane0_f64(all.n), shfl_lane0_f64(all.mean), shfl_lane0_f64(all.m2)};
-  normalise_items<VEC>(a, all.n, all.mean, all.m2);
+  m2 = wave_sum_f64(m2);
+  if (lane == 0) lds_m2[wave] = m2;
+  __syncthreads();
+  m2 = row_sum_f64(lane < kWhWaves ? lds_m2[lane] : 0.0);
+  return Moments{n, mean, m2};
 }
 
+// The same from at most kWhMaxGroups sets about one shift.
+__device__ __forceinline__ Moments moments_of_parts(const Sums* __restrict__ parts, int count, double* lds) {
+  Sums mine{0.0, 0.0, 0.0, 0};
+  if ((int)threadIdx.x < count) mine = parts[threadIdx.x];
+  double v[3] = {mine.s1, mine.s2, (double)mine.n};
+  const double shift = parts[0].shift;
+  block_sums(v, lds);
+  const double md = v[2] > 0.0 ? v[0] / v[2] : 0.0;
+  return Moments{v[2], shift + md, fma(-v[2] * md, md, v[1])};  // s2 - n md^2: the squared deviations from the mean
+}
+
+// The rewrite, from the sums of `count` rows or parts.  The first item's loads are issued before the sums are
+// merged, and every next one's before the current one is stored.
+template <bool Rows>
+__global__ __launch_bounds__(kWhThreads, 8) void whiten_apply_kernel(WhArgs a, const Sums* __restrict__ sets, int64_t count) {
+  __shared__ Sums lds[Rows ? kWhWaves : 1];
+  __shared__ double lds_d[3 * kWhWaves];
+  struct Held {
+    f32x4 g[kWhQuads];
+    uint32_t in;  // four bits per group of four
+    int64_t at;
+  };
+  auto fetch = [&](int k) {
+    Held h;
+    const Item im = item_of(a, item_index(a, k));
+    h.at = im.start;
+    h.in = 0;
+#pragma unroll
+    for (int q = 0; q < kWhQuads; ++q) h.in |= load_quad(a.adv, im, quad_at(q), h.g[q]) << (4 * q);
+    return h;
+  };
+  Held cur = fetch(0);
+  Moments m;
+  if constexpr (Rows) m = moments_of_rows(sets, count, lds, lds_d);
+  else m = moments_of_parts(sets, (int)count, lds_d);
+  const Scale s = scale_of(a, m, blockIdx.x == 0 && threadIdx.x == 0);
+  for (int k = 0; item_index(a, k) < (uint32_t)a.items; ++k) {
+    Held nxt;
+    const bool more = item_index(a, k + 1) < (uint32_t)a.items;
+    if (more) nxt = fetch(k + 1);
+#pragma unroll
+    for (int q = 0; q < kWhQuads; ++q) store_quad(a.out + cur.at + quad_at(q), cur.g[q], (cur.in >> (4 * q)) & 0xfu, s);
+    if (more) cur = nxt;
+  }
+}
+
+// A small batch in one launch: one workgroup holds all positions (rows of at least four) in registers.
+__global__ __launch_bounds__(kWhThreads) void whiten_small_kernel(WhArgs a) {
+  __shared__ double lds[3 * kWhWaves];
+  const uint32_t T = (uint32_t)a.T, total = (uint32_t)(a.B * a.T);
+  f32x4 g[kWhSmallQuads];
+  uint32_t in[kWhSmallQuads];
+  const int quads = (int)((total + 4 * kWhThreads - 1) / (4 * kWhThreads));
+#pragma unroll
+  for (int u = 0; u < kWhSmallQuads; ++u) {
+    in[u] = 0;
+    g[u] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    const uint32_t f = ((uint32_t)u * kWhThreads + threadIdx.x) * 4u;
+    if (u < quads && f < total) {  // the four positions lie in one row or at the end of it and the start of the next
+      const uint32_t row = f / T, t = f - row * T;
+      auto valid = [&](uint32_t r) {
+        const int32_t L = r < (uint32_t)a.B ? a.lengths[r] : 0;
+        return L < 0 ? 0u : min((uint32_t)L, T);
+      };
+      const uint32_t L0 = valid(row), L1 = t + 4u > T ? valid(row + 1u) : 0u;
+#pragma unroll
+      for (uint32_t j = 0; j < 4; ++j) in[u] |= (t + j < T ? t + j < L0 : t + j - T < L1) ? 1u << j : 0u;
+      if (in[u] == 0xfu) {
+        g[u] = *(const f32x4*)(a.adv + f);
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if ((in[u] >> j) & 1u) g[u][j] = a.adv[f + (uint32_t)j];
+      }
+    }
+  }
+  const double shift = batch_shift(a);
+  LaneSums w;
+#pragma unroll
+  for (int u = 0; u < kWhSmallQuads; ++u)
+    if (u < quads) w.add(g[u], in[u], shift);
+  double v[3] = {w.s1, w.s2, (threadIdx.x & (kWave - 1)) == 0 ? (double)w.n : 0.0};
+  block_sums(v, lds);
+  const double md = v[2] > 0.0 ? v[0] / v[2] : 0.0;
+  const Scale s = scale_of(a, Moments{v[2], shift + md, fma(-v[2] * md, md, v[1])}, threadIdx.x == 0);
+#pragma unroll
+  for (int u = 0; u < kWhSmallQuads; ++u)
+    if (u < quads) store_quad(a.out + ((uint32_t)u * kWhThreads + threadIdx.x) * 4u, g[u], in[u], s);
+}
+
+// One workgroup per 4096 positions of a row, up to what the chip holds.
 int whiten_groups(int64_t B, int64_t T) {
-  const int64_t nch = (T + kWhItem - 1) / kWhItem;
-  const int64_t items = B * nch;
-  return (int)(items < 1 ? 1 : (items > kWhMaxGroups ? kWhMaxGroups : items));
+  const int64_t want = B * ((T + 4095) / 4096);
+  return (int)(want < 1 ? 1 : (want > kWhMaxGroups ? kWhMaxGroups : want));
 }
 
-}  // namespace
-
-size_t whiten_workspace(int64_t B, int64_t T) { return (size_t)whiten_groups(B, T) * sizeof(WhPartial); }
-
-int launch_whiten(const float* adv, const int32_t* lengths, int64_t B, int64_t T, float eps, int shift_mean,
-                  int unbiased, float* out, double* stats, void* workspace, hipStream_t stream) {
+WhArgs whiten_args(const float* adv, const int32_t* lengths, int64_t B, int64_t T, float eps, int shift_mean, int unbiased,
+                   float* out, double* stats) {
   WhArgs a;
   a.adv = adv;
   a.lengths = lengths;
   a.B = B;
   a.T = T;
-  a.nch = (T + kWhItem - 1) / kWhItem;
-  a.items = B * a.nch;
-  a.groups = whiten_groups(B, T);
-  a.eps = eps;
-  a.shift_mean = shift_mean;
-  a.ddof = unbiased ? 1 : 0;
-  a.out = out;
-  a.stats = stats;
-  a.part = (WhPartial*)workspace;
-  const bool vec = (T % 4 == 0);
-  hipLaunchKernelGGL(vec ? whiten_partial_kernel<true> : whiten_partial_kernel<false>, dim3(a.groups), dim3(kWhThreads), 0,
-                     stream, a);
-  if (hipGetLastError() != hipSuccess) return ESPO_EHIP;
-  hipLaunchKernelGGL(vec ? whiten_apply_kernel<true> : whiten_apply_kernel<false>, dim3(a.groups), dim3(kWhThreads), 0,
-                     stream, a);
-  return hipGetLastError() == hipSuccess ? ESPO_OK : ESPO_EHIP;
-}
-
-int launch_whiten_rows(const float* adv, const int32_t* lengths, int64_t B, int64_t T, float eps, int shift_mean,
-                       int unbiased, float* out, double* stats, const AdvRowStats* rows, hipStream_t stream) {
-  WhArgs a;
-  a.adv = adv;
-  a.lengths = lengths;
-  a.B = B;
-  a.T = T;
-  a.nch = (T + kWhItem - 1) / kWhItem;
+  a.nch = (T + (T % 4 != 0 ? 3 : 0) + kWhItem - 1) / kWhItem;  // a row that starts between boundaries spans up to 3 positions more
   a.items = B * a.nch;
   a.groups = whiten_groups(B, T);
   a.eps = eps;
@@ -310,9 +390,31 @@ int launch_whiten_rows(const float* adv, const int32_t* lengths, int64_t B, int6
   a.out = out;
   a.stats = stats;
   a.part = nullptr;
-  const bool vec = (T % 4 == 0);
-  hipLaunchKernelGGL(vec ? whiten_apply_rows_kernel<true> : whiten_apply_rows_kernel<false>, dim3(a.groups),
-                     dim3(kWhThreads), 0, stream, a, rows);
+  return a;
+}
+
+}  // namespace
+
+size_t whiten_workspace(int64_t B, int64_t T) { return (size_t)whiten_groups(B, T) * sizeof(Sums); }
+
+int launch_whiten(const float* adv, const int32_t* lengths, int64_t B, int64_t T, float eps, int shift_mean,
+                  int unbiased, float* out, double* stats, void* workspace, hipStream_t stream) {
+  WhArgs a = whiten_args(adv, lengths, B, T, eps, shift_mean, unbiased, out, stats);
+  if (T >= 4 && B * T <= kWhSmall) {
+    hipLaunchKernelGGL(whiten_small_kernel, dim3(1), dim3(kWhThreads), 0, stream, a);
+    return hipGetLastError() == hipSuccess ? ESPO_OK : ESPO_EHIP;
+  }
+  a.part = (Sums*)workspace;
+  hipLaunchKernelGGL(whiten_partial_kernel, dim3(a.groups), dim3(kWhThreads), 0, stream, a);
+  if (hipGetLastError() != hipSuccess) return ESPO_EHIP;
+  hipLaunchKernelGGL(whiten_apply_kernel<false>, dim3(a.groups), dim3(kWhThreads), 0, stream, a, a.part, (int64_t)a.groups);
+  return hipGetLastError() == hipSuccess ? ESPO_OK : ESPO_EHIP;
+}
+
+int launch_whiten_rows(const float* adv, const int32_t* lengths, int64_t B, int64_t T, float eps, int shift_mean,
+                       int unbiased, float* out, double* stats, const AdvRowStats* rows, hipStream_t stream) {
+  const WhArgs a = whiten_args(adv, lengths, B, T, eps, shift_mean, unbiased, out, stats);
+  hipLaunchKernelGGL(whiten_apply_kernel<true>, dim3(a.groups), dim3(kWhThreads), 0, stream, a, rows, B);
   return hipGetLastError() == hipSuccess ? ESPO_OK : ESPO_EHIP;
 }
 

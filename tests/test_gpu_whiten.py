@@ -73,6 +73,21 @@ def test_shapes_lengths_and_options(T):
     _check(a, Lt, eps=0.5, in_place=True)
 
 
+@pytest.mark.parametrize("B,T", [(3, 4), (4096, 4), (5000, 3), (4097, 4), (2340, 7), (16, 1024), (4, 4096), (17, 964), (2, 8193), (33, 1023),
+                                 (33, 1025), (700, 1026), (1025, 2047)])
+def test_rows_that_start_anywhere_and_the_one_launch_form(B, T):
+    # Up to 16384 positions (rows of at least 4) are one launch of one workgroup, whose groups of four positions may lie in
+    # two rows; larger batches are cut into items of 1024 positions from the 16-byte boundary before each row.
+    _say(f"[case] whiten B={B} T={T}")
+    a, L = _batch(B, T, seed=B + T, mean=3.0, std=0.5)
+    _check(a, L)
+    _check(a, L, unbiased=True, in_place=True)
+    a, L = _batch(B, T, seed=B + T + 1, lengths=[T] * B, mean=-20.0)
+    _check(a, L, eps=0.0)
+    a, L = _batch(B, T, seed=B + T + 2, lengths=[0] * (B - 1) + [T])     # the first valid token is far from the start
+    _check(a, L, in_place=True)
+
+
 def test_mean_far_from_zero_and_tiny_spread():
     _say("[case] whiten, mean far from zero")
     # values 1000 +- 0.01: a one-pass variance about zero would lose every digit in fp32 and ten in double
