@@ -18,11 +18,12 @@
 // r_fail or the row's terminal reward, and on request the value targets A_t + V(s_t) are
 // stored and the padding beyond the lengths is left alone.
 //
-// It also serves trajectories stored back to back (extents from cu_seqlens): the workgroup
-// then works on the span that starts at the 16-byte boundary at or before the trajectory's
-// first token, so every lane still moves 16 aligned bytes; the up to three tokens before the
-// first one belong to the neighbour, come last in the backward scan (nothing valid depends on
-// them) and are not stored, and neither is anything at or after the trajectory's end.
+// It also serves trajectories stored back to back (extents from cu_seqlens) and rows whose length
+// is no multiple of four: the workgroup then works on the span that starts at the 16-byte
+// boundary at or before the row's first token, so every lane still moves 16 aligned bytes; the up
+// to three tokens before the first one belong to the neighbour, come last in the backward scan
+// (nothing valid depends on them) and are not stored, and neither is anything at or after the end
+// of what the row owns.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -34,10 +35,9 @@
 namespace espo {
 namespace {
 
-constexpr int kAdvThreads = 1024;
-constexpr int kAdvWaves = kAdvThreads / kWave;
+// A workgroup has W wavefronts, 16 or 4 (a template parameter of what depends on it): tiles of 4096 or 1024 tokens.
 constexpr int kPerLane = 4;
-constexpr int kAdvTile = kAdvThreads * kPerLane;  // 4096 tokens
+constexpr int kWaveTokens = kWave * kPerLane;
 constexpr int kDppWaveShr1 = 0x138;               // lane i takes lane i-1 across the whole wave
 
 struct AdvArgs {
@@ -51,17 +51,18 @@ struct AdvArgs {
   const int32_t* lengths;
   const uint8_t* stopped;
   int64_t T;
-  int32_t B;  // rows; with zero padding the grid has 2 B workgroups, the second B only fill
+  int32_t B;  // rows; with zero padding and more than one tile per row the grid has 2 B workgroups, the second B only fill
+  int32_t ordered_from;  // rows from here on (kAdvFirstRows or none) are scanned longest first
   float r_fail, gamma, c;
   float cj[kPerLane + 1];  // c^0 .. c^4
   float clane[6];          // c^(4*2^k), k = 0..5: a distance of 2^k lanes
-  float cwave[5];          // c^(256*2^k), k = 0..4: a distance of 2^k waves; cwave[4] spans a tile
+  float cwave[5];          // c^(256*2^k), k = 0..4: a distance of 2^k waves; cwave[log2 W] spans a tile
   float* td;
   float* adv;
   const int32_t* order;    // optional [B]: the rows, longest first (padded forms)
   AdvRowStats* row_stats;  // optional [B]: sums of every row's advantages (padded forms)
   int32_t* sorted;         // optional [B - kAdvFirstRows]: the rows from kAdvFirstRows on, longest first, written by
-                           //   workgroup 0 of this launch (padded forms, no `order` given)
+                           //   workgroup 0 of this launch (padded forms, no `order` given) and followed by workgroups of 16 waves
   uint32_t* sync;          // with `sorted`: [0] set once `sorted` is complete, [32] readers so far; both 0 between launches
 };
 
@@ -69,28 +70,36 @@ struct AdvArgs {
 // their lengths.  Only the order of the rows that follow decides how ragged the launch's end is (measured: rows
 // 512.. of 1024 longest first gives what a full order gives, 39.9 us against 45.3 in index order; rows 768.. 43.3).
 constexpr int kAdvFirstRows = 512;
+// The order is followed in batches of at most three rows per workgroup slot, where it decides how ragged the launch's
+// end is, and only for rows of several tiles, which take longer than finding one's row (2 to 3 us); us per launch
+// with / without: B = 1024, T = 16384: 39.5 / 43.0; 9000: 25.0 / 26.0; B = 1300, T = 16384: 50.3 / 53.2;
+// B = 2000, T = 10000: 52.1 / 48.0, T = 3000: 30.6 / 22.6; B = 1024, T = 1500: 13.2 / 10.9.
+constexpr int kAdvSelectRows = 3 * kAdvFirstRows;
+constexpr int64_t kAdvSelectTokens = 8192;
 // The word that says "sorted" and the count of its readers lie in different 128-byte lines: loads of the one and
 // read-modify-writes of the other on the same line cost the readers 15 us per launch between them.
 constexpr int kAdvSyncStride = 32;       // words
 constexpr size_t kAdvSyncBytes = 256;
 constexpr int kOrderClasses = 256;
 
+__device__ __forceinline__ int class_of_length(int64_t L, int64_t T) {  // class 0 is the longest
+  L = L < 0 ? 0 : (L > T ? T : L);
+  return kOrderClasses - 1 - (int)((L * kOrderClasses) / (T + 1));
+}
+
 // Writes the rows first .. B-1 to order[0 .. B-first), longest first: a counting sort of the clipped lengths into
 // 256 classes by one workgroup (rows of one class in no particular order; no result depends on it).  The entries
 // are written past the caches that other parts of the chip do not see, and are complete when the call returns.
+template <int W>
 __device__ __forceinline__ void sort_rows_by_length(const int32_t* __restrict__ lengths, int32_t first, int32_t B, int64_t T,
                                                     int32_t* __restrict__ order) {
   __shared__ int count[kOrderClasses];
   __shared__ int wave_total[kOrderClasses / kWave];
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
-  auto class_of = [&](int32_t i) {
-    int64_t L = lengths[i];
-    L = L < 0 ? 0 : (L > T ? T : L);
-    return kOrderClasses - 1 - (int)((L * kOrderClasses) / (T + 1));
-  };
+  auto class_of = [&](int32_t i) { return class_of_length(lengths[i], T); };
   if (tid < kOrderClasses) count[tid] = 0;
   __syncthreads();
-  for (int32_t i = first + tid; i < B; i += kAdvThreads) atomicAdd(&count[class_of(i)], 1);
+  for (int32_t i = first + tid; i < B; i += W * kWave) atomicAdd(&count[class_of(i)], 1);
   __syncthreads();
   int mine = 0, incl = 0;
   if (tid < kOrderClasses) {  // inclusive prefix over the classes: inside each wave, then over the four waves
@@ -110,30 +119,24 @@ __device__ __forceinline__ void sort_rows_by_length(const int32_t* __restrict__ 
     count[tid] = before + incl - mine;  // where the class starts
   }
   __syncthreads();
-  for (int32_t i = first + tid; i < B; i += kAdvThreads)
+  for (int32_t i = first + tid; i < B; i += W * kWave)
     __hip_atomic_store(order + atomicAdd(&count[class_of(i)], 1), i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
 }
 
-// The k-th row of that same order (rows first .. B-1 by class of length, longest first; inside a class by
-// index), found by the calling workgroup for itself: every workgroup that asks gets the same permutation, so
+// The k-th of the rows first .. B-1 in order of their classes (class 0 first; inside a class by index), found by the calling workgroup for itself: every workgroup that asks gets the same permutation, so
 // no memory and no waiting is needed.  All threads must call it; the result is uniform.
-__device__ __forceinline__ int32_t kth_row_by_length(const int32_t* __restrict__ lengths, int32_t first, int32_t B, int64_t T,
-                                                     int32_t k) {
+template <int W, typename ClassOf>
+__device__ __forceinline__ int32_t kth_row_by_length(ClassOf&& class_of, int32_t first, int32_t B, int32_t k) {
   __shared__ int count[kOrderClasses];
-  __shared__ int wave_total[kAdvWaves];
+  __shared__ int wave_total[W];
   __shared__ int s_class, s_rank, s_found;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
-  auto class_of = [&](int32_t i) {
-    int64_t L = lengths[i];
-    L = L < 0 ? 0 : (L > T ? T : L);
-    return kOrderClasses - 1 - (int)((L * kOrderClasses) / (T + 1));
-  };
   if (tid < kOrderClasses) count[tid] = 0;
   if (tid == 0) s_found = -1;
   __syncthreads();
-  for (int32_t i = first + tid; i < B; i += kAdvThreads) atomicAdd(&count[class_of(i)], 1);
+  for (int32_t i = first + tid; i < B; i += W * kWave) atomicAdd(&count[class_of(i)], 1);
   __syncthreads();
   int mine = 0, incl = 0;
   if (tid < kOrderClasses) {  // inclusive prefix over the classes: inside each wave, then over the four waves
@@ -159,14 +162,14 @@ __device__ __forceinline__ int32_t kth_row_by_length(const int32_t* __restrict__
   __syncthreads();
   const int want_class = s_class, want_rank = s_rank;
   int seen = 0;  // rows of the class before this chunk (uniform)
-  for (int32_t chunk = first; chunk < B; chunk += kAdvThreads) {
+  for (int32_t chunk = first; chunk < B; chunk += W * kWave) {
     const int32_t i = chunk + tid;
     const bool in = i < B && class_of(i) == want_class;
     const uint64_t who = __builtin_amdgcn_ballot_w64(in);
     if (lane == 0) wave_total[wave] = (int)__builtin_popcountll(who);
     __syncthreads();
     int before = seen, all = 0;
-    for (int w = 0; w < kAdvWaves; ++w) {
+    for (int w = 0; w < W; ++w) {
       const int n = wave_total[w];
       before += w < wave ? n : 0;
       all += n;
@@ -196,14 +199,14 @@ __device__ __forceinline__ float pow_from_table(const float* tab, int e) {
 
 // Loads the lane's 4 tokens starting at t0 and, in lane 0, the value at t0 + 4; tokens at or
 // beyond L are never read.
-template <bool VEC, bool Dense>
+template <bool Dense>
 __device__ __forceinline__ TileIn load_tile(const float* __restrict__ rrow, const float* __restrict__ vrow, int64_t t0,
                                             int64_t L, bool want_halo) {
   TileIn in;
 #pragma unroll
   for (int j = 0; j < kPerLane; ++j) { in.r[j] = 0.0f; in.v[j] = 0.0f; }
   in.halo = 0.0f;
-  if (VEC && t0 + kPerLane <= L) {
+  if (t0 + kPerLane <= L) {
     if constexpr (Dense) {
       const f32x4 a = __builtin_nontemporal_load((const f32x4*)(rrow + t0));
 #pragma unroll
@@ -224,15 +227,9 @@ __device__ __forceinline__ TileIn load_tile(const float* __restrict__ rrow, cons
   return in;
 }
 
-template <bool VEC>
+// Stores x at t0 .. t0 + 3 where the row goes on (T % 4 == 0 here).
 __device__ __forceinline__ void store4(float* __restrict__ row, int64_t t0, int64_t T, const float x[kPerLane]) {
-  if (VEC) {
-    if (t0 < T) __builtin_nontemporal_store(f32x4{x[0], x[1], x[2], x[3]}, (f32x4*)(row + t0));  // T % 4 == 0 here
-    return;
-  }
-#pragma unroll
-  for (int j = 0; j < kPerLane; ++j)
-    if (t0 + j < T) row[t0 + j] = x[j];
+  if (t0 < T) __builtin_nontemporal_store(f32x4{x[0], x[1], x[2], x[3]}, (f32x4*)(row + t0));
 }
 
 // Stores x[j] at t0 + j for lo <= t0 + j < hi (t0 a multiple of 4, the row 16-byte aligned).
@@ -252,9 +249,14 @@ __device__ __forceinline__ float scan_step(float s, float w) {
   return fmaf(w, dpp_f32<Ctrl, RowMask>(0.0f, s), s);
 }
 
-template <bool VEC, bool Dense, bool Packed>
-__global__ __launch_bounds__(kAdvThreads, 8) void espo_advantages_kernel(AdvArgs a) {
-  __shared__ float s_tot[2][kAdvWaves];  // wave totals, double-buffered by tile parity
+// Layout of the rows: [B, T] with T a multiple of four, [B, T] with any T, or back to back.
+enum RowLayout { kAligned, kShifted, kPacked };
+
+template <bool Dense, RowLayout Layout, int W>
+__global__ __launch_bounds__(W * kWave, W == 4 ? 6 : 8) void espo_advantages_kernel(AdvArgs a) {
+  constexpr bool Packed = Layout == kPacked, Span = Layout != kAligned;
+  constexpr int kTile = W * kWaveTokens;
+  __shared__ float s_tot[2][W];  // wave totals, double-buffered by tile parity
   // With zero padding, the tiles wholly beyond a trajectory are filled by a workgroup of their
   // own (the second half of the grid): the two kinds of work of a row are then dispatched
   // separately, which evens out the rows (a row costs 16 bytes per valid and 8 per padded token):
@@ -262,14 +264,15 @@ __global__ __launch_bounds__(kAdvThreads, 8) void espo_advantages_kernel(AdvArgs
   // when they come in random order.  (Ranking the rows by length inside every workgroup, 8 or 64
   // classes, cost 3 to 5 us per launch, as much as the order gains; only the order of the rows that do
   // not fit the chip at once matters, and only their scans look their row up: see below.)
+  constexpr bool kOrdered = W == 16;  // of the smaller workgroups, for short rows, the chip holds 2048, and rows differ little
   int unit = (int)blockIdx.x;
   if (!Packed && a.sorted) {
     // No order was given and the batch has more rows than the chip holds workgroups: workgroup 0 of this launch
     // sorts the later rows while the first kAdvFirstRows are being scanned, and tells the others when it is done.
     // It waits for nobody and is dispatched before every workgroup that waits for it.
     if (unit == 0) {
-      sort_rows_by_length(a.lengths, kAdvFirstRows, a.B, a.T, a.sorted);
-      if (threadIdx.x == 0) __hip_atomic_store(a.sync, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      sort_rows_by_length<W>(a.lengths, kAdvFirstRows, a.B, a.T, a.sorted);
+      if (kOrdered && a.ordered_from < a.B && threadIdx.x == 0) __hip_atomic_store(a.sync, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       return;
     }
     unit -= 1;
@@ -282,7 +285,7 @@ __global__ __launch_bounds__(kAdvThreads, 8) void espo_advantages_kernel(AdvArgs
   if (!Packed && a.order) {
     row = a.order[fill_only ? a.B - 1 - row : row];
     if ((unsigned)row >= (unsigned)a.B) return;
-  } else if (!Packed && a.sorted && !fill_only && row >= kAdvFirstRows) {
+  } else if (kOrdered && !Packed && a.sorted && !fill_only && row >= a.ordered_from) {
     // one of the later scans: its row comes from the sorted list.  The last reader clears the two words, so the
     // next launch finds them as this one did.
     __shared__ int s_row;
@@ -296,12 +299,18 @@ __global__ __launch_bounds__(kAdvThreads, 8) void espo_advantages_kernel(AdvArgs
     __syncthreads();
     row = s_row;
     if ((unsigned)row >= (unsigned)a.B) return;
-  } else if (!Packed && !fill_only && row >= kAdvFirstRows) {
+  } else if (kOrdered && !fill_only && row >= a.ordered_from) {
     // No order and nowhere to keep one: each of the later scans finds its row for itself, the
     // (row - kAdvFirstRows)-th longest of the later rows (five barriers and a few hundred LDS operations
     // before its first load, while the other workgroups of the compute unit stream).  Measured on the
-    // B = 1024, T = 16384 batches: 40.6 against 43.7 us per launch.
-    row = kth_row_by_length(a.lengths, kAdvFirstRows, a.B, a.T, row - kAdvFirstRows);
+    // B = 1024, T = 16384 batches: 40.6 against 43.7 us per launch; stored back to back 30.5 against 33.0.
+    // Without a T, the classes of length divide up to four times the mean length.
+    if constexpr (Packed) {
+      const int64_t most = 4 * (a.N / a.B) + 3;
+      row = kth_row_by_length<W>([&](int32_t i) { return class_of_length(a.cu[i + 1] - a.cu[i], most); }, kAdvFirstRows, a.B, row - kAdvFirstRows);
+    } else {
+      row = kth_row_by_length<W>([&](int32_t i) { return class_of_length(a.lengths[i], a.T); }, kAdvFirstRows, a.B, row - kAdvFirstRows);
+    }
     if ((unsigned)row >= (unsigned)a.B) return;
   }
   const int tid = threadIdx.x;
@@ -322,6 +331,12 @@ __global__ __launch_bounds__(kAdvThreads, 8) void espo_advantages_kernel(AdvArgs
   } else {
     L = a.lengths[row];
     L = L < 0 ? 0 : (L > T ? T : L);
+    if constexpr (Layout == kShifted) {  // positions count from the boundary: the row is [head, T), its valid part [head, L)
+      head = base & (kPerLane - 1);
+      base -= head;
+      L = L > 0 ? L + head : 0;
+      T += head;
+    }
   }
   const bool stopped = a.stopped[row] != 0;
   // reward of the last token where it does not come from the reward array: r_fail after a stop
@@ -335,21 +350,30 @@ __global__ __launch_bounds__(kAdvThreads, 8) void espo_advantages_kernel(AdvArgs
   float* arow = a.adv + base;
   float* trow = a.returns ? a.returns + base : nullptr;
 
-  const int64_t ntiles = (T + kAdvTile - 1) / kAdvTile;
-  const int64_t nvalid = (L + kAdvTile - 1) / kAdvTile;  // tiles that hold at least one valid token
-  const int64_t lane_off = (int64_t)(kAdvThreads - 1 - tid) * kPerLane;  // backwards: thread 0 holds the last tokens
+  const int64_t ntiles = (T + kTile - 1) / kTile;
+  const int64_t nvalid = (L + kTile - 1) / kTile;  // tiles that hold at least one valid token
+  const int64_t lane_off = (int64_t)(W * kWave - 1 - tid) * kPerLane;  // backwards: thread 0 holds the last tokens
 
+  auto put = [&](float* out, int64_t t0, const float x[kPerLane]) {  // what the row owns of four positions
+    if constexpr (Span) store_span(out, t0, head, Packed ? L : T, x);
+    else store4(out, t0, T, x);
+  };
   // tiles wholly beyond the trajectory: outputs are exactly zero
   const float zero[kPerLane] = {0, 0, 0, 0};
   if (fill_only) {
     for (int64_t k = ntiles - 1; k >= nvalid; --k) {
-      store4<VEC>(drow, k * kAdvTile + lane_off, T, zero);
-      store4<VEC>(arow, k * kAdvTile + lane_off, T, zero);
-      if (trow) store4<VEC>(trow, k * kAdvTile + lane_off, T, zero);
+      put(drow, k * kTile + lane_off, zero);
+      put(arow, k * kTile + lane_off, zero);
+      if (trow) put(trow, k * kTile + lane_off, zero);
     }
     return;
   }
   if (nvalid == 0) {
+    if (!Packed && a.zero_padding && T <= kTile) {  // a row of one tile has no workgroup that only fills
+      put(drow, lane_off, zero);
+      put(arow, lane_off, zero);
+      if (trow) put(trow, lane_off, zero);
+    }
     if (!Packed && a.row_stats && tid == 0) a.row_stats[row] = AdvRowStats{0.0, 0.0, 0.0, 0};
     return;
   }
@@ -366,11 +390,11 @@ __global__ __launch_bounds__(kAdvThreads, 8) void espo_advantages_kernel(AdvArgs
   const float w_wave = pow_from_table<4>(a.cwave, wave);            // c^(256 wave): the tile's carry-in seen from this wave
 
   float carry = 0.0f;  // A at the first token of the tile processed before (the later one)
-  TileIn cur = load_tile<VEC, Dense>(rrow, vrow, (nvalid - 1) * kAdvTile + lane_off, L, lane == 0);
+  TileIn cur = load_tile<Dense>(rrow, vrow, (nvalid - 1) * kTile + lane_off, L, lane == 0);
   for (int64_t k = nvalid - 1; k >= 0; --k) {
-    const int64_t t0 = k * kAdvTile + lane_off;
+    const int64_t t0 = k * kTile + lane_off;
     TileIn nxt;
-    if (k > 0) nxt = load_tile<VEC, Dense>(rrow, vrow, t0 - kAdvTile, L, lane == 0);  // the earlier tile, in flight during the scan
+    if (k > 0) nxt = load_tile<Dense>(rrow, vrow, t0 - kTile, L, lane == 0);  // the earlier tile, in flight during the scan
 
     // V_{t+1} of the lane's last token: first value of the lane that holds the following tokens
     float vnext = dpp_f32<kDppWaveShr1, 0xf>(0.0f, cur.v[0]);
@@ -414,16 +438,18 @@ __global__ __launch_bounds__(kAdvThreads, 8) void espo_advantages_kernel(AdvArgs
     const int par = (int)(k & 1);
     if (lane == kWave - 1) s_tot[par][wave] = s;
     __syncthreads();
-    // the same scan over the sixteen wave totals, one per lane of the first row
-    float p = lane < kAdvWaves ? s_tot[par][lane] : 0.0f;
+    // the same scan over the wave totals, one per lane of the first row
+    float p = lane < W ? s_tot[par][lane] : 0.0f;
     p = scan_step<kDppRowShr1, 0xf>(p, a.cwave[0]);
     p = scan_step<kDppRowShr2, 0xf>(p, a.cwave[1]);
-    p = scan_step<kDppRowShr4, 0xf>(p, a.cwave[2]);
-    p = scan_step<kDppRowShr8, 0xf>(p, a.cwave[3]);
+    if constexpr (W > 4) {
+      p = scan_step<kDppRowShr4, 0xf>(p, a.cwave[2]);
+      p = scan_step<kDppRowShr8, 0xf>(p, a.cwave[3]);
+    }
     // A at the first token after this wave's span
     const float before = wave > 0 ? uniform_f32(p, wave - 1) : 0.0f;
     const float wave_in = fmaf(w_wave, carry, before);
-    carry = fmaf(a.cwave[4], carry, uniform_f32(p, kAdvWaves - 1));  // A at the tile's first token
+    carry = fmaf(a.cwave[W == 16 ? 4 : 2], carry, uniform_f32(p, W - 1));  // A at the tile's first token
     // A at the first token after this lane's span
     const float s_prev = dpp_f32<kDppWaveShr1, 0xf>(0.0f, s);
     const float a_next = fmaf(w_lane, wave_in, s_prev);
@@ -436,21 +462,15 @@ __global__ __launch_bounds__(kAdvThreads, 8) void espo_advantages_kernel(AdvArgs
 #pragma unroll
       for (int j = 0; j < kPerLane; ++j) outR[j] = (j < rem) ? outA[j] + cur.v[j] : 0.0f;
     }
-    if constexpr (Packed) {  // only what the trajectory owns
-      if (rem > 0 && t0 + kPerLane > head) {
-        store_span(drow, t0, head, L, d);
-        store_span(arow, t0, head, L, outA);
-        if (trow) store_span(trow, t0, head, L, outR);
-      }
-    } else if (a.zero_padding || rem > 0) {  // lanes wholly beyond L only ever hold zeros
-      store4<VEC>(drow, t0, T, d);
-      store4<VEC>(arow, t0, T, outA);
-      if (trow) store4<VEC>(trow, t0, T, outR);
+    if ((!Packed && a.zero_padding) || rem > 0) {  // lanes wholly beyond L only ever hold zeros
+      put(drow, t0, d);
+      put(arow, t0, outA);
+      if (trow) put(trow, t0, outR);
     }
     if (want_stats) {
 #pragma unroll
       for (int j = 0; j < kPerLane; ++j)
-        if (j < rem) {
+        if (j < rem && (!Span || t0 + j >= head)) {
           const double dd = (double)outA[j] - st_shift;
           st_s1 += dd;
           st_s2 += dd * dd;
@@ -459,7 +479,7 @@ __global__ __launch_bounds__(kAdvThreads, 8) void espo_advantages_kernel(AdvArgs
     if (k > 0) cur = nxt;
   }
   if (want_stats) {  // lanes, then waves, in a fixed order
-    __shared__ double s_stats[2][kAdvWaves];
+    __shared__ double s_stats[2][W];
     st_s1 = wave_sum_f64(st_s1);
     st_s2 = wave_sum_f64(st_s2);
     if (lane == 0) {
@@ -469,18 +489,24 @@ __global__ __launch_bounds__(kAdvThreads, 8) void espo_advantages_kernel(AdvArgs
     __syncthreads();
     if (tid == 0) {
       double t1 = 0.0, t2 = 0.0;
-      for (int w = 0; w < kAdvWaves; ++w) {
+      for (int w = 0; w < W; ++w) {
         t1 += s_stats[0][w];
         t2 += s_stats[1][w];
       }
-      a.row_stats[row] = AdvRowStats{t1, t2, st_shift, (long long)L};
+      a.row_stats[row] = AdvRowStats{t1, t2, st_shift, (long long)(L - head)};
     }
   }
 }
 
-__global__ __launch_bounds__(kAdvThreads) void length_order_kernel(const int32_t* __restrict__ lengths, int32_t B, int64_t T,
+__global__ __launch_bounds__(16 * kWave) void length_order_kernel(const int32_t* __restrict__ lengths, int32_t B, int64_t T,
                                                                   int32_t* __restrict__ order) {
-  sort_rows_by_length(lengths, 0, B, T, order);
+  sort_rows_by_length<16>(lengths, 0, B, T, order);
+}
+
+template <RowLayout Layout>
+void (*pick_kernel(bool dense, bool shortrows))(AdvArgs) {
+  if (shortrows) return dense ? espo_advantages_kernel<true, Layout, 4> : espo_advantages_kernel<false, Layout, 4>;
+  return dense ? espo_advantages_kernel<true, Layout, 16> : espo_advantages_kernel<false, Layout, 16>;
 }
 
 }  // namespace
@@ -515,14 +541,20 @@ int launch_advantages(const float* rewards, const float* terminal_reward, const 
   for (int k = 0; k < 5; ++k) a.cwave[k] = (float)pow(c, (double)((kPerLane * kWave) << k));
   a.td = td;
   a.adv = adv;
-  const bool vec = (T % 4 == 0);
-  const dim3 grid((unsigned)((cu == nullptr && zero_padding ? 2 * B : B) + (sort_here ? 1 : 0))), block(kAdvThreads);
+  // Workgroups of 4 waves for short rows: more rows at once, fewer waves without work, no second round of workgroups
+  // (B = 1024: T = 1000: 5.3 against 14.1 us, 2048: 8.2 / 11.0, 3000: 11.0 / 13.3, 4096: 13.6 / 14.7; B = 300,
+  // T = 2001: 5.9 / 7.4).  A few rows of several of their tiles are better walked by 16 (B = 8, T = 8192).
+  // Trajectories stored back to back: by their mean length.
+  const int64_t longest = cu ? 2 * (N / B) : T + (T % 4 != 0 ? 3 : 0);
+  const bool shortrows = longest <= 8 * kWaveTokens || (longest <= 16 * kWaveTokens && B > kAdvFirstRows);
+  a.ordered_from = !shortrows && B <= kAdvSelectRows && longest > kAdvSelectTokens ? kAdvFirstRows : 0x7fffffff;
+  const int64_t tile = (shortrows ? 4 : 16) * kWaveTokens;
+  const bool fillers = cu == nullptr && zero_padding && longest > tile;
+  const dim3 grid((unsigned)((fillers ? 2 * B : B) + (sort_here ? 1 : 0))), block(shortrows ? 4 * kWave : 16 * kWave);
   void (*kernel)(AdvArgs);
-  if (cu)
-    kernel = rewards ? espo_advantages_kernel<true, true, true> : espo_advantages_kernel<true, false, true>;
-  else
-    kernel = rewards ? (vec ? espo_advantages_kernel<true, true, false> : espo_advantages_kernel<false, true, false>)
-                     : (vec ? espo_advantages_kernel<true, false, false> : espo_advantages_kernel<false, false, false>);
+  if (cu) kernel = pick_kernel<kPacked>(rewards != nullptr, shortrows);
+  else if (T % 4 == 0) kernel = pick_kernel<kAligned>(rewards != nullptr, shortrows);
+  else kernel = pick_kernel<kShifted>(rewards != nullptr, shortrows);
   hipLaunchKernelGGL(kernel, grid, block, 0, stream, a);
   return hipGetLastError() == hipSuccess ? ESPO_OK : ESPO_EHIP;
 }
@@ -537,7 +569,7 @@ size_t advantages_workspace_layout(int64_t B, size_t* stats_offset, size_t* sort
 }
 
 int launch_length_order(const int32_t* lengths, int64_t B, int64_t T, int32_t* order, hipStream_t stream) {
-  hipLaunchKernelGGL(length_order_kernel, dim3(1), dim3(kAdvThreads), 0, stream, lengths, (int32_t)B, T, order);
+  hipLaunchKernelGGL(length_order_kernel, dim3(1), dim3(16 * kWave), 0, stream, lengths, (int32_t)B, T, order);
   return hipGetLastError() == hipSuccess ? ESPO_OK : ESPO_EHIP;
 }
 

@@ -225,6 +225,22 @@ def test_seeded_sweep_of_both_forms(part):
     _say(f"  worst scaled error {worst:.2e}")
 
 
+@pytest.mark.parametrize("B,T", [(5, 1021), (5, 2045), (5, 2046), (5, 2048), (5, 2049), (5, 4099), (2, 8195), (513, 2047), (513, 2049), (513, 4093),
+                                 (513, 4094), (513, 4096), (513, 4099), (514, 8193), (520, 9001), (1537, 8196)])
+def test_rows_of_any_length_start_anywhere(B, T):
+    # Rows whose length is no multiple of four start between 16-byte boundaries; short rows have workgroups of four
+    # waves, several tiles long at most; from 513 long rows on the later ones are looked up by length.  Lengths sit at
+    # the ends of tiles of 1024 and 4096 positions as counted from the boundary before a row.
+    _say(f"[case] advantages B={B} T={T}")
+    edges = [0, 1, 2, 3, 4, 5, 1021, 1022, 1023, 1024, 1025, 2048, 4093, 4094, 4095, 4096, 4097, T - 3, T - 1, T, T]
+    lengths = [min(max(edges[b % len(edges)], 0), T) for b in range(B)]
+    r, v, L, s = _batch(B, T, seed=T, lengths=lengths)
+    H.check_advantages(r, v, L, s, -1.0, 1.0, 0.95)
+    v, L, s, term = _terminal_batch(B, T, seed=T + 1, lengths=lengths)
+    H.check_advantages_terminal(v, L, s, term, -1.0, 0.99, 0.97, zero_padding=True, want_returns=True)
+    H.check_advantages_terminal(v, L, s, term, -1.0, 0.99, 0.97, zero_padding=False, want_returns=True)
+
+
 # ------------------------------------------------------------------ trajectories stored back to back
 
 def _packed(lens, seed, gaps=None, scale=1.0, stop_p=0.4):
@@ -274,6 +290,17 @@ def test_packed_every_alignment_of_start_and_end(L):
     lens = [L, 1, L, 2, L, 3, L, 0, L, 5, 0, 0, L]
     for gamma, lam in ((1.0, 0.95), (0.99, 0.9), (1.0, 1.0), (0.9, 0.0)):
         _check_packed_both_forms(lens, seed=L, gamma=gamma, lam=lam)
+
+
+@pytest.mark.parametrize("B,mean", [(3, 1023), (3, 1025), (513, 500), (600, 2047), (600, 2049), (600, 4200)])
+def test_packed_batches_of_short_and_long_trajectories(B, mean):
+    # the number of waves and the order follow from the mean length; a few trajectories are many times as long
+    _say(f"[case] packed advantages, B={B} mean length {mean}")
+    g = torch.Generator().manual_seed(B + mean)
+    lens = torch.randint(0, mean, (B,), generator=g).tolist()
+    lens[0], lens[-1], lens[B // 2] = 0, 5 * mean + 3, 9 * mean + 1
+    lens[1] = max(0, mean * B - (sum(lens) - lens[1]))
+    _check_packed_both_forms(lens, seed=B)
 
 
 def test_packed_gaps_are_neither_read_nor_written():
