@@ -3,6 +3,7 @@ from __future__ import annotations
 
 import os
 import subprocess
+import sysconfig
 import tempfile
 from concurrent.futures import ThreadPoolExecutor
 
@@ -20,6 +21,7 @@ HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibil
 
 
 def build_library(verbose: bool = False) -> str:
+    """Builds libespo.so and, beside it, the module that checks the binding's tensor arguments."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     with tempfile.TemporaryDirectory() as tmp:
         def run(cmd):
@@ -27,8 +29,10 @@ def build_library(verbose: bool = False) -> str:
 
         objs = [os.path.join(tmp, f"{i}.o") for i in range(len(SOURCES))]
         cmds = [[hipcc, *HIPCC_FLAGS, *flags, "-c", os.path.join(CSRC, src), "-o", obj] for (src, flags), obj in zip(SOURCES, objs)]
-        with ThreadPoolExecutor(len(cmds)) as pool:
+        with ThreadPoolExecutor(len(cmds) + 1) as pool:
+            checker = pool.submit(build_tensor_checker, verbose)
             results = list(pool.map(run, cmds))
+            checker.result()
         out = os.path.join(tmp, "libespo.so")
         if all(r.returncode == 0 for r in results):
             results.append(run([hipcc, "--offload-arch=gfx950", "-shared", "-o", out, *objs]))
@@ -40,6 +44,29 @@ def build_library(verbose: bool = False) -> str:
             raise RuntimeError("hipcc failed building libespo.so")
         os.replace(out, LIB)
     return LIB
+
+
+TENSOR_SRC = os.path.join(CSRC, "espo_tensor.cpp")
+TENSOR_LIB = os.path.join(_HERE, "_espo_tensor.so")
+
+
+def build_tensor_checker(verbose: bool = False) -> str:
+    """Builds the Python module that checks the binding's tensor arguments (host code against torch's headers)."""
+    import torch
+    home = os.path.dirname(torch.__file__)
+    with tempfile.TemporaryDirectory() as tmp:
+        out = os.path.join(tmp, "_espo_tensor.so")
+        cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+               f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}", "-I" + os.path.join(home, "include"),
+               "-I" + os.path.join(home, "include", "torch", "csrc", "api", "include"), "-I" + sysconfig.get_path("include"),
+               TENSOR_SRC, "-o", out, "-L" + os.path.join(home, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+        res = subprocess.run(cmd, capture_output=True, text=True)
+        if verbose or res.returncode != 0:
+            print(res.stdout + res.stderr)
+        if res.returncode != 0:
+            raise RuntimeError("g++ failed building _espo_tensor.so")
+        os.replace(out, TENSOR_LIB)
+    return TENSOR_LIB
 
 
 ABI_CHECK_SRC = os.path.join(os.path.dirname(_HERE), "tests", "native", "abi_check.cpp")

@@ -188,3 +188,29 @@ def test_binding_refuses_tensors_that_are_too_short(monkeypatch):
     with pytest.raises(ValueError, match="order"):
         b.espo_advantages_terminal_ws(**term_args(), workspace=wsp, order=mk(B - 2, i32))
     assert Recorder.calls == calls
+
+
+@pytest.mark.parametrize("make,kw,err", [
+    (lambda: torch.zeros(4, 6), dict(numel=24, shape=(4, 6)), None),
+    (lambda: torch.zeros(4, 6), dict(numel=25), ValueError),
+    (lambda: torch.zeros(4, 6), dict(shape=(4, 7)), ValueError),
+    (lambda: torch.zeros(4, 6), dict(shape=(24,)), ValueError),
+    (lambda: torch.zeros(4, 6).t(), {}, TypeError),
+    (lambda: torch.zeros(4, 6)[:, ::2], {}, TypeError),
+    (lambda: torch.zeros(4, 6, dtype=torch.float64), {}, TypeError),
+    (lambda: torch.zeros(4, 6)[1:2].expand(3, 6), dict(numel=18), TypeError),
+    (lambda: torch.zeros(0), dict(numel=0, shape=(0,)), None),
+    (lambda: torch.zeros(5)[1:], dict(shape=torch.Size([4])), None),
+])
+def test_tensor_checks_of_the_binding(monkeypatch, make, kw, err):
+    from paper_2605_29860_amd import binding as b
+    t = make()
+    with pytest.raises(TypeError, match="thing: need a contiguous GPU tensor of torch.float32"):
+        b._dev(t, torch.float32, "thing", **kw)               # a host tensor never gets as far as its layout
+    monkeypatch.setattr(b, "_on_gpu", lambda t: True)
+    assert b._dev(None, torch.float32, "thing", **kw) is None
+    if err is None:
+        assert b._dev(t, torch.float32, "thing", **kw) == t.data_ptr()
+    else:
+        with pytest.raises(err, match="thing: need"):
+            b._dev(t, torch.float32, "thing", **kw)
