@@ -20,18 +20,18 @@ extern "C" {
  *                       huge value sends every row through the double-precision search).  The
  *                       sampled token does not depend on it.  ESPO_EINVAL below 1 or for NaN.
  *   waves               wavefronts per workgroup: 4, 8 or 16, or 0 for the library's choice (16; 8 from
- *                       256 rows on).
- *   chunks              workgroups a row is split over, or 0 for the library's choice (1).  With
+ *                       256 rows on, and for the chunks of split fp32 rows).
+ *   chunks              workgroups a row is split over, or 0 for the library's choice (1 if `waves` is
+ *                       given; else as espo_step, workspace included).  With
  *                       more than one, every workgroup streams a run of 512-index tiles of its row,
  *                       finds the exact winner of that run and leaves it in the workspace with the
  *                       run's maximum and softmax sum; the last workgroup of a row to arrive
  *                       combines them (tokens, regret, state and masks are the same bits as without
  *                       a split; logprob and entropy may differ in the last bits, their sums being
- *                       added in another order).  Needs a zeroed workspace of
+ *                       added in another order).  Needs a workspace of
  *                       espo_debug_step_workspace_bytes(B, chunks) bytes (ESPO_EWORKSPACE
- *                       otherwise), which comes back zero; the value is lowered to the number of
- *                       tiles of a row and to 64 if it exceeds them.  espo_step itself never splits
- *                       rows: on an MI355X every split measured slower than one workgroup per row.
+ *                       otherwise; its contents do not matter), which comes back zero; the value is lowered to the number of
+ *                       tiles of a row and to 64 if it exceeds them.
  * A filtered draw (top_p / top_k) has one layout: waves 0 or 8, chunks 0 or 1.
  * Everything else is espo_step.
  */

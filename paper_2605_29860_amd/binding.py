@@ -281,7 +281,7 @@ def espo_step(logits: torch.Tensor, temperature: float, seed: int, step: int, va
               entropy: torch.Tensor | None = None, margin_scale: float | None = None, waves: int | None = None,
               chunks: int | None = None) -> None:
     """One decode step; see `espo_step` in include/espo.h.  `logits` is [B, row_stride].  `workspace`: a
-    zero-initialised uint8 GPU tensor of `espo_step_workspace_bytes` bytes (rows are then split over several
+    uint8 GPU tensor of `espo_step_workspace_bytes` bytes (long rows of a small batch are then split over several
     workgroups) or None.  With any of `margin_scale`, `waves`, `chunks` the call goes through
     `espo_debug_step` (include/espo_debug.h), which exposes those choices for this call."""
     lib = load_library()

@@ -105,7 +105,10 @@ int step_checked(const void* logits, espo_dtype dt, int64_t B, int64_t V, int64_
   if (!aligned16(logits) || ((size_t)row_stride * esize) % 16 != 0) return ESPO_EALIGN;
   const bool filter = filtered(params);
   if (filter && ((waves != 0 && waves != 8) || chunks > 1)) return ESPO_EINVAL;  // a filtered draw has one layout
-  const espo::StepPlan plan = espo::plan_step(dt, B, V, filter, waves, chunks);
+  espo::StepPlan plan = espo::plan_step(dt, B, V, filter, waves, chunks);
+  // the library's own split is an offer: without a workspace that fits, one workgroup handles a whole row
+  if (chunks == 0 && plan.workspace > 0 && (!workspace || workspace_bytes < plan.workspace || !aligned16(workspace)))
+    plan = espo::plan_step(dt, B, V, filter, waves, 1);
   if (plan.lds > espo::kMaxStepLds) return ESPO_ERANGE;
   if (plan.workspace > 0 && (!workspace || workspace_bytes < plan.workspace || !aligned16(workspace))) return ESPO_EWORKSPACE;
   return espo::launch_step(logits, dt, B, V, row_stride, temperature, seed, step, values, *params, margin_scale, z, alive,

@@ -49,6 +49,8 @@ constexpr int kRing = 4;                          // 16-byte loads kept in fligh
 constexpr int kCandCap = 1024;                    // candidate indices kept for a row with a long survivor list
 constexpr float kRescaleAt = 64.0f;               // advance a lane's softmax reference when topped by 2^64
 
+constexpr unsigned long long kTicketMark = 0x4553504F00000000ull;  // marks a ticket word that this kernel wrote
+
 // What the workgroup of one chunk hands to the combine: the chunk's largest logit, its softmax
 // sums relative to that logit, and its exact local winner (score known to within +-e).
 struct __attribute__((aligned(16))) ChunkResult {
@@ -83,7 +85,7 @@ struct StepArgs {
   // a row split over `nch` workgroups: workgroup row * nch + c streams tiles [c ntiles / nch, (c + 1) ntiles / nch)
   int32_t nch;
   ChunkResult* partials;         // [B * nch] what each chunk found, combined by the last one of a row to arrive
-  uint32_t* tickets;             // [B] arrivals per row; zero before the launch and again after it
+  unsigned long long* tickets;   // [B] arrivals per row: kTicketMark above a count; anything else counts as none, and zero is left behind
 };
 
 
@@ -1014,9 +1016,14 @@ __device__ __forceinline__ void step_row(const StepArgs& a, unsigned char* smem_
   if (lane == 0) sh.m[wave] = mw;
   if ((lane & 7) == 0) sh.top_q[wave * kGroups + grp] = top_q;
   float z_prev = 0.0f, value = 0.0f;  // wanted at the very end: fetched now, off the critical path
-  if (tid == 0 && nch == 1) {
-    z_prev = a.z[row];
-    value = a.values[row];
+  unsigned long long ticket = 0;
+  if (tid == 0) {
+    if (nch == 1) {
+      z_prev = a.z[row];
+      value = a.values[row];
+    } else {
+      ticket = __hip_atomic_load(a.tickets + row, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // what the ticket is most likely taken from
+    }
   }
 
   // ------------------------------------------------------------ phase 2: argmax of y + G
@@ -1213,8 +1220,9 @@ __device__ __forceinline__ void step_row(const StepArgs& a, unsigned char* smem_
       // are private to a part of the chip, and a workgroup takes its ticket only once its stores have
       // been acknowledged, so whoever sees the last ticket also sees every result.  (A device-scope
       // fence would do too, but writes back and invalidates a whole L2 per workgroup: measured, 50 ns
-      // of serialised work per workgroup, 100 us per launch.)  atomicInc wraps to zero at nch - 1, so
-      // the ticket is ready for the next launch without anyone clearing it.
+      // of serialised work per workgroup, 100 us per launch.)  A ticket is a mark and a count: a word
+      // without the mark counts as no arrival, so the workspace may hold anything before the launch, and the
+      // last to arrive clears it, so that a replay of the same launch starts over.
       uint32_t arrived = 0;
       if (lane == 0) {
         uint32_t* const dst = (uint32_t*)(a.partials + (size_t)unit);
@@ -1224,10 +1232,19 @@ __device__ __forceinline__ void step_row(const StepArgs& a, unsigned char* smem_
 #pragma unroll
         for (int j = 0; j < 7; ++j) __hip_atomic_store(dst + j, w[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the stores are done before the ticket is taken
-        arrived = atomicInc(a.tickets + row, (uint32_t)(nch - 1));
+        while (true) {  // (a failed exchange means that another chunk of the row has arrived: at most nch rounds)
+          const unsigned long long next = (ticket & ~0xffffffffull) == kTicketMark ? ticket + 1 : kTicketMark + 1;
+          const unsigned long long was = atomicCAS(a.tickets + row, ticket, next);
+          if (was == ticket) {
+            arrived = (uint32_t)next;
+            break;
+          }
+          ticket = was;
+        }
+        if (arrived == (uint32_t)nch) __hip_atomic_store(a.tickets + row, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
       arrived = (uint32_t)__builtin_amdgcn_readfirstlane((int)arrived);
-      if (arrived != (uint32_t)(nch - 1)) return;
+      if (arrived != (uint32_t)nch) return;
       if (lane == 0) {
         z_prev = a.z[row];
         value = a.values[row];
@@ -1240,8 +1257,8 @@ __device__ __forceinline__ void step_row(const StepArgs& a, unsigned char* smem_
         uint32_t w[7];
 #pragma unroll
         for (int j = 0; j < 7; ++j) w[j] = __hip_atomic_load(src + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        // hand the workspace back as it came: all zero (the tickets clear themselves), so that a later call of
-        // another shape, whose tickets may lie where these results were, can use the same buffer
+        // hand the workspace back all zero, like the tickets: nothing of this launch can pass for a ticket of a later
+        // call of another shape
         u32x4* const back = (u32x4*)(a.partials + (size_t)row * nch + lane);
         back[0] = u32x4{0u, 0u, 0u, 0u};
         back[1] = u32x4{0u, 0u, 0u, 0u};
@@ -2020,8 +2037,8 @@ int launch_math_errors(float* out, hipStream_t stream) {
 }
 
 // ---------------------------------------------------------------- launch configuration
-// How a call is laid out on the GPU.  One workgroup streams a whole row: 8 waves, three workgroups to a
-// compute unit, from 256 rows on; 16 waves, two to a compute unit, for smaller batches, where a
+// How a call is laid out on the GPU.  Unless it is split (own_split below), one workgroup streams a row: 8 waves, three
+// workgroups to a compute unit, from 256 rows on; 16 waves, two to a compute unit, for smaller batches, where a
 // compute unit has one row at most and more waves stream it faster (B = 128: 17.0 against 18.5 us).
 // With every row live the two are within 1 us of each other from B = 256 to 4096; with rows that are
 // done in the batch the smaller workgroups are 2 to 5 us faster (B = 1024 with 431 live rows: 36.8
@@ -2029,30 +2046,62 @@ int launch_math_errors(float* out, hipStream_t stream) {
 // only 512 slots live rows further back in the batch wait for one (timestamps: a tenth of them start
 // more than 8 us late); with 768 slots all have started within 4 us.  A filtered draw always runs 8 waves, with
 // twice the registers each.  The diagnostics
-// entry point can force fewer waves per workgroup and a split of every row into `chunks` runs of
-// tiles, each streamed by a workgroup of its own and combined by the last one to arrive.  Measured on
-// an MI355X (B = 512, V = 152064 bf16, all rows live): 34.7 us unsplit, 41 us in 2 chunks of 16 waves,
-// 39.6 us in 2 chunks of 8 waves, 53 us in 8 chunks of 4 waves: every chunk pays for a search of its
+// entry point can force the waves per workgroup and a split of every row into `chunks` runs of
+// tiles, each streamed by a workgroup of its own and combined by the last one to arrive.  Where all compute
+// units have rows enough, no split pays (B = 512, V = 152064 bf16, all rows live): 34.7 us unsplit, 41 us in 2 chunks
+// of 16 waves, 39.6 us in 2 chunks of 8 waves, 53 us in 8 chunks of 4 waves: every chunk pays for a search of its
 // own and the row for one more round trip through memory (ticket, then the partial results), which is
-// more than the finer grain gains, so the library itself never splits.  (Also measured and left out:
+// more than the finer grain gains.  (Also measured and left out:
 // 512 resident workgroups that claim rows from a counter in the workspace instead of one workgroup
 // per row, meant to make rows that are done cost a claim instead of a workgroup: 512 device-scope
 // atomics on one address take 50 ns each, and a launch of B = 1024 live rows went from 56 to 82 us.)
 
 // tickets first (256-byte aligned size), then the chunk results
 size_t step_workspace_layout(int64_t B, int chunks, size_t* partials_offset) {
-  const size_t tickets = (((size_t)B * sizeof(uint32_t)) + 255) & ~(size_t)255;
+  const size_t tickets = (((size_t)B * sizeof(unsigned long long)) + 255) & ~(size_t)255;
   if (partials_offset) *partials_offset = tickets;
   return tickets + (size_t)B * (size_t)chunks * sizeof(ChunkResult);
 }
 
 constexpr int64_t kEightWavesFrom = 256;
 
+// How the library itself splits the rows of a plain draw, given a workspace: chunks per row and waves per chunk.
+// A compute unit takes 4.9 to 8.3 us to stream a bf16 row of 152064 logits (its vector units are the limit: some 45
+// operations per tile and wave, 8 of them exponentials) while, below 256 rows, others have none, or, just above,
+// have one row where some have two.  A split costs two more trips through memory (results and ticket, then the
+// other chunks' results), 2 to 3 us, so it pays for long rows only.  us per launch, one workgroup per row -> split:
+//   up to 64 rows, 4 chunks:  bf16 V = 152064: B = 1: 14.7 -> 11.5, 16: 16.2 -> 12.5, 64: 17.0 -> 14.0; f32 V = 66000:
+//     B = 4: 15.7 -> 11.9, 64: 17.7 -> 13.5.  Rows of 131 KB: B = 4, f32: 9.7 -> 10.5; B = 64, bf16: 12.5 -> 12.0.
+//     8 chunks up to 16 rows of 512 KB on (f32 V = 200000, B = 16: 31.8 -> 14.8, in 4 chunks 17.3).
+//   up to 128 rows, 2 chunks: bf16 V = 152064: B = 96: 17.3 -> 15.8, 128: 17.5 -> 17.2; f32 V = 66000, B = 128: 19.9 -> 16.6.
+//   129 to 256 rows: f32 V = 150001: B = 200: 36.0 -> 35.0, 256: 36.6 -> 37.5; bf16: 18.9 -> 21.9.  Not split.
+//   257 to 640 rows of f32 from 512 KB on, V = 150001: 3 chunks up to 400 rows: B = 272: 56.0 -> 44.1, 320: 56.8 -> 46.5,
+//     400: 62.9 -> 57.7; then 2: B = 512: 67.2 -> 64.9, 640: 90.7 -> 81.1.  V = 50000, B = 400: 25.6 -> 27.3; bf16
+//     V = 150001, B = 320: 30.3 -> 29.8, 512: 34.9 -> 40.8: not split.
+// A chunk of bf16 is streamed by 16 waves, one of f32 by 8, which was the faster of the two at every one of these sizes.
+struct RowSplit {
+  int chunks, waves;
+};
+
+RowSplit own_split(int dt, int64_t B, int64_t V) {
+  const int64_t row_bytes = V * (dt == ESPO_BF16 ? 2 : 4);
+  const int waves = dt == ESPO_BF16 ? 16 : 8;
+  constexpr int64_t kLong = 256 * 1024, kVeryLong = 512 * 1024;
+  if (B <= 128 && row_bytes >= kLong) return RowSplit{B > 64 ? 2 : B <= 16 && row_bytes >= kVeryLong ? 8 : 4, waves};
+  if (dt == ESPO_F32 && B > 256 && B <= 640 && row_bytes >= kVeryLong) return RowSplit{B <= 400 ? 3 : 2, waves};
+  return RowSplit{1, 0};
+}
+
 StepPlan plan_step(int dt, int64_t B, int64_t V, bool filter, int waves, int chunks) {
   StepPlan p;
   const int ntiles = (int)((V + kTile - 1) / kTile);
   p.waves = waves > 0 ? waves : B >= kEightWavesFrom ? 8 : 16;
   int nch = filter || chunks <= 0 ? 1 : chunks;
+  if (!filter && waves <= 0 && chunks <= 0) {
+    const RowSplit own = own_split(dt, B, V);
+    nch = own.chunks;
+    if (nch > 1) p.waves = own.waves;
+  }
   if (nch > ntiles) nch = ntiles;
   if (nch > kMaxChunks) nch = kMaxChunks;
   p.chunks = nch;
@@ -2116,7 +2165,7 @@ int launch_step(const void* logits, int dt, int64_t B, int64_t V, int64_t row_st
   if (plan.chunks > 1) {
     size_t off = 0;
     step_workspace_layout(B, plan.chunks, &off);
-    a.tickets = (uint32_t*)workspace;
+    a.tickets = (unsigned long long*)workspace;
     a.partials = (ChunkResult*)((char*)workspace + off);
   }
 

@@ -587,6 +587,47 @@ def test_workspace_contract():
             np.testing.assert_array_equal(o3.host()[k].view(np.uint8), b.host()[k].view(np.uint8))
 
 
+# The library's own split: shapes on both sides of its rule, workspaces that are zero, hold anything, are too short,
+# misaligned or missing.  The words and the state are the bits of one workgroup per row; the softmax sums may be
+# added in another order: log-probability and entropy to 2e-6 of their size (sums of V terms in fp32, by chunks).
+@pytest.mark.parametrize("B,V,dtype", [(1, 32768, torch.bfloat16), (3, 16383, torch.float32), (5, 70001, torch.bfloat16), (16, 152064, torch.bfloat16),
+                                       (32, 66001, torch.float32), (33, 152064, torch.bfloat16), (64, 50003, torch.float32),
+                                       (65, 152064, torch.bfloat16), (129, 40000, torch.bfloat16), (257, 40003, torch.float32), (384, 70000, torch.float32)])
+def test_rows_the_library_splits_itself(B, V, dtype):
+    _say(f"[case] own split B={B} V={V} {dtype}")
+    stride = (V + 7) // 8 * 8
+    logits = torch.zeros(B, stride, dtype=dtype, device="cuda")
+    W.ZipfLogits(V=V, seed=B + V, device="cuda", dtype=dtype).rows(B, out=logits[:, :V])
+    logits[B // 2, :V] = 0.25                                 # ties everywhere: the combine decides between chunks
+    vals = torch.rand(B, generator=torch.Generator().manual_seed(V)).cuda()
+    gp, _ = H.params_pair(mu_g=1.0, var_g=2.0, beta=1.5)
+    alive = (torch.arange(B) % 7 != 5).to(torch.uint8)
+    need = espo.espo_step_workspace_bytes(B, V, dtype)
+    buffers = {"none": None, "short": torch.full((max(need - 16, 0),), 0xCD, dtype=torch.uint8, device="cuda"),
+               "misaligned": torch.full((need + 16,), 0xCD, dtype=torch.uint8, device="cuda")[4:],
+               "zero": torch.zeros(need, dtype=torch.uint8, device="cuda"),
+               "noise": torch.randint(0, 256, (need + 64,), dtype=torch.uint8, device="cuda")}
+    results = {}
+    for name, ws in buffers.items():
+        st = H.GpuState(B, alive=alive, z=torch.zeros(B))
+        st.entropy = torch.zeros(B, device="cuda")
+        out = []
+        for step in range(3):
+            espo.espo_step(logits, 0.8, 5, step, vals, gp, st.z, st.alive, st.stop_step, st.tokens, st.regret, st.logprob, V=V,
+                           workspace=ws, entropy=st.entropy)
+            out.append([getattr(st, k).cpu().numpy().copy() for k in ("tokens", "regret", "z", "alive", "stop_step", "logprob", "entropy")])
+        results[name] = out
+    if need:
+        assert not bool(buffers["zero"].any())                # handed back as it came
+    for name, out in results.items():
+        for step in range(3):
+            for k, (got, want) in enumerate(zip(out[step], results["none"][step])):
+                if k < 5:
+                    np.testing.assert_array_equal(got.view(np.uint8), want.view(np.uint8), err_msg=f"{name} step {step} output {k}")
+                else:
+                    np.testing.assert_allclose(got, want, rtol=2e-6, atol=2e-6, err_msg=f"{name} step {step} output {k}")
+
+
 @pytest.mark.parametrize("B", [513, 600, 1024, 1500, 2600])
 def test_more_rows_than_resident_workgroups(B):
     _say(f"[case] more rows than resident workgroups, B={B}")
