@@ -113,7 +113,7 @@ def main() -> int:
     tokens = torch.empty(B_STEP, dtype=torch.int32, device=dev)
     regret = torch.empty(B_STEP, dtype=torch.float32, device=dev)
     logprob = torch.empty(B_STEP, dtype=torch.float32, device=dev)
-    nws = espo.espo_step_workspace_bytes(B_STEP, V_STEP, torch.bfloat16)      # 0 in this version: one workgroup per row
+    nws = espo.espo_step_workspace_bytes(B_STEP, V_STEP, torch.bfloat16)      # 0 for this shape: one workgroup per row
     step_ws = torch.zeros(nws, dtype=torch.uint8, device=dev) if nws else None
 
     def run(first, last, z, alive, ss, events=None, entropy=None, params=params, lp=logprob, temperature=tau, ws=step_ws, **layout):

@@ -919,6 +919,8 @@ __device__ __forceinline__ void step_row(const StepArgs& a, unsigned char* smem_
   auto iteration = [&](auto steady, int d, int i) {
     constexpr bool Steady = decltype(steady)::value;
     const int t = tile0 + i * kStepWaves + wave;
+    float* const mu = mu_lane + (size_t)i * (2 * kStepWaves * kGroups);
+    const float mub = mu[0];  // asked for before the tile is waited for
     float x[8];
     unpack<DT>(ring[d], x);
     if (!Steady && (t + 1) * kTile > a.V) {  // ragged last tile: indices at or beyond V do not exist
@@ -973,8 +975,7 @@ __device__ __forceinline__ void step_row(const StepArgs& a, unsigned char* smem_
     }
     // upper bound of every perturbed score in the lane group's block: y_max + M_q
     const float bm = group8_max(gm);
-    float* const mu = mu_lane + (size_t)i * (2 * kStepWaves * kGroups);
-    const float ub = fmaf(bm, a.inv_tau, mu[0]);
+    const float ub = fmaf(bm, a.inv_tau, mub);
     mu[1] = ub;  // the 8 lanes of the group store the same value
     if constexpr (Filter) bmx_lane[(size_t)i * (kStepWaves * kGroups)] = bm;
     mx = fmaxf(mx, bm);
