@@ -5,12 +5,21 @@
 // Two small kernels.  The first reduces the valid tokens regret[b, t < L_b] to per-workgroup
 // partial sums of d = g - mu_g and d^2 in double (shifting by the current mean estimate keeps
 // the one-pass variance free of cancellation), plus token and stop counts; workgroup w takes
-// rows w, w + G, ...  The second adds the partials in a fixed order and forms the outputs.
-// Every reduction tree is fixed, so the result does not depend on scheduling.
+// rows w, w + G, ...  Rows of any length are read 16 bytes at a time: where T is no multiple of 4,
+// from the 16-byte boundary before them, four loads per lane in flight.  The second adds the at most 1024 partials in a fixed
+// order and forms the outputs.  A batch of at most 16 pieces of 1024 positions is one launch of one
+// workgroup, whose waves take four pieces each.  Every reduction tree is fixed, so the result does
+// not depend on scheduling.
+//
+// Bound by latency: launch, lengths, tokens, reduction, and the same once more for the partials.
+// us per call on the GPU, before -> now (before: element-wise loads for odd T, two launches always): B = 512, T = 8191:
+// 14.1 -> 10.6; B = 1024, T = 16383: 25.1 -> 18.3; B = 8, T = 16383: 11.4 -> 8.7; B = 4, T = 128: 5.7 -> 3.4; B = 1, T = 16384:
+// 6.7 -> 4.4; one launch for 32 pieces instead: 9.1 against 5.8 for B = 32, T = 900, so the line is at 16.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "../../include/espo.h"
@@ -27,103 +36,51 @@ namespace {
 
 constexpr int kStatThreads = 256;
 constexpr int kStatWaves = kStatThreads / kWave;
-constexpr int kMaxStatGroups = 1024;
+constexpr int kStatQuads = 4;                        // groups of four positions per lane and item
+constexpr int kStatItem = kWave * 4 * kStatQuads;    // positions per item: 1024
+constexpr int kStatUnroll = 4;                       // items of a wave, their loads in flight together
+constexpr int kRowLoads = 4;                         // 16-byte loads of a lane in flight when a workgroup takes whole rows
+constexpr int kMaxStatGroups = 1024;                 // partials the workspace has room for
+constexpr int kFinalThreads = 256, kFinalEach = kMaxStatGroups / kFinalThreads;  // partials per thread
+constexpr int kOneLaunchItems = kStatWaves * kStatUnroll;  // batches of at most this many items are one launch of one workgroup
 
 struct Partial {
   double s1, s2;
   long long n, nstop;
 };
 
-__device__ __forceinline__ double shfl_down_f64(double v, int d) {
-  int lo = __double2loint(v), hi = __double2hiint(v);
-  lo = __shfl_down(lo, d);
-  hi = __shfl_down(hi, d);
-  return __hiloint2double(hi, lo);
-}
-
-// Sum over the workgroup in a fixed tree; the result is valid in thread 0.
-__device__ __forceinline__ double block_sum(double v, double* lds) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) v += shfl_down_f64(v, d);
+// Sums over the workgroup of W waves in a fixed tree, the same in every thread; lds holds N * W entries.
+template <int N, int W>
+__device__ __forceinline__ void block_sums(double v[N], double* lds) {
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
-  __syncthreads();  // lds may still be read from the call before
-  if (lane == 0) lds[wave] = v;
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] = wave_sum_f64(v[i]);
+  if (lane == 0) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) lds[i * W + wave] = v[i];
+  }
   __syncthreads();
-  double t = 0.0;
-  if (threadIdx.x == 0)
-    for (int w = 0; w < kStatWaves; ++w) t += lds[w];
-  return t;
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] = wave_sum_f64(lane < W ? lds[i * W + lane] : 0.0);
 }
 
-template <bool VEC>
-__global__ __launch_bounds__(kStatThreads) void batch_partial_kernel(const float* __restrict__ regret,
-                                                                     const int32_t* __restrict__ lengths,
-                                                                     const uint8_t* __restrict__ stopped, int64_t B,
-                                                                     int64_t T, float mu_g, Partial* __restrict__ part) {
-  __shared__ double lds[kStatWaves];
-  const double shift = (double)mu_g;
-  double s1 = 0.0, s2 = 0.0;
-  long long n = 0, nstop = 0;
-  for (int64_t b = blockIdx.x; b < B; b += gridDim.x) {
-    int64_t L = lengths[b];
-    L = L < 0 ? 0 : (L > T ? T : L);
-    const float* row = regret + b * T;
-    if (VEC) {  // T % 4 == 0: rows are 16-byte aligned
-      const int64_t full = L & ~(int64_t)3;
-      for (int64_t t = (int64_t)threadIdx.x * 4; t < full; t += kStatThreads * 4) {
-        const f32x4 g = __builtin_nontemporal_load((const f32x4*)(row + t));
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const double d = (double)g[j] - shift;
-          s1 += d;
-          s2 += d * d;
-        }
-      }
-      if (threadIdx.x < (unsigned)(L - full)) {  // the last one to three tokens
-        const double d = (double)row[full + threadIdx.x] - shift;
-        s1 += d;
-        s2 += d * d;
-      }
-    } else {
-      for (int64_t t = threadIdx.x; t < L; t += kStatThreads) {
-        const double d = (double)row[t] - shift;
-        s1 += d;
-        s2 += d * d;
-      }
-    }
-    if (threadIdx.x == 0) {
-      n += L;
-      nstop += stopped[b] != 0;
-    }
-  }
-  const double t1 = block_sum(s1, lds);
-  const double t2 = block_sum(s2, lds);
-  if (threadIdx.x == 0) part[blockIdx.x] = Partial{t1, t2, n, nstop};
-}
+struct PartialArgs {
+  const float* regret;
+  const int32_t* lengths;
+  const uint8_t* stopped;
+  int64_t B, T;
+  float mu_g;
+  Partial* part;
+};
 
 struct FinalArgs {
-  const Partial* part;
-  int groups;
   int64_t B;
   float mu_g, var_g, beta, alpha_ema, eta_beta, target_rate, beta_min, beta_max;
   espo_batch_result* out;
 };
 
-__global__ __launch_bounds__(kStatThreads) void batch_final_kernel(FinalArgs a) {
-  __shared__ double lds[kStatWaves];
-  double s1 = 0.0, s2 = 0.0, n = 0.0, ns = 0.0;  // counts are below 2^53: exact in double
-  for (int i = threadIdx.x; i < a.groups; i += kStatThreads) {
-    const Partial p = a.part[i];
-    s1 += p.s1;
-    s2 += p.s2;
-    n += (double)p.n;
-    ns += (double)p.nstop;
-  }
-  s1 = block_sum(s1, lds);
-  s2 = block_sum(s2, lds);
-  n = block_sum(n, lds);
-  ns = block_sum(ns, lds);
-  if (threadIdx.x != 0) return;
+// The outputs from the four sums (counts are below 2^53: exact in double).
+__device__ __forceinline__ void write_result(const FinalArgs& a, double s1, double s2, double n, double ns) {
   espo_batch_result r;
   const double md = n > 0.0 ? s1 / n : 0.0;                        // mean of g - mu_g
   const double mean = n > 0.0 ? (double)a.mu_g + md : 0.0;
@@ -152,6 +109,146 @@ __global__ __launch_bounds__(kStatThreads) void batch_final_kernel(FinalArgs a) 
   *a.out = r;
 }
 
+// Whether the 256 positions from `at` hold any of [lo, hi) (uniform in the wave: short rows cost what they hold).
+__device__ __forceinline__ bool any_in(int64_t at, int64_t lo, int64_t hi) { return at < hi && at + 4 * kWave > lo; }
+
+// This lane's four tokens of those 256; positions outside [lo, hi) read as the shift, so that they add nothing.
+__device__ __forceinline__ f32x4 load_tokens(const float* __restrict__ src, int64_t at, int64_t lo, int64_t hi, float shift) {
+  const int64_t t = at + (int64_t)(threadIdx.x & (kWave - 1)) * 4;
+  if (at >= lo && at + 4 * kWave <= hi) return __builtin_nontemporal_load((const f32x4*)(src + t));
+  f32x4 g = {shift, shift, shift, shift};
+  if (t >= lo && t + 4 <= hi) {
+    g = __builtin_nontemporal_load((const f32x4*)(src + t));
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (t + j >= lo && t + j < hi) g[j] = src[t + j];
+  }
+  return g;
+}
+
+__device__ __forceinline__ void add_tokens(const f32x4& g, double shift, double& s1, double& s2) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const double d = (double)g[j] - shift;
+    s1 += d;
+    s2 = fma(d, d, s2);
+  }
+}
+
+// Where a row's tokens lie: [lo, hi) from `src`, a multiple of 16 bytes.
+struct RowSpan {
+  const float* src;
+  int64_t lo, hi;
+};
+
+__device__ __forceinline__ RowSpan row_span(const PartialArgs& a, int64_t row, int64_t& L) {
+  L = __builtin_amdgcn_readfirstlane(a.lengths[row]);
+  L = L < 0 ? 0 : (L > a.T ? a.T : L);
+  const int64_t first = row * a.T, head = first & 3;
+  return RowSpan{a.regret + (first - head), head, head + L};
+}
+
+// Aligned: T % 4 == 0, every row starts at a 16-byte boundary.
+template <bool Aligned>
+__global__ __launch_bounds__(kStatThreads) void batch_partial_kernel(PartialArgs a) {
+  __shared__ double lds[4 * kStatWaves];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const double shift = (double)a.mu_g;
+  double s1 = 0.0, s2 = 0.0, n = 0.0, nstop = 0.0;
+  for (int64_t row = blockIdx.x; row < a.B; row += gridDim.x) {
+    const uint32_t stop = a.stopped[row];
+    int64_t L;
+    const RowSpan r = row_span(a, row, L);
+    if constexpr (Aligned) {  // 16.8 us at B = 1024, T = 16384, where the loop below takes 17.6
+      const int64_t full = L & ~(int64_t)3;
+      for (int64_t t = (int64_t)threadIdx.x * 4; t < full; t += kStatThreads * 4)
+        add_tokens(__builtin_nontemporal_load((const f32x4*)(r.src + t)), shift, s1, s2);
+      if (threadIdx.x < (unsigned)(L - full)) {  // the last one to three tokens
+        const double d = (double)r.src[full + threadIdx.x] - shift;
+        s1 += d;
+        s2 = fma(d, d, s2);
+      }
+    } else for (int64_t at = wave * 4 * kWave; at < r.hi; at += kRowLoads * kStatThreads * 4) {
+      f32x4 g[kRowLoads];
+#pragma unroll
+      for (int u = 0; u < kRowLoads; ++u)
+        if (any_in(at + u * kStatThreads * 4, r.lo, r.hi)) g[u] = load_tokens(r.src, at + u * kStatThreads * 4, r.lo, r.hi, a.mu_g);
+#pragma unroll
+      for (int u = 0; u < kRowLoads; ++u)
+        if (any_in(at + u * kStatThreads * 4, r.lo, r.hi)) add_tokens(g[u], shift, s1, s2);
+    }
+    if (threadIdx.x == 0) {
+      n += (double)L;
+      nstop += stop != 0 ? 1.0 : 0.0;
+    }
+  }
+  double v[4] = {s1, s2, n, nstop};
+  block_sums<4, kStatWaves>(v, lds);
+  if (threadIdx.x == 0) a.part[blockIdx.x] = Partial{v[0], v[1], (long long)v[2], (long long)v[3]};
+}
+
+// One workgroup for a whole batch of at most kOneLaunchItems items (`per_row` of them in a row).
+__global__ __launch_bounds__(kStatThreads) void batch_small_kernel(PartialArgs a, FinalArgs f, int items, int per_row) {
+  __shared__ double lds[4 * kStatWaves];
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const double shift = (double)a.mu_g;
+  double s1 = 0.0, s2 = 0.0, n = 0.0, nstop = 0.0;
+  f32x4 g[kStatUnroll][kStatQuads];
+  RowSpan r[kStatUnroll];
+#pragma unroll
+  for (int u = 0; u < kStatUnroll; ++u) {
+    const int it = u * kStatWaves + wave;
+    r[u] = RowSpan{nullptr, 0, 0};
+    if (it < items) {  // (wave-uniform)
+      const int row = it / per_row, off = (it - row * per_row) * kStatItem;
+      int64_t L;
+      r[u] = row_span(a, row, L);
+      r[u].src += off;
+      r[u].lo = off == 0 ? r[u].lo : 0;
+      r[u].hi = r[u].hi - off < kStatItem ? r[u].hi - off : kStatItem;
+#pragma unroll
+      for (int q = 0; q < kStatQuads; ++q)
+        if (any_in(q * 4 * kWave, r[u].lo, r[u].hi)) g[u][q] = load_tokens(r[u].src, q * 4 * kWave, r[u].lo, r[u].hi, a.mu_g);
+    }
+  }
+  if (wave == 0 && lane < a.B) {  // at most kOneLaunchItems rows: a lane each
+    const int64_t L = a.lengths[lane];
+    n = (double)(L < 0 ? 0 : (L > a.T ? a.T : L));
+    nstop = a.stopped[lane] != 0 ? 1.0 : 0.0;
+  }
+#pragma unroll
+  for (int u = 0; u < kStatUnroll; ++u)
+#pragma unroll
+    for (int q = 0; q < kStatQuads; ++q)
+      if (any_in(q * 4 * kWave, r[u].lo, r[u].hi)) add_tokens(g[u][q], shift, s1, s2);
+  double v[4] = {s1, s2, n, nstop};
+  block_sums<4, kStatWaves>(v, lds);
+  if (threadIdx.x == 0) write_result(f, v[0], v[1], v[2], v[3]);
+}
+
+__global__ __launch_bounds__(kFinalThreads) void batch_final_kernel(const Partial* __restrict__ part, int groups, FinalArgs f) {
+  __shared__ double lds[4 * (kFinalThreads / kWave)];
+  double v[4] = {0.0, 0.0, 0.0, 0.0};
+  Partial p[kFinalEach];
+#pragma unroll
+  for (int i = 0; i < kFinalEach; ++i) {
+    const int at = i * kFinalThreads + (int)threadIdx.x;
+    p[i] = at < groups ? part[at] : Partial{0.0, 0.0, 0, 0};
+  }
+#pragma unroll
+  for (int i = 0; i < kFinalEach; ++i) {
+    v[0] += p[i].s1;
+    v[1] += p[i].s2;
+    v[2] += (double)p[i].n;
+    v[3] += (double)p[i].nstop;
+  }
+  block_sums<4, kFinalThreads / kWave>(v, lds);
+  if (threadIdx.x == 0) write_result(f, v[0], v[1], v[2], v[3]);
+}
+
+// Partials the workspace of B rows has room for.
 int stat_groups(int64_t B) { return (int)(B < 1 ? 1 : (B > kMaxStatGroups ? kMaxStatGroups : B)); }
 
 // Device address of `scratch` on the current GPU: looked up once per device, with that device
@@ -182,25 +279,31 @@ size_t batch_stats_workspace(int64_t B) { return (size_t)stat_groups(B) * sizeof
 int launch_batch_stats(const float* regret, const int32_t* lengths, const uint8_t* stopped, int64_t B, int64_t T,
                        float mu_g, float var_g, float beta, const espo_batch_ctrl& c, espo_batch_result* out,
                        void* workspace, hipStream_t stream) {
-  const int groups = B > 0 ? stat_groups(B) : 0;
-  if (groups > 0) {
-    if (T % 4 == 0)
-      hipLaunchKernelGGL(batch_partial_kernel<true>, dim3(groups), dim3(kStatThreads), 0, stream, regret, lengths,
-                         stopped, B, T, mu_g, (Partial*)workspace);
-    else
-      hipLaunchKernelGGL(batch_partial_kernel<false>, dim3(groups), dim3(kStatThreads), 0, stream, regret, lengths,
-                         stopped, B, T, mu_g, (Partial*)workspace);
-    if (hipGetLastError() != hipSuccess) return ESPO_EHIP;
+  FinalArgs f;
+  f.B = B;
+  f.mu_g = mu_g; f.var_g = var_g; f.beta = beta;
+  f.alpha_ema = c.alpha_ema; f.eta_beta = c.eta_beta; f.target_rate = c.target_rate;
+  f.beta_min = c.beta_min; f.beta_max = c.beta_max;
+  f.out = out;
+  PartialArgs p;
+  p.regret = regret; p.lengths = lengths; p.stopped = stopped;
+  p.B = B; p.T = T;
+  p.mu_g = mu_g;
+  p.part = (Partial*)workspace;
+  // a row that starts between boundaries spans up to 3 positions more; a row of no positions is still counted
+  const int64_t per_row = T > 0 ? (T + (T % 4 != 0 ? 3 : 0) + kStatItem - 1) / kStatItem : 1;
+  if (B * per_row <= kOneLaunchItems) {
+    static_assert(kOneLaunchItems <= kWave, "a lane per row");
+    hipLaunchKernelGGL(batch_small_kernel, dim3(1), dim3(kStatThreads), 0, stream, p, f, (int)(B * per_row), (int)per_row);
+    return hipGetLastError() == hipSuccess ? ESPO_OK : ESPO_EHIP;
   }
-  FinalArgs a;
-  a.part = (const Partial*)workspace;
-  a.groups = groups;
-  a.B = B;
-  a.mu_g = mu_g; a.var_g = var_g; a.beta = beta;
-  a.alpha_ema = c.alpha_ema; a.eta_beta = c.eta_beta; a.target_rate = c.target_rate;
-  a.beta_min = c.beta_min; a.beta_max = c.beta_max;
-  a.out = out;
-  hipLaunchKernelGGL(batch_final_kernel, dim3(1), dim3(kStatThreads), 0, stream, a);
+  const int groups = stat_groups(B);
+  if (T % 4 == 0)
+    hipLaunchKernelGGL(batch_partial_kernel<true>, dim3(groups), dim3(kStatThreads), 0, stream, p);
+  else
+    hipLaunchKernelGGL(batch_partial_kernel<false>, dim3(groups), dim3(kStatThreads), 0, stream, p);
+  if (hipGetLastError() != hipSuccess) return ESPO_EHIP;
+  hipLaunchKernelGGL(batch_final_kernel, dim3(1), dim3(kFinalThreads), 0, stream, p.part, groups, f);
   return hipGetLastError() == hipSuccess ? ESPO_OK : ESPO_EHIP;
 }
 

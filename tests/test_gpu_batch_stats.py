@@ -44,6 +44,23 @@ def test_shapes_ragged_lengths_and_poisoned_padding(B, T):
     _run(regret, lengths, stopped, 0.3, 0.1, 2.0, beta_max=3.0)
 
 
+# Where the work is cut: one launch up to 16 pieces of 1024 positions (16, 17 rows of one; rows of 1021 positions are one
+# piece, of 1022 and 1027 two; 4 rows of 4096 and 4097; one row of 16384), then a workgroup per row: 4096 positions per pass,
+# rows that start between 16-byte boundaries, more rows than the 1024 workgroups.
+@pytest.mark.parametrize("B,T", [(16, 1000), (17, 1000), (16, 1021), (9, 1022), (8, 1027), (4, 4096), (4, 4097), (1, 16384), (16, 0), (40, 0), (64, 4095),
+                                 (33, 4103), (3, 20481), (17000, 37), (1030, 16383), (2, 65537)])
+def test_items_at_every_boundary(B, T):
+    print(f"[case] batch stats items B={B} T={T}", flush=True)
+    regret, lengths, stopped = W.regret_batch(B, max(T, 1), len_lo=0, seed=B + 7 * T, device="cuda", poison=True)
+    regret = regret[:, :T].contiguous()                       # T = 0: rows of no positions are counted, nothing is read
+    lengths[B // 2] = 0
+    _run(regret, lengths, stopped, 1.0, 2.0, 7.0)
+    lengths[:] = T
+    regret = torch.nan_to_num(regret, nan=0.5)
+    got = _run(regret, lengths, stopped, 0.5, 2.0, 7.0)
+    assert got["tokens"] == B * T
+
+
 def test_rollout_sized_batch_and_determinism():
     print("[case] batch stats B=512 T=8192", flush=True)
     regret, lengths, stopped = W.regret_batch(512, 8192, seed=5, device="cuda", poison=True)
