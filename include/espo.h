@@ -168,7 +168,8 @@ typedef enum {
  *   logits      device, [B, row_stride] elements of `dt` (row-major, row b starts
  *               at element b*row_stride); only the first V of each row are read.
  *               Base address and row pitch in bytes must be multiples of 16.
- *               -inf entries are allowed (masked vocabulary); NaN and +inf are not
+ *               -inf entries are allowed (masked vocabulary), and so is the type's lowest value
+ *               in their place (anything at or below -1e30 counts as masked); NaN and +inf are not
  *               supported (results for that row are unspecified, no fault).
  *   dt          ESPO_F32 or ESPO_BF16.
  *   B, V        rows and vocabulary size; B >= 0 (0 is a no-op), 1 <= V <= 400000

@@ -157,6 +157,15 @@ __device__ __forceinline__ float elem_at(const void* base, int64_t idx) {
     return ((const float*)base)[idx];
 }
 
+// Logits at or below this are masked like -inf, whatever they are filled with (often the type's lowest value): they hold
+// no probability beside any other logit and no search offers them.
+constexpr float kMaskedBelow = -1e30f;
+constexpr float kNoReference = 1e30f;  // a lane's softmax reference before its first logit that counts
+
+// The negated reference of a lane's softmax sum at logit g.  A masked g over the temperature may overflow; the reference then
+// stays where it is before the first logit, so that masked logits add nothing (and no infinity).
+__device__ __forceinline__ float lane_reference(float g, float k2) { return fminf(-g * k2, kNoReference); }
+
 // ---------------------------------------------------------------- scores
 // A candidate for the argmax: score s = y + G known to within +-e, its index and logit.
 template <typename F>
@@ -524,7 +533,7 @@ __device__ __forceinline__ Search<F> find_argmax(const StepArgs& a, const StepSh
       // blocks whose bound reaches the best score found so far
       for (int b = sh.q0 + tid; b < sh.q0 + nslots; b += kStepThreads) {
         const float u = sh.ub(b);
-        if (u > -1e30f && ub_rounded_up(u) >= bound_f && sh.visq[wave_of<W>(sh, b)] != b && holds_eligible(sh, b))
+        if (u > kMaskedBelow && ub_rounded_up(u) >= bound_f && sh.visq[wave_of<W>(sh, b)] != b && holds_eligible(sh, b))
           sh.surv(atomicAdd(sh.nsurv, 1)) = b;
       }
       __syncthreads();
@@ -678,7 +687,7 @@ __device__ __forceinline__ bool exact_among_candidates(const StepArgs& a, const 
   __syncthreads();
   for (int b = sh.q0 + tid; b < sh.q0 + nslots; b += kStepThreads) {
     const float u = sh.ub(b);
-    if (u > -1e30f && ub_rounded_up(u) >= lower && holds_eligible(sh, b)) sh.surv(atomicAdd(sh.nsurv, 1)) = b;
+    if (u > kMaskedBelow && ub_rounded_up(u) >= lower && holds_eligible(sh, b)) sh.surv(atomicAdd(sh.nsurv, 1)) = b;
   }
   __syncthreads();
   collect_candidates<DT, W>(a, sh, rowp, *sh.nsurv, lower);
@@ -759,7 +768,7 @@ __device__ __forceinline__ Best fast_argmax(const StepArgs& a, const StepShared&
       for (int b = sh.q0 + tid; b < sh.q0 + nslots; b += kStepThreads) {  // blocks whose bound reaches the best score found so far
         const float u = sh.ub(b);
         const int w_b = wave_of<W>(sh, b);
-        if (u > -1e30f && ub_rounded_up(u) >= bound && sh.visq[w_b] != b && sh.visq[kStepWaves + w_b] != b && holds_eligible(sh, b))
+        if (u > kMaskedBelow && ub_rounded_up(u) >= bound && sh.visq[w_b] != b && sh.visq[kStepWaves + w_b] != b && holds_eligible(sh, b))
           sh.surv(atomicAdd(sh.nsurv, 1)) = b;
       }
       if (tid == 0) *sh.bkey = float_key(bound);
@@ -902,7 +911,7 @@ __device__ __forceinline__ void step_row(const StepArgs& a, unsigned char* smem_
   // sum_v 2^(x_v k2 + nrk) with nrk = -(reference logit) * k2; the final combine multiplies
   // by 2^-(m k2 + nrk), so the rounding of nrk itself cancels.  `lead` is the logit beyond
   // which the reference has to move up (the sum would grow past 2^64 per term otherwise).
-  float nrk = 1e30f;
+  float nrk = kNoReference;
   float lead = kNegInf;
   float sum = 0.0f;
   float sumw = 0.0f;         // entropy output: sum_v 2^t_v t_v with t_v = x_v k2 + nrk (see below)
@@ -934,7 +943,7 @@ __device__ __forceinline__ void step_row(const StepArgs& a, unsigned char* smem_
       if (__builtin_amdgcn_ballot_w64(gm > lead) != 0) {  // rare after the first tile
         asm volatile("" ::: "memory");  // keep this rare path out of the straight-line code
         if (gm > lead) {  // move this lane's reference up to gm
-          const float nrk_new = -gm * a.k2;
+          const float nrk_new = lane_reference(gm, a.k2);
           const float shift = nrk_new - nrk;  // every t_v moves by this much
           const float f = __builtin_amdgcn_exp2f(shift);
           if (Entropy) sumw = f * fmaf(shift, sum, sumw);
@@ -1765,12 +1774,12 @@ __device__ __forceinline__ bool filtered_row(const StepArgs& a, unsigned char* s
     *f.nmem = 0;
   }
 
-  float nrk = 1e30f, lead = kNegInf, sum = 0.0f, sumw = 0.0f;  // the lane's softmax sum against its lazy reference
+  float nrk = kNoReference, lead = kNegInf, sum = 0.0f, sumw = 0.0f;  // the lane's softmax sum against its lazy reference
   float mx = kNegInf;
   uint32_t* const my_raw = f.raw + (size_t)wave * Lim::kRoom * kWords;
   uint16_t* const my_id = f.id + (size_t)wave * Lim::kRoom;
   int n = 0;                    // packs in this wave's list (wave-uniform)
-  float thr = kNegInf;          // every logit above it that the wave has seen is in the list
+  float thr = kMaskedBelow;     // every logit above it that the wave has seen is in the list
   float low = __builtin_huge_valf();  // the smallest pack maximum this lane has put there
   bool flooded = false;         // a compaction found most of the list tied at its threshold
   int dry = 0;                  // passes since then that have left the list next to empty
@@ -1791,7 +1800,7 @@ __device__ __forceinline__ bool filtered_row(const StepArgs& a, unsigned char* s
     if (__builtin_amdgcn_ballot_w64(gm > lead) != 0) {  // rare after the first tile
       asm volatile("" ::: "memory");  // keep this rare path out of the straight-line code
       if (gm > lead) {  // move this lane's reference up to gm
-        const float nrk_new = -gm * a.k2;
+        const float nrk_new = lane_reference(gm, a.k2);
         const float shift = nrk_new - nrk;
         const float g = __builtin_amdgcn_exp2f(shift);
         if (Entropy) sumw = g * fmaf(shift, sum, sumw);
@@ -1881,7 +1890,7 @@ __device__ __forceinline__ bool filtered_row(const StepArgs& a, unsigned char* s
   // ------------------------------------------------------------ m, T and S
   const float m = wave_max(lane < W ? f.m[lane] : kNegInf);
   float bottom = wave_max(lane < W ? f.thr[lane] : kNegInf);  // every logit above it is in a list
-  if (!(bottom > kNegInf)) {  // no list was ever compacted: the smallest pack maximum leaves a logit of every pack above
+  if (!(bottom > kMaskedBelow)) {  // no list was ever compacted: the smallest pack maximum leaves a logit of every pack above
     const float lowest = -wave_max(lane < W ? -f.low[lane] : kNegInf);
     const int32_t bits = __builtin_bit_cast(int32_t, lowest);
     bottom = lowest == 0.0f ? -1.401298464e-45f : __builtin_bit_cast(float, bits + (lowest > 0.0f ? -1 : 1));
@@ -1909,7 +1918,7 @@ __device__ __forceinline__ bool filtered_row(const StepArgs& a, unsigned char* s
       // of the lanes' largest logits.  (Of n lanes with V / n values each, about n ln n values of the row lie above the
       // smallest maximum: 3200 with 8 waves, 7100 with 16, whatever V is.)
       const float floor2 = -wave_max(lane < W ? -f.least[lane] : kNegInf);
-      if (!(floor2 < bottom && floor2 > kNegInf)) return false;
+      if (!(floor2 < bottom && floor2 > kMaskedBelow)) return false;
       __syncthreads();  // the packs and the bins have been read by everyone
       for (int b = tid; b < kEdgeBins; b += W * kWave) f.bins[b] = 0;
       if (tid == 0) {

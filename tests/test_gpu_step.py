@@ -56,6 +56,37 @@ def test_masked_vocabulary_and_ties():
             assert (got["tokens"][live] % 2 == 1).all()
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("where", ["random", "front", "back", "all but a few"])
+def test_masks_of_the_lowest_value(where, dtype):
+    _say(f"[case] masked entries at the type's lowest value, {where} {dtype}")
+    # A masked vocabulary is often filled with the most negative finite number instead of -inf.  Over the temperature that
+    # overflows (tau < 1.44), also where all of a lane's first logits are masked; such an entry has probability 0 either way.
+    for V, tau, layouts in [(152064, 0.6, (dict(), dict(workspace=False), dict(waves=8))), (152064, 2.0, (dict(),)),
+                            (70001, 1.0, (dict(), dict(chunks=5))), (5003, 0.6, (dict(), dict(waves=4))), (5003, 8.0, (dict(),)), (37, 1.0, (dict(),))]:
+        B = 4
+        stride = (V + 7) // 8 * 8
+        g = torch.Generator().manual_seed(V + int(10 * tau))
+        x = torch.randn(B, stride, generator=g) * 3.0
+        hide = {"random": torch.rand(stride, generator=g) < 0.6, "front": torch.arange(stride) < 0.7 * V,
+                "back": torch.arange(stride) > 0.3 * V, "all but a few": torch.rand(stride, generator=g) < 1.0 - 12.0 / V}[where]
+        hide[V - 1 if where == "front" else V // 4] = False
+        lowest = torch.finfo(dtype).min
+        logits = x.to(dtype).masked_fill(hide, lowest)
+        logits[:, V:] = 1e4
+        logits = logits.cuda()
+        vals = torch.rand(B, generator=g).cuda()
+        for f in (dict(), dict(top_k=5), dict(top_p=0.8)):
+            for layout in layouts if not f else (dict(), dict(waves=8)):
+                gp, op = H.params_pair(mu_g=1.0, var_g=2.0, beta=3.0, stop_enabled=0, **f)
+                st = H.GpuState(B)
+                try:
+                    for step in range(2):
+                        H.compare_step(logits, tau, 29, step, vals, gp, op, st, V=V, entropy=True, **layout)
+                except AssertionError as err:
+                    raise AssertionError(f"V={V} tau={tau} {f} {layout}: {err}")
+
+
 def test_flat_rows_visit_many_blocks():
     _say("[case] flat rows")
     # uniform logits: no block stands out, so the bound-based pruning has the least to work with
