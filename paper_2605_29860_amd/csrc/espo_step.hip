@@ -166,6 +166,11 @@ constexpr float kNoReference = 1e30f;  // a lane's softmax reference before its 
 // stays where it is before the first logit, so that masked logits add nothing (and no infinity).
 __device__ __forceinline__ float lane_reference(float g, float k2) { return fminf(-g * k2, kNoReference); }
 
+// The weight of logit x beside the row maximum m, on the scale of the softmax sum (in which the rounding of every lane's
+// reference cancels).  The difference comes first: as 2^(x k2 - m k2) with m k2 rounded, all weights of a row would be off by
+// a common factor, up to 4e-5 for logits around 1000 times the temperature, which is more than the 1e-5 trusted below.
+__device__ __forceinline__ float weight_below(float x, float m, float k2) { return __builtin_amdgcn_exp2f((x - m) * k2); }
+
 // ---------------------------------------------------------------- scores
 // A candidate for the argmax: score s = y + G known to within +-e, its index and logit.
 template <typename F>
@@ -1097,7 +1102,6 @@ __device__ __forceinline__ void step_row(const StepArgs& a, unsigned char* smem_
     // over the whole row, in the oracle's arithmetic.
     const auto nothing = [] {};
     const bool by_count = a.top_k > 0;
-    const float nrk_row = -m * a.k2;
     const float total = wave_sum(lane < kStepWaves ? sh.sum[lane] : 0.0f);  // S, as the last step forms it
     const float want = a.top_p * total;
     float mass = 0.0f, count = 0.0f;
@@ -1117,7 +1121,7 @@ __device__ __forceinline__ void step_row(const StepArgs& a, unsigned char* smem_
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
           const bool above = valid && v0 + u < a.V && x[u] > floor_x;
-          acc_m += above ? __builtin_amdgcn_exp2f(fmaf(x[u], a.k2, nrk_row)) : 0.0f;
+          acc_m += above ? weight_below(x[u], m, a.k2) : 0.0f;
           acc_n += above ? 1.0f : 0.0f;  // counts stay exact in fp32: V < 2^24
         }
       };
@@ -1600,7 +1604,6 @@ __device__ __forceinline__ DrawResult draw_from_list(const StepArgs& a, const Fi
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const bool by_count = a.top_k > 0;
   // ---------------------------------------------------------- bins
-  const float nrk_row = -m * a.k2;
   const float want = a.top_p * S;
   const float slack = by_count ? 0.0f : 1e-5f * S;  // what an fp32 sum may be off by
   const float per_logit = (float)kEdgeBins / (m - bottom);
@@ -1609,7 +1612,7 @@ __device__ __forceinline__ DrawResult draw_from_list(const StepArgs& a, const Fi
     return (int)min((uint32_t)(int)((m - x) * per_logit), (uint32_t)kEdgeBins - 1u);
   };
   auto weight_of = [&](float x) {
-    return by_count ? 1u : (uint32_t)(__builtin_amdgcn_exp2f(fmaf(x, a.k2, nrk_row)) * scale + 0.5f);
+    return by_count ? 1u : (uint32_t)(weight_below(x, m, a.k2) * scale + 0.5f);
   };
   list.fill_bins(bottom, bin_of, weight_of);
   __syncthreads();

@@ -912,6 +912,34 @@ def test_top_p_at_the_edge_of_the_kept_set_is_decided_like_the_oracle():
                 H.compare_step(x.cuda(), tau, 99, step, torch.zeros(B, device="cuda"), gp, op, st)
 
 
+@pytest.mark.parametrize("ties", [200, 1000])                 # decided among the edge's members; by the general search
+@pytest.mark.parametrize("tau,offset", [(0.1, 30.0), (0.1, 40.0), (0.2, 35.0), (1.0, 300.0), (1.0, 1000.0)])
+def test_top_p_at_the_edge_with_logits_far_from_zero(tau, offset, ties):
+    _say(f"[case] filtered draws, mass next to p, logits around {offset} at temperature {tau}, {ties} ties")
+    # As above, with logits whose scaled size is hundreds of times their spread: the masses must not carry the rounding
+    # of the row maximum's own exponent.  Logits are multiples of 2^-10, so every row has the same probabilities; the
+    # equal ones hold about a third of the mass, and p lies 1e-6 to 2e-5 on either side of the tall one's.
+    B, V = 32, 4096
+    inv = np.float64(np.float32(1.0) / np.float32(tau))
+    d = np.round(tau * np.log(ties / 0.5) * 1024) / 1024
+    pa = 1.0 / (1.0 + ties * np.exp(-d * inv))
+    g = torch.Generator().manual_seed(int(offset))
+    x = torch.full((B, V), float("-inf"))
+    tall = offset + torch.arange(B, dtype=torch.float64) * (37.0 / 1024)
+    at = torch.randperm(V, generator=g)[:ties + 1]
+    x[:, at] = (tall - d).float()[:, None]
+    x[:, at[0]] = tall.float()
+    for e in (1e-6, 3e-6, 6e-6, 9e-6, 2e-5):
+        for p_val in (pa * (1.0 + e), pa * (1.0 - e)):
+            gp, op = H.params_pair(stop_enabled=0, top_p=float(np.float32(p_val)))
+            st = H.GpuState(B)
+            for step in range(2):
+                try:
+                    H.compare_step(x.cuda(), tau, 99, step, torch.zeros(B, device="cuda"), gp, op, st)
+                except AssertionError as err:
+                    raise AssertionError(f"p {p_val / pa - 1.0:+.1e} off the edge, step {step}: {err}")
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("order", ["ascending", "descending", "clustered", "tied"])
 def test_filtered_draws_whatever_order_the_logits_come_in(order, dtype):
