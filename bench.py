@@ -246,7 +246,7 @@ def main() -> int:
     out["step_without_logprob"] = {"avg_launch_us": nolp_us, "frac": frac_of(nolp_us),
                                    "note": "logprob = NULL: token, regret, state and masks only, no softmax sum"}
     out["step_top_p_0.7"] = {"avg_launch_us": topp_us, "live_rows_last": float((alive4 > 0).sum()),
-                             "note": "filtered draw: own kernel instantiation, reads parts of the row again"}
+                             "note": "filtered draw: a kernel of its own, which reads the row once"}
     out["step_top_p_0.7_tau1"] = {"avg_launch_us": topp1_us, "plain_step_at_tau1_us": plain1_us,
                                   "ratio_to_plain": topp1_us / plain1_us, "live_rows_last": float((alive7 > 0).sum()),
                                   "note": "the paper's evaluation sampling (temperature 1.0, nucleus 0.7) on the same rows, stop rule "

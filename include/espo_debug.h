@@ -32,7 +32,8 @@ extern "C" {
  *                       espo_debug_step_workspace_bytes(B, chunks) bytes (ESPO_EWORKSPACE
  *                       otherwise; its contents do not matter), which comes back zero; the value is lowered to the number of
  *                       tiles of a row and to 64 if it exceeds them.
- * A filtered draw (top_p / top_k) has one layout: waves 0 or 8, chunks 0 or 1.
+ * A filtered draw (top_p / top_k) is never split, and runs 8 waves, or 16 below 256 rows if the choice is the
+ * library's: waves 0 or 8, chunks 0 or 1 (ESPO_EINVAL otherwise).
  * Everything else is espo_step.
  */
 int espo_debug_step(const void* logits, espo_dtype dt, int64_t B, int64_t V, int64_t row_stride,

@@ -20,8 +20,8 @@ struct StepPlan {
 };
 
 // The plan for this shape.  `filter`: a top-p / top-k draw (one more table in LDS, never split).
-// waves / chunks > 0 force those values (the diagnostics entry point); 0 is the library's choice
-// (16 waves, no split).
+// waves / chunks > 0 force those values (the diagnostics entry point); 0 is the library's choice: 16 waves, 8 from
+// 256 rows on, and long rows of a batch that leaves compute units idle split, if `waves` is its choice too.
 StepPlan plan_step(int dt, int64_t B, int64_t V, bool filter, int waves, int chunks);
 
 // Bytes of workspace for B rows split `chunks` ways; the offset of the chunk results behind the tickets.

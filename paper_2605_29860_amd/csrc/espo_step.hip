@@ -2063,8 +2063,8 @@ int launch_math_errors(float* out, hipStream_t stream) {
 // done in the batch the smaller workgroups are 2 to 5 us faster (B = 1024 with 431 live rows: 36.8
 // against 41.7 us; B = 512 with 446: 30.6 against 32.9): workgroups are dispatched in order, and with
 // only 512 slots live rows further back in the batch wait for one (timestamps: a tenth of them start
-// more than 8 us late); with 768 slots all have started within 4 us.  A filtered draw always runs 8 waves, with
-// twice the registers each.  The diagnostics
+// more than 8 us late); with 768 slots all have started within 4 us.  A filtered draw has the same two sizes, with
+// twice the registers per wave, so half as many workgroups to a compute unit.  The diagnostics
 // entry point can force the waves per workgroup and a split of every row into `chunks` runs of
 // tiles, each streamed by a workgroup of its own and combined by the last one to arrive.  Where all compute
 // units have rows enough, no split pays (B = 512, V = 152064 bf16, all rows live): 34.7 us unsplit, 41 us in 2 chunks

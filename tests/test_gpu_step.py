@@ -491,8 +491,8 @@ def test_seeded_sweep_of_shapes_structures_and_margins(part):
         paths[scale] += 1
         mode, simulate = int(rng.choice([0, 0, 0, 1, 2, 3])), int(rng.random() < 0.15)
         filt = [dict(), dict(), dict(top_p=float(rng.choice([0.3, 0.7, 0.95]))), dict(top_k=int(rng.choice([1, 3, 40])))][int(rng.integers(0, 4))]
-        if filt:                                             # a filtered draw has one layout
-            layout = dict()
+        if filt:                                             # the library's choice for a small batch, and for 256 rows and more
+            layout = dict(waves=8) if case % 2 else dict()
         else:
             layout = [dict(), dict(), dict(workspace=False), dict(chunks=int(rng.choice([1, 2, 3, 5, 8, 13, 64]))),
                       dict(chunks=int(rng.choice([2, 4, 7])), waves=int(rng.choice([4, 8, 16]))),
@@ -800,6 +800,10 @@ def test_step_without_logprob_gives_the_same_token_and_state(dtype):
 
 
 # --------------------------------------------------------------------------- filtered draws
+# Workgroups of 16 waves below 256 rows, of 8 from there on: lists of other sizes, checked at other tiles.
+FILTER_LAYOUTS = [dict(), dict(waves=8)]
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_top_p_and_top_k_draws_match_the_oracle(dtype):
     _say(f"[case] filtered draws {dtype}")
@@ -827,14 +831,14 @@ def test_top_p_and_top_k_draws_match_the_oracle(dtype):
         x[:, V:] = 1e4
         logits = x.to(dtype).cuda()
         vals = torch.rand(B, generator=g).cuda()
-        for f in filters:
+        for f, layout in [(f, layout) for f in filters for layout in FILTER_LAYOUTS]:
             gp, op = H.params_pair(mu_g=1.0, var_g=2.0, beta=3.0, **f)
             st = H.GpuState(B, alive=torch.tensor([1, 1, 0, 1, 1, 1], dtype=torch.uint8))
             for step in range(3):
                 try:
-                    got = H.compare_step(logits, tau, 61, step, vals, gp, op, st, V=V, stats=stats, entropy=(step == 1))
+                    got = H.compare_step(logits, tau, 61, step, vals, gp, op, st, V=V, stats=stats, entropy=(step == 1), **layout)
                 except AssertionError as err:
-                    raise AssertionError(f"case {case} V={V} {kind} tau={tau} {f} step {step}: {err}")
+                    raise AssertionError(f"case {case} V={V} {kind} tau={tau} {f} {layout} step {step}: {err}")
             if f.get("top_k") == 1:
                 live = got["tokens"] >= 0
                 assert (got["regret"][live] == 0).all()          # only modes are kept
@@ -851,7 +855,7 @@ def test_top_p_and_top_k_draws_match_the_oracle(dtype):
     for o in outs[1:3]:
         for k in ("tokens", "regret", "z"):
             np.testing.assert_array_equal(o[k].view(np.uint8), outs[0][k].view(np.uint8))
-        # the filtered draw streams the row with 8 waves instead of 16: the softmax sum is associated differently
+        # another kernel streams the row: the softmax sum may be associated differently
         np.testing.assert_allclose(o["logprob"], outs[0]["logprob"], rtol=2e-6, atol=2e-6)
     with pytest.raises(espo.EspoError):
         gp, _ = H.params_pair(top_p=0.5, top_k=3)
@@ -863,10 +867,8 @@ def test_top_p_and_top_k_draws_match_the_oracle(dtype):
 def test_filtered_draws_on_flat_rows_match_the_oracle(dtype):
     _say(f"[case] filtered draws, nuclei of hundreds of tokens {dtype}")
     # At temperature 1 and above the synthetic rows are flat: the kept set has from a few dozen to a few
-    # thousand tokens, below the first trial floor on many rows.  These rows take the second trial floor,
-    # the selection of the edge through bins (several hundred collected logits) and, for the widest
-    # filters, the loop over successive winners.  V = 30000 has too few blocks for the bins and compares
-    # all collected logits with each other instead.
+    # thousand tokens.  Some lie in the lists that were collected while the row streamed, some reach below their
+    # thresholds and are collected again, logit by logit, and the widest go through the loop over successive winners.
     stats = {}
     for case, (V, B, tau, filters) in enumerate([
             (152064, 40, 1.0, [dict(top_p=0.7), dict(top_p=0.5), dict(top_p=0.85), dict(top_k=96), dict(top_k=400)]),
@@ -880,14 +882,14 @@ def test_filtered_draws_on_flat_rows_match_the_oracle(dtype):
         x[:, V:] = 1e4
         logits = x.to(dtype).cuda()
         vals = torch.rand(B, generator=g).cuda()
-        for f in filters:
+        for f, layout in [(f, layout) for f in filters for layout in FILTER_LAYOUTS]:
             gp, op = H.params_pair(mu_g=1.0, var_g=2.0, beta=3.0, stop_enabled=0, **f)
             st = H.GpuState(B)
             for step in range(2):
                 try:
-                    H.compare_step(logits, tau, 67, step, vals, gp, op, st, V=V, stats=stats)
+                    H.compare_step(logits, tau, 67, step, vals, gp, op, st, V=V, stats=stats, **layout)
                 except AssertionError as err:
-                    raise AssertionError(f"case {case} V={V} tau={tau} {f} step {step}: {err}")
+                    raise AssertionError(f"case {case} V={V} tau={tau} {f} {layout} step {step}: {err}")
     _say(f"  {stats}")
 
 
@@ -907,9 +909,10 @@ def test_top_p_at_the_edge_of_the_kept_set_is_decided_like_the_oracle():
             if not 0.0 < p_val < 1.0:
                 continue
             gp, op = H.params_pair(stop_enabled=0, top_p=p_val)
-            st = H.GpuState(B)
-            for step in range(2):
-                H.compare_step(x.cuda(), tau, 99, step, torch.zeros(B, device="cuda"), gp, op, st)
+            for layout in FILTER_LAYOUTS:
+                st = H.GpuState(B)
+                for step in range(2):
+                    H.compare_step(x.cuda(), tau, 99, step, torch.zeros(B, device="cuda"), gp, op, st, **layout)
 
 
 @pytest.mark.parametrize("ties", [200, 1000])                 # decided among the edge's members; by the general search
@@ -932,12 +935,13 @@ def test_top_p_at_the_edge_with_logits_far_from_zero(tau, offset, ties):
     for e in (1e-6, 3e-6, 6e-6, 9e-6, 2e-5):
         for p_val in (pa * (1.0 + e), pa * (1.0 - e)):
             gp, op = H.params_pair(stop_enabled=0, top_p=float(np.float32(p_val)))
-            st = H.GpuState(B)
-            for step in range(2):
-                try:
-                    H.compare_step(x.cuda(), tau, 99, step, torch.zeros(B, device="cuda"), gp, op, st)
-                except AssertionError as err:
-                    raise AssertionError(f"p {p_val / pa - 1.0:+.1e} off the edge, step {step}: {err}")
+            for layout in FILTER_LAYOUTS:
+                st = H.GpuState(B)
+                for step in range(2):
+                    try:
+                        H.compare_step(x.cuda(), tau, 99, step, torch.zeros(B, device="cuda"), gp, op, st, **layout)
+                    except AssertionError as err:
+                        raise AssertionError(f"p {p_val / pa - 1.0:+.1e} off the edge, {layout} step {step}: {err}")
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
@@ -966,12 +970,36 @@ def test_filtered_draws_whatever_order_the_logits_come_in(order, dtype):
         stride = (V + 7) // 8 * 8
         logits = torch.nn.functional.pad(x, (0, stride - V), value=1e4).to(dtype).cuda()
         gp, op = H.params_pair(mu_g=1.0, var_g=2.0, beta=3.0, stop_enabled=0, **f)
-        st = H.GpuState(B)
+        for layout in FILTER_LAYOUTS:
+            st = H.GpuState(B)
+            for step in range(2):
+                try:
+                    H.compare_step(logits, tau, 83, step, torch.zeros(B, device="cuda"), gp, op, st, V=V, entropy=step == 1, **layout)
+                except AssertionError as err:
+                    raise AssertionError(f"V={V} tau={tau} {f} {layout} step {step}: {err}")
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("B,V", [(255, 20011), (256, 20011), (300, 152064), (1024, 6007)])
+def test_filtered_draws_of_full_batches_match_the_oracle(B, V, dtype):
+    _say(f"[case] filtered draws of {B} rows, V={V} {dtype}")
+    # Through the public call, on both sides of the row count at which the workgroups change; the oracle follows 24 rows.
+    logits = torch.zeros(B, (V + 7) // 8 * 8, dtype=dtype, device="cuda")
+    W.ZipfLogits(V=V, seed=B, device="cuda", dtype=dtype).rows(B, out=logits[:, :V])
+    logits[7, :V] = logits[7, :V].round()
+    logits[11, :V] = float("-inf")
+    logits[11, V // 2:V // 2 + 9] = 1.0
+    alive = (torch.arange(B) % 5 != 3).to(torch.uint8)
+    rows = np.unique(np.concatenate([np.arange(12), np.linspace(12, B - 1, 12).astype(int)]))
+    vals = torch.rand(B, generator=torch.Generator().manual_seed(B)).cuda()
+    for tau, f in ((1.0, dict(top_p=0.7)), (1.3, dict(top_p=0.95)), (0.6, dict(top_k=50)), (1.0, dict(top_k=1)), (1.0, dict(top_k=2000))):
+        gp, op = H.params_pair(mu_g=1.0, var_g=2.0, beta=3.0, **f)
+        st = H.GpuState(B, alive=alive)
         for step in range(2):
             try:
-                H.compare_step(logits, tau, 83, step, torch.zeros(B, device="cuda"), gp, op, st, V=V, entropy=step == 1)
+                H.compare_step(logits, tau, 43, step, vals, gp, op, st, V=V, rows=rows, entropy=step == 1)
             except AssertionError as err:
-                raise AssertionError(f"V={V} tau={tau} {f} step {step}: {err}")
+                raise AssertionError(f"tau={tau} {f} step {step}: {err}")
 
 
 # --------------------------------------------------------------------------- HIP graph capture
