@@ -38,6 +38,7 @@ namespace {
 // A workgroup has W wavefronts, 16 or 4 (a template parameter of what depends on it): tiles of 4096 or 1024 tokens.
 constexpr int kPerLane = 4;
 constexpr int kWaveTokens = kWave * kPerLane;
+constexpr int kPair = 2;                          // inner tiles of a workgroup of 4 waves that share a barrier
 constexpr int kDppWaveShr1 = 0x138;               // lane i takes lane i-1 across the whole wave
 
 struct AdvArgs {
@@ -249,11 +250,114 @@ __device__ __forceinline__ float scan_step(float s, float w) {
   return fmaf(w, dpp_f32<Ctrl, RowMask>(0.0f, s), s);
 }
 
+// The tiles last .. 1 of a trajectory stored back to back, in a workgroup of 4 waves.  The number of waves follows from the
+// mean length, so a trajectory many times as long can come this way, and four waves are alone on their SIMDs: what
+// bounds them is what they issue and the chain of each tile, not memory.  These tiles lie wholly inside the trajectory and none is
+// its last: nothing is checked, addresses are 32-bit offsets from a uniform base, and two tiles share a barrier while the next
+// two are on their way.  us per call, with the loop below for every tile / with this / with workgroups of 16 waves:
+//   1000 trajectories of 300 tokens and one of 100000: 83.6 / 40.1 / 35.0;  512 of 400, one of 16384: 16.0 / 9.7 / 10.2;
+//   63 of 100, one of 30000: 25.9 / 14.3 / 11.7;  256 of 250, one of 4000: 5.9 / 5.0 / 5.2;
+//   1024 of up to 500, 1000, 3800 tokens: 5.5, 5.8, 11.7 / 5.5, 5.9, 10.3 / 9.9, 10.4, 11.9.
+// Takes A at the first token after tile `last`, returns A at tile 1's first.
+template <bool Dense>
+__device__ __forceinline__ float walk_inner(const AdvArgs& a, const float* __restrict__ r, const float* __restrict__ v, float* __restrict__ td,
+                                            float* __restrict__ adv, float* __restrict__ ret, int64_t last, float carry,
+                                            float w_b15, float w_b31, float w_lane, float w_wave) {
+  constexpr int kTile = 4 * kWaveTokens;
+  __shared__ float s_tot[2][4 * kPair];  // wave totals of a group, double-buffered
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t at = (uint32_t)(4 * kWave - 1 - threadIdx.x) * kPerLane;
+  struct In {
+    f32x4 r, v;
+    float halo;
+  };
+  auto load = [&](int64_t k) {
+    In in;
+    in.r = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    if constexpr (Dense) in.r = __builtin_nontemporal_load((const f32x4*)(r + k * kTile + at));
+    in.v = __builtin_nontemporal_load((const f32x4*)(v + k * kTile + at));
+    in.halo = 0.0f;
+    if (lane == 0) in.halo = v[k * kTile + at + kPerLane];
+    return in;
+  };
+  In ring[2][kPair];
+  auto fetch = [&](In (&to)[kPair], int64_t k) {
+#pragma unroll
+    for (int g = 0; g < kPair; ++g)
+      if (k - g > 0) to[g] = load(k - g);
+  };
+  fetch(ring[0], last);
+  int par = 0;
+#pragma unroll 1
+  for (int64_t k0 = last; k0 > 0; k0 -= kPair) {
+    fetch(ring[1], k0 - kPair);
+    f32x4 d[kPair], loc[kPair];
+    float s[kPair];
+#pragma unroll
+    for (int g = 0; g < kPair; ++g) {
+      if (k0 - g <= 0) break;  // (uniform)
+      const In& in = ring[0][g];
+      float vnext = dpp_f32<kDppWaveShr1, 0xf>(0.0f, in.v[0]);
+      if (lane == 0) vnext = in.halo;
+      float acc = 0.0f;
+#pragma unroll
+      for (int j = kPerLane - 1; j >= 0; --j) {
+        d[g][j] = (in.r[j] + a.gamma * (j == kPerLane - 1 ? vnext : in.v[j + 1])) - in.v[j];
+        acc = d[g][j] + a.c * acc;
+        loc[g][j] = acc;
+      }
+      s[g] = acc;
+    }
+    // the scan over the lanes, step by step for all of them
+#pragma unroll
+    for (int g = 0; g < kPair; ++g) s[g] = scan_step<kDppRowShr1, 0xf>(s[g], a.clane[0]);
+#pragma unroll
+    for (int g = 0; g < kPair; ++g) s[g] = scan_step<kDppRowShr2, 0xf>(s[g], a.clane[1]);
+#pragma unroll
+    for (int g = 0; g < kPair; ++g) s[g] = scan_step<kDppRowShr4, 0xf>(s[g], a.clane[2]);
+#pragma unroll
+    for (int g = 0; g < kPair; ++g) s[g] = scan_step<kDppRowShr8, 0xf>(s[g], a.clane[3]);
+#pragma unroll
+    for (int g = 0; g < kPair; ++g) s[g] = scan_step<kDppBcast15, 0xa>(s[g], w_b15);
+#pragma unroll
+    for (int g = 0; g < kPair; ++g) {
+      s[g] = scan_step<kDppBcast31, 0xc>(s[g], w_b31);
+      if (lane == kWave - 1) s_tot[par][g * 4 + wave] = s[g];
+    }
+    __syncthreads();
+    // lanes 4 g .. 4 g + 3 hold the totals of tile g; the scan over four of them does not cross into the next
+    float p = lane < 4 * kPair ? s_tot[par][lane] : 0.0f;
+    const float p1 = dpp_f32<kDppRowShr1, 0xf>(0.0f, p);
+    p = (lane & 3) >= 1 ? fmaf(a.cwave[0], p1, p) : p;
+    const float p2 = dpp_f32<kDppRowShr2, 0xf>(0.0f, p);
+    p = (lane & 3) >= 2 ? fmaf(a.cwave[1], p2, p) : p;
+#pragma unroll
+    for (int g = 0; g < kPair; ++g) {
+      const int64_t k = k0 - g;
+      if (k <= 0) break;  // (uniform)
+      const float before = wave > 0 ? uniform_f32(p, 4 * g + wave - 1) : 0.0f;
+      const float wave_in = fmaf(w_wave, carry, before);
+      carry = fmaf(a.cwave[2], carry, uniform_f32(p, 4 * g + 3));
+      const float a_next = fmaf(w_lane, wave_in, dpp_f32<kDppWaveShr1, 0xf>(0.0f, s[g]));
+#pragma unroll
+      for (int j = 0; j < kPerLane; ++j) loc[g][j] = fmaf(a.cj[kPerLane - j], a_next, loc[g][j]);
+      __builtin_nontemporal_store(d[g], (f32x4*)(td + k * kTile + at));
+      __builtin_nontemporal_store(loc[g], (f32x4*)(adv + k * kTile + at));
+      if (ret) __builtin_nontemporal_store(loc[g] + ring[0][g].v, (f32x4*)(ret + k * kTile + at));
+    }
+#pragma unroll
+    for (int g = 0; g < kPair; ++g) ring[0][g] = ring[1][g];
+    par ^= 1;
+  }
+  return carry;
+}
+
 // Layout of the rows: [B, T] with T a multiple of four, [B, T] with any T, or back to back.
 enum RowLayout { kAligned, kShifted, kPacked };
 
 template <bool Dense, RowLayout Layout, int W>
-__global__ __launch_bounds__(W * kWave, W == 4 ? 6 : 8) void espo_advantages_kernel(AdvArgs a) {
+__global__ __launch_bounds__(W * kWave, W == 4 ? (Dense && Layout == kPacked ? 5 : 6) : 8) void espo_advantages_kernel(AdvArgs a) {
   constexpr bool Packed = Layout == kPacked, Span = Layout != kAligned;
   constexpr int kTile = W * kWaveTokens;
   __shared__ float s_tot[2][W];  // wave totals, double-buffered by tile parity
@@ -394,7 +498,7 @@ __global__ __launch_bounds__(W * kWave, W == 4 ? 6 : 8) void espo_advantages_ker
   for (int64_t k = nvalid - 1; k >= 0; --k) {
     const int64_t t0 = k * kTile + lane_off;
     TileIn nxt;
-    if (k > 0) nxt = load_tile<Dense>(rrow, vrow, t0 - kTile, L, lane == 0);  // the earlier tile, in flight during the scan
+    if (k > 0) nxt = load_tile<Dense>(rrow, vrow, Packed && W == 4 ? lane_off : t0 - kTile, L, lane == 0);  // the earlier tile, in flight during the scan
 
     // V_{t+1} of the lane's last token: first value of the lane that holds the following tokens
     float vnext = dpp_f32<kDppWaveShr1, 0xf>(0.0f, cur.v[0]);
@@ -477,6 +581,12 @@ __global__ __launch_bounds__(W * kWave, W == 4 ? 6 : 8) void espo_advantages_ker
         }
     }
     if (k > 0) cur = nxt;
+    if constexpr (Packed && W == 4) {
+      if (k > 1) {
+        carry = walk_inner<Dense>(a, rrow, vrow, drow, arow, trow, k - 1, carry, w_b15, w_b31, w_lane, w_wave);
+        k = 1;
+      }
+    }
   }
   if (want_stats) {  // lanes, then waves, in a fixed order
     __shared__ double s_stats[2][W];

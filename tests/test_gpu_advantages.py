@@ -303,6 +303,19 @@ def test_packed_batches_of_short_and_long_trajectories(B, mean):
     _check_packed_both_forms(lens, seed=B)
 
 
+@pytest.mark.parametrize("gamma,lam", [(1.0, 0.95), (0.999, 0.9995)])
+def test_packed_long_trajectories_among_many_short_ones(gamma, lam):
+    _say(f"[case] packed advantages, long trajectories in workgroups of four waves, gamma {gamma} lambda {lam}")
+    # The waves follow from the mean length.  Of a long trajectory the tiles of 1024 tokens between the first and the last are
+    # walked in pairs: none to eight of them here, both ends on and beside the edges, starts at all four alignments.
+    lens = []
+    for n in (2046, 2048, 2049, 2052, 3071, 3072, 3073, 3076, 4096, 4097, 5119, 5121, 6144, 6147, 7170, 8193, 9217, 10243, 30001):
+        lens += [n] + [1, 2, 3, 7, 50][:1 + len(lens) % 4] * 8
+    lens += [300] * 200
+    assert 2 * (sum(lens) // len(lens)) <= 2048
+    _check_packed_both_forms(lens, seed=11, gamma=gamma, lam=lam)
+
+
 def test_packed_gaps_are_neither_read_nor_written():
     _say("[case] packed advantages, unowned gaps")
     lens = [5, 4096, 1, 300, 4099, 2, 8193]
