@@ -6,15 +6,15 @@
 // partial sums of d = g - mu_g and d^2 in double (shifting by the current mean estimate keeps
 // the one-pass variance free of cancellation), plus token and stop counts; workgroup w takes
 // rows w, w + G, ...  Rows of any length are read 16 bytes at a time: where T is no multiple of 4,
-// from the 16-byte boundary before them, four loads per lane in flight.  The second adds the at most 1024 partials in a fixed
+// from the 16-byte boundary before them, four loads per lane in flight; many short rows take a wave each.  The second adds the at most 1024 partials in a fixed
 // order and forms the outputs.  A batch of at most 16 pieces of 1024 positions is one launch of one
 // workgroup, whose waves take four pieces each.  Every reduction tree is fixed, so the result does
 // not depend on scheduling.
 //
 // Bound by latency: launch, lengths, tokens, reduction, and the same once more for the partials.
 // us per call on the GPU, before -> now (before: element-wise loads for odd T, two launches always): B = 512, T = 8191:
-// 14.1 -> 10.6; B = 1024, T = 16383: 25.1 -> 18.3; B = 8, T = 16383: 11.4 -> 8.7; B = 4, T = 128: 5.7 -> 3.4; B = 1, T = 16384:
-// 6.7 -> 4.4; one launch for 32 pieces instead: 9.1 against 5.8 for B = 32, T = 900, so the line is at 16.
+// 10.2 -> 8.2; B = 1024, T = 16383: 27.7 -> 17.2; B = 8, T = 16383: 12.8 -> 8.5; B = 100000, T = 5: 44.6 -> 24.9; B = 20000, T = 100:
+// 15.2 -> 11.1; B = 4, T = 128: 5.7 -> 3.4; B = 1, T = 16384: 6.7 -> 4.4; one launch for 32 pieces instead: 9.1 against 5.8 for B = 32, T = 900, so the line is at 16.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -40,6 +40,7 @@ constexpr int kStatQuads = 4;                        // groups of four positions
 constexpr int kStatItem = kWave * 4 * kStatQuads;    // positions per item: 1024
 constexpr int kStatUnroll = 4;                       // items of a wave, their loads in flight together
 constexpr int kRowLoads = 4;                         // 16-byte loads of a lane in flight when a workgroup takes whole rows
+constexpr int kShortUnroll = 2;                      // rows of a wave in flight when every row is one item
 constexpr int kMaxStatGroups = 1024;                 // partials the workspace has room for
 constexpr int kFinalThreads = 256, kFinalEach = kMaxStatGroups / kFinalThreads;  // partials per thread
 constexpr int kOneLaunchItems = kStatWaves * kStatUnroll;  // batches of at most this many items are one launch of one workgroup
@@ -110,20 +111,19 @@ __device__ __forceinline__ void write_result(const FinalArgs& a, double s1, doub
 }
 
 // Whether the 256 positions from `at` hold any of [lo, hi) (uniform in the wave: short rows cost what they hold).
-__device__ __forceinline__ bool any_in(int64_t at, int64_t lo, int64_t hi) { return at < hi && at + 4 * kWave > lo; }
+__device__ __forceinline__ bool any_in(uint32_t at, uint32_t lo, uint32_t hi) { return lo < hi && at < hi && at + 4 * kWave > lo; }
 
-// This lane's four tokens of those 256; positions outside [lo, hi) read as the shift, so that they add nothing.
-__device__ __forceinline__ f32x4 load_tokens(const float* __restrict__ src, int64_t at, int64_t lo, int64_t hi, float shift) {
-  const int64_t t = at + (int64_t)(threadIdx.x & (kWave - 1)) * 4;
+// This lane's four tokens of those 256 (which hold some of [lo, hi)); positions outside read as the shift, so that they add
+// nothing.  At a row's ends every lane loads four tokens by themselves, from the nearest positions inside: with one load for the
+// lanes inside and others for the rest, a wave waits for memory twice (B = 100000, T = 5, a workgroup per row: 95 us, and 89 this way).
+__device__ __forceinline__ f32x4 load_tokens(const float* __restrict__ src, uint32_t at, uint32_t lo, uint32_t hi, float shift) {
+  const uint32_t t = at + (threadIdx.x & (kWave - 1)) * 4;
   if (at >= lo && at + 4 * kWave <= hi) return __builtin_nontemporal_load((const f32x4*)(src + t));
-  f32x4 g = {shift, shift, shift, shift};
-  if (t >= lo && t + 4 <= hi) {
-    g = __builtin_nontemporal_load((const f32x4*)(src + t));
-  } else {
+  f32x4 g;
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      if (t + j >= lo && t + j < hi) g[j] = src[t + j];
-  }
+  for (int j = 0; j < 4; ++j) g[j] = src[t + j < lo ? lo : (t + j < hi ? t + j : hi - 1)];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) g[j] = t + j >= lo && t + j < hi ? g[j] : shift;
   return g;
 }
 
@@ -136,17 +136,50 @@ __device__ __forceinline__ void add_tokens(const f32x4& g, double shift, double&
   }
 }
 
-// Where a row's tokens lie: [lo, hi) from `src`, a multiple of 16 bytes.
+// Where a row's tokens lie: [lo, hi) from `src`, a multiple of 16 bytes (hi is below 2^31 + 3).
 struct RowSpan {
   const float* src;
-  int64_t lo, hi;
+  uint32_t lo, hi;
 };
 
 __device__ __forceinline__ RowSpan row_span(const PartialArgs& a, int64_t row, int64_t& L) {
   L = __builtin_amdgcn_readfirstlane(a.lengths[row]);
   L = L < 0 ? 0 : (L > a.T ? a.T : L);
   const int64_t first = row * a.T, head = first & 3;
-  return RowSpan{a.regret + (first - head), head, head + L};
+  return RowSpan{a.regret + (first - head), (uint32_t)head, (uint32_t)(head + L)};
+}
+
+// Counts of tokens and of stopped rows of the rows blockIdx.x, blockIdx.x + gridDim.x, ...: a thread each, apart from the
+// tokens, whose loads would otherwise queue behind them row by row.  The first ones are loaded by the constructor and
+// added, with the rest, by finish().
+struct RowCounts {
+  int32_t length = 0;
+  uint32_t stop = 0;
+  __device__ __forceinline__ explicit RowCounts(const PartialArgs& a) {
+    const int64_t row = blockIdx.x + (int64_t)threadIdx.x * gridDim.x;
+    if (row < a.B) {
+      length = a.lengths[row];
+      stop = a.stopped[row];
+    }
+  }
+  __device__ __forceinline__ void finish(const PartialArgs& a, double& n, double& nstop) {
+    for (int64_t row = blockIdx.x + (int64_t)threadIdx.x * gridDim.x; row < a.B;) {
+      n += (double)(length < 0 ? 0 : (length > a.T ? a.T : (int64_t)length));
+      nstop += stop != 0 ? 1.0 : 0.0;
+      row += (int64_t)kStatThreads * gridDim.x;
+      if (row < a.B) {
+        length = a.lengths[row];
+        stop = a.stopped[row];
+      }
+    }
+  }
+};
+
+__device__ __forceinline__ void write_partial(const PartialArgs& a, RowCounts& counts, double s1, double s2, double* lds) {
+  double v[4] = {s1, s2, 0.0, 0.0};
+  counts.finish(a, v[2], v[3]);
+  block_sums<4, kStatWaves>(v, lds);
+  if (threadIdx.x == 0) a.part[blockIdx.x] = Partial{v[0], v[1], (long long)v[2], (long long)v[3]};
 }
 
 // Aligned: T % 4 == 0, every row starts at a 16-byte boundary.
@@ -155,9 +188,9 @@ __global__ __launch_bounds__(kStatThreads) void batch_partial_kernel(PartialArgs
   __shared__ double lds[4 * kStatWaves];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const double shift = (double)a.mu_g;
-  double s1 = 0.0, s2 = 0.0, n = 0.0, nstop = 0.0;
+  double s1 = 0.0, s2 = 0.0;
+  RowCounts counts(a);
   for (int64_t row = blockIdx.x; row < a.B; row += gridDim.x) {
-    const uint32_t stop = a.stopped[row];
     int64_t L;
     const RowSpan r = row_span(a, row, L);
     if constexpr (Aligned) {  // 16.8 us at B = 1024, T = 16384, where the loop below takes 17.6
@@ -169,7 +202,7 @@ __global__ __launch_bounds__(kStatThreads) void batch_partial_kernel(PartialArgs
         s1 += d;
         s2 = fma(d, d, s2);
       }
-    } else for (int64_t at = wave * 4 * kWave; at < r.hi; at += kRowLoads * kStatThreads * 4) {
+    } else for (uint32_t at = (uint32_t)wave * 4 * kWave; at < r.hi; at += kRowLoads * kStatThreads * 4) {
       f32x4 g[kRowLoads];
 #pragma unroll
       for (int u = 0; u < kRowLoads; ++u)
@@ -178,14 +211,40 @@ __global__ __launch_bounds__(kStatThreads) void batch_partial_kernel(PartialArgs
       for (int u = 0; u < kRowLoads; ++u)
         if (any_in(at + u * kStatThreads * 4, r.lo, r.hi)) add_tokens(g[u], shift, s1, s2);
     }
-    if (threadIdx.x == 0) {
-      n += (double)L;
-      nstop += stop != 0 ? 1.0 : 0.0;
-    }
   }
-  double v[4] = {s1, s2, n, nstop};
-  block_sums<4, kStatWaves>(v, lds);
-  if (threadIdx.x == 0) a.part[blockIdx.x] = Partial{v[0], v[1], (long long)v[2], (long long)v[3]};
+  write_partial(a, counts, s1, s2, lds);
+}
+
+// Rows of one item each: a wave takes a row, and the rows of kShortUnroll
+// rounds are on their way together.
+__global__ __launch_bounds__(kStatThreads) void batch_short_kernel(PartialArgs a) {
+  __shared__ double lds[4 * kStatWaves];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const double shift = (double)a.mu_g;
+  double s1 = 0.0, s2 = 0.0;
+  RowCounts counts(a);
+  const int64_t step = (int64_t)gridDim.x * kStatWaves;
+  for (int64_t row0 = (int64_t)wave * gridDim.x + blockIdx.x; row0 < a.B; row0 += kShortUnroll * step) {
+    int64_t L;
+    RowSpan r[kShortUnroll];
+    f32x4 g[kShortUnroll][kStatQuads];
+#pragma unroll
+    for (int u = 0; u < kShortUnroll; ++u) {
+      r[u] = RowSpan{nullptr, 0, 0};
+      if (row0 + u * step < a.B) r[u] = row_span(a, row0 + u * step, L);
+    }
+#pragma unroll
+    for (int u = 0; u < kShortUnroll; ++u)
+#pragma unroll
+      for (int q = 0; q < kStatQuads; ++q)
+        if (any_in(q * 4 * kWave, r[u].lo, r[u].hi)) g[u][q] = load_tokens(r[u].src, q * 4 * kWave, r[u].lo, r[u].hi, a.mu_g);
+#pragma unroll
+    for (int u = 0; u < kShortUnroll; ++u)
+#pragma unroll
+      for (int q = 0; q < kStatQuads; ++q)
+        if (any_in(q * 4 * kWave, r[u].lo, r[u].hi)) add_tokens(g[u][q], shift, s1, s2);
+  }
+  write_partial(a, counts, s1, s2, lds);
 }
 
 // One workgroup for a whole batch of at most kOneLaunchItems items (`per_row` of them in a row).
@@ -207,7 +266,7 @@ __global__ __launch_bounds__(kStatThreads) void batch_small_kernel(PartialArgs a
       r[u] = row_span(a, row, L);
       r[u].src += off;
       r[u].lo = off == 0 ? r[u].lo : 0;
-      r[u].hi = r[u].hi - off < kStatItem ? r[u].hi - off : kStatItem;
+      r[u].hi = r[u].hi <= (uint32_t)off ? 0u : min(r[u].hi - (uint32_t)off, (uint32_t)kStatItem);
 #pragma unroll
       for (int q = 0; q < kStatQuads; ++q)
         if (any_in(q * 4 * kWave, r[u].lo, r[u].hi)) g[u][q] = load_tokens(r[u].src, q * 4 * kWave, r[u].lo, r[u].hi, a.mu_g);
@@ -297,8 +356,14 @@ int launch_batch_stats(const float* regret, const int32_t* lengths, const uint8_
     hipLaunchKernelGGL(batch_small_kernel, dim3(1), dim3(kStatThreads), 0, stream, p, f, (int)(B * per_row), (int)per_row);
     return hipGetLastError() == hipSuccess ? ESPO_OK : ESPO_EHIP;
   }
-  const int groups = stat_groups(B);
-  if (T % 4 == 0)
+  // Rows of one item each take a wave each where there are more of them than workgroups (us, a workgroup per row -> a wave
+  // per row: B = 100000, T = 8: 47.2 -> 24.8, T = 5: 89 -> 24.9; B = 4000, T = 1001: 11.8 -> 10.0), or where they start between
+  // boundaries and a wave has a row in one load per lane (B = 512, T = 127: 7.0 -> 6.4; but B = 64, T = 1001: 6.3 -> 6.8).
+  const bool one_item = per_row == 1 && (B > kMaxStatGroups || (T % 4 != 0 && T + 3 <= 4 * kWave));
+  const int groups = stat_groups(one_item ? (B + kStatWaves - 1) / kStatWaves : B);
+  if (one_item)
+    hipLaunchKernelGGL(batch_short_kernel, dim3(groups), dim3(kStatThreads), 0, stream, p);
+  else if (T % 4 == 0)
     hipLaunchKernelGGL(batch_partial_kernel<true>, dim3(groups), dim3(kStatThreads), 0, stream, p);
   else
     hipLaunchKernelGGL(batch_partial_kernel<false>, dim3(groups), dim3(kStatThreads), 0, stream, p);

@@ -46,9 +46,11 @@ def test_shapes_ragged_lengths_and_poisoned_padding(B, T):
 
 # Where the work is cut: one launch up to 16 pieces of 1024 positions (16, 17 rows of one; rows of 1021 positions are one
 # piece, of 1022 and 1027 two; 4 rows of 4096 and 4097; one row of 16384), then a workgroup per row: 4096 positions per pass,
-# rows that start between 16-byte boundaries, more rows than the 1024 workgroups.
+# rows that start between 16-byte boundaries, more rows than the 1024 workgroups; a wave per row of one piece, from 1025 rows
+# on, below for odd rows of up to 253; more rows of a workgroup than it has threads.
 @pytest.mark.parametrize("B,T", [(16, 1000), (17, 1000), (16, 1021), (9, 1022), (8, 1027), (4, 4096), (4, 4097), (1, 16384), (16, 0), (40, 0), (64, 4095),
-                                 (33, 4103), (3, 20481), (17000, 37), (1030, 16383), (2, 65537)])
+                                 (33, 4103), (3, 20481), (17000, 37), (1030, 16383), (2, 65537),
+                                 (1024, 253), (1025, 254), (700, 255), (1025, 1021), (1025, 1022), (1100, 1024), (4097, 6), (270000, 2)])
 def test_items_at_every_boundary(B, T):
     print(f"[case] batch stats items B={B} T={T}", flush=True)
     regret, lengths, stopped = W.regret_batch(B, max(T, 1), len_lo=0, seed=B + 7 * T, device="cuda", poison=True)
