@@ -421,8 +421,8 @@ size_t espo_whiten_workspace_bytes(int64_t B, int64_t T);
  * scanned in an order that suits their lengths instead of 0, 1, 2, ...: with the long rows
  * first, a batch of more than 512 rows of mixed lengths takes about an eighth less time, and
  * no row has to be moved for it.  If `order` is given, that is the order.  If it is NULL and
- * the batch has more than 512 rows (what the chip works on at once), the launch's first
- * workgroup sorts the rows from the 513th on by length while the first 512 are scanned in index
+ * the batch has 513 to 1536 rows (512 are what the chip works on at once) of more than 4608 steps, the
+ * launch's first workgroup sorts the rows from the 513th on by length while the first 512 are scanned in index
  * order, which gains as much as a full order does.
  *
  * espo_length_order writes such an order: the rows 0 .. B-1 by length (clamped to [0, T]) in
@@ -438,7 +438,7 @@ size_t espo_whiten_workspace_bytes(int64_t B, int64_t T);
  *
  * Arguments as for espo_advantages and espo_whiten, and
  *   order      device, [B] int32, every row once, or NULL (the launch then sorts its later rows
- *              itself, as described above).  An entry
+ *              itself where that pays, as described above).  An entry
  *              outside [0, B) is skipped; a row that is missing from the order is not computed,
  *              one that is named twice is computed twice.
  *   workspace  device, at least espo_advantages_ws_bytes(B) bytes (256, plus 32 per row, plus 4

@@ -63,7 +63,7 @@ struct AdvArgs {
   const int32_t* order;    // optional [B]: the rows, longest first (padded forms)
   AdvRowStats* row_stats;  // optional [B]: sums of every row's advantages (padded forms)
   int32_t* sorted;         // optional [B - kAdvFirstRows]: the rows from kAdvFirstRows on, longest first, written by
-                           //   workgroup 0 of this launch (padded forms, no `order` given) and followed by workgroups of 16 waves
+                           //   workgroup 0 of this launch (padded forms in workgroups of 16 waves, no `order` given)
   uint32_t* sync;          // with `sorted`: [0] set once `sorted` is complete, [32] readers so far; both 0 between launches
 };
 
@@ -77,6 +77,10 @@ constexpr int kAdvFirstRows = 512;
 // B = 2000, T = 10000: 52.1 / 48.0, T = 3000: 30.6 / 22.6; B = 1024, T = 1500: 13.2 / 10.9.
 constexpr int kAdvSelectRows = 3 * kAdvFirstRows;
 constexpr int64_t kAdvSelectTokens = 8192;
+// Read from a list that the launch makes, the order costs its readers one load, so it pays for shorter rows, too; us per
+// launch with / without, dense: T = 4100: B = 1024: 19.5 / 18.4, 1536: 28.5 / 26.4; T = 5000: B = 800: 17.7 / 19.2,
+// 1024: 20.7 / 22.4, 1536: 30.2 / 29.4; T = 8192: B = 600: 19.4 / 19.3, 1024: 25.2 / 25.8 (terminal rewards 24.3 / 26.0).
+constexpr int64_t kAdvSortTokens = 4608;
 // The word that says "sorted" and the count of its readers lie in different 128-byte lines: loads of the one and
 // read-modify-writes of the other on the same line cost the readers 15 us per launch between them.
 constexpr int kAdvSyncStride = 32;       // words
@@ -89,9 +93,8 @@ __device__ __forceinline__ int class_of_length(int64_t L, int64_t T) {  // class
 }
 
 // Writes the rows first .. B-1 to order[0 .. B-first), longest first: a counting sort of the clipped lengths into
-// 256 classes by one workgroup (rows of one class in no particular order; no result depends on it).  The entries
+// 256 classes by one workgroup of 16 waves (rows of one class in no particular order; no result depends on it).  The entries
 // are written past the caches that other parts of the chip do not see, and are complete when the call returns.
-template <int W>
 __device__ __forceinline__ void sort_rows_by_length(const int32_t* __restrict__ lengths, int32_t first, int32_t B, int64_t T,
                                                     int32_t* __restrict__ order) {
   __shared__ int count[kOrderClasses];
@@ -100,7 +103,7 @@ __device__ __forceinline__ void sort_rows_by_length(const int32_t* __restrict__ 
   auto class_of = [&](int32_t i) { return class_of_length(lengths[i], T); };
   if (tid < kOrderClasses) count[tid] = 0;
   __syncthreads();
-  for (int32_t i = first + tid; i < B; i += W * kWave) atomicAdd(&count[class_of(i)], 1);
+  for (int32_t i = first + tid; i < B; i += 16 * kWave) atomicAdd(&count[class_of(i)], 1);
   __syncthreads();
   int mine = 0, incl = 0;
   if (tid < kOrderClasses) {  // inclusive prefix over the classes: inside each wave, then over the four waves
@@ -120,7 +123,7 @@ __device__ __forceinline__ void sort_rows_by_length(const int32_t* __restrict__ 
     count[tid] = before + incl - mine;  // where the class starts
   }
   __syncthreads();
-  for (int32_t i = first + tid; i < B; i += W * kWave)
+  for (int32_t i = first + tid; i < B; i += 16 * kWave)
     __hip_atomic_store(order + atomicAdd(&count[class_of(i)], 1), i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
@@ -370,16 +373,16 @@ __global__ __launch_bounds__(W * kWave, W == 4 ? (Dense && Layout == kPacked ? 5
   // not fit the chip at once matters, and only their scans look their row up: see below.)
   constexpr bool kOrdered = W == 16;  // of the smaller workgroups, for short rows, the chip holds 2048, and rows differ little
   int unit = (int)blockIdx.x;
-  if (!Packed && a.sorted) {
-    // No order was given and the batch has more rows than the chip holds workgroups: workgroup 0 of this launch
-    // sorts the later rows while the first kAdvFirstRows are being scanned, and tells the others when it is done.
+  if constexpr (kOrdered && !Packed) {
+    // No order was given and the later rows are to be scanned longest first: workgroup 0 of this launch
+    // sorts them while the first kAdvFirstRows are being scanned, and tells the others when it is done.
     // It waits for nobody and is dispatched before every workgroup that waits for it.
-    if (unit == 0) {
-      sort_rows_by_length<W>(a.lengths, kAdvFirstRows, a.B, a.T, a.sorted);
-      if (kOrdered && a.ordered_from < a.B && threadIdx.x == 0) __hip_atomic_store(a.sync, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (a.sorted && unit == 0) {
+      sort_rows_by_length(a.lengths, kAdvFirstRows, a.B, a.T, a.sorted);
+      if (threadIdx.x == 0) __hip_atomic_store(a.sync, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       return;
     }
-    unit -= 1;
+    if (a.sorted) unit -= 1;
   }
   const bool fill_only = !Packed && unit >= a.B;
   int row = fill_only ? unit - a.B : unit;
@@ -610,7 +613,7 @@ __global__ __launch_bounds__(W * kWave, W == 4 ? (Dense && Layout == kPacked ? 5
 
 __global__ __launch_bounds__(16 * kWave) void length_order_kernel(const int32_t* __restrict__ lengths, int32_t B, int64_t T,
                                                                   int32_t* __restrict__ order) {
-  sort_rows_by_length<16>(lengths, 0, B, T, order);
+  sort_rows_by_length(lengths, 0, B, T, order);
 }
 
 template <RowLayout Layout>
@@ -628,9 +631,6 @@ int launch_advantages(const float* rewards, const float* terminal_reward, const 
   AdvArgs a;
   a.order = order;
   a.row_stats = row_stats;
-  const bool sort_here = cu == nullptr && order == nullptr && sorted != nullptr && sync != nullptr && B > kAdvFirstRows;
-  a.sorted = sort_here ? sorted : nullptr;
-  a.sync = sort_here ? sync : nullptr;
   a.rewards = rewards;
   a.terminal_reward = terminal_reward;
   a.returns = returns;
@@ -657,7 +657,12 @@ int launch_advantages(const float* rewards, const float* terminal_reward, const 
   // Trajectories stored back to back: by their mean length.
   const int64_t longest = cu ? 2 * (N / B) : T + (T % 4 != 0 ? 3 : 0);
   const bool shortrows = longest <= 8 * kWaveTokens || (longest <= 16 * kWaveTokens && B > kAdvFirstRows);
-  a.ordered_from = !shortrows && B <= kAdvSelectRows && longest > kAdvSelectTokens ? kAdvFirstRows : 0x7fffffff;
+  const bool can_sort = cu == nullptr && order == nullptr && sorted != nullptr && sync != nullptr;
+  a.ordered_from = !shortrows && B <= kAdvSelectRows && longest > (can_sort ? kAdvSortTokens : kAdvSelectTokens) ? kAdvFirstRows : 0x7fffffff;
+  // a list that nobody reads is not made (us with / without: B = 20000, T = 1000: 94.0 / 65.8; 100000, 100: 330 / 224)
+  const bool sort_here = can_sort && a.ordered_from < B;
+  a.sorted = sort_here ? sorted : nullptr;
+  a.sync = sort_here ? sync : nullptr;
   const int64_t tile = (shortrows ? 4 : 16) * kWaveTokens;
   const bool fillers = cu == nullptr && zero_padding && longest > tile;
   const dim3 grid((unsigned)((fillers ? 2 * B : B) + (sort_here ? 1 : 0))), block(shortrows ? 4 * kWave : 16 * kWave);

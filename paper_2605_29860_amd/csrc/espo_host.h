@@ -64,8 +64,8 @@ int launch_math_errors(float* out, hipStream_t stream);
 // cu != nullptr: trajectories stored back to back in arrays of N tokens (lengths, T, zero_padding unused).
 // order != nullptr (padded forms only): the scanning workgroups take their rows in that order.
 // row_stats != nullptr (padded forms only): every row's sums of its advantages are left there.
-// sorted, sync != nullptr, no order and more rows than the chip holds workgroups (padded forms only): the
-// launch's first workgroup sorts the later rows by length into `sorted`, and `sync` (words 0 and 32, zero between
+// sorted, sync != nullptr, no order (padded forms only): where the later rows are to be scanned longest first, the
+// launch's first workgroup sorts them by length into `sorted`, and `sync` (words 0 and 32, zero between
 // launches) tells the others when it is done.
 int launch_advantages(const float* rewards, const float* terminal_reward, const float* values, const int32_t* lengths,
                       const int64_t* cu, int64_t N, const uint8_t* stopped, int64_t B, int64_t T, float r_fail, float gamma,

@@ -37,6 +37,12 @@ FIRST = 512  # rows that are scanned in index order when the launch sorts the re
 HEAD = 256   # bytes at the start of the workspace that must be zero before its first use
 
 
+def _sorts_itself(B, T):
+    """Whether a call without an order sorts its rows from FIRST on: 513 to 1536 rows of more than 4608 steps, as counted from
+    the 16-byte boundary before a row."""
+    return FIRST < B <= 3 * FIRST and T + (3 if T % 4 else 0) > 4608
+
+
 def _workspace(B):
     n = espo.espo_advantages_ws_bytes(B)
     assert n == HEAD + 32 * B + (4 * max(B - FIRST, 0) + 15) // 16 * 16
@@ -69,7 +75,9 @@ def _run(r, v, L, s, r_fail=-1.0, gamma=1.0, lam=0.95, eps=1e-8, shift_mean=True
     assert torch.equal(adv0.view(torch.int32), adv1.view(torch.int32)), "adv differs from espo_advantages"
 
     assert not bool(ws[:HEAD].any()), "the first 256 bytes of the workspace must be zero again after the call"
-    if not ordered and B > FIRST:  # the launch sorted rows FIRST.. itself: a permutation of them, longest first
+    if B > FIRST and (ordered or not _sorts_itself(B, T)):
+        assert bool((ws[HEAD + 32 * B:] == 0xA5).all()), "rows were sorted for nobody"
+    elif B > FIRST:  # the launch sorted rows FIRST.. itself: a permutation of them, longest first
         srt = ws[HEAD + 32 * B:HEAD + 32 * B + 4 * (B - FIRST)].view(torch.int32).cpu().numpy()
         assert sorted(srt.tolist()) == list(range(FIRST, B)), "the launch's own order is not a permutation of the later rows"
         assert (np.diff((Lc[srt] * CLASSES) // (T + 1)) <= 0).all()
@@ -237,6 +245,34 @@ def test_config5_full_size():
         espo.espo_advantages_ws(r, v, L, s, -1.0, 1.0, 0.95, td, adv, ws)
         torch.cuda.synchronize()
         assert torch.equal(td, td_ref) and torch.equal(adv, adv_ref) and not bool(ws[:HEAD].any())
+
+
+@pytest.mark.parametrize("B,T", [(513, 4612), (600, 4607), (514, 4606), (513, 4605), (640, 4608), (1536, 4700), (1537, 4700)])
+def test_batches_beside_the_line_from_which_rows_are_sorted(B, T):
+    _say(f"[case] advantages_ws, own order B={B} T={T}")
+    r, v, L, s = _batch(B, T, seed=B + T)
+    _run(r, v, L, s, oracle_pass=False, ordered=False)
+    if not _sorts_itself(B, T):
+        return
+    # captured, with eager work between the replays: the two words at the head of the workspace are zero after every one
+    ws = _workspace(B)
+    td, adv = torch.empty_like(r), torch.empty_like(r)
+    want_td, want_adv = torch.empty_like(r), torch.empty_like(r)
+    espo.espo_advantages(r, v, L, s, -1.0, 1.0, 0.95, want_td, want_adv)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        espo.espo_advantages_ws(r, v, L, s, -1.0, 1.0, 0.95, td, adv, ws)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        espo.espo_advantages_ws(r, v, L, s, -1.0, 1.0, 0.95, td, adv, ws)
+    for replay in range(3):
+        td.fill_(FILL); adv.fill_(FILL); ws[HEAD:].fill_(0x5a)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(td, want_td) and torch.equal(adv, want_adv) and not bool(ws[:HEAD].any()), replay
 
 
 def test_seeded_sweep():
