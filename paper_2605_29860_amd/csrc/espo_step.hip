@@ -2088,26 +2088,45 @@ constexpr int64_t kEightWavesFrom = 256;
 // A compute unit takes 4.9 to 8.3 us to stream a bf16 row of 152064 logits (its vector units are the limit: some 45
 // operations per tile and wave, 8 of them exponentials) while, below 256 rows, others have none, or, just above,
 // have one row where some have two.  A split costs two more trips through memory (results and ticket, then the
-// other chunks' results), 2 to 3 us, so it pays for long rows only.  us per launch, one workgroup per row -> split:
-//   up to 64 rows, 4 chunks:  bf16 V = 152064: B = 1: 14.7 -> 11.5, 16: 16.2 -> 12.5, 64: 17.0 -> 14.0; f32 V = 66000:
-//     B = 4: 15.7 -> 11.9, 64: 17.7 -> 13.5.  Rows of 131 KB: B = 4, f32: 9.7 -> 10.5; B = 64, bf16: 12.5 -> 12.0.
-//     8 chunks up to 16 rows of 512 KB on (f32 V = 200000, B = 16: 31.8 -> 14.8, in 4 chunks 17.3).
-//   up to 128 rows, 2 chunks: bf16 V = 152064: B = 96: 17.3 -> 15.8, 128: 17.5 -> 17.2; f32 V = 66000, B = 128: 19.9 -> 16.6.
+// other chunks' results), 2 to 3 us, so it pays for long rows only; how long follows from how much a row's workgroup is held up by
+// others that stream beside it, and for fp32 rows, whose sums hide behind the loads, from more rows on.  us per launch, one workgroup
+// per row -> split, with log-probabilities / without (all rows live, synthetic language-model rows, temperature 0.6):
+//   up to 64 rows, 4 chunks:
+//     bf16 from 256 KB on: V = 131500: B = 1: 14.6 -> 11.4 / 11.2 -> 10.2, 64: 15.9 -> 13.3 / 14.0 -> 12.1; 152064: 64: 16.6 -> 13.7
+//     f32, B <= 32, from 384 KB on: V = 100000: B = 1: 13.4 -> 12.9 / 12.3 -> 12.1, 32: 17.4 -> 14.4 / 16.4 -> 13.9; but V = 75000:
+//       B = 4: 10.9 -> 11.5 / 9.9 -> 10.9, 17: 11.7 -> 12.5 / 10.7 -> 12.1, 32: 14.6 -> 13.8 / 14.1 -> 13.3
+//     f32, B = 33 to 64, from 256 KB on: V = 66000: 33: 14.3 -> 13.4 / 13.9 -> 12.9, 64: 16.2 -> 13.7 / 15.8 -> 13.4
+//     8 chunks up to 16 rows from 512 KB on (f32 V = 200000, B = 16: 31.8 -> 14.8, in 4 chunks 17.3).
+//   65 to 128 rows, 2 chunks:
+//     bf16 from 288 KB on: V = 151936: B = 65: 16.8 -> 15.5 / 13.8 -> 14.0, 128: 17.0 -> 15.9 / 14.9 -> 14.8; but V = 140000: 65:
+//       16.3 -> 15.3 / 13.4 -> 14.2, 128: 16.4 -> 16.1 / 14.0 -> 15.2
+//     f32 beyond 256 KB: V = 66000: 65: 16.3 -> 15.8 / 15.6 -> 15.5, 128: 17.8 -> 16.5 / 17.4 -> 16.2; but V = 65536 (eight tiles
+//       for each of 16 waves): 65: 15.2 -> 15.5 / 14.6 -> 15.2
 //   129 to 256 rows: f32 V = 150001: B = 200: 36.0 -> 35.0, 256: 36.6 -> 37.5; bf16: 18.9 -> 21.9.  Not split.
-//   257 to 640 rows of f32 from 512 KB on, V = 150001: 3 chunks up to 400 rows: B = 272: 56.0 -> 44.1, 320: 56.8 -> 46.5,
-//     400: 62.9 -> 57.7; then 2: B = 512: 67.2 -> 64.9, 640: 90.7 -> 81.1.  V = 50000, B = 400: 25.6 -> 27.3; bf16
-//     V = 150001, B = 320: 30.3 -> 29.8, 512: 34.9 -> 40.8: not split.
+//   257 to 400 rows of f32 from 512 KB on, 3 chunks: V = 131072: B = 257: 41.8 -> 37.1, 350: 47.5 -> 45.1, 400: 49.3 -> 48.4;
+//     V = 150001: 57.4 -> 44.8 at 300 (with half the rows done 53.2 -> 33.5).  V = 80000, B = 400: 33.7 -> 36.0: not split.
+//   401 to 512 rows: V = 140000, B = 480: 54.9 -> 57.2 in 2 chunks, 59.0 in 3; 512: 56.1 -> 59.1, 63.8: not split.
+//   513 to 640 rows of f32 from 512 KB on (more rows than two a compute unit), 2 chunks: V = 131500: B = 513: 66.5 -> 61.0,
+//     570: 76.0 -> 68.4; V = 150001, B = 640: 88.4 -> 81.7.  bf16 V = 150001, B = 320: 30.3 -> 29.8, 512: 34.9 -> 40.8: not split.
 // A chunk of bf16 is streamed by 16 waves, one of f32 by 8, which was the faster of the two at every one of these sizes.
 struct RowSplit {
   int chunks, waves;
 };
 
 RowSplit own_split(int dt, int64_t B, int64_t V) {
-  const int64_t row_bytes = V * (dt == ESPO_BF16 ? 2 : 4);
-  const int waves = dt == ESPO_BF16 ? 16 : 8;
-  constexpr int64_t kLong = 256 * 1024, kVeryLong = 512 * 1024;
-  if (B <= 128 && row_bytes >= kLong) return RowSplit{B > 64 ? 2 : B <= 16 && row_bytes >= kVeryLong ? 8 : 4, waves};
-  if (dt == ESPO_F32 && B > 256 && B <= 640 && row_bytes >= kVeryLong) return RowSplit{B <= 400 ? 3 : 2, waves};
+  const bool bf16 = dt == ESPO_BF16;
+  const int64_t row_bytes = V * (bf16 ? 2 : 4);
+  const int waves = bf16 ? 16 : 8;
+  constexpr int64_t kKB = 1024, kVeryLong = 512 * kKB;
+  if (B <= 64) {
+    if (row_bytes < (!bf16 && B <= 32 ? 384 * kKB : 256 * kKB)) return RowSplit{1, 0};
+    return RowSplit{B <= 16 && row_bytes >= kVeryLong ? 8 : 4, waves};
+  }
+  if (B <= 128) return bf16 ? (row_bytes >= 288 * kKB ? RowSplit{2, waves} : RowSplit{1, 0}) : (row_bytes > 256 * kKB ? RowSplit{2, waves} : RowSplit{1, 0});
+  if (!bf16 && row_bytes >= kVeryLong) {
+    if (B > 256 && B <= 400) return RowSplit{3, waves};
+    if (B > 512 && B <= 640) return RowSplit{2, waves};
+  }
   return RowSplit{1, 0};
 }
 
