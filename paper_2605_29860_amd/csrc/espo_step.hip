@@ -1516,6 +1516,13 @@ struct PackList {  // the wave's packs of 8, some 250 of them; each lane owns ev
   // of each of this lane's packs: the bin of its largest logit (kEdgeBins: none above T), and from bit 16 on
   // which of its logits are above T (most packs in the list hold one)
   uint32_t info[kRounds];
+  float mass;  // of all logits above T, set by a draw that reaches below it
+  __device__ __forceinline__ int count() const {  // this lane's logits above T
+    int c = 0;
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) c += (int)__builtin_popcount(info[r] >> 16);
+    return c;
+  }
   __device__ __forceinline__ uint32_t place(int r) const {
     return (uint32_t)((threadIdx.x >> 6) * kRoom + r * kWave + (threadIdx.x & (kWave - 1))) * 8u;
   }
@@ -1564,6 +1571,7 @@ struct LogitList {  // single logits with their indices, in the space of the pac
   static constexpr int kRoom = kBytes / (DT == ESPO_BF16 ? 6 : 8) / 8 * 8;
   const FilterShared<DT, W>& f;
   int n;  // logits of this wave
+  float mass;
   __device__ __forceinline__ int32_t* index_area() const { return (int32_t*)f.raw; }                             // [W][kRoom]
   __device__ __forceinline__ void* logit_area() const { return index_area() + W * kRoom; }            // [W][kRoom]
   __device__ __forceinline__ float logit(uint32_t at) const { return elem_at<DT>(logit_area(), (int64_t)at); }
@@ -1633,7 +1641,10 @@ __device__ __forceinline__ DrawResult draw_from_list(const StepArgs& a, const Fi
   incl += dpp_u32<kDppBcast15, 0xa>(0u, incl);
   incl += dpp_u32<kDppBcast31, 0xc>(0u, incl);
   const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
-  if (by_count ? total < (uint32_t)a.top_k : !((float)total / scale - want > slack)) return kReachesBelow;
+  if (by_count ? total < (uint32_t)a.top_k : !((float)total / scale - want > slack)) {
+    list.mass = (float)total / scale;
+    return kReachesBelow;
+  }
   uint32_t above[4];
   above[0] = incl - lane_total;
 #pragma unroll
@@ -1850,7 +1861,7 @@ __device__ __forceinline__ bool filtered_row(const StepArgs& a, unsigned char* s
       ring[d] = load_raw_inner<DT>((const char*)rowp + (size_t)(t + kRing * W) * kTile * elem_bytes<DT>(), lane_bytes);
     else if (i + kRing < my_tiles)
       ring[d] = load_tile(t + kRing * W);
-    if ((d + 1) % Lim::kCheckTiles == 0 && n > Lim::kCompactAt) {
+    if ((d + 1) % Lim::kCheckTiles == 0 && n >= Lim::kCompactAt) {
       compact_list<DT, W>(my_raw, my_id, a.V, n, thr);
       flooded = flooded || n < Lim::kKeepMin / 2;
     }
@@ -1862,9 +1873,9 @@ __device__ __forceinline__ bool filtered_row(const StepArgs& a, unsigned char* s
 #pragma unroll
     for (int d = 0; d < kRing; ++d) iteration(std::true_type{}, d, i0 + d);
     // Ties at the wave's largest logits: the kept set most likely reaches down to them, and they are not in the
-    // list.  Given up early, such a row costs the general search and a few tiles (76032 equal logits, B = 256: 29.1 us
-    // instead of 49.1, the general search alone 26.4).
-    if (flooded && n < Lim::kKeepMin / 4 && ++dry == 2) {
+    // list.  Given up early, such a row costs the general search and a few tiles (all logits equal, V = 152064, bf16 / fp32: B = 64: 23.6 / 35.1 us,
+    // streamed to the end 26.2 / 38.6, the general search alone 22.9 / 31.0).
+    if (flooded && (n == 0 || (n < Lim::kKeepMin / 4 && ++dry == 2))) {
       thr = __builtin_huge_valf();  // nothing is above it: the row is handed on
       i0 = my_tiles;
       break;
@@ -1914,12 +1925,24 @@ __device__ __forceinline__ bool filtered_row(const StepArgs& a, unsigned char* s
   float x_a = 0.0f;
   if (m > kNegInf) {
     if (!(bottom < m)) return false;  // ties at the row's largest logit fill a list
-    PackList<DT, W> packs{f, n, a.V, {}};
+    PackList<DT, W> packs{f, n, a.V, {}, 0.0f};
     DrawResult res = draw_from_list<DT, W>(a, f, packs, row, m, S, bottom, tok, x_a);
     if (res == kReachesBelow) {
       // A flat row: the row is read once more and its single logits above a lower floor are collected, the smallest
       // of the lanes' largest logits.  (Of n lanes with V / n values each, about n ln n values of the row lie above the
       // smallest maximum: 3200 with 8 waves, 7100 with 16, whatever V is.)
+      if (a.top_k == 0) {
+        // How many logits it would take: those in the list, and for the missing mass more than as many of the threshold's
+        // weight, since the weights fall on.  Where that is more than a draw has room for, the row is not read for
+        // nothing (us, V = 152064, rows of normal logits: deviation 2, p = 0.9, B = 64: 84 -> 67; deviation 1, p = 0.7, B = 512: 187 -> 156).
+        // With a factor of 1.25 fewer rows are spared (synthetic rows at temperature 1.3, p = 0.9, B = 64: 85 instead of 70); with
+        // 2.5 rows that fit are sent away (temperature 1.3, p = 0.7, B = 512: 111 instead of 78).
+        const float mine = wave_sum((float)packs.count());
+        if (lane == 0) atomicAdd(f.nkept, (int)mine);
+        __syncthreads();
+        const float missing = a.top_p * S - packs.mass;
+        if ((float)*f.nkept + 1.6f * missing / weight_below(bottom, m, a.k2) > (float)(kKeptCap2 + kEdgeMembers)) return false;
+      }
       const float floor2 = -wave_max(lane < W ? -f.least[lane] : kNegInf);
       if (!(floor2 < bottom && floor2 > kMaskedBelow)) return false;
       __syncthreads();  // the packs and the bins have been read by everyone
@@ -1929,7 +1952,7 @@ __device__ __forceinline__ bool filtered_row(const StepArgs& a, unsigned char* s
         *f.nmem = 0;
         *f.nover = 0;
       }
-      LogitList<DT, W> logits{f, 0};
+      LogitList<DT, W> logits{f, 0, 0.0f};
       constexpr int kDeep = 6;
 #pragma unroll 1
       for (int i1 = 0; i1 < my_tiles; i1 += kDeep) {
@@ -1979,8 +2002,10 @@ __global__ __launch_bounds__(W * kWave, 4) void espo_filtered_kernel(StepArgs a)
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int row = (int)blockIdx.x;
   // top-k 1 needs the row maximum and its ties only, which the general search finds with less work per tile than the
-  // lists take (us, V = 30000 bf16, B = 30: 8.8, through the lists 13.4; V = 60000, B = 300: 15.9 against 20.4)
-  if (a.top_k != 1 && !row_is_done(a.alive, row)) {
+  // lists take (us, V = 30000 bf16, B = 30: 8.8, through the lists 13.4; V = 60000, B = 300: 15.9 against 20.4).
+  // A kept set of more logits than a draw from the lists has room for goes there at once, too (top-k 4000, B = 64, V = 152064:
+  // 73 -> 38).
+  if (a.top_k != 1 && a.top_k <= kKeptCap2 + kEdgeMembers && !row_is_done(a.alive, row)) {
     if (filtered_row<DT, Entropy, W>(a, smem_raw, row)) return;
     __syncthreads();  // the general search uses the same shared memory
   }

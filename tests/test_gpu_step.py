@@ -960,7 +960,7 @@ def test_filtered_draws_whatever_order_the_logits_come_in(order, dtype):
     # a list and the kept logits have room for, and one more).
     B = 6
     for V, tau, f in [(30011, 1.0, dict(top_k=1)), (30011, 1.0, dict(top_p=0.7)), (30011, 2.0, dict(top_p=0.9)), (30011, 1.0, dict(top_k=300)),
-                      (30011, 1.0, dict(top_k=3072)), (30011, 1.0, dict(top_k=3073)), (511, 1.0, dict(top_p=0.8)), (4096, 0.5, dict(top_k=40))]:
+                      (30011, 1.0, dict(top_k=3072)), (30011, 1.0, dict(top_k=3073)), (30011, 1.0, dict(top_k=3328)), (30011, 1.0, dict(top_k=3329)), (511, 1.0, dict(top_p=0.8)), (4096, 0.5, dict(top_k=40))]:
         g = torch.Generator().manual_seed(V + int(10 * tau))
         x = (torch.randn(B, V, generator=g) * 2.0).sort(dim=1, descending=order == "descending")[0]
         if order == "clustered":                              # groups of eight neighbours, in random order
