@@ -201,8 +201,11 @@ typedef enum {
  *               16-byte aligned.  With it, the long rows of a small batch are split over several workgroups
  *               that combine through it (B = 64, V = 152064 bf16: 17.0 -> 14.0 us; fp32: 28.1 -> 16.9).
  *               Without it (NULL, too short or misaligned), and where that size is 0, one workgroup
- *               handles a whole row.  Its contents before the call do not matter; the bytes used are
- *               zero afterwards.  Calls that may run at the same time need a workspace each.
+ *               handles a whole row.  What it holds before the call does not matter, unless calls that overlapped
+ *               in time have shared it: two such calls write into each other's rows, and what they leave can still be
+ *               taken for an arrival by a later call, so the buffer has to be cleared before it is used again.
+ *               Calls that may run at the same time need a workspace each (up to version 310 no call
+ *               wrote to it).  After the call the bytes of live rows are zero, those of rows that are done are as before.
  *   stream      hipStream_t as void*.
  */
 int espo_step(const void* logits, espo_dtype dt, int64_t B, int64_t V, int64_t row_stride,
@@ -227,8 +230,9 @@ size_t espo_step_workspace_bytes(int64_t B, int64_t V, espo_dtype dt);
  *   V_L = 0                                             (no bootstrap past the end),
  *   td[b,t]  = r_t + gamma * values[b,t+1] - values[b,t]            for t < L,
  *   adv[b,t] = sum_{l=0}^{L-1-t} (gamma*lambda)^l td[b,t+l]          for t < L,
- * and td[b,t] = adv[b,t] = 0 for L <= t < T.  rewards and values are never read at
- * t >= L.  (The ablation without the terminal failure penalty, Section 6 variant C, is this
+ * and td[b,t] = adv[b,t] = 0 for L <= t < T.  What rewards and values hold at t >= L has no
+ * influence, and it is not read, except that with T % 4 != 0 the last one to three positions of
+ * a row may be loaded (and dropped) with the 16 bytes that the next row starts in.  (The ablation without the terminal failure penalty, Section 6 variant C, is this
  * call with all `stopped` flags zero: the truncated trajectory then keeps its stored last
  * reward.)  Rows are independent and may come in any order: in a batch of 513 to 1536 rows of
  * more than 8192 steps the library itself scans the rows from the 513th on longest first (the workgroups
@@ -278,7 +282,8 @@ int espo_advantages_terminal(const float* values, const int32_t* lengths, const 
  * cu_seqlens[b] .. cu_seqlens[b+1]-1 of arrays of N tokens and only those are read and
  * written: delta_t, A_t (Section 3, Eq. gae) and optionally A_t + V(s_t) over each
  * trajectory on its own, V := 0 after its last token, r_fail at the last token of a stopped
- * one (Eq. failure_reward).
+ * one (Eq. failure_reward).  (Up to three positions before a trajectory's first may be loaded with
+ * the 16 bytes that it starts in; they are dropped.)
  *
  * Exactly one of rewards / terminal_reward is given (ESPO_EINVAL otherwise):
  *   rewards          device, [N] fp32 in the same layout: the dense form of espo_advantages;

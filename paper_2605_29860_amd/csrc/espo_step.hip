@@ -85,7 +85,7 @@ struct StepArgs {
   // a row split over `nch` workgroups: workgroup row * nch + c streams tiles [c ntiles / nch, (c + 1) ntiles / nch)
   int32_t nch;
   ChunkResult* partials;         // [B * nch] what each chunk found, combined by the last one of a row to arrive
-  unsigned long long* tickets;   // [B] arrivals per row: kTicketMark above a count; anything else counts as none, and zero is left behind
+  unsigned long long* tickets;   // [B] arrivals per row: kTicketMark above a count; anything else counts as none, and a live row's is left zero
 };
 
 

@@ -644,6 +644,7 @@ def test_rows_the_library_splits_itself(B, V, dtype, chunks):
                "misaligned": torch.full((need + 16,), 0xCD, dtype=torch.uint8, device="cuda")[4:],
                "zero": torch.zeros(need, dtype=torch.uint8, device="cuda"),
                "noise": torch.randint(0, 256, (need + 64,), dtype=torch.uint8, device="cuda")}
+    noise = buffers["noise"].clone()
     results = {}
     for name, ws in buffers.items():
         st = H.GpuState(B, alive=alive, z=torch.zeros(B))
@@ -656,6 +657,16 @@ def test_rows_the_library_splits_itself(B, V, dtype, chunks):
         results[name] = out
     if need:
         assert not bool(buffers["zero"].any())                # handed back as it came
+        # whatever it held: the tickets and results of live rows are zero again, those of done rows are as they were
+        head = need - 32 * B * chunks
+        tickets = buffers["noise"][:8 * B].view(B, 8).cpu()
+        parts = buffers["noise"][head:need].view(B, 32 * chunks).cpu()
+        live = alive == 1
+        assert not bool(tickets[live].any()) and not bool(parts[live].any())
+        noise = noise.cpu()
+        assert torch.equal(tickets[~live], noise[:8 * B].view(B, 8)[~live])
+        assert torch.equal(parts[~live], noise[head:need].view(B, 32 * chunks)[~live])
+        assert torch.equal(buffers["noise"][need:].cpu(), noise[need:])
     for name, out in results.items():
         for step in range(3):
             for k, (got, want) in enumerate(zip(out[step], results["none"][step])):
