@@ -398,8 +398,8 @@ int espo_batch_stats_static(const float* regret, const int32_t* lengths, const u
  *   adv        device, [B, T] fp32 row-major, 16-byte aligned base.  Trajectories stored
  *              back to back (espo_advantages_packed) are the case B = 1, T = N, lengths = {N}.
  *   lengths    device, [B] int32.
- *   B, T       B >= 0, T >= 0 (either 0 is a no-op); B, T and B * ceil(T / 4096) below 2^31
- *              (ESPO_ERANGE).
+ *   B, T       B >= 0, T >= 0 (either 0 is a no-op); B, T and B * ceil(T / 4096) below 2^31, and
+ *              B * ceil((T + 3) / 1024) below 2^32 - 2^15 (ESPO_ERANGE).
  *   eps        >= 0, finite (common choice: 1e-8).
  *   shift_mean, unbiased   flags as above.
  *   out        device, [B, T] fp32, 16-byte aligned base; may be the same array as adv.

@@ -52,6 +52,8 @@ struct AdvRowStats {
 };
 
 size_t whiten_workspace(int64_t B, int64_t T);
+// Whether the batch's items fit the index that the kernels count them with (B, T below 2^31; beyond it are 16 TB of advantages).
+bool whiten_indexable(int64_t B, int64_t T);
 // The second half of the whitening alone: mean and variance from the rows' sums, then the rewrite.
 int launch_whiten_rows(const float* adv, const int32_t* lengths, int64_t B, int64_t T, float eps, int shift_mean,
                        int unbiased, float* out, double* stats, const AdvRowStats* rows, hipStream_t stream);

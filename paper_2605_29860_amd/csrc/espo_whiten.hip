@@ -368,6 +368,9 @@ __global__ __launch_bounds__(kWhThreads) void whiten_small_kernel(WhArgs a) {
     if (u < quads) store_quad(a.out + ((uint32_t)u * kWhThreads + threadIdx.x) * 4u, g[u], in[u], s);
 }
 
+// Items of a row: one that starts between boundaries spans up to 3 positions more.
+int64_t items_per_row(int64_t T) { return (T + (T % 4 != 0 ? 3 : 0) + kWhItem - 1) / kWhItem; }
+
 // One workgroup per 4096 positions of a row, up to what the chip holds.
 int whiten_groups(int64_t B, int64_t T) {
   const int64_t want = B * ((T + 4095) / 4096);
@@ -381,7 +384,7 @@ WhArgs whiten_args(const float* adv, const int32_t* lengths, int64_t B, int64_t 
   a.lengths = lengths;
   a.B = B;
   a.T = T;
-  a.nch = (T + (T % 4 != 0 ? 3 : 0) + kWhItem - 1) / kWhItem;  // a row that starts between boundaries spans up to 3 positions more
+  a.nch = items_per_row(T);
   a.items = B * a.nch;
   a.groups = whiten_groups(B, T);
   a.eps = eps;
@@ -394,6 +397,13 @@ WhArgs whiten_args(const float* adv, const int32_t* lengths, int64_t B, int64_t 
 }
 
 }  // namespace
+
+// item_index counts in 32 bits, and past the last item by up to kWhUnroll rounds of the waves.
+bool whiten_indexable(int64_t B, int64_t T) {
+  constexpr int64_t kRoom = 1 << 15;
+  static_assert((kWhUnroll + 1) * kWhWaves * kWhMaxGroups <= kRoom, "room for the index of a loop's last step");
+  return B * ((T + 3 + kWhItem - 1) / kWhItem) < (1ll << 32) - kRoom;
+}
 
 size_t whiten_workspace(int64_t B, int64_t T) { return (size_t)whiten_groups(B, T) * sizeof(Sums); }
 

@@ -89,6 +89,7 @@ def test_argument_checks_need_no_gpu(lib):
     assert wh(B=-1) == -1 and wh(eps=-1.0) == -1 and wh(eps=float("nan")) == -1 and wh(adv=None) == -1
     assert wh(out=ctypes.c_void_p(0x1004)) == -2 and wh(stats=ctypes.c_void_p(0x1004)) == -2
     assert wh(ws=None) == -3 and wh(nws=need - 1) == -3
+    assert wh(B=0x7fffffff, T=4096) == -5 and wh(B=1 << 30, T=4094) == -5     # more items than 32 bits index
     assert lib.espo_step_workspace_bytes(1024, 152064, 1) == 0 and lib.espo_step_workspace_bytes(0, 152064, 1) == 0
     lib.espo_debug_step.argtypes = lib.espo_step.argtypes + [ctypes.c_float, ctypes.c_int32, ctypes.c_int32]
     dbg = lambda scale=1.0, waves=0, chunks=0: lib.espo_debug_step(fake, 1, 4, 4096, 4096, 1.0, 0, 0, fake, ctypes.byref(p), fake, fake,
