@@ -19,7 +19,6 @@
 #include <math.h>
 #include <stdint.h>
 
-#include <algorithm>
 #include <mutex>
 
 #include "../../include/espo.h"

@@ -98,14 +98,6 @@ __device__ __forceinline__ float uniform_f32(float v, int lane) {
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
 }
 
-// A double from `d` lanes further on in the wave (the lane's own where there is none).
-__device__ __forceinline__ double shfl_down_f64(double v, int d) {
-  int lo = __double2loint(v), hi = __double2hiint(v);
-  lo = __shfl_down(lo, d);
-  hi = __shfl_down(hi, d);
-  return __hiloint2double(hi, lo);
-}
-
 // ---------------------------------------------------------------- Philox4x32-10
 // Salmon et al., SC'11: ten rounds; each round multiplies words 0 and 2 by fixed odd
 // constants, keeps the low halves and folds the high halves with the other words and
