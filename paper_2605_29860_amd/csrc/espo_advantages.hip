@@ -78,8 +78,8 @@ constexpr int kAdvFirstRows = 512;
 constexpr int kAdvSelectRows = 3 * kAdvFirstRows;
 constexpr int64_t kAdvSelectTokens = 8192;
 // Read from a list that the launch makes, the order costs its readers one load, so it pays for shorter rows, too; us per
-// launch with / without, dense: T = 4100: B = 1024: 19.5 / 18.4, 1536: 28.5 / 26.4; T = 5000: B = 800: 17.7 / 19.2,
-// 1024: 20.7 / 22.4, 1536: 30.2 / 29.4; T = 8192: B = 600: 19.4 / 19.3, 1024: 25.2 / 25.8 (terminal rewards 24.3 / 26.0).
+// launch with / without, dense: T = 4100: B = 1024: 19.5 / 17.3, 1536: 28.5 / 26.4; T = 5000: B = 800: 17.7 / 19.2,
+// 1024: 20.9 / 22.4, 1536: 30.2 / 29.4; T = 8192: B = 1024: 24.1 / 25.8 (terminal rewards, padding filled: 24.2 / 26.0).
 constexpr int64_t kAdvSortTokens = 4608;
 // The word that says "sorted" and the count of its readers lie in different 128-byte lines: loads of the one and
 // read-modify-writes of the other on the same line cost the readers 15 us per launch between them.
@@ -373,16 +373,16 @@ __global__ __launch_bounds__(W * kWave, W == 4 ? (Dense && Layout == kPacked ? 5
   // not fit the chip at once matters, and only their scans look their row up: see below.)
   constexpr bool kOrdered = W == 16;  // of the smaller workgroups, for short rows, the chip holds 2048, and rows differ little
   int unit = (int)blockIdx.x;
-  if constexpr (kOrdered && !Packed) {
+  if (kOrdered && !Packed && a.sorted) {
     // No order was given and the later rows are to be scanned longest first: workgroup 0 of this launch
     // sorts them while the first kAdvFirstRows are being scanned, and tells the others when it is done.
     // It waits for nobody and is dispatched before every workgroup that waits for it.
-    if (a.sorted && unit == 0) {
+    if (unit == 0) {
       sort_rows_by_length(a.lengths, kAdvFirstRows, a.B, a.T, a.sorted);
       if (threadIdx.x == 0) __hip_atomic_store(a.sync, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       return;
     }
-    if (a.sorted) unit -= 1;
+    unit -= 1;
   }
   const bool fill_only = !Packed && unit >= a.B;
   int row = fill_only ? unit - a.B : unit;
