@@ -30,7 +30,7 @@ extern "C" {
  *                       a split; logprob and entropy may differ in the last bits, their sums being
  *                       added in another order).  Needs a workspace of
  *                       espo_debug_step_workspace_bytes(B, chunks) bytes (ESPO_EWORKSPACE
- *                       otherwise; its contents do not matter), which comes back zero; the value is lowered to the number of
+ *                       otherwise; contents and what comes back as for espo_step); the value is lowered to the number of
  *                       tiles of a row and to 64 if it exceeds them.
  * A filtered draw (top_p / top_k) is never split, and runs 8 waves, or 16 below 256 rows if the choice is the
  * library's: waves 0 or 8, chunks 0 or 1 (ESPO_EINVAL otherwise).
