@@ -25,8 +25,8 @@ extern "C" {
  *                       given; else as espo_step, workspace included).  With
  *                       more than one, every workgroup streams a run of 512-index tiles of its row,
  *                       finds the exact winner of that run and leaves it in the workspace with the
- *                       run's maximum and softmax sum; the last workgroup of a row to arrive
- *                       combines them (tokens, regret, state and masks are the same bits as without
+ *                       run's maximum and softmax sum; a workgroup that finds all of a row's
+ *                       results there combines them (tokens, regret, state and masks are the same bits as without
  *                       a split; logprob and entropy may differ in the last bits, their sums being
  *                       added in another order).  Needs a workspace of
  *                       espo_debug_step_workspace_bytes(B, chunks) bytes (ESPO_EWORKSPACE

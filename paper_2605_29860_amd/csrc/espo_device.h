@@ -26,15 +26,29 @@ __device__ __forceinline__ float dpp_f32(float identity, float v) {
                                                                __builtin_bit_cast(int, v), Ctrl, RowMask, 0xf, false));
 }
 
+// One step of a reduction: v = op(v of the lane that `ctrl` names, v); lanes without a source keep v.  As one instruction and
+// the two wait states a DPP read needs after a write: through the builtins a maximum takes four (the identity moved in, the wait,
+// the shifted copy, the maximum), and a row's search has some ten such reductions on its critical path.
+#define ESPO_DPP_STEP(op, v, ctrl) asm("s_nop 1\n\t" op "_dpp %0, %0, %0 " ctrl : "+v"(v))
+
 // Maximum over the 64 lanes, returned to every lane as a wave-uniform value.
 __device__ __forceinline__ float wave_max(float v) {
-  v = fmaxf(v, dpp_f32<kDppRowShr1, 0xf>(kNegInf, v));
-  v = fmaxf(v, dpp_f32<kDppRowShr2, 0xf>(kNegInf, v));
-  v = fmaxf(v, dpp_f32<kDppRowShr4, 0xf>(kNegInf, v));
-  v = fmaxf(v, dpp_f32<kDppRowShr8, 0xf>(kNegInf, v));
-  v = fmaxf(v, dpp_f32<kDppBcast15, 0xa>(kNegInf, v));
-  v = fmaxf(v, dpp_f32<kDppBcast31, 0xc>(kNegInf, v));
+  ESPO_DPP_STEP("v_max_f32", v, "row_shr:1 row_mask:0xf bank_mask:0xf");
+  ESPO_DPP_STEP("v_max_f32", v, "row_shr:2 row_mask:0xf bank_mask:0xf");
+  ESPO_DPP_STEP("v_max_f32", v, "row_shr:4 row_mask:0xf bank_mask:0xf");
+  ESPO_DPP_STEP("v_max_f32", v, "row_shr:8 row_mask:0xf bank_mask:0xf");
+  ESPO_DPP_STEP("v_max_f32", v, "row_bcast:15 row_mask:0xa bank_mask:0xf");
+  ESPO_DPP_STEP("v_max_f32", v, "row_bcast:31 row_mask:0xc bank_mask:0xf");
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
+}
+
+// The same over lanes 0 to 15 alone: what a workgroup's waves (at most 16) have left, one per lane.
+__device__ __forceinline__ float row_max(float v) {
+  ESPO_DPP_STEP("v_max_f32", v, "row_shr:1 row_mask:0xf bank_mask:0xf");
+  ESPO_DPP_STEP("v_max_f32", v, "row_shr:2 row_mask:0xf bank_mask:0xf");
+  ESPO_DPP_STEP("v_max_f32", v, "row_shr:4 row_mask:0xf bank_mask:0xf");
+  ESPO_DPP_STEP("v_max_f32", v, "row_shr:8 row_mask:0xf bank_mask:0xf");
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 15));
 }
 
 // Minimum of unsigned values over the 64 lanes, wave-uniform.

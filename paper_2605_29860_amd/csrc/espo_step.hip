@@ -9,10 +9,10 @@
 //     DPP steps) and an fp32 upper bound ub_q >= max_v (y_v + G_v) built from the block's
 //     largest Gumbel variate M_q, kept in LDS.  Each lane group also keeps the raw data of
 //     the block with the largest bound it has seen, so that phase 2 seldom re-reads memory.
-//   phase 2 (a handful of blocks, lanes = the 64 indices of a block): every wave scores the
-//     block with the largest bound it has streamed, the best score found rules out every
-//     block with a lower bound, the few survivors are scored by the waves in parallel (a long
-//     list is first reduced to the indices whose own bound y_v + M_q still reaches the score
+//   phase 2 (a handful of indices, behind two barriers): every lane scores the largest logit it
+//     has kept, the best score found rules out every block with a lower bound, and each wave
+//     looks at what is left of its own blocks (many of them go to a list for the whole workgroup,
+//     which is reduced to the indices whose own bound y_v + M_q still reaches the score
 //     attained, and those are scored one per thread).  Scores are first formed in fp32 with a
 //     proven error margin; if the best two cannot be told apart within that margin, the
 //     indices that reach the fp32 winner's lower end are scored again in double, which
@@ -49,16 +49,11 @@ constexpr int kRing = 4;                          // 16-byte loads kept in fligh
 constexpr int kCandCap = 1024;                    // candidate indices kept for a row with a long survivor list
 constexpr float kRescaleAt = 64.0f;               // advance a lane's softmax reference when topped by 2^64
 
-constexpr unsigned long long kTicketMark = 0x4553504F00000000ull;  // marks a ticket word that this kernel wrote
-
-// What the workgroup of one chunk hands to the combine: the chunk's largest logit, its softmax
-// sums relative to that logit, and its exact local winner (score known to within +-e).
-struct __attribute__((aligned(16))) ChunkResult {
-  float m, sum, sumw, s;
-  float e, x;
-  int32_t v;
-  int32_t pad;
-};
+// What the workgroup of one chunk hands to the combine: the chunk's largest logit, its softmax sums relative to that logit,
+// and its exact local winner (score known to within +-e): m, sum, sumw, s, e, x, v.  Each goes into the workspace as a
+// 64-bit word of its own with this mark above it, so that a word is either there as a whole or recognised as not there.
+constexpr uint32_t kMailMark = 0x4553504Fu;
+constexpr int kMailWords = 7;
 
 struct StepArgs {
   const void* logits;
@@ -82,10 +77,10 @@ struct StepArgs {
   float* regret;
   float* logprob;
   float* entropy;
-  // a row split over `nch` workgroups: workgroup row * nch + c streams tiles [c ntiles / nch, (c + 1) ntiles / nch)
-  int32_t nch;
-  ChunkResult* partials;         // [B * nch] what each chunk found, combined by the last one of a row to arrive
-  unsigned long long* tickets;   // [B] arrivals per row: kTicketMark above a count; anything else counts as none, and a live row's is left zero
+  // a row split over `nch` workgroups: workgroup (row, c) streams `chunk_tiles` tiles, one more for the first `chunk_extra` chunks
+  int32_t nch, chunk_tiles, chunk_extra;
+  unsigned long long* row_words;  // [B] 8 bytes per row at the head of the workspace, left zero for live rows
+  unsigned long long *mail_lo, *mail_hi;  // [B * nch][4] each: words 0 to 3 and 4 to 6 of what each chunk found; left zero
 };
 
 
@@ -135,6 +130,24 @@ __device__ __forceinline__ Raw<DT> load_raw_inner(const void* tile, uint32_t lan
   return r;
 }
 
+// The same words in LDS.
+template <int DT>
+__device__ __forceinline__ Raw<DT> pack_load(const uint32_t* raw) {
+  Raw<DT> r;
+#pragma unroll
+  for (int h = 0; h < Raw<DT>::kWords / 4; ++h) {
+    const u32x4 t = ((const u32x4*)raw)[h];
+    r.w[4 * h] = t.x; r.w[4 * h + 1] = t.y; r.w[4 * h + 2] = t.z; r.w[4 * h + 3] = t.w;
+  }
+  return r;
+}
+template <int DT>
+__device__ __forceinline__ void pack_store(uint32_t* raw, const Raw<DT>& r) {
+#pragma unroll
+  for (int h = 0; h < Raw<DT>::kWords / 4; ++h)
+    ((u32x4*)raw)[h] = u32x4{r.w[4 * h], r.w[4 * h + 1], r.w[4 * h + 2], r.w[4 * h + 3]};
+}
+
 template <int DT>
 __device__ __forceinline__ void unpack(const Raw<DT>& r, float x[8]) {
   if constexpr (DT == ESPO_BF16) {
@@ -147,6 +160,10 @@ __device__ __forceinline__ void unpack(const Raw<DT>& r, float x[8]) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) x[i] = __builtin_bit_cast(float, r.w[i]);
   }
+}
+
+__device__ __forceinline__ float max8(const float x[8]) {
+  return fmaxf(fmaxf(fmaxf(fmaxf(fmaxf(x[0], x[1]), x[2]), fmaxf(fmaxf(x[3], x[4]), x[5])), x[6]), x[7]);
 }
 
 template <int DT>
@@ -293,8 +310,7 @@ __device__ __forceinline__ void score_index(const StepArgs& a, int row, int32_t 
   }
 }
 
-// Scores the 64 indices of block q, one per lane.  `data` points at the block's 64 elements
-// (LDS copy or the row itself).
+// Scores the 64 indices of block q, one per lane.  `data` points at the block's 64 elements.
 template <int DT, typename F>
 __device__ __forceinline__ void visit_block(const StepArgs& a, int row, int q, const void* data, F bound, float floor,
                                             Search<F>& st) {
@@ -362,7 +378,7 @@ __device__ __forceinline__ void finish_row(const StepArgs& a, int row, const voi
 }
 
 // ---------------------------------------------------------------- shared memory
-// Blocks are named by their index q in the row everywhere (survivor lists, top_q, visq); the
+// Blocks are named by their index q in the row everywhere (survivor lists, own, visq); the
 // per-block tables only cover the workgroup's chunk and are reached through the accessors, which
 // subtract q0, the chunk's first block (a multiple of 8).
 struct StepShared {
@@ -376,24 +392,24 @@ struct StepShared {
   __device__ __forceinline__ float& blockmax(int q) const { return bmx[q - q0]; }
   __device__ __forceinline__ int& surv(int k) const { return ((int*)mu)[2 * k]; }
   void* top_raw;    // [8 W][64 elements] data of each lane group's best block
-  int* top_q;       // [8 W] which block each lane group kept
   float* m;         // [W] wave maxima
-  float* sum;       // [W] wave softmax sums (relative to the chunk maximum)
-  float* sumw;      // [W] wave sums of 2^t t, t = (y_v - y_max) log2 e (entropy output only)
+  float* sum;       // [W] wave softmax sums, relative to the wave's own maximum
+  float* sumw;      // [W] wave sums of 2^t t, t = (y_v - y_max) log2 e with the wave's y_max (entropy output only)
   double* res_s;    // [W] per-wave search results
   double* res_hi2;
   float* res_e;
   int* res_v;
   float* res_x;
   float* lo;        // [W] score each wave knows to be attained
-  int* visq;        // [2][W] blocks each wave scored before the first barrier, or -1
-  float* fres;      // [5][W] per-wave results of the fp32 search: s, e, x, hi2, v
+  int* visq;        // [W] block each wave scored before the first barrier of the search in double, or -1
+  int* own;         // [W][8] blocks that a wave has to read again
+  float* fres;      // [W][8] per-wave results of the fp32 search: s, e, x, hi2, v
   int32_t* cand_v;  // [kCandCap] long survivor lists: indices that can still win ...
   float* cand_x;    // [kCandCap] ... and their logits
   int* ncand;       // [1]
   int* nsurv;       // [1]
   int* bkey;        // [1] best attained score published during long survivor lists (order-preserving key)
-  float floor;      // only logits above this take part in the search (-inf unless the draw is filtered)
+  float floor;      // only logits above this take part in the search (what counts as masked, or more if the draw is filtered)
   float* bmx;       // [nslots] largest logit of every block (filtered draws only, else null)
 };
 
@@ -401,14 +417,13 @@ template <int DT, bool Filter, int W>
 __device__ __forceinline__ StepShared carve(unsigned char* base, int nslots, int q0) {
   constexpr int kStepWaves = W, kSlots = W * kGroups;
   StepShared s;
-  s.floor = kNegInf;
+  s.floor = kMaskedBelow;
   s.q0 = q0;
   size_t off = 0;
   auto take = [&](size_t bytes) { void* p = base + off; off += (bytes + 15) & ~(size_t)15; return p; };
   s.res_s = (double*)take(kStepWaves * 8);
   s.res_hi2 = (double*)take(kStepWaves * 8);
   s.top_raw = take((size_t)kSlots * kDrawBlock * elem_bytes<DT>());
-  s.top_q = (int*)take(kSlots * 4);
   s.m = (float*)take(kStepWaves * 4);
   s.sum = (float*)take(kStepWaves * 4);
   s.sumw = (float*)take(kStepWaves * 4);
@@ -416,8 +431,9 @@ __device__ __forceinline__ StepShared carve(unsigned char* base, int nslots, int
   s.res_v = (int*)take(kStepWaves * 4);
   s.res_x = (float*)take(kStepWaves * 4);
   s.lo = (float*)take(kStepWaves * 4);
-  s.visq = (int*)take(2 * kStepWaves * 4);
-  s.fres = (float*)take(5 * kStepWaves * 4);
+  s.visq = (int*)take(kStepWaves * 4);
+  s.own = (int*)take(kSlots * 4);
+  s.fres = (float*)take(8 * kStepWaves * 4);
   s.cand_v = (int32_t*)take(kCandCap * 4);
   s.cand_x = (float*)take(kCandCap * 4);
   s.nsurv = (int*)take(16);
@@ -433,7 +449,7 @@ __device__ __forceinline__ StepShared carve(unsigned char* base, int nslots, int
 [[maybe_unused]] size_t step_lds_bytes(int dt, int ntiles, bool filter, int waves) {
   const size_t esz = dt == ESPO_BF16 ? 2 : 4;
   const size_t nslots = (size_t)ntiles * kGroups, slots = (size_t)waves * kGroups;
-  return 2 * (size_t)waves * 8 + slots * kDrawBlock * esz + slots * 4 + 14 * (size_t)waves * 4 + 16 + 2 * kCandCap * 4 +
+  return 2 * (size_t)waves * 8 + slots * kDrawBlock * esz + slots * 4 + 16 * (size_t)waves * 4 + 16 + 2 * kCandCap * 4 +
          ((nslots * 8 + 15) & ~(size_t)15) + (filter ? 2 : 1) * ((nslots * 4 + 15) & ~(size_t)15);
 }
 
@@ -445,13 +461,15 @@ __device__ __forceinline__ float ub_rounded_up(float u) { return fmaf(fabsf(u), 
 // filtered; then only if its largest logit is above the floor.
 __device__ __forceinline__ bool holds_eligible(const StepShared& sh, int q) { return sh.bmx == nullptr || sh.blockmax(q) > sh.floor; }
 
-// Wave that streamed block q in phase 1, and the slot (wave, group) of that block.
+// Wave that streamed block q in phase 1.
 template <int W>
 __device__ __forceinline__ int wave_of(const StepShared& sh, int q) { return ((q - sh.q0) >> 3) & (W - 1); }
-template <int W>
-__device__ __forceinline__ int slot_of(const StepShared& sh, int q) { return wave_of<W>(sh, q) * kGroups + (q & (kGroups - 1)); }
-
 // ---------------------------------------------------------------- phase 2
+// Lanes below this one whose bit is set in `mask`.
+__device__ __forceinline__ int rank_below(uint64_t mask) {
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+
 __device__ __forceinline__ int float_key(float f) {  // order-preserving map to signed int
   const int b = __builtin_bit_cast(int, f);
   return b >= 0 ? b : b ^ 0x7fffffff;
@@ -496,21 +514,15 @@ __device__ __forceinline__ Search<F> combine_search(const StepShared& sh, Search
 // Finds the argmax over the row in precision F.  `bound0` is a score that is known to be
 // attained or exceeded (prunes from the start); `q_own` is the block this wave scores
 // first, without waiting for the others (or -1).  Every block whose bound reaches the best
-// score found that way is then scored, one block per wave visit.  `between` runs right
-// after the first barrier.  Returns the winner, the same in every thread; all threads of
+// score found that way is then scored, one block per wave visit.  Returns the winner, the same in every thread; all threads of
 // the workgroup must call it.
-template <int DT, typename F, int W, typename Between>
+template <int DT, typename F, int W>
 __device__ __forceinline__ Search<F> find_argmax(const StepArgs& a, const StepShared& sh, const void* rowp, int row,
-                                                 int nslots, int q_own, F bound0, Between between) {
+                                                 int nslots, int q_own, F bound0) {
   constexpr int kStepWaves = W, kStepThreads = W * kWave;
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  auto data_of = [&](int q) -> const void* {  // LDS copy if a lane group kept this block, else the row
-    const int slot = slot_of<W>(sh, q);
-    if (sh.top_q[slot] == q) return (const char*)sh.top_raw + (size_t)slot * kDrawBlock * elem_bytes<DT>();
-    return (const char*)rowp + (size_t)q * kDrawBlock * elem_bytes<DT>();
-  };
   Search<F> st;
   st.init();
   F bound = bound0;
@@ -519,7 +531,7 @@ __device__ __forceinline__ Search<F> find_argmax(const StepArgs& a, const StepSh
 #pragma unroll 1
   while (true) {  // one visit site for the wave's own block and for the survivors
     if (q >= 0) {
-      visit_block<DT, F>(a, row, q, data_of(q), bound, sh.floor, st);
+      visit_block<DT, F>(a, row, q, (const char*)rowp + (size_t)q * kDrawBlock * elem_bytes<DT>(), bound, sh.floor, st);
       const float lo = wave_max(round_down_f32(st.lower()));  // best score this wave has seen, rounded down
       bound = bound > (F)lo ? bound : (F)lo;
     }
@@ -531,7 +543,6 @@ __device__ __forceinline__ Search<F> find_argmax(const StepArgs& a, const StepSh
       }
       if (tid == 0) *sh.nsurv = 0;
       __syncthreads();
-      between();
       float bound_f = sh.lo[0];
 #pragma unroll
       for (int w = 1; w < kStepWaves; ++w) bound_f = fmaxf(bound_f, sh.lo[w]);
@@ -564,26 +575,31 @@ struct Best {
 
 __device__ __forceinline__ Best no_best() { return Best{kNegInf, 0.0f, 0.0f, kNegInf, -1}; }
 
-// Scores index v (logit x) in fp32 and offers it to the lane's state, with `wb` the random word of its
-// block.  An index is scored at most once in a search, so a lane never meets the same index twice.
-// `v_named` is what the state calls the index (the index itself, or the index with a flag on top).
-__device__ __forceinline__ void score_drawn(const StepArgs& a, int row, int32_t v, int32_t v_named, float x, uint32_t wb,
-                                            bool valid, Best& st) {
-  const int32_t q = v >> 6;
+// The block-level part of an fp32 score, from the block's random word: its largest variate M_q = ln n - ln(-ln u),
+// exp(-M_q) = (-ln u) / n, and the index that receives M_q.
+struct FastDraw {
+  float M, emM;
+  int32_t vpos;
+};
+
+__device__ __forceinline__ FastDraw fast_draw(const StepArgs& a, int row, int32_t q, uint32_t wb) {
   const int32_t first = q * kDrawBlock;
   const int32_t n = a.V - first < kDrawBlock ? a.V - first : kDrawBlock;
-  // the index's own word depends on nothing else here: its ten rounds overlap the loads
-  const Philox4 p = philox4x32_10((uint32_t)(v >> 2), (uint32_t)a.step, (uint32_t)row, kTagElem, a.key0, a.key1);
-  const uint32_t w = (v & 3) == 0 ? p.w[0] : (v & 3) == 1 ? p.w[1] : (v & 3) == 2 ? p.w[2] : p.w[3];
   const float nlb = neg_log_uniform<float>(wb);
-  const float M = flog((float)n) - flog(nlb);                 // M_q = ln n - ln(-ln u)
-  const float emM = nlb * __builtin_amdgcn_rcpf((float)n);    // exp(-M_q) = (-ln u) / n
-  int32_t vpos = first + (int32_t)((wb >> 3) & 63u);
+  FastDraw d;
+  d.M = flog((float)n) - flog(nlb);
+  d.emM = nlb * __builtin_amdgcn_rcpf((float)n);
+  d.vpos = first + (int32_t)((wb >> 3) & 63u);
   if (n < kDrawBlock) {  // ragged last block: own position draw
     const Philox4 pr = philox4x32_10((uint32_t)q, (uint32_t)a.step, (uint32_t)row, kTagRagged, a.key0, a.key1);
-    vpos = first + (int32_t)(((uint64_t)pr.w[0] * (uint64_t)n) >> 32);
+    d.vpos = first + (int32_t)(((uint64_t)pr.w[0] * (uint64_t)n) >> 32);
   }
-  const float G = v == vpos ? M : -flog(emM + neg_log_uniform<float>(w));
+  return d;
+}
+
+// Offers index v (logit x) with variate G to the lane's state.  An index is offered at most once in a search.
+// `v_named` is what the state calls the index (the index itself, or the index with a flag on top).
+__device__ __forceinline__ void offer_score(const StepArgs& a, int32_t v_named, float x, float G, bool valid, Best& st) {
   const float y = x * a.inv_tau;
   const float sc = y + G;
   const float e = score_margin(a, y);
@@ -597,30 +613,41 @@ __device__ __forceinline__ void score_drawn(const StepArgs& a, int row, int32_t 
   }
 }
 
+// The index's own word of the random stream.  (The four words are formed before one is picked: left to itself the compiler
+// puts the last rounds of each behind a branch.)
+__device__ __forceinline__ uint32_t element_word(const StepArgs& a, int row, int32_t v) {
+  Philox4 p = philox4x32_10((uint32_t)(v >> 2), (uint32_t)a.step, (uint32_t)row, kTagElem, a.key0, a.key1);
+  asm("" : "+v"(p.w[0]), "+v"(p.w[1]), "+v"(p.w[2]), "+v"(p.w[3]));
+  const uint32_t low = (v & 1) ? p.w[1] : p.w[0], high = (v & 1) ? p.w[3] : p.w[2];
+  return (v & 2) ? high : low;
+}
+
+// Scores index v (logit x) in fp32 and offers it to the lane's state, with `d` the draw of its block.
+__device__ __forceinline__ void score_with(const StepArgs& a, int row, int32_t v, int32_t v_named, float x, const FastDraw& d,
+                                           bool valid, Best& st) {
+  float G = -flog(d.emM + neg_log_uniform<float>(element_word(a, row, v)));
+  G = v == d.vpos ? d.M : G;
+  offer_score(a, v_named, x, G, valid, st);
+}
+__device__ __forceinline__ void score_drawn(const StepArgs& a, int row, int32_t v, int32_t v_named, float x, uint32_t wb,
+                                            bool valid, Best& st) {
+  score_with(a, row, v, v_named, x, fast_draw(a, row, v >> 6, wb), valid, st);
+}
+
 __device__ __forceinline__ void score_element(const StepArgs& a, const StepShared& sh, int row, int32_t v, float x,
                                               bool valid, Best& st) {
   score_drawn(a, row, v, v, x, sh.word(v >> 6), valid && x > sh.floor, st);  // masked (-inf) and filtered entries never win
 }
 
-// This lane's element of block q: from LDS if a lane group kept the block, else from the row.
-template <int DT, int W>
-__device__ __forceinline__ float block_elem(const StepArgs& a, const StepShared& sh, const void* rowp, int q) {
-  const int lane = threadIdx.x & (kWave - 1);
-  const int32_t first = q * kDrawBlock;
-  const int32_t n = a.V - first < kDrawBlock ? a.V - first : kDrawBlock;
-  const int slot = slot_of<W>(sh, q);
-  const int idx = lane < n ? lane : n - 1;  // stay inside the row in a ragged last block
-  if (sh.top_q[slot] == q) return elem_at<DT>((const char*)sh.top_raw + (size_t)slot * kDrawBlock * elem_bytes<DT>(), idx);
-  return elem_at<DT>((const char*)rowp + (size_t)first * elem_bytes<DT>(), idx);
-}
-
 // Scores the 64 indices of block q, one per lane.
-template <int DT, int W>
+template <int DT>
 __device__ __forceinline__ void fast_visit(const StepArgs& a, const StepShared& sh, const void* rowp, int row, int q,
                                            Best& st) {
   const int lane = threadIdx.x & (kWave - 1);
-  const int32_t n = a.V - q * kDrawBlock < kDrawBlock ? a.V - q * kDrawBlock : kDrawBlock;
-  score_element(a, sh, row, q * kDrawBlock + lane, block_elem<DT, W>(a, sh, rowp, q), lane < n, st);
+  const int32_t first = q * kDrawBlock;
+  const int32_t n = a.V - first < kDrawBlock ? a.V - first : kDrawBlock;
+  const float x = elem_at<DT>((const char*)rowp + (size_t)first * elem_bytes<DT>(), lane < n ? lane : n - 1);  // stay inside the row
+  score_element(a, sh, row, first + lane, x, lane < n, st);
 }
 
 // For a row with a long survivor list: instead of scoring every index of every surviving
@@ -710,117 +737,264 @@ __device__ __forceinline__ bool exact_among_candidates(const StepArgs& a, const 
   return true;
 }
 
-// Combines the lanes' states into the wave's: highest score, lowest index among equals.
-__device__ __forceinline__ Best wave_best(const Best& st) {
-  const float smax = wave_max(st.s);
+// The lane that holds the highest score, the lowest index among equals, or -1; wave-uniform.  `smax` is that score.
+__device__ __forceinline__ int best_lane(const Best& st, float smax) {
   const bool cand = st.v >= 0 && st.s == smax;
-  const uint32_t vmin = wave_min_u32(cand ? (uint32_t)st.v : 0xffffffffu);
-  if (vmin == 0xffffffffu) return no_best();
-  const bool win = cand && (uint32_t)st.v == vmin;
-  const int src = (int)__builtin_ctzll(__builtin_amdgcn_ballot_w64(win));
+  uint64_t mask = __builtin_amdgcn_ballot_w64(cand);
+  if (mask == 0) return -1;
+  if ((mask & (mask - 1)) != 0) {  // (rare)
+    const uint32_t vmin = wave_min_u32(cand ? (uint32_t)st.v : 0xffffffffu);
+    mask = __builtin_amdgcn_ballot_w64(cand && (uint32_t)st.v == vmin);
+  }
+  return (int)__builtin_ctzll(mask);
+}
+
+// Combines the states of 64 lanes, or of the first 16, into one.
+template <bool Row = false>
+__device__ __forceinline__ Best wave_best(const Best& st) {
+  const float smax = Row ? row_max(st.s) : wave_max(st.s);
+  const int src = best_lane(st, smax);
+  if (src < 0) return no_best();
+  const float other = (int)(threadIdx.x & (kWave - 1)) == src ? st.hi2 : fmaxf(st.hi2, st.s + st.e);
   Best r;
   r.s = smax;
-  r.v = (int32_t)vmin;
+  r.v = __builtin_amdgcn_readlane(st.v, src);
   r.e = uniform_f32(st.e, src);
   r.x = uniform_f32(st.x, src);
-  r.hi2 = wave_max(win ? st.hi2 : fmaxf(st.hi2, st.s + st.e));
+  r.hi2 = Row ? row_max(other) : wave_max(other);
   return r;
 }
 
 __device__ __forceinline__ float key_float(int k) { return __builtin_bit_cast(float, k >= 0 ? k : k ^ 0x7fffffff); }
 
-// The fp32 search over the row.  Every wave first scores `q_own`, the block with the largest
-// bound it has streamed, and `q_own2`, its second (or -1: a workgroup of 16 waves scores one each,
-// one of 8 waves two each: with fewer first blocks the bound is poorer and flat rows keep many more
-// survivors; measured at temperature 1.0, B = 512: 58 us per launch with 8 first blocks, 38 with 16);
-// the best lower end s - e found that way is a score known to be
-// attained, and every other block whose bound reaches it is then scored, one block per wave
-// visit.  `between` runs right after the first barrier.  Returns the wave-uniform result,
-// the same in every wave; all threads of the workgroup must call it.
-template <int DT, int W, typename Between>
-__device__ __forceinline__ Best fast_argmax(const StepArgs& a, const StepShared& sh, const void* rowp, int row, int nslots,
-                                            int q_own, int q_own2, Between between) {
-  constexpr int kStepWaves = W, kStepThreads = W * kWave;
+// A wave's state, to LDS: the lane that holds the best writes it itself.
+template <int W>
+__device__ __forceinline__ void publish_wave(float* fres, const Best& st) {
+  static_assert(W <= 16, "row_max: a lane per wave");
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int src = best_lane(st, wave_max(st.s));
+  const float hi2 = wave_max(lane == src ? st.hi2 : fmaxf(st.hi2, st.s + st.e));
+  float* const to = fres + wave * 8;
+  if (lane == (src < 0 ? 0 : src)) {  // (without a best, lane 0 holds an empty state like every other)
+    *(f32x4*)to = f32x4{st.s, st.e, st.x, hi2};
+    to[4] = __builtin_bit_cast(float, st.v);
+  }
+}
+
+// Every wave's state, merged; the same in every wave.
+template <int W>
+__device__ __forceinline__ Best merge_waves(const float* fres) {
+  const int lane = threadIdx.x & (kWave - 1);
+  Best t = no_best();
+  if (lane < W) {
+    const f32x4 from = *(const f32x4*)(fres + lane * 8);
+    t.s = from[0];
+    t.e = from[1];
+    t.x = from[2];
+    t.hi2 = from[3];
+    t.v = __builtin_bit_cast(int32_t, fres[lane * 8 + 4]);
+  }
+  return wave_best<true>(t);
+}
+
+// The fp32 search over the row, behind two barriers.  Every lane group still has in LDS the 64 logits of `q_top`, the block
+// with the largest bound among those it has streamed, 8 of them at `my_raw` of each lane.  Before the first barrier each
+// lane scores the largest of its 8, and the lane that holds the index that received the block's M_q scores that one,
+// which needs no random word of its own: 8 blocks per wave, one Philox call.  The best lower end s - e found that way
+// is a score known to be attained.  After the barrier a wave looks through its own blocks only: what else of them reaches
+// that score is scored in place, at most kGroups blocks read again from the row; with more than that to read the
+// wave puts them on a list for the whole workgroup, which reduces it to the indices that can still win.  Of 152064 logits
+// at temperature 0.6 a row has 0.7 (16 waves) to 1.2 (8 waves) such blocks on average, none in half of the rows; at
+// temperature 1.0 2.7 and 7.8.  (One block per wave scored whole, two with 8 waves, then the survivors of the row
+// dealt to the waves through a list and a barrier of its own left 4 and, at temperature 1.0, 40 to 46.)
+// Bound by what a wave issues, about 4.4 cycles an instruction, since the last waves to end their streaming have the
+// compute unit to themselves: so a maximum is one instruction a step (espo_device.h), blocks' bounds are read ahead of the
+// barrier, and the lane that holds a wave's best hands it on itself.  us per launch from a graph, before -> now, V = 152064 bf16,
+// all rows live: B = 1: 11.5 -> 10.2, 64: 14.0 -> 12.8 (both with the cheaper combine of step_row), 512: 34.5 -> 33.2,
+// 1024: 59.4 -> 57.5; at temperature 1.0 / 1.3, B = 512: 39.7 -> 36.5 / 65.3 -> 37.6; all logits equal, B = 512: 32.9 -> 32.3.
+// Returns the wave-uniform result, the same in every wave; all threads of the workgroup must call it.
+template <int DT, bool Filter, int W>
+__device__ __forceinline__ Best fast_argmax(const StepArgs& a, const StepShared& sh, const void* rowp, int row, int my_tiles,
+                                            int q_top, float top_ub, const char* my_raw) {
+  constexpr int kStepThreads = W * kWave;
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int grp = lane >> 3;
+  const uint32_t sub = (uint32_t)(lane & 7) * 8u;  // the lane's 8 elements within a block
   Best st = no_best();
-  int q = q_own, k = wave, nsurv = 0;
-  bool first = true, second = q_own2 >= 0;
-#pragma unroll 1
-  while (true) {  // one visit site for the wave's own blocks and for the survivors
-    if (q >= 0) fast_visit<DT, W>(a, sh, rowp, row, q, st);
-    if (first && second) {  // (wave-uniform)
-      second = false;
-      q = q_own2;
-      continue;
-    }
-    if (first) {
-      first = false;
-      const float lo = wave_max(st.s - st.e);
-      if (lane == 0) {
-        sh.lo[wave] = lo;
-        sh.visq[wave] = q_own;
-        sh.visq[kStepWaves + wave] = q_own2;
-      }
-      if (tid == 0) {
-        *sh.nsurv = 0;
-        *sh.ncand = 0;
-      }
-      __syncthreads();
-      between();
-      const float bound = wave_max(lane < kStepWaves ? sh.lo[lane] : kNegInf);
-      for (int b = sh.q0 + tid; b < sh.q0 + nslots; b += kStepThreads) {  // blocks whose bound reaches the best score found so far
-        const float u = sh.ub(b);
-        const int w_b = wave_of<W>(sh, b);
-        if (u > kMaskedBelow && ub_rounded_up(u) >= bound && sh.visq[w_b] != b && sh.visq[kStepWaves + w_b] != b && holds_eligible(sh, b))
-          sh.surv(atomicAdd(sh.nsurv, 1)) = b;
-      }
-      if (tid == 0) *sh.bkey = float_key(bound);
-      __syncthreads();
-      nsurv = *sh.nsurv;
-      if (nsurv > kStepWaves) {  // long list
-        collect_candidates<DT, W>(a, sh, rowp, nsurv, bound);
-        __syncthreads();
-        const int ncand = *sh.ncand;
-        if (ncand <= kCandCap) {  // else (tie-heavy rows): block by block below
-          for (int i = tid; i < ncand; i += kStepThreads) score_element(a, sh, row, sh.cand_v[i], sh.cand_x[i], true, st);
-          k = nsurv;
-        }
-      }
-    } else {
-      if (nsurv > kStepWaves) {  // long list: publish what this wave has attained, later visits may then be skipped
-        const float lo = wave_max(st.s - st.e);
-        if (lane == 0) atomicMax(sh.bkey, float_key(lo));
-      }
-      k += kStepWaves;
-    }
-    q = -1;
-    while (k < nsurv) {  // this wave's next survivor that can still matter
-      const int c = sh.surv(k);
-      if (nsurv <= kStepWaves || ub_rounded_up(sh.ub(c)) >= key_float(*sh.bkey)) { q = c; break; }
-      k += kStepWaves;
-    }
-    if (q < 0) break;
+  Raw<DT> raw = pack_load<DT>((const uint32_t*)my_raw);  // this lane's 8 logits of the group's best block (those at or beyond V are -inf there)
+  FastDraw d = {};
+  uint32_t scored = 0;  // which of the lane's 8 logits need no more looking at
+  if (q_top >= 0) {     // (the same in the lanes of a group)
+    const int32_t v0 = q_top * kDrawBlock + (int32_t)sub;
+    float x[8];
+    unpack<DT>(raw, x);
+    const float top = max8(x);
+    int at = 7;
+#pragma unroll
+    for (int j = 6; j >= 0; --j) at = x[j] == top ? j : at;
+    d = fast_draw(a, row, q_top, sh.word(q_top));
+    const int drawn = d.vpos - v0;
+    const bool mine = (uint32_t)drawn < 8u;
+    const float xd = elem_at<DT>(my_raw, mine ? drawn : 0);
+    // above the floor of a filtered draw few waves hold anything, and the random words are most of the work
+    if (!Filter || __builtin_amdgcn_ballot_w64(top > sh.floor) != 0) score_with(a, row, v0 + at, v0 + at, top, d, top > sh.floor, st);
+    offer_score(a, d.vpos, xd, d.M, mine && drawn != at && xd > sh.floor, st);  // (vpos is below V)
+    scored = 1u << at | (mine ? 1u << drawn : 0u);
   }
-  const Best mine = wave_best(st);
-  if (lane == 0) {
-    sh.fres[0 * kStepWaves + wave] = mine.s;
-    sh.fres[1 * kStepWaves + wave] = mine.e;
-    sh.fres[2 * kStepWaves + wave] = mine.x;
-    sh.fres[3 * kStepWaves + wave] = mine.hi2;
-    sh.fres[4 * kStepWaves + wave] = __builtin_bit_cast(float, mine.v);
+  const float lo = wave_max(st.s - st.e);
+  if (lane == 0) sh.lo[wave] = lo;
+  if (tid == 0) {
+    *sh.nsurv = 0;
+    *sh.ncand = 0;
+  }
+  // this wave's blocks, except the groups' best: block k & 7 of its tile k >> 3
+  const int slots = my_tiles * kGroups;
+  const int q_first = sh.q0 + wave * kGroups;
+  const int skip = __shfl(q_top, (lane & 7) * 8);
+  auto block_at = [&](int k) { return q_first + (k >> 3) * (W * kGroups) + (k & 7); };
+  auto bound_of = [&](int k) {  // of block k, rounded up; -inf for one that cannot win or is none of these
+    if (k >= slots) return kNegInf;
+    const int b = block_at(k);
+    const float u = sh.ub(b);
+    return u > kMaskedBelow && b != skip && holds_eligible(sh, b) ? ub_rounded_up(u) : kNegInf;
+  };
+  constexpr int kAhead = W == 16 ? 3 : 5;  // read before the barrier: all blocks of a wave for V up to 196608 (16 waves) or 163840
+  float ahead[kAhead];
+#pragma unroll
+  for (int i = 0; i < kAhead; ++i) {
+    ahead[i] = kNegInf;
+    if (i * kWave < slots) ahead[i] = bound_of(i * kWave + lane);  // (wave-uniform)
   }
   __syncthreads();
-  Best t = no_best();
-  if (lane < kStepWaves) {
-    t.s = sh.fres[0 * kStepWaves + lane];
-    t.e = sh.fres[1 * kStepWaves + lane];
-    t.x = sh.fres[2 * kStepWaves + lane];
-    t.hi2 = sh.fres[3 * kStepWaves + lane];
-    t.v = __builtin_bit_cast(int32_t, sh.fres[4 * kStepWaves + lane]);
+  // (a row without a candidate so far has no bound: every block with a logit that counts is then looked at)
+  const float bound = fmaxf(row_max(lane < W ? sh.lo[lane] : kNegInf), -3.0e38f);
+  int nown = 0;  // blocks whose bound reaches the best score found so far
+  auto look = [&](auto&& use) {
+    auto one = [&](int k0, float u) {
+      const bool in = u >= bound;
+      const uint64_t mask = __builtin_amdgcn_ballot_w64(in);
+      if (mask != 0) use(k0 + lane, in, mask);
+    };
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) one(i * kWave, ahead[i]);
+#pragma unroll 1
+    for (int k0 = kAhead * kWave; k0 < slots; k0 += kWave) one(k0, bound_of(k0 + lane));  // (wave-uniform)
+  };
+  look([&](int k, bool in, uint64_t mask) {
+    const int at = nown + rank_below(mask);
+    if (in && at < kGroups) sh.own[wave * kGroups + at] = block_at(k);
+    nown += (int)__builtin_popcountll(mask);
+  });
+  if (nown > kGroups) {  // too many to read again one after the other: to the workgroup's list
+    look([&](int k, bool in, uint64_t mask) {
+      int base = 0;
+      if (lane == 0) base = atomicAdd(sh.nsurv, (int)__builtin_popcountll(mask));
+      base = __builtin_amdgcn_readfirstlane(base);
+      if (in) sh.surv(base + rank_below(mask)) = block_at(k);
+    });
+    nown = 0;
   }
-  return wave_best(t);
+  // the groups' best blocks once more, then the wave's list, a block per lane group
+  int q = q_top >= 0 && ub_rounded_up(top_ub) >= bound ? q_top : -1;
+#pragma unroll 1
+  for (int pass = 0; pass < 2; ++pass) {
+    if (pass == 1) {
+      if (nown == 0) break;
+      asm volatile("" ::: "memory");  // the list was written by this wave's other lanes (LDS keeps a wave's order)
+      q = grp < nown ? sh.own[wave * kGroups + grp] : -1;
+      const uint32_t last_group = (uint32_t)(a.V - 1) & ~7u;
+      const uint32_t e0 = (uint32_t)(q < 0 ? 0 : q) * kDrawBlock + sub;  // a group without a block reads block 0 and drops it
+      raw = load_raw<DT>(rowp, e0 < last_group ? e0 : last_group, (uint32_t)a.V);
+      if (q >= 0) d = fast_draw(a, row, q, sh.word(q));
+      scored = 0;
+    }
+    if (__builtin_amdgcn_ballot_w64(q >= 0) == 0) continue;
+    const int32_t v0 = q * kDrawBlock + (int32_t)sub;
+    float x[8];
+    unpack<DT>(raw, x);
+    uint32_t todo = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const float y = x[j] * a.inv_tau;
+      todo |= x[j] > sh.floor && (y + d.M) + 2.0f * score_margin(a, y) >= bound ? 1u << j : 0u;
+    }
+    todo &= ~scored & (q < 0 ? 0u : a.V - v0 >= 8 ? 0xffu : a.V > v0 ? (1u << (a.V - v0)) - 1u : 0u);
+    while (__builtin_amdgcn_ballot_w64(todo != 0) != 0) {
+      const uint64_t many = __builtin_amdgcn_ballot_w64((todo & (todo - 1)) != 0);
+      int32_t v;
+      float xv;
+      bool valid;
+      FastDraw dv = d;
+      if (many == 0) {  // one for each lane at most (the usual case): all at once
+        const int j = __builtin_ctz(todo | 0x100u) & 7;
+        xv = x[0];
+#pragma unroll
+        for (int i = 1; i < 8; ++i) xv = i == j ? x[i] : xv;
+        v = v0 + j;
+        valid = todo != 0;
+        todo = 0;
+      } else {  // several (equal logits, flat rows): one group's block, an index per lane
+        const int from = (int)__builtin_ctzll(many) & ~7;
+        valid = (__shfl(todo, from + grp) >> (lane & 7) & 1) != 0;
+        v = __builtin_amdgcn_readlane(v0, from) + lane;
+        if (pass == 0)
+          xv = elem_at<DT>(my_raw + ((from - (lane & ~7)) * 8 - (int)sub) * elem_bytes<DT>(), lane);
+        else
+          xv = elem_at<DT>(rowp, v < a.V ? v : a.V - 1);
+        dv.M = uniform_f32(d.M, from);
+        dv.emM = uniform_f32(d.emM, from);
+        dv.vpos = __builtin_amdgcn_readlane(d.vpos, from);
+        todo = grp == from >> 3 ? 0u : todo;
+      }
+      score_with(a, row, v, v, xv, dv, valid, st);
+    }
+  }
+  publish_wave<W>(sh.fres, st);
+  __syncthreads();
+  const int nsurv = *sh.nsurv;
+  if (nsurv > 0) {  // blocks that some wave left to all
+    const float reached = row_max(lane < W ? sh.fres[lane * 8] - sh.fres[lane * 8 + 1] : kNegInf);
+    if (tid == 0) *sh.bkey = float_key(reached);
+    collect_candidates<DT, W>(a, sh, rowp, nsurv, reached);
+    __syncthreads();
+    const int ncand = *sh.ncand;
+    if (ncand <= kCandCap) {
+      for (int i = tid; i < ncand; i += kStepThreads) score_element(a, sh, row, sh.cand_v[i], sh.cand_x[i], true, st);
+    } else {  // tie-heavy rows: block by block, skipping what the waves' best scores rule out
+#pragma unroll 1
+      for (int k = wave; k < nsurv; k += W) {
+        const int c = sh.surv(k);
+        if (ub_rounded_up(sh.ub(c)) < key_float(*sh.bkey)) continue;
+        fast_visit<DT>(a, sh, rowp, row, c, st);
+        const float low = wave_max(st.s - st.e);
+        if (lane == 0) atomicMax(sh.bkey, float_key(low));
+      }
+    }
+    publish_wave<W>(sh.fres, st);
+    __syncthreads();
+  }
+  return merge_waves<W>(sh.fres);
+}
+
+// Softmax sums over parts of a row, one part per lane (its largest logit, and its sums relative to that), moved to the
+// largest of all; wave-uniform.
+struct RowSums {
+  float m, S, Sw;
+};
+
+template <bool Entropy, bool Row>
+__device__ __forceinline__ RowSums merge_sums(const StepArgs& a, float m_c, float S_c, float Sw_c) {
+  RowSums r;
+  r.m = Row ? row_max(m_c) : wave_max(m_c);
+  const float shift = (m_c - r.m) * a.k2;
+  const float f = __builtin_amdgcn_exp2f(shift);
+  r.S = wave_sum(S_c > 0.0f ? S_c * f : 0.0f);
+  r.Sw = 0.0f;
+  if constexpr (Entropy) r.Sw = wave_sum(S_c > 0.0f ? f * fmaf(shift, S_c, Sw_c) : 0.0f);
+  return r;
 }
 
 // ---------------------------------------------------------------- the kernel
@@ -842,11 +1016,10 @@ __device__ __forceinline__ void step_row(const StepArgs& a, unsigned char* smem_
   static_assert(Sum || (!Entropy && !Filter), "entropy and filtered draws need the softmax sum");
   constexpr int kStepWaves = W, kStepThreads = W * kWave, kSlots = W * kGroups;
   const int tid = threadIdx.x;
-  // workgroup row * nch + c owns chunk c of the row: tiles [tile0, tile1)
-  const unsigned unit = blockIdx.x;
+  // workgroup (row, chunk) owns tiles [tile0, tile1) of the row
   const int nch = Filter ? 1 : a.nch;
-  const int row = nch == 1 ? (int)unit : (int)(unit / (unsigned)nch);
-  const int chunk = (int)unit - row * nch;
+  const int row = (int)blockIdx.x;
+  const int chunk = Filter ? 0 : (int)blockIdx.y;
   if (row_is_done(a.alive, row)) {  // done rows are not decoded (Algorithm 1, loop condition)
     if (tid == 0 && chunk == 0) {
       a.tokens[row] = -1;
@@ -860,9 +1033,9 @@ __device__ __forceinline__ void step_row(const StepArgs& a, unsigned char* smem_
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int grp = lane >> 3;
   const int ntiles = a.ntiles;  // of the row
-  const int tile0 = nch == 1 ? 0 : (int)(((int64_t)chunk * ntiles) / nch);
-  const int tile1 = nch == 1 ? ntiles : (int)(((int64_t)(chunk + 1) * ntiles) / nch);
-  const int ctiles = tile1 - tile0;
+  const int tile0 = Filter ? 0 : chunk * a.chunk_tiles + min(chunk, a.chunk_extra);
+  const int ctiles = Filter ? ntiles : a.chunk_tiles + (chunk < a.chunk_extra ? 1 : 0);
+  const int tile1 = tile0 + ctiles;
   const int nslots = ctiles * kGroups;  // block slots of the chunk incl. the non-existent ones of the row's last tile
   const StepShared sh = carve<DT, Filter, W>(smem_raw, nslots, tile0 * kGroups);
   const void* rowp = (const char*)a.logits + (size_t)row * (size_t)a.row_stride * elem_bytes<DT>();
@@ -942,8 +1115,16 @@ __device__ __forceinline__ void step_row(const StepArgs& a, unsigned char* smem_
 #pragma unroll
       for (int j = 0; j < 8; ++j)
         if (e0 + j >= a.V) x[j] = kNegInf;
+      if constexpr (DT == ESPO_BF16) {  // and in what is kept of the tile
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          ring[d].w[j] = (__builtin_bit_cast(uint32_t, x[2 * j]) >> 16) | (__builtin_bit_cast(uint32_t, x[2 * j + 1]) & 0xFFFF0000u);
+      } else {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) ring[d].w[j] = __builtin_bit_cast(uint32_t, x[j]);
+      }
     }
-    const float gm = fmaxf(fmaxf(fmaxf(fmaxf(fmaxf(x[0], x[1]), x[2]), fmaxf(fmaxf(x[3], x[4]), x[5])), x[6]), x[7]);
+    const float gm = max8(x);
     if constexpr (Sum) {
       if (__builtin_amdgcn_ballot_w64(gm > lead) != 0) {  // rare after the first tile
         asm volatile("" ::: "memory");  // keep this rare path out of the straight-line code
@@ -1018,50 +1199,37 @@ __device__ __forceinline__ void step_row(const StepArgs& a, unsigned char* smem_
     for (int d = 0; d < kRing; ++d)
       if (i0 + d < my_tiles) iteration(std::false_type{}, d, i0 + d);  // wave-uniform
   }
-  // The wave's largest logit, and the block with its largest bound (lowest block among equals).
+  // The wave's largest logit and its share of the softmax sums relative to that.  All of it, like the first scores of the
+  // search, comes before the barrier: the waves of a workgroup end their streaming microseconds apart.
   const float mw = wave_max(mx);
-  const float ubw = wave_max(top_ub);
-  const int q_own = (int)wave_min_u32(top_q >= 0 && top_ub == ubw ? (uint32_t)top_q : 0xffffffffu);  // -1 if none
-  int q_own2 = -1;  // with fewer than 16 waves, also the best block of the wave's other lane groups
-  if constexpr (W < 16) {
-    const bool other = top_q >= 0 && top_q != q_own;
-    const float ubw2 = wave_max(other ? top_ub : kNegInf);
-    q_own2 = (int)wave_min_u32(other && top_ub == ubw2 ? (uint32_t)top_q : 0xffffffffu);
-  }
   if (lane == 0) sh.m[wave] = mw;
-  if ((lane & 7) == 0) sh.top_q[wave * kGroups + grp] = top_q;
-  float z_prev = 0.0f, value = 0.0f;  // wanted at the very end: fetched now, off the critical path
-  unsigned long long ticket = 0;
-  if (tid == 0) {
-    if (nch == 1) {
-      z_prev = a.z[row];
-      value = a.values[row];
-    } else {
-      ticket = __hip_atomic_load(a.tickets + row, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // what the ticket is most likely taken from
-    }
-  }
-
-  // ------------------------------------------------------------ phase 2: argmax of y + G
-  float m = kNegInf;
-  auto softmax_sum = [&]() {  // after the first barrier: row maximum, then the wave's share of the sum
-    m = wave_max(lane < kStepWaves ? sh.m[lane] : kNegInf);
-    if constexpr (!Sum) return;
-    const float shift = -fmaf(m, a.k2, nrk);  // from this lane's reference to the row maximum
+  if constexpr (Sum) {
+    const float shift = -fmaf(mw, a.k2, nrk);  // from this lane's reference to the wave's maximum
     const float f = __builtin_amdgcn_exp2f(shift);
-    const float part = sum > 0.0f ? sum * f : 0.0f;
-    const float tot = wave_sum(part);
+    const float tot = wave_sum(sum > 0.0f ? sum * f : 0.0f);
     if (lane == 0) sh.sum[wave] = tot;
     if constexpr (Entropy) {
       const float totw = wave_sum(sum > 0.0f ? f * fmaf(shift, sum, sumw) : 0.0f);
       if (lane == 0) sh.sumw[wave] = totw;
     }
+  }
+  float z_prev = 0.0f, value = 0.0f;  // wanted at the very end: fetched now, off the critical path
+  if (tid == 0) {
+    z_prev = a.z[row];
+    value = a.values[row];
+  }
+
+  // ------------------------------------------------------------ phase 2: argmax of y + G
+  auto row_sums = [&]() {  // after a barrier: the waves' shares put together (in a fixed order, the same in every wave)
+    return merge_sums<Entropy, true>(a, lane < kStepWaves ? sh.m[lane] : kNegInf, Sum && lane < kStepWaves ? sh.sum[lane] : 0.0f,
+                               Entropy && lane < kStepWaves ? sh.sumw[lane] : 0.0f);
   };
   int32_t tok;
   float x_a;
   float s_a = kNegInf, e_a = 0.0f;  // the winner's score as a float known to within +-e_a (what the combine of a split row compares)
   // the argmax over the indices whose logit is above shx.floor: fp32 search, decided in double where needed
-  auto search = [&](const StepShared& shx, auto between) {
-    const Best fast = fast_argmax<DT, W>(a, shx, rowp, row, nslots, q_own, q_own2, between);
+  auto search = [&](const StepShared& shx) {
+    const Best fast = fast_argmax<DT, Filter, W>(a, shx, rowp, row, my_tiles, top_q, top_ub, my_raw);
     tok = fast.v;
     x_a = fast.x;
     s_a = fast.s;
@@ -1072,7 +1240,7 @@ __device__ __forceinline__ void step_row(const StepArgs& a, unsigned char* smem_
       Search<double> exact;
       if (!exact_among_candidates<DT, W>(a, shx, rowp, row, nslots, fast.s - fast.e, exact)) {
         __syncthreads();
-        exact = find_argmax<DT, double, W>(a, shx, rowp, row, nslots, q_own, (double)fast.s - (double)fast.e, [] {});
+        exact = find_argmax<DT, double, W>(a, shx, rowp, row, nslots, -1, (double)fast.s - (double)fast.e);
       }
       tok = exact.best.v;
       x_a = exact.best.x;
@@ -1080,12 +1248,12 @@ __device__ __forceinline__ void step_row(const StepArgs& a, unsigned char* smem_
       e_a = fmaf(fabsf(s_a), 1.2e-7f, 1e-30f);
     }
   };
+  RowSums sums;
   if constexpr (!Filter) {
-    search(sh, softmax_sum);
+    search(sh);
   } else {
-    __syncthreads();  // the waves' maxima are in place
-    softmax_sum();    // m, and the waves' shares of S
-    __syncthreads();
+    __syncthreads();  // the waves' maxima and sums are in place
+    sums = row_sums();
     tok = -1;         // a row without a finite logit keeps this
     x_a = 0.0f;
   }
@@ -1100,9 +1268,8 @@ __device__ __forceinline__ void step_row(const StepArgs& a, unsigned char* smem_
     // names the blocks that hold any; up to two thirds of the row's blocks are read again block by block, more of
     // them by one more pass over the row.  Sums within 1e-5 of p times the softmax sum are formed again in double
     // over the whole row, in the oracle's arithmetic.
-    const auto nothing = [] {};
     const bool by_count = a.top_k > 0;
-    const float total = wave_sum(lane < kStepWaves ? sh.sum[lane] : 0.0f);  // S, as the last step forms it
+    const float m = sums.m, total = sums.S;
     const float want = a.top_p * total;
     float mass = 0.0f, count = 0.0f;
 
@@ -1177,7 +1344,7 @@ __device__ __forceinline__ void step_row(const StepArgs& a, unsigned char* smem_
       above.floor = m == 0.0f ? -1.401298464e-45f : __builtin_bit_cast(float, bits + (m > 0.0f ? -1 : 1));
     }
     while (m > kNegInf) {  // (a row without a finite logit has no winner)
-      search(above, nothing);
+      search(above);
       if (tok < 0 || a.top_k == 1) break;
       measure(x_a);
       bool kept;
@@ -1227,59 +1394,44 @@ __device__ __forceinline__ void step_row(const StepArgs& a, unsigned char* smem_
 
   // ------------------------------------------------------------ finalize: one lane
   if (wave != 0) return;
-  float S = wave_sum(lane < kStepWaves ? sh.sum[lane] : 0.0f);  // sum_v exp((x_v - m)/tau) over the chunk, fixed order
-  float Sw = 0.0f;
-  if constexpr (Entropy) Sw = wave_sum(lane < kStepWaves ? sh.sumw[lane] : 0.0f);
+  if constexpr (!Filter) sums = row_sums();
+  float m = sums.m, S = sums.S, Sw = sums.Sw;  // over the chunk
   if constexpr (!Filter) {
     if (nch > 1) {
-      // A row split over nch workgroups: each leaves its chunk's result in the workspace and takes a
-      // ticket; the one that takes the row's last ticket finishes the row.  Results, tickets and the
-      // reads of the results all go through device-scope atomic accesses, which bypass the caches that
-      // are private to a part of the chip, and a workgroup takes its ticket only once its stores have
-      // been acknowledged, so whoever sees the last ticket also sees every result.  (A device-scope
+      // A row split over nch workgroups: each leaves its chunk's result in the workspace and then looks at what all of them
+      // have left; the one that finds every result there finishes the row.  The last to write does find them all: its
+      // own have been acknowledged before it looks, and so have the others'.  Two may: they come to the same outputs, from a z that both
+      // have read before either could write it.  Nobody waits for another workgroup.  Words are written and read with
+      // device-scope atomic accesses, which bypass the caches that are private to a part of the chip.  (A device-scope
       // fence would do too, but writes back and invalidates a whole L2 per workgroup: measured, 50 ns
-      // of serialised work per workgroup, 100 us per launch.)  A ticket is a mark and a count: a word
-      // without the mark counts as no arrival, so the workspace may hold anything before the launch, and the
-      // last to arrive clears it, so that a replay of the same launch starts over.
-      uint32_t arrived = 0;
-      if (lane == 0) {
-        uint32_t* const dst = (uint32_t*)(a.partials + (size_t)unit);
-        const uint32_t w[7] = {__builtin_bit_cast(uint32_t, m),   __builtin_bit_cast(uint32_t, S),   __builtin_bit_cast(uint32_t, Sw),
-                               __builtin_bit_cast(uint32_t, s_a), __builtin_bit_cast(uint32_t, e_a), __builtin_bit_cast(uint32_t, x_a),
-                               (uint32_t)tok};
-#pragma unroll
-        for (int j = 0; j < 7; ++j) __hip_atomic_store(dst + j, w[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the stores are done before the ticket is taken
-        while (true) {  // (a failed exchange means that another chunk of the row has arrived: at most nch rounds)
-          const unsigned long long next = (ticket & ~0xffffffffull) == kTicketMark ? ticket + 1 : kTicketMark + 1;
-          const unsigned long long was = atomicCAS(a.tickets + row, ticket, next);
-          if (was == ticket) {
-            arrived = (uint32_t)next;
-            break;
-          }
-          ticket = was;
-        }
-        if (arrived == (uint32_t)nch) __hip_atomic_store(a.tickets + row, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-      arrived = (uint32_t)__builtin_amdgcn_readfirstlane((int)arrived);
-      if (arrived != (uint32_t)nch) return;
-      if (lane == 0) {
-        z_prev = a.z[row];
-        value = a.values[row];
+      // of serialised work per workgroup, 100 us per launch.  A ticket taken by compare-and-swap after the results
+      // is one more trip through memory, and one more again where two chunks take it at a time: 7200 cycles from the search
+      // to the outputs of B = 64, V = 152064 bf16, against 5000 now; B = 4, V = 150001 fp32 with the entropy, 8 chunks: 13.8 -> 11.3 us,
+      // the shorter search included.)  A word without the mark is not there, so the workspace may hold anything before the launch; who
+      // finishes a row leaves its words zero, so that nothing of this launch can pass for a result in a later one.
+      const size_t unit = (size_t)row * nch + chunk;
+      {
+        const uint32_t w = lane == 0 ? __builtin_bit_cast(uint32_t, m) : lane == 1 ? __builtin_bit_cast(uint32_t, S)
+                           : lane == 2 ? __builtin_bit_cast(uint32_t, Sw) : lane == 3 ? __builtin_bit_cast(uint32_t, s_a)
+                           : lane == 4 ? __builtin_bit_cast(uint32_t, e_a) : lane == 5 ? __builtin_bit_cast(uint32_t, x_a) : (uint32_t)tok;
+        unsigned long long* const dst = lane < 4 ? a.mail_lo + unit * 4 + lane : a.mail_hi + unit * 4 + (lane - 4);
+        if (lane < kMailWords) __hip_atomic_store(dst, (unsigned long long)kMailMark << 32 | w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // acknowledged before the others' words are read
       }
       // lane c holds chunk c (nch <= 64); the other lanes hold a chunk without any finite logit
       float m_c = kNegInf, S_c = 0.0f, Sw_c = 0.0f;
       Best win = no_best();
+      bool there = true;
       if (lane < nch) {
-        const uint32_t* src = (const uint32_t*)(a.partials + (size_t)row * nch + lane);
-        uint32_t w[7];
+        unsigned long long* const lo = a.mail_lo + ((size_t)row * nch + lane) * 4;
+        unsigned long long* const hi = a.mail_hi + ((size_t)row * nch + lane) * 4;
+        uint32_t w[kMailWords];
 #pragma unroll
-        for (int j = 0; j < 7; ++j) w[j] = __hip_atomic_load(src + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        // hand the workspace back all zero, like the tickets: nothing of this launch can pass for a ticket of a later
-        // call of another shape
-        u32x4* const back = (u32x4*)(a.partials + (size_t)row * nch + lane);
-        back[0] = u32x4{0u, 0u, 0u, 0u};
-        back[1] = u32x4{0u, 0u, 0u, 0u};
+        for (int j = 0; j < kMailWords; ++j) {
+          const unsigned long long word = __hip_atomic_load(j < 4 ? lo + j : hi + (j - 4), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          w[j] = (uint32_t)word;
+          there = there && (uint32_t)(word >> 32) == kMailMark;
+        }
         m_c = __builtin_bit_cast(float, w[0]);
         S_c = __builtin_bit_cast(float, w[1]);
         Sw_c = __builtin_bit_cast(float, w[2]);
@@ -1289,12 +1441,17 @@ __device__ __forceinline__ void step_row(const StepArgs& a, unsigned char* smem_
         win.v = (int32_t)w[6];
         if (win.v < 0) win = no_best();
       }
-      m = wave_max(m_c);
-      // the chunks' sums are relative to their own maxima: moved to the row maximum like a lane's in phase 1
-      const float shift = (m_c - m) * a.k2;
-      const float f = __builtin_amdgcn_exp2f(shift);
-      S = wave_sum(S_c > 0.0f ? S_c * f : 0.0f);
-      if constexpr (Entropy) Sw = wave_sum(S_c > 0.0f ? f * fmaf(shift, S_c, Sw_c) : 0.0f);
+      if (__builtin_amdgcn_ballot_w64(!there) != 0) return;
+      if (lane < nch) {
+        u32x4* const lo = (u32x4*)(a.mail_lo + ((size_t)row * nch + lane) * 4);
+        u32x4* const hi = (u32x4*)(a.mail_hi + ((size_t)row * nch + lane) * 4);
+        lo[0] = lo[1] = hi[0] = hi[1] = u32x4{0u, 0u, 0u, 0u};
+        if (lane == 0) a.row_words[row] = 0;
+      }
+      sums = merge_sums<Entropy, false>(a, m_c, S_c, Sw_c);  // the chunks' sums are relative to their own maxima
+      m = sums.m;
+      S = sums.S;
+      Sw = sums.Sw;
       // every chunk's winner is its exact argmax, so the row's is the best of them: decided in fp32
       // where the margins allow, else by scoring those few indices in double
       const Best top = wave_best(win);
@@ -1317,9 +1474,9 @@ __device__ __forceinline__ void step_row(const StepArgs& a, unsigned char* smem_
 }
 
 template <int DT, bool Entropy, bool Sum, int W>
-// Registers: 64 per lane for 16 waves (two workgroups on a compute unit); workgroups of 8 waves get up
-// to 80 (three of them fit, in registers and in LDS) and use 75 without spilling.
-__global__ __launch_bounds__(W * kWave, W == 8 ? 6 : 8) void espo_step_kernel(StepArgs a) {
+// Registers: workgroups of 8 waves get up to 80 (three of them fit on a compute unit, in registers and in LDS) and use 77
+// without spilling; one of 16 waves, which has a compute unit to itself (plan_step), up to 128.
+__global__ __launch_bounds__(W * kWave, W == 8 ? 6 : W == 16 ? 4 : 8) void espo_step_kernel(StepArgs a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   step_row<DT, Entropy, false, Sum, W>(a, smem_raw);
 }
@@ -1370,7 +1527,7 @@ struct FilterShared {
   uint32_t* mem_w;
   uint16_t* mem_at;
   float *m, *thr, *low, *least, *sum, *sumw;  // [W]
-  float* fres;       // [5][W]
+  float* fres;       // [W][8]
   double *res_s, *res_hi2;
   float* res_e;
   int* res_v;
@@ -1382,7 +1539,7 @@ template <int DT, int W>
 __host__ __device__ constexpr size_t filter_lds_bytes() {
   constexpr size_t packs = (size_t)W * CollectLimits<DT, W>::kRoom;
   return packs * (DT == ESPO_BF16 ? 16 : 32) + packs * 2 + kKeptCap2 * 2 + kEdgeBins * 4 + kEdgeMembers * 10 +
-         W * (6 + 5 + 3) * 4 + W * 16 + 16;
+         W * (6 + 8 + 3) * 4 + W * 16 + 16;
 }
 
 template <int DT, int W>
@@ -1403,7 +1560,7 @@ __device__ __forceinline__ FilterShared<DT, W> carve_filter(unsigned char* base)
   f.least = (float*)take(W * 4);
   f.sum = (float*)take(W * 4);
   f.sumw = (float*)take(W * 4);
-  f.fres = (float*)take(5 * W * 4);
+  f.fres = (float*)take(8 * W * 4);
   f.res_e = (float*)take(W * 4);
   f.res_v = (int*)take(W * 4);
   f.res_x = (float*)take(W * 4);
@@ -1416,23 +1573,6 @@ __device__ __forceinline__ FilterShared<DT, W> carve_filter(unsigned char* base)
   return f;
 }
 
-template <int DT>
-__device__ __forceinline__ Raw<DT> pack_load(const uint32_t* raw) {
-  Raw<DT> r;
-#pragma unroll
-  for (int h = 0; h < Raw<DT>::kWords / 4; ++h) {
-    const u32x4 t = ((const u32x4*)raw)[h];
-    r.w[4 * h] = t.x; r.w[4 * h + 1] = t.y; r.w[4 * h + 2] = t.z; r.w[4 * h + 3] = t.w;
-  }
-  return r;
-}
-template <int DT>
-__device__ __forceinline__ void pack_store(uint32_t* raw, const Raw<DT>& r) {
-#pragma unroll
-  for (int h = 0; h < Raw<DT>::kWords / 4; ++h)
-    ((u32x4*)raw)[h] = u32x4{r.w[4 * h], r.w[4 * h + 1], r.w[4 * h + 2], r.w[4 * h + 3]};
-}
-
 // The lane's logits; those at or beyond V, which a ragged row's last pack holds, become -inf.
 template <int DT>
 __device__ __forceinline__ void pack_unpack(const Raw<DT>& r, int32_t v0, int32_t V, float x[8]) {
@@ -1442,15 +1582,6 @@ __device__ __forceinline__ void pack_unpack(const Raw<DT>& r, int32_t v0, int32_
     for (int j = 0; j < 8; ++j)
       if (v0 + j >= V) x[j] = kNegInf;
   }
-}
-
-__device__ __forceinline__ float max8(const float x[8]) {
-  return fmaxf(fmaxf(fmaxf(fmaxf(fmaxf(x[0], x[1]), x[2]), fmaxf(fmaxf(x[3], x[4]), x[5])), x[6]), x[7]);
-}
-
-// Lanes below this one whose bit is set in `mask`.
-__device__ __forceinline__ int rank_below(uint64_t mask) {
-  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
 // Raises a wave's threshold to a value that at most kKeep of the list's packs reach beyond and drops the
@@ -1705,24 +1836,9 @@ __device__ __forceinline__ DrawResult draw_from_list(const StepArgs& a, const Fi
     score_drawn(a, row, v, member && !sure_member ? v | kInDoubt : v, list.logit(at), word_of(v), true, st);
     if (member) break;
   }
-  const Best mine = wave_best(st);
-  if (lane == 0) {
-    f.fres[0 * W + wave] = mine.s;
-    f.fres[1 * W + wave] = mine.e;
-    f.fres[2 * W + wave] = mine.x;
-    f.fres[3 * W + wave] = mine.hi2;
-    f.fres[4 * W + wave] = __builtin_bit_cast(float, mine.v);
-  }
+  publish_wave<W>(f.fres, st);
   __syncthreads();
-  Best all = no_best();
-  if (lane < W) {
-    all.s = f.fres[0 * W + lane];
-    all.e = f.fres[1 * W + lane];
-    all.x = f.fres[2 * W + lane];
-    all.hi2 = f.fres[3 * W + lane];
-    all.v = __builtin_bit_cast(int32_t, f.fres[4 * W + lane]);
-  }
-  all = wave_best(all);
+  const Best all = merge_waves<W>(f.fres);
   tok = all.v;
   x_a = all.x;
   if (!(all.s - all.e > all.hi2)) {
@@ -2094,17 +2210,19 @@ int launch_math_errors(float* out, hipStream_t stream) {
 // tiles, each streamed by a workgroup of its own and combined by the last one to arrive.  Where all compute
 // units have rows enough, no split pays (B = 512, V = 152064 bf16, all rows live): 34.7 us unsplit, 41 us in 2 chunks
 // of 16 waves, 39.6 us in 2 chunks of 8 waves, 53 us in 8 chunks of 4 waves: every chunk pays for a search of its
-// own and the row for one more round trip through memory (ticket, then the partial results), which is
+// own and the row for two more trips through memory (a chunk's result written, then all of them read), which is
 // more than the finer grain gains.  (Also measured and left out:
 // 512 resident workgroups that claim rows from a counter in the workspace instead of one workgroup
 // per row, meant to make rows that are done cost a claim instead of a workgroup: 512 device-scope
 // atomics on one address take 50 ns each, and a launch of B = 1024 live rows went from 56 to 82 us.)
 
-// tickets first (256-byte aligned size), then the chunk results
-size_t step_workspace_layout(int64_t B, int chunks, size_t* partials_offset) {
-  const size_t tickets = (((size_t)B * sizeof(unsigned long long)) + 255) & ~(size_t)255;
-  if (partials_offset) *partials_offset = tickets;
-  return tickets + (size_t)B * (size_t)chunks * sizeof(ChunkResult);
+// 8 bytes per row first (256-byte aligned size), then words 4 to 6 of the chunk results, then words 0 to 3
+size_t step_workspace_layout(int64_t B, int chunks, size_t* hi_offset, size_t* lo_offset) {
+  const size_t head = (((size_t)B * sizeof(unsigned long long)) + 255) & ~(size_t)255;
+  const size_t half = (size_t)B * (size_t)chunks * 4 * sizeof(unsigned long long);
+  if (hi_offset) *hi_offset = head;
+  if (lo_offset) *lo_offset = head + half;
+  return head + 2 * half;
 }
 
 constexpr int64_t kEightWavesFrom = 256;
@@ -2112,7 +2230,7 @@ constexpr int64_t kEightWavesFrom = 256;
 // How the library itself splits the rows of a plain draw, given a workspace: chunks per row and waves per chunk.
 // A compute unit takes 4.9 to 8.3 us to stream a bf16 row of 152064 logits (its vector units are the limit: some 45
 // operations per tile and wave, 8 of them exponentials) while, below 256 rows, others have none, or, just above,
-// have one row where some have two.  A split costs two more trips through memory (results and ticket, then the
+// have one row where some have two.  A split costs two more trips through memory (results written, then the
 // other chunks' results), 2 to 3 us, so it pays for long rows only; how long follows from how much a row's workgroup is held up by
 // others that stream beside it, and for fp32 rows, whose sums hide behind the loads, from more rows on.  us per launch, one workgroup
 // per row -> split, with log-probabilities / without (all rows live, synthetic language-model rows, temperature 0.6):
@@ -2133,6 +2251,7 @@ constexpr int64_t kEightWavesFrom = 256;
 //   401 to 512 rows: V = 140000, B = 480: 54.9 -> 57.2 in 2 chunks, 59.0 in 3; 512: 56.1 -> 59.1, 63.8: not split.
 //   513 to 640 rows of f32 from 512 KB on (more rows than two a compute unit), 2 chunks: V = 131500: B = 513: 66.5 -> 61.0,
 //     570: 76.0 -> 68.4; V = 150001, B = 640: 88.4 -> 81.7.  bf16 V = 150001, B = 320: 30.3 -> 29.8, 512: 34.9 -> 40.8: not split.
+// (The lines were drawn when the combine took a third trip; a split now gains 1 to 2 us more on either side of them.)
 // A chunk of bf16 is streamed by 16 waves, one of f32 by 8, which was the faster of the two at every one of these sizes.
 struct RowSplit {
   int chunks, waves;
@@ -2168,7 +2287,6 @@ StepPlan plan_step(int dt, int64_t B, int64_t V, bool filter, int waves, int chu
   if (nch > ntiles) nch = ntiles;
   if (nch > kMaxChunks) nch = kMaxChunks;
   p.chunks = nch;
-  p.grid = B * nch;
   const int ctiles = (ntiles + nch - 1) / nch;
   auto lds = [&](int w) {
     const size_t tables = step_lds_bytes(dt, ctiles, filter, w);
@@ -2179,7 +2297,7 @@ StepPlan plan_step(int dt, int64_t B, int64_t V, bool filter, int waves, int chu
   };
   p.lds = lds(p.waves);
   if (filter && waves <= 0 && p.lds > kMaxStepLds) p.lds = lds(p.waves = 8);  // the widest vocabularies: 8 waves need less
-  p.workspace = nch > 1 ? step_workspace_layout(B, nch, nullptr) : 0;
+  p.workspace = nch > 1 ? step_workspace_layout(B, nch, nullptr, nullptr) : 0;
   return p;
 }
 
@@ -2223,13 +2341,15 @@ int launch_step(const void* logits, int dt, int64_t B, int64_t V, int64_t row_st
   a.logprob = logprob;
   a.entropy = entropy;
   a.nch = plan.chunks;
-  a.partials = nullptr;
-  a.tickets = nullptr;
+  a.chunk_tiles = a.ntiles / plan.chunks;
+  a.chunk_extra = a.ntiles % plan.chunks;
+  a.row_words = a.mail_lo = a.mail_hi = nullptr;
   if (plan.chunks > 1) {
-    size_t off = 0;
-    step_workspace_layout(B, plan.chunks, &off);
-    a.tickets = (unsigned long long*)workspace;
-    a.partials = (ChunkResult*)((char*)workspace + off);
+    size_t lo = 0, hi = 0;
+    step_workspace_layout(B, plan.chunks, &hi, &lo);
+    a.row_words = (unsigned long long*)workspace;
+    a.mail_lo = (unsigned long long*)((char*)workspace + lo);
+    a.mail_hi = (unsigned long long*)((char*)workspace + hi);
   }
 
   // the entropy output costs two more vector operations per logit: its own instantiation
@@ -2247,7 +2367,7 @@ int launch_step(const void* logits, int dt, int64_t B, int64_t V, int64_t row_st
     if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxStepLds) != hipSuccess)
       return ESPO_EHIP;
   }
-  const dim3 grid((unsigned)plan.grid), block((unsigned)(plan.waves * kWave));
+  const dim3 grid((unsigned)B, (unsigned)plan.chunks), block((unsigned)(plan.waves * kWave));
   void* args[] = {&a};
   return hipLaunchKernel(kernel, grid, block, args, plan.lds, stream) == hipSuccess ? ESPO_OK : ESPO_EHIP;
 }

@@ -574,6 +574,35 @@ def test_every_split_of_a_row_gives_the_bits_of_the_whole_row(dtype):
             np.testing.assert_allclose(got["entropy"], ref["entropy"], rtol=0, atol=1e-5 * max(1.0, float(ref["entropy"].max())))
 
 
+# Which blocks are looked at after the first scores: none, the groups' best again, a wave's few others, lists that go to the
+# whole workgroup (one logit per block, far more blocks than a wave reads itself); several indices of one lane at once (equal
+# logits); the bounds a wave reads ahead of the barrier and those behind them (200001 logits: 25 and 49 tiles a wave); and the ragged last
+# block, of 1 and of 33 indices, as the best one.
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("V", [65, 4097, 33 * 512 + 33, 200001])
+def test_blocks_left_after_the_first_scores(V, dtype):
+    _say(f"[case] blocks left after the first scores V={V} {dtype}")
+    B = 6
+    stride = (V + 7) // 8 * 8
+    x = torch.full((B, stride), -40.0)
+    x[0, 17::64] = 3.0                                       # one logit per block
+    x[1, 0::64] = x[1, 1::64] = x[1, 9::64] = 2.0             # two of one lane, one of the next
+    x[2] = 0.25                                              # equal everywhere
+    x[3] = torch.randn(stride, generator=torch.Generator().manual_seed(V)) * 1.5
+    x[4] = torch.randn(stride, generator=torch.Generator().manual_seed(V + 1))
+    x[4, V - 1] = 9.0                                         # the last index of the ragged block
+    x[5, :V] = float("-inf")
+    x[5, (V - 1) // 64 * 64:V] = 1.0                          # the ragged block and nothing else
+    x[:, V:] = 1e4
+    logits = x.to(dtype).cuda()
+    vals = torch.zeros(B, device="cuda")
+    gp, op = H.params_pair(stop_enabled=0)
+    for layout in (dict(), dict(waves=16), dict(waves=8), dict(waves=4), dict(chunks=2), dict(waves=16, margin_scale=3e4)):
+        st = H.GpuState(B)
+        for step in range(3):
+            H.compare_step(logits, 1.0, 91, step, vals, gp, op, st, V=V, **layout)
+
+
 def test_workspace_contract():
     _say("[case] workspace contract of espo_step and of a forced split")
     B, V = 600, 3000
