@@ -1514,8 +1514,17 @@ struct CollectLimits {  // packs of a wave's list: room, when it is compacted, w
   static constexpr int kRoom = W == 8 ? (DT == ESPO_BF16 ? 448 : 256) : (DT == ESPO_BF16 ? 320 : 192);
   static constexpr int kCheckTiles = W == 8 && DT == ESPO_BF16 ? 2 : 1;
   static constexpr int kCompactAt = kRoom - kCheckTiles * kWave;
-  static constexpr int kKeep = (DT == ESPO_BF16 ? 160 : 112) * 8 / W, kKeepMin = kKeep / 2;
+  static constexpr int kKeep = (DT == ESPO_BF16 ? 160 : 112) * 8 / W;
 };
+
+// What a compaction keeps of a wave's list: half as many packs at the least.  A nucleus may need them all.  Of a top-k draw's
+// the waves together keep five times k at the least, so that fewer logits are binned and collected afterwards (us, V = 50003 bf16, top-k 50,
+// B = 100: 13.3 with what a nucleus gets, 12.7 so; V = 152064, B = 64: 19.3, 17.9; V = 60000, B = 300: 21.4, 18.8).
+template <int DT, int W>
+__device__ __forceinline__ int packs_kept(const StepArgs& a) {
+  constexpr int kAll = CollectLimits<DT, W>::kKeep;
+  return a.top_k > 0 && a.top_k < kAll * W / 10 ? max(10 * a.top_k / W, 16) : kAll;
+}
 
 template <int DT, int W>
 struct FilterShared {
@@ -1533,13 +1542,14 @@ struct FilterShared {
   int* res_v;
   float* res_x;
   int *nkept, *nmem, *nover;
+  int* edge;         // [4] weight of all bins, the two edges' bins, the weight above the first of them
 };
 
 template <int DT, int W>
 __host__ __device__ constexpr size_t filter_lds_bytes() {
   constexpr size_t packs = (size_t)W * CollectLimits<DT, W>::kRoom;
   return packs * (DT == ESPO_BF16 ? 16 : 32) + packs * 2 + kKeptCap2 * 2 + kEdgeBins * 4 + kEdgeMembers * 10 +
-         W * (6 + 8 + 3) * 4 + W * 16 + 16;
+         W * (6 + 8 + 3) * 4 + W * 16 + 32;
 }
 
 template <int DT, int W>
@@ -1567,6 +1577,7 @@ __device__ __forceinline__ FilterShared<DT, W> carve_filter(unsigned char* base)
   f.nkept = (int*)take(16);
   f.nmem = f.nkept + 1;
   f.nover = f.nkept + 2;
+  f.edge = (int*)take(16);
   f.id = (uint16_t*)take(packs * 2);
   f.kept = (uint16_t*)take(kKeptCap2 * 2);
   f.mem_at = (uint16_t*)take(kEdgeMembers * 2);
@@ -1584,10 +1595,10 @@ __device__ __forceinline__ void pack_unpack(const Raw<DT>& r, int32_t v0, int32_
   }
 }
 
-// Raises a wave's threshold to a value that at most kKeep of the list's packs reach beyond and drops the
+// Raises a wave's threshold to a value that at most `keep` of the list's packs reach beyond and drops the
 // others.  (Packs that tie at the threshold are dropped as well: what is kept is everything above it.)
 template <int DT, int W>
-__device__ __forceinline__ void compact_list(uint32_t* raw, uint16_t* id, int32_t V, int& n, float& thr) {
+__device__ __forceinline__ void compact_list(uint32_t* raw, uint16_t* id, int32_t V, int keep, int& n, float& thr) {
   using Lim = CollectLimits<DT, W>;
   constexpr int kRounds = Lim::kRoom / kWave, kWords = Raw<DT>::kWords;
   const int lane = threadIdx.x & (kWave - 1);
@@ -1605,27 +1616,27 @@ __device__ __forceinline__ void compact_list(uint32_t* raw, uint16_t* id, int32_
     }
     top = fmaxf(top, pm[r]);
   }
-  float hi = wave_max(top), lo = -wave_max(bottom);  // none above hi; the search keeps at most kKeep above hi
+  float hi = wave_max(top), lo = -wave_max(bottom);  // none above hi; the search leaves at most `keep` above hi
 #pragma unroll 1
   for (int it = 0; it < 12; ++it) {
     const float mid = 0.5f * lo + 0.5f * hi;
     int c = 0;
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) c += (int)__builtin_popcountll(__builtin_amdgcn_ballot_w64(pm[r] > mid));
-    if (c > Lim::kKeep) {
+    if (c > keep) {
       lo = mid;
     } else {
       hi = mid;
-      if (c >= Lim::kKeepMin) break;
+      if (2 * c >= keep) break;
     }
   }
   thr = hi;
   int kept = 0;
 #pragma unroll
   for (int r = 0; r < kRounds; ++r) {  // in place: an entry never moves up, and a round reads before it writes
-    const bool keep = pm[r] > thr;
-    const uint64_t mask = __builtin_amdgcn_ballot_w64(keep);
-    if (keep) {
+    const bool stays = pm[r] > thr;
+    const uint64_t mask = __builtin_amdgcn_ballot_w64(stays);
+    if (stays) {
       const int i = r * kWave + lane, to = kept + rank_below(mask);
       const Raw<DT> p = pack_load<DT>(raw + i * kWords);
       const uint16_t which = id[i];
@@ -1755,42 +1766,57 @@ __device__ __forceinline__ DrawResult draw_from_list(const StepArgs& a, const Fi
   };
   list.fill_bins(bottom, bin_of, weight_of);
   __syncthreads();
-  // every wave for itself: the weight above each bin, and the last bins that have logits and less than the
-  // two limits above them: the two edges (kept for sure, may be kept) lie in these bins or between them
+  // the weight above each bin, and the last bins that have logits and less than the two limits above them: the two edges
+  // (kept for sure, may be kept) lie in these bins or between them.  One wave works them out while the others wait: all of
+  // them together, four to a SIMD, took 1900 cycles for what this one, alone on its own, does in 1000 (V = 30000 bf16, top-p 0.7, B = 30: 12.0 -> 11.6 us, the
+  // sums formed ahead of the first barrier included).
   static_assert(kEdgeBins == 4 * kWave, "four bins per lane");
-  const float limit_f = by_count ? (float)a.top_k : (want + slack) * scale;
-  const float limit_sure_f = by_count ? (float)a.top_k : (want - slack) * scale;
-  const uint32_t limit = limit_f < 1.0f ? 1u : limit_f < 4.0e9f ? (uint32_t)limit_f : 4000000000u;
-  const uint32_t limit_sure = limit_sure_f < 1.0f ? 1u : limit_sure_f < 4.0e9f ? (uint32_t)limit_sure_f : 4000000000u;
-  const u32x4 h = ((const u32x4*)f.bins)[lane];
-  const uint32_t lane_total = h[0] + h[1] + h[2] + h[3];
-  uint32_t incl = lane_total;
-  incl += dpp_u32<kDppRowShr1, 0xf>(0u, incl);
-  incl += dpp_u32<kDppRowShr2, 0xf>(0u, incl);
-  incl += dpp_u32<kDppRowShr4, 0xf>(0u, incl);
-  incl += dpp_u32<kDppRowShr8, 0xf>(0u, incl);
-  incl += dpp_u32<kDppBcast15, 0xa>(0u, incl);
-  incl += dpp_u32<kDppBcast31, 0xc>(0u, incl);
-  const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
+  if (wave == 0) {
+    const float limit_f = by_count ? (float)a.top_k : (want + slack) * scale;
+    const float limit_sure_f = by_count ? (float)a.top_k : (want - slack) * scale;
+    const uint32_t limit = limit_f < 1.0f ? 1u : limit_f < 4.0e9f ? (uint32_t)limit_f : 4000000000u;
+    const uint32_t limit_sure = limit_sure_f < 1.0f ? 1u : limit_sure_f < 4.0e9f ? (uint32_t)limit_sure_f : 4000000000u;
+    const u32x4 h = ((const u32x4*)f.bins)[lane];
+    const uint32_t lane_total = h[0] + h[1] + h[2] + h[3];
+    uint32_t incl = lane_total;
+    incl += dpp_u32<kDppRowShr1, 0xf>(0u, incl);
+    incl += dpp_u32<kDppRowShr2, 0xf>(0u, incl);
+    incl += dpp_u32<kDppRowShr4, 0xf>(0u, incl);
+    incl += dpp_u32<kDppRowShr8, 0xf>(0u, incl);
+    incl += dpp_u32<kDppBcast15, 0xa>(0u, incl);
+    incl += dpp_u32<kDppBcast31, 0xc>(0u, incl);
+    uint32_t above[4];
+    above[0] = incl - lane_total;
+#pragma unroll
+    for (int u = 1; u < 4; ++u) above[u] = above[u - 1] + h[u - 1];
+    float best = -1.0f, best_sure = -1.0f;
+    uint32_t above_best = 0;  // the weight above the lane's best_sure
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (h[u] != 0 && above[u] < limit) best = (float)(4 * lane + u);
+      if (h[u] != 0 && above[u] < limit_sure) {
+        best_sure = (float)(4 * lane + u);
+        above_best = above[u];
+      }
+    }
+    const int last = (int)wave_max(best);       // the bin of the largest logit at least: nothing is above it
+    const int edge = (int)wave_max(best_sure);  // not after `last`: its limit is the smaller one
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
+    const uint32_t at_edge = (uint32_t)__builtin_amdgcn_readlane((int)above_best, edge >> 2);
+    if (lane == 0) {
+      f.edge[0] = (int)total;
+      f.edge[1] = last;
+      f.edge[2] = edge;
+      f.edge[3] = (int)at_edge;
+    }
+  }
+  __syncthreads();
+  const uint32_t total = (uint32_t)f.edge[0], above_edge = (uint32_t)f.edge[3];
+  const int last_bin = __builtin_amdgcn_readfirstlane(f.edge[1]), edge_bin = __builtin_amdgcn_readfirstlane(f.edge[2]);
   if (by_count ? total < (uint32_t)a.top_k : !((float)total / scale - want > slack)) {
     list.mass = (float)total / scale;
     return kReachesBelow;
   }
-  uint32_t above[4];
-  above[0] = incl - lane_total;
-#pragma unroll
-  for (int u = 1; u < 4; ++u) above[u] = above[u - 1] + h[u - 1];
-  float best = -1.0f, best_sure = -1.0f;
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    if (h[u] != 0 && above[u] < limit) best = (float)(4 * lane + u);
-    if (h[u] != 0 && above[u] < limit_sure) best_sure = (float)(4 * lane + u);
-  }
-  const int last_bin = (int)wave_max(best);       // the bin of the largest logit at least: nothing is above it
-  const int edge_bin = (int)wave_max(best_sure);  // not after last_bin: its limit is the smaller one
-  const int u_sel = edge_bin & 3;
-  const uint32_t above_sel = u_sel == 0 ? above[0] : u_sel == 1 ? above[1] : u_sel == 2 ? above[2] : above[3];
-  const uint32_t above_edge = (uint32_t)__builtin_amdgcn_readlane((int)above_sel, edge_bin >> 2);
   // ---------------------------------------------------------- the kept logits, and the edge bin's members
   list.for_each(bottom, last_bin, bin_of, [&](uint32_t at, float x, int b) {
     if (b < edge_bin) {
@@ -1911,6 +1937,7 @@ __device__ __forceinline__ bool filtered_row(const StepArgs& a, unsigned char* s
   int n = 0;                    // packs in this wave's list (wave-uniform)
   float thr = kMaskedBelow;     // every logit above it that the wave has seen is in the list
   float low = __builtin_huge_valf();  // the smallest pack maximum this lane has put there
+  const int keep = packs_kept<DT, W>(a);
   bool flooded = false;         // a compaction found most of the list tied at its threshold
   int dry = 0;                  // passes since then that have left the list next to empty
 
@@ -1978,8 +2005,8 @@ __device__ __forceinline__ bool filtered_row(const StepArgs& a, unsigned char* s
     else if (i + kRing < my_tiles)
       ring[d] = load_tile(t + kRing * W);
     if ((d + 1) % Lim::kCheckTiles == 0 && n >= Lim::kCompactAt) {
-      compact_list<DT, W>(my_raw, my_id, a.V, n, thr);
-      flooded = flooded || n < Lim::kKeepMin / 2;
+      compact_list<DT, W>(my_raw, my_id, a.V, keep, n, thr);
+      flooded = flooded || 4 * n < keep;
     }
   };
   const int steady_end = my_tiles > 2 * kRing ? ((my_tiles - kRing - 1) / kRing) * kRing : 0;
@@ -1991,7 +2018,7 @@ __device__ __forceinline__ bool filtered_row(const StepArgs& a, unsigned char* s
     // Ties at the wave's largest logits: the kept set most likely reaches down to them, and they are not in the
     // list.  Given up early, such a row costs the general search and a few tiles (all logits equal, V = 152064, bf16 / fp32: B = 64: 23.6 / 35.1 us,
     // streamed to the end 26.2 / 38.6, the general search alone 22.9 / 31.0).
-    if (flooded && (n == 0 || (n < Lim::kKeepMin / 4 && ++dry == 2))) {
+    if (flooded && (n == 0 || (8 * n < keep && ++dry == 2))) {
       thr = __builtin_huge_valf();  // nothing is above it: the row is handed on
       i0 = my_tiles;
       break;
@@ -2003,12 +2030,22 @@ __device__ __forceinline__ bool filtered_row(const StepArgs& a, unsigned char* s
     for (int d = 0; d < kRing; ++d)
       if (i0 + d < my_tiles) iteration(std::false_type{}, d, i0 + d);  // wave-uniform
   }
+  // the wave's extremes, and its share of the softmax sums relative to its own maximum (see step_row)
   const float mw = wave_max(mx), loww = -wave_max(-low), leastw = -wave_max(-mx);
-  if (lane == 0) {
-    f.least[wave] = leastw;
-    f.m[wave] = mw;
-    f.thr[wave] = thr;
-    f.low[wave] = loww;
+  {
+    const float shift = -fmaf(mw, a.k2, nrk);
+    const float g = __builtin_amdgcn_exp2f(shift);
+    const float tot = wave_sum(sum > 0.0f ? sum * g : 0.0f);
+    float totw = 0.0f;
+    if constexpr (Entropy) totw = wave_sum(sum > 0.0f ? g * fmaf(shift, sum, sumw) : 0.0f);
+    if (lane == 0) {
+      f.least[wave] = leastw;
+      f.m[wave] = mw;
+      f.thr[wave] = thr;
+      f.low[wave] = loww;
+      f.sum[wave] = tot;
+      f.sumw[wave] = totw;
+    }
   }
   float z_prev = 0.0f, value = 0.0f;  // wanted at the very end: fetched now, off the critical path
   if (tid == 0) {
@@ -2018,25 +2055,15 @@ __device__ __forceinline__ bool filtered_row(const StepArgs& a, unsigned char* s
   __syncthreads();
 
   // ------------------------------------------------------------ m, T and S
-  const float m = wave_max(lane < W ? f.m[lane] : kNegInf);
-  float bottom = wave_max(lane < W ? f.thr[lane] : kNegInf);  // every logit above it is in a list
+  const RowSums sums = merge_sums<Entropy, true>(a, lane < W ? f.m[lane] : kNegInf, lane < W ? f.sum[lane] : 0.0f,
+                                                 lane < W ? f.sumw[lane] : 0.0f);
+  const float m = sums.m, S = sums.S;
+  float bottom = row_max(lane < W ? f.thr[lane] : kNegInf);  // every logit above it is in a list
   if (!(bottom > kMaskedBelow)) {  // no list was ever compacted: the smallest pack maximum leaves a logit of every pack above
-    const float lowest = -wave_max(lane < W ? -f.low[lane] : kNegInf);
+    const float lowest = -row_max(lane < W ? -f.low[lane] : kNegInf);
     const int32_t bits = __builtin_bit_cast(int32_t, lowest);
     bottom = lowest == 0.0f ? -1.401298464e-45f : __builtin_bit_cast(float, bits + (lowest > 0.0f ? -1 : 1));
   }
-  {
-    const float shift = -fmaf(m, a.k2, nrk);  // from this lane's reference to the row maximum
-    const float g = __builtin_amdgcn_exp2f(shift);
-    const float tot = wave_sum(sum > 0.0f ? sum * g : 0.0f);
-    if (lane == 0) f.sum[wave] = tot;
-    if constexpr (Entropy) {
-      const float totw = wave_sum(sum > 0.0f ? g * fmaf(shift, sum, sumw) : 0.0f);
-      if (lane == 0) f.sumw[wave] = totw;
-    }
-  }
-  __syncthreads();
-  const float S = wave_sum(lane < W ? f.sum[lane] : 0.0f);
   int32_t tok = -1;
   float x_a = 0.0f;
   if (m > kNegInf) {
@@ -2059,7 +2086,7 @@ __device__ __forceinline__ bool filtered_row(const StepArgs& a, unsigned char* s
         const float missing = a.top_p * S - packs.mass;
         if ((float)*f.nkept + 1.6f * missing / weight_below(bottom, m, a.k2) > (float)(kKeptCap2 + kEdgeMembers)) return false;
       }
-      const float floor2 = -wave_max(lane < W ? -f.least[lane] : kNegInf);
+      const float floor2 = -row_max(lane < W ? -f.least[lane] : kNegInf);
       if (!(floor2 < bottom && floor2 > kMaskedBelow)) return false;
       __syncthreads();  // the packs and the bins have been read by everyone
       for (int b = tid; b < kEdgeBins; b += W * kWave) f.bins[b] = 0;
@@ -2106,9 +2133,7 @@ __device__ __forceinline__ bool filtered_row(const StepArgs& a, unsigned char* s
   }
 
   if (wave != 0) return true;
-  float Sw = 0.0f;
-  if constexpr (Entropy) Sw = wave_sum(lane < W ? f.sumw[lane] : 0.0f);
-  if (lane == 0) finish_row<DT, Entropy, true>(a, row, rowp, tok, x_a, m, S, Sw, z_prev, value);
+  if (lane == 0) finish_row<DT, Entropy, true>(a, row, rowp, tok, x_a, m, S, sums.Sw, z_prev, value);
   return true;
 }
 

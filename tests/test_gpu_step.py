@@ -990,6 +990,30 @@ def test_top_p_at_the_edge_with_logits_far_from_zero(tau, offset, ties):
                         raise AssertionError(f"p {p_val / pa - 1.0:+.1e} off the edge, {layout} step {step}: {err}")
 
 
+# What a wave's list is cut down to follows from k: both sides of its lower and of its upper end, with 8 and 16 waves and
+# for both types, on rows whose largest logits are spread, come last, or lie in the tiles of a single wave (whose threshold
+# then leaves fewer than k logits above it).
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("order", ["random", "ascending", "one wave"])
+def test_top_k_lists_cut_by_k(order, dtype):
+    _say(f"[case] top-k lists, logits {order} {dtype}")
+    B, V = 4, 60001
+    stride = (V + 7) // 8 * 8
+    x = torch.randn(B, stride, generator=torch.Generator().manual_seed(5)) * 3.0
+    if order == "ascending":
+        x = x.sort(dim=1).values
+    elif order == "one wave":
+        x[:, torch.arange(stride) // 512 % 16 == 3] += 12.0
+    x[:, V:] = 1e4
+    logits = x.to(dtype).cuda()
+    vals = torch.zeros(B, device="cuda")
+    for k in (2, 12, 13, 25, 26, 88, 90, 127, 128, 700):
+        gp, op = H.params_pair(stop_enabled=0, top_k=k)
+        for layout in FILTER_LAYOUTS:
+            st = H.GpuState(B)
+            H.compare_step(logits, 1.0, 43, 0, vals, gp, op, st, V=V, **layout)
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("order", ["ascending", "descending", "clustered", "tied"])
 def test_filtered_draws_whatever_order_the_logits_come_in(order, dtype):
