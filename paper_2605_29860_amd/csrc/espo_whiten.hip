@@ -32,14 +32,20 @@
 namespace espo {
 namespace {
 
-constexpr int kWhThreads = 1024;
-constexpr int kWhWaves = kWhThreads / kWave;
+// A workgroup has W waves, 16 or 8 (a template parameter of what depends on it).
 constexpr int kWhQuads = 4;                         // groups of four positions per lane and item
 constexpr int kWhItem = kWave * 4 * kWhQuads;       // positions per item: 1024
 constexpr int kWhUnroll = 2;                        // items of a wave whose loads are in flight together
-constexpr int kWhMaxGroups = 512;                   // one workgroup per slot of the chip
+constexpr int kWhMaxGroups = 512;                   // workgroups of a launch: what the chip holds of the larger ones
+// Up to these many items, workgroups of 8 waves and an item or two for each, not of 16 of which half had none where T is 4096 or
+// more: the waves of a launch start over some microseconds, so waves with little to do cost more than they bring (us, B = 512, T = 8192: 14.4 -> 11.9;
+// packed, 2.1 M tokens: 13.1 -> 11.3; B = 300, T = 2001: 12.9 -> 9.1; 2000, 3000: 16.6 -> 15.4).  Beyond, the larger workgroups keep twice as
+// much in flight on a compute unit (B = 1024, T = 16384: 25.5, with 8 waves 28.0).  From the rows' sums the line lies where a wave has
+// one item (B = 512, T = 8192: 9.0 -> 7.5; 2000, 3000: 12.1 -> 12.4).
+constexpr int64_t kWhEightWavesTo = 8192, kWhEightWavesRowsTo = 4096;
+constexpr int kWhSmallThreads = 1024, kWhSmallWaves = kWhSmallThreads / kWave;
 constexpr int kWhSmallQuads = 4;                    // groups of four positions per lane of the one-workgroup form
-constexpr int64_t kWhSmall = (int64_t)kWhThreads * 4 * kWhSmallQuads;
+constexpr int64_t kWhSmall = (int64_t)kWhSmallThreads * 4 * kWhSmallQuads;
 constexpr uint32_t kWhSkew = 389;                   // rows between a wave's items of neighbouring chunk positions
 
 // Sums of some tokens about a shift of their own: the same fields as AdvRowStats.
@@ -50,7 +56,7 @@ struct WhArgs {
   const int32_t* lengths;
   int64_t B, T, nch;  // nch: items per row
   int64_t items;      // B * nch
-  int groups;
+  int groups, waves;
   float eps;
   int shift_mean, ddof;
   float* out;
@@ -90,29 +96,53 @@ __device__ __forceinline__ Item item_of(const WhArgs& a, uint32_t it) {
 }
 
 // Item k of this wave: the waves of one workgroup take items a whole grid apart.
+template <int W>
 __device__ __forceinline__ uint32_t item_index(const WhArgs& a, int k) {
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  return ((uint32_t)k * kWhWaves + wave) * (uint32_t)a.groups + blockIdx.x;
-}
-
-// This lane's four tokens at position t of an item, and which of them are valid (bit j).
-__device__ __forceinline__ uint32_t load_quad(const float* __restrict__ src, const Item& im, int t, f32x4& g) {
-  if (t >= im.lo && t + 4 <= im.hi) {
-    g = __builtin_nontemporal_load((const f32x4*)(src + im.start + t));
-    return 0xfu;
-  }
-  uint32_t in = 0;
-  g = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-    if (t + j >= im.lo && t + j < im.hi) {
-      g[j] = src[im.start + t + j];
-      in |= 1u << j;
-    }
-  return in;
+  return ((uint32_t)k * W + wave) * (uint32_t)a.groups + blockIdx.x;
 }
 
 __device__ __forceinline__ int quad_at(int q) { return q * kWave * 4 + (int)(threadIdx.x & (kWave - 1)) * 4; }
+
+// This lane's four tokens at position t of an item, and which of them are valid (bit j).  At a row's ends a lane of the smaller workgroups
+// loads all four where any is valid and the array goes on behind them (`end`: its positions from the item's start on), and drops the
+// others: with single loads there, a wave waits for memory twice (B = 1000, T = 300: 13.0 -> 8.9 us, the smaller workgroups
+// included).  The larger ones have no registers for that (B = 1024, T = 16384: 25.5 -> 27.4).
+template <int W>
+__device__ __forceinline__ uint32_t load_quad(const float* __restrict__ src, int end, const Item& im, int t, f32x4& g) {
+  g = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  uint32_t in = 0;
+  if constexpr (W == 16) {
+    if (t >= im.lo && t + 4 <= im.hi) {
+      g = __builtin_nontemporal_load((const f32x4*)(src + im.start + t));
+      return 0xfu;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (t + j >= im.lo && t + j < im.hi) {
+        g[j] = src[im.start + t + j];
+        in |= 1u << j;
+      }
+  } else {
+    const int lo = im.lo - t, hi = im.hi - t;  // valid: lo <= j < hi
+    in = (hi >= 4 ? 0xfu : hi > 0 ? (1u << hi) - 1u : 0u) & (lo <= 0 ? 0xfu : lo < 4 ? 0xfu << lo : 0u);
+    if (in != 0) {
+      if (t + 4 <= end) {
+        g = __builtin_nontemporal_load((const f32x4*)(src + im.start + t));
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if ((in >> j) & 1u) g[j] = src[im.start + t + j];
+      }
+    }
+  }
+  return in;
+}
+
+__device__ __forceinline__ int item_end(const WhArgs& a, const Item& im) {
+  const int64_t left = a.B * a.T - im.start;
+  return (int)(left < kWhItem ? left : kWhItem);
+}
 
 // ---------------------------------------------------------------- sums
 // A lane's running sums about a shift that is the same in the whole batch.
@@ -149,19 +179,20 @@ __device__ __forceinline__ double row_sum_f64(double v) {
   return lane_f64(v, 15);
 }
 
-// Three sums over the workgroup in a fixed tree, the same in every thread; lds holds 3 * kWhWaves entries.
+// Three sums over the workgroup in a fixed tree, the same in every thread; lds holds 3 * W entries.
+template <int W>
 __device__ __forceinline__ void block_sums(double v[3], double* lds) {
+  static_assert(W <= 16, "one row of lanes holds the waves' sums");
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
 #pragma unroll
   for (int i = 0; i < 3; ++i) v[i] = wave_sum_f64(v[i]);
   if (lane == 0) {
 #pragma unroll
-    for (int i = 0; i < 3; ++i) lds[i * kWhWaves + wave] = v[i];
+    for (int i = 0; i < 3; ++i) lds[i * W + wave] = v[i];
   }
   __syncthreads();
-  static_assert(kWhWaves == 16, "one row of lanes holds the waves' sums");
 #pragma unroll
-  for (int i = 0; i < 3; ++i) v[i] = row_sum_f64(lane < kWhWaves ? lds[i * kWhWaves + lane] : 0.0);
+  for (int i = 0; i < 3; ++i) v[i] = row_sum_f64(lane < W ? lds[i * W + lane] : 0.0);
 }
 
 // The first valid token of the batch, as its shift (0 without any).
@@ -176,26 +207,29 @@ struct Moments {
   double n, mean, m2;
 };
 
-__global__ __launch_bounds__(kWhThreads, 8) void whiten_partial_kernel(WhArgs a) {
-  __shared__ double lds[3 * kWhWaves];
-  const double shift = batch_shift(a);
+template <int W>
+__global__ __launch_bounds__(W * kWave, W == 16 ? 8 : 4) void whiten_partial_kernel(WhArgs a) {
+  __shared__ double lds[3 * W];
   LaneSums w;
-  for (int k = 0; item_index(a, k) < (uint32_t)a.items; k += kWhUnroll) {
+  double shift = W == 16 ? batch_shift(a) : 0.0;
+  for (int k = 0; item_index<W>(a, k) < (uint32_t)a.items; k += kWhUnroll) {  // (wave 0 always has an item)
     f32x4 g[kWhUnroll][kWhQuads];
     uint32_t in[kWhUnroll][kWhQuads];
 #pragma unroll
     for (int u = 0; u < kWhUnroll; ++u) {
-      const Item im = item_of(a, item_index(a, k + u));
+      const Item im = item_of(a, item_index<W>(a, k + u));
+      const int end = item_end(a, im);
 #pragma unroll
-      for (int q = 0; q < kWhQuads; ++q) in[u][q] = load_quad(a.adv, im, quad_at(q), g[u][q]);
+      for (int q = 0; q < kWhQuads; ++q) in[u][q] = load_quad<W>(a.adv, end, im, quad_at(q), g[u][q]);
     }
+    if (W != 16 && k == 0) shift = batch_shift(a);  // two loads one after the other, behind those of the first items
 #pragma unroll
     for (int u = 0; u < kWhUnroll; ++u)
 #pragma unroll
       for (int q = 0; q < kWhQuads; ++q) w.add(g[u][q], in[u][q], shift);
   }
   double v[3] = {w.s1, w.s2, (threadIdx.x & (kWave - 1)) == 0 ? (double)w.n : 0.0};
-  block_sums(v, lds);
+  block_sums<W>(v, lds);
   if (threadIdx.x == 0) a.part[blockIdx.x] = Sums{v[0], v[1], shift, (long long)v[2]};
 }
 
@@ -231,15 +265,16 @@ __device__ __forceinline__ void store_quad(float* __restrict__ dst, const f32x4&
     if ((in >> j) & 1u) dst[j] = normalised(g[j], s);
 }
 
-// The moments of the batch from sums about a shift of each set's own, thread i taking sets i, i + 1024, ...; the
+// The moments of the batch from sums about a shift of each set's own, thread i of n taking sets i, i + n, ...; the
 // same bits in every workgroup.  Mean first, then the squared deviations from it (each set's about its own shift, moved to the
 // mean), so that nothing cancels however far the sets' levels are apart.  The sums on the way to the mean are about
 // one of the sets' shifts: a constant batch has its exact mean.
+template <int W>
 __device__ __forceinline__ Moments moments_of_rows(const Sums* __restrict__ sets, int64_t count, Sums* lds, double* lds_m2) {
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
   Sums mine{0.0, 0.0, 0.0, 0};
   double n = 0.0, s1 = 0.0, to = 0.0;
-  for (int64_t i = threadIdx.x; i < count; i += kWhThreads) {
+  for (int64_t i = threadIdx.x; i < count; i += W * kWave) {
     mine = sets[i];
     if (mine.n > 0) {
       if (n == 0.0) to = mine.shift;
@@ -255,7 +290,7 @@ __device__ __forceinline__ Moments moments_of_rows(const Sums* __restrict__ sets
   }
   __syncthreads();
   Sums s{0.0, 0.0, 0.0, 0};
-  if (lane < kWhWaves) s = lds[lane];
+  if (lane < W) s = lds[lane];
   const uint64_t who = __builtin_amdgcn_ballot_w64(s.n > 0);
   to = who != 0 ? lane_f64(s.shift, (int)__builtin_ctzll(who)) : 0.0;
   n = row_sum_f64((double)s.n);
@@ -266,35 +301,37 @@ __device__ __forceinline__ Moments moments_of_rows(const Sums* __restrict__ sets
     const double d = x.shift - mean;
     return x.n > 0 ? fma(d, fma((double)x.n, d, 2.0 * x.s1), x.s2) : 0.0;
   };
-  if (count <= kWhThreads) {
+  if (count <= W * kWave) {
     m2 = deviations(mine);
   } else {
-    for (int64_t i = threadIdx.x; i < count; i += kWhThreads) m2 += deviations(sets[i]);
+    for (int64_t i = threadIdx.x; i < count; i += W * kWave) m2 += deviations(sets[i]);
   }
   m2 = wave_sum_f64(m2);
   if (lane == 0) lds_m2[wave] = m2;
   __syncthreads();
-  m2 = row_sum_f64(lane < kWhWaves ? lds_m2[lane] : 0.0);
+  m2 = row_sum_f64(lane < W ? lds_m2[lane] : 0.0);
   return Moments{n, mean, m2};
 }
 
 // The same from at most kWhMaxGroups sets about one shift.
+template <int W>
 __device__ __forceinline__ Moments moments_of_parts(const Sums* __restrict__ parts, int count, double* lds) {
   Sums mine{0.0, 0.0, 0.0, 0};
+  static_assert(W * kWave >= kWhMaxGroups, "a thread per part");
   if ((int)threadIdx.x < count) mine = parts[threadIdx.x];
   double v[3] = {mine.s1, mine.s2, (double)mine.n};
   const double shift = parts[0].shift;
-  block_sums(v, lds);
+  block_sums<W>(v, lds);
   const double md = v[2] > 0.0 ? v[0] / v[2] : 0.0;
   return Moments{v[2], shift + md, fma(-v[2] * md, md, v[1])};  // s2 - n md^2: the squared deviations from the mean
 }
 
 // The rewrite, from the sums of `count` rows or parts.  The first item's loads are issued before the sums are
 // merged, and every next one's before the current one is stored.
-template <bool Rows>
-__global__ __launch_bounds__(kWhThreads, 8) void whiten_apply_kernel(WhArgs a, const Sums* __restrict__ sets, int64_t count) {
-  __shared__ Sums lds[Rows ? kWhWaves : 1];
-  __shared__ double lds_d[3 * kWhWaves];
+template <bool Rows, int W>
+__global__ __launch_bounds__(W * kWave, W == 16 ? 8 : 4) void whiten_apply_kernel(WhArgs a, const Sums* __restrict__ sets, int64_t count) {
+  __shared__ Sums lds[Rows ? W : 1];
+  __shared__ double lds_d[3 * W];
   struct Held {
     f32x4 g[kWhQuads];
     uint32_t in;  // four bits per group of four
@@ -302,21 +339,22 @@ __global__ __launch_bounds__(kWhThreads, 8) void whiten_apply_kernel(WhArgs a, c
   };
   auto fetch = [&](int k) {
     Held h;
-    const Item im = item_of(a, item_index(a, k));
+    const Item im = item_of(a, item_index<W>(a, k));
+    const int end = item_end(a, im);
     h.at = im.start;
     h.in = 0;
 #pragma unroll
-    for (int q = 0; q < kWhQuads; ++q) h.in |= load_quad(a.adv, im, quad_at(q), h.g[q]) << (4 * q);
+    for (int q = 0; q < kWhQuads; ++q) h.in |= load_quad<W>(a.adv, end, im, quad_at(q), h.g[q]) << (4 * q);
     return h;
   };
   Held cur = fetch(0);
   Moments m;
-  if constexpr (Rows) m = moments_of_rows(sets, count, lds, lds_d);
-  else m = moments_of_parts(sets, (int)count, lds_d);
+  if constexpr (Rows) m = moments_of_rows<W>(sets, count, lds, lds_d);
+  else m = moments_of_parts<W>(sets, (int)count, lds_d);
   const Scale s = scale_of(a, m, blockIdx.x == 0 && threadIdx.x == 0);
-  for (int k = 0; item_index(a, k) < (uint32_t)a.items; ++k) {
+  for (int k = 0; item_index<W>(a, k) < (uint32_t)a.items; ++k) {
     Held nxt;
-    const bool more = item_index(a, k + 1) < (uint32_t)a.items;
+    const bool more = item_index<W>(a, k + 1) < (uint32_t)a.items;
     if (more) nxt = fetch(k + 1);
 #pragma unroll
     for (int q = 0; q < kWhQuads; ++q) store_quad(a.out + cur.at + quad_at(q), cur.g[q], (cur.in >> (4 * q)) & 0xfu, s);
@@ -325,17 +363,17 @@ __global__ __launch_bounds__(kWhThreads, 8) void whiten_apply_kernel(WhArgs a, c
 }
 
 // A small batch in one launch: one workgroup holds all positions (rows of at least four) in registers.
-__global__ __launch_bounds__(kWhThreads) void whiten_small_kernel(WhArgs a) {
-  __shared__ double lds[3 * kWhWaves];
+__global__ __launch_bounds__(kWhSmallThreads) void whiten_small_kernel(WhArgs a) {
+  __shared__ double lds[3 * kWhSmallWaves];
   const uint32_t T = (uint32_t)a.T, total = (uint32_t)(a.B * a.T);
   f32x4 g[kWhSmallQuads];
   uint32_t in[kWhSmallQuads];
-  const int quads = (int)((total + 4 * kWhThreads - 1) / (4 * kWhThreads));
+  const int quads = (int)((total + 4 * kWhSmallThreads - 1) / (4 * kWhSmallThreads));
 #pragma unroll
   for (int u = 0; u < kWhSmallQuads; ++u) {
     in[u] = 0;
     g[u] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    const uint32_t f = ((uint32_t)u * kWhThreads + threadIdx.x) * 4u;
+    const uint32_t f = ((uint32_t)u * kWhSmallThreads + threadIdx.x) * 4u;
     if (u < quads && f < total) {  // the four positions lie in one row or at the end of it and the start of the next
       const uint32_t row = f / T, t = f - row * T;
       auto valid = [&](uint32_t r) {
@@ -360,25 +398,27 @@ __global__ __launch_bounds__(kWhThreads) void whiten_small_kernel(WhArgs a) {
   for (int u = 0; u < kWhSmallQuads; ++u)
     if (u < quads) w.add(g[u], in[u], shift);
   double v[3] = {w.s1, w.s2, (threadIdx.x & (kWave - 1)) == 0 ? (double)w.n : 0.0};
-  block_sums(v, lds);
+  block_sums<kWhSmallWaves>(v, lds);
   const double md = v[2] > 0.0 ? v[0] / v[2] : 0.0;
   const Scale s = scale_of(a, Moments{v[2], shift + md, fma(-v[2] * md, md, v[1])}, threadIdx.x == 0);
 #pragma unroll
   for (int u = 0; u < kWhSmallQuads; ++u)
-    if (u < quads) store_quad(a.out + ((uint32_t)u * kWhThreads + threadIdx.x) * 4u, g[u], in[u], s);
+    if (u < quads) store_quad(a.out + ((uint32_t)u * kWhSmallThreads + threadIdx.x) * 4u, g[u], in[u], s);
 }
 
 // Items of a row: one that starts between boundaries spans up to 3 positions more.
 int64_t items_per_row(int64_t T) { return (T + (T % 4 != 0 ? 3 : 0) + kWhItem - 1) / kWhItem; }
 
-// One workgroup per 4096 positions of a row, up to what the chip holds.
-int whiten_groups(int64_t B, int64_t T) {
-  const int64_t want = B * ((T + 4095) / 4096);
+int whiten_waves(int64_t items, bool rows) { return items <= (rows ? kWhEightWavesRowsTo : kWhEightWavesTo) ? 8 : 16; }
+
+// An item for every wave of the smaller workgroups, up to what the chip holds of the larger ones.
+int whiten_groups(int64_t items, int waves) {
+  const int64_t want = waves == 16 ? kWhMaxGroups : (items + waves - 1) / waves;
   return (int)(want < 1 ? 1 : (want > kWhMaxGroups ? kWhMaxGroups : want));
 }
 
 WhArgs whiten_args(const float* adv, const int32_t* lengths, int64_t B, int64_t T, float eps, int shift_mean, int unbiased,
-                   float* out, double* stats) {
+                   float* out, double* stats, bool rows) {
   WhArgs a;
   a.adv = adv;
   a.lengths = lengths;
@@ -386,7 +426,8 @@ WhArgs whiten_args(const float* adv, const int32_t* lengths, int64_t B, int64_t 
   a.T = T;
   a.nch = items_per_row(T);
   a.items = B * a.nch;
-  a.groups = whiten_groups(B, T);
+  a.waves = whiten_waves(a.items, rows);
+  a.groups = whiten_groups(a.items, a.waves);
   a.eps = eps;
   a.shift_mean = shift_mean;
   a.ddof = unbiased ? 1 : 0;
@@ -401,30 +442,37 @@ WhArgs whiten_args(const float* adv, const int32_t* lengths, int64_t B, int64_t 
 // item_index counts in 32 bits, and past the last item by up to kWhUnroll rounds of the waves.
 bool whiten_indexable(int64_t B, int64_t T) {
   constexpr int64_t kRoom = 1 << 15;
-  static_assert((kWhUnroll + 1) * kWhWaves * kWhMaxGroups <= kRoom, "room for the index of a loop's last step");
+  static_assert((kWhUnroll + 1) * 16 * kWhMaxGroups <= kRoom, "room for the index of a loop's last step");
   return B * ((T + 3 + kWhItem - 1) / kWhItem) < (1ll << 32) - kRoom;
 }
 
-size_t whiten_workspace(int64_t B, int64_t T) { return (size_t)whiten_groups(B, T) * sizeof(Sums); }
+size_t whiten_workspace(int64_t B, int64_t T) {
+  const int64_t items = B * items_per_row(T);
+  return (size_t)whiten_groups(items, whiten_waves(items, false)) * sizeof(Sums);
+}
 
 int launch_whiten(const float* adv, const int32_t* lengths, int64_t B, int64_t T, float eps, int shift_mean,
                   int unbiased, float* out, double* stats, void* workspace, hipStream_t stream) {
-  WhArgs a = whiten_args(adv, lengths, B, T, eps, shift_mean, unbiased, out, stats);
+  WhArgs a = whiten_args(adv, lengths, B, T, eps, shift_mean, unbiased, out, stats, false);
   if (T >= 4 && B * T <= kWhSmall) {
-    hipLaunchKernelGGL(whiten_small_kernel, dim3(1), dim3(kWhThreads), 0, stream, a);
+    hipLaunchKernelGGL(whiten_small_kernel, dim3(1), dim3(kWhSmallThreads), 0, stream, a);
     return hipGetLastError() == hipSuccess ? ESPO_OK : ESPO_EHIP;
   }
   a.part = (Sums*)workspace;
-  hipLaunchKernelGGL(whiten_partial_kernel, dim3(a.groups), dim3(kWhThreads), 0, stream, a);
+  const dim3 grid(a.groups), block(a.waves * kWave);
+  const auto partial = a.waves == 16 ? whiten_partial_kernel<16> : whiten_partial_kernel<8>;
+  hipLaunchKernelGGL(partial, grid, block, 0, stream, a);
   if (hipGetLastError() != hipSuccess) return ESPO_EHIP;
-  hipLaunchKernelGGL(whiten_apply_kernel<false>, dim3(a.groups), dim3(kWhThreads), 0, stream, a, a.part, (int64_t)a.groups);
+  const auto apply = a.waves == 16 ? whiten_apply_kernel<false, 16> : whiten_apply_kernel<false, 8>;
+  hipLaunchKernelGGL(apply, grid, block, 0, stream, a, (const Sums*)a.part, (int64_t)a.groups);
   return hipGetLastError() == hipSuccess ? ESPO_OK : ESPO_EHIP;
 }
 
 int launch_whiten_rows(const float* adv, const int32_t* lengths, int64_t B, int64_t T, float eps, int shift_mean,
                        int unbiased, float* out, double* stats, const AdvRowStats* rows, hipStream_t stream) {
-  const WhArgs a = whiten_args(adv, lengths, B, T, eps, shift_mean, unbiased, out, stats);
-  hipLaunchKernelGGL(whiten_apply_kernel<true>, dim3(a.groups), dim3(kWhThreads), 0, stream, a, rows, B);
+  const WhArgs a = whiten_args(adv, lengths, B, T, eps, shift_mean, unbiased, out, stats, true);
+  const auto apply = a.waves == 16 ? whiten_apply_kernel<true, 16> : whiten_apply_kernel<true, 8>;
+  hipLaunchKernelGGL(apply, dim3(a.groups), dim3(a.waves * kWave), 0, stream, a, rows, B);
   return hipGetLastError() == hipSuccess ? ESPO_OK : ESPO_EHIP;
 }
 

@@ -131,6 +131,13 @@ def _run(r, v, L, s, r_fail=-1.0, gamma=1.0, lam=0.95, eps=1e-8, shift_mean=True
     return worst
 
 
+@pytest.mark.parametrize("B", [4096, 4097])                    # items of 1024 positions: the most for workgroups of 8 waves, and one more
+def test_whitening_from_the_rows_with_both_sizes_of_workgroups(B):
+    _say(f"[case] whitening from the rows' sums, B={B}")
+    r, v, L, s = _batch(B, 1021, seed=B)
+    _run(r, v, L, s, oracle_pass=False, ordered=False)
+
+
 @pytest.mark.parametrize("T", [1, 3, 4, 7, 64, 1023, 4096, 4097, 9001])
 def test_shapes_and_ragged_lengths(T):
     _say(f"[case] advantages_ws T={T}")

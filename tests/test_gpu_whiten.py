@@ -88,6 +88,18 @@ def test_rows_that_start_anywhere_and_the_one_launch_form(B, T):
     _check(a, L, in_place=True)
 
 
+@pytest.mark.parametrize("B,T", [(4096, 1021), (4097, 1021), (8192, 1021), (8193, 1021), (1, 8192 * 1024), (1, 8192 * 1024 + 1)])
+def test_both_sizes_of_workgroups(B, T):
+    # 8192 items of 1024 positions are the most that workgroups of 8 waves take; the last row ends with the array, not at a
+    # multiple of four positions
+    _say(f"[case] whiten, both sizes of workgroups, B={B} T={T}")
+    a, L = _batch(B, T, seed=T, lengths=[T - b % 7 for b in range(B - 1)] + [T], mean=0.3)
+    _check(a, L, in_place=True)
+    if B > 1:
+        a, L = _batch(B, T, seed=T + 1)
+        _check(a, L, unbiased=True)
+
+
 def test_mean_far_from_zero_and_tiny_spread():
     _say("[case] whiten, mean far from zero")
     # values 1000 +- 0.01: a one-pass variance about zero would lose every digit in fp32 and ten in double
