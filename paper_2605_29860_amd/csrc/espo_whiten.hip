@@ -37,12 +37,16 @@ constexpr int kWhQuads = 4;                         // groups of four positions 
 constexpr int kWhItem = kWave * 4 * kWhQuads;       // positions per item: 1024
 constexpr int kWhUnroll = 2;                        // items of a wave whose loads are in flight together
 constexpr int kWhMaxGroups = 512;                   // workgroups of a launch: what the chip holds of the larger ones
-// Up to these many items, workgroups of 8 waves and an item or two for each, not of 16 of which half had none where T is 4096 or
-// more: the waves of a launch start over some microseconds, so waves with little to do cost more than they bring (us, B = 512, T = 8192: 14.4 -> 11.9;
-// packed, 2.1 M tokens: 13.1 -> 11.3; B = 300, T = 2001: 12.9 -> 9.1; 2000, 3000: 16.6 -> 15.4).  Beyond, the larger workgroups keep twice as
-// much in flight on a compute unit (B = 1024, T = 16384: 25.5, with 8 waves 28.0).  From the rows' sums the line lies where a wave has
-// one item (B = 512, T = 8192: 9.0 -> 7.5; 2000, 3000: 12.1 -> 12.4).
-constexpr int64_t kWhEightWavesTo = 8192, kWhEightWavesRowsTo = 4096;
+// Up to these many items the sums are formed by workgroups of 8 waves with an item or two for each, not of 16 of which half had none where T is
+// 4096 or more: the waves of a launch start over some microseconds, so waves with little to do cost more than they bring (us, both launches,
+// B = 512, T = 8192: 14.4 -> 11.9; packed, 2.1 M tokens: 13.1 -> 11.1; B = 300, T = 2001: 13.0 -> 8.9; 2000, 3000: 16.6 -> 14.4).  Beyond, the larger
+// workgroups keep twice as much in flight on a compute unit (B = 1024, T = 16384: 7.2, with 8 waves 7.6).
+constexpr int64_t kWhEightWavesTo = 8192;
+// The rewrite takes workgroups of 8 waves as long as a wave can hold all its items, at most kWhHold, whose loads are then all on their way before the
+// sums are merged; beyond, 16 waves that have one item on its way at a time (us, from the rows' sums, with 16 waves / now:
+// B = 512, T = 8192, an item a wave: 9.1 / 7.5; 2000, 3000: 12.1 / 11.4 (one item on its way at a time: 12.4); 1024, 16384: 18.5 / 15.6;
+// but 1024, 16383, 17408 items in two rounds: 19.8 / 21.8).
+constexpr int kWhHold = 4;
 constexpr int kWhSmallThreads = 1024, kWhSmallWaves = kWhSmallThreads / kWave;
 constexpr int kWhSmallQuads = 4;                    // groups of four positions per lane of the one-workgroup form
 constexpr int64_t kWhSmall = (int64_t)kWhSmallThreads * 4 * kWhSmallQuads;
@@ -56,7 +60,7 @@ struct WhArgs {
   const int32_t* lengths;
   int64_t B, T, nch;  // nch: items per row
   int64_t items;      // B * nch
-  int groups, waves;
+  int groups;
   float eps;
   int shift_mean, ddof;
   float* out;
@@ -326,9 +330,9 @@ __device__ __forceinline__ Moments moments_of_parts(const Sums* __restrict__ par
   return Moments{v[2], shift + md, fma(-v[2] * md, md, v[1])};  // s2 - n md^2: the squared deviations from the mean
 }
 
-// The rewrite, from the sums of `count` rows or parts.  The first item's loads are issued before the sums are
-// merged, and every next one's before the current one is stored.
-template <bool Rows, int W>
+// The rewrite, from the sums of `count` rows or parts.  Hold: items of a wave, all of them, whose loads are issued before the sums
+// are merged; 0: as many as it takes, the first one's loads before that, and every next one's before the current one is stored.
+template <bool Rows, int W, int Hold>
 __global__ __launch_bounds__(W * kWave, W == 16 ? 8 : 4) void whiten_apply_kernel(WhArgs a, const Sums* __restrict__ sets, int64_t count) {
   __shared__ Sums lds[Rows ? W : 1];
   __shared__ double lds_d[3 * W];
@@ -347,18 +351,28 @@ __global__ __launch_bounds__(W * kWave, W == 16 ? 8 : 4) void whiten_apply_kerne
     for (int q = 0; q < kWhQuads; ++q) h.in |= load_quad<W>(a.adv, end, im, quad_at(q), h.g[q]) << (4 * q);
     return h;
   };
-  Held cur = fetch(0);
+  auto store = [&](const Held& h, const Scale& s) {
+#pragma unroll
+    for (int q = 0; q < kWhQuads; ++q) store_quad(a.out + h.at + quad_at(q), h.g[q], (h.in >> (4 * q)) & 0xfu, s);
+  };
+  Held held[Hold > 0 ? Hold : 1];
+#pragma unroll
+  for (int i = 0; i < (Hold > 0 ? Hold : 1); ++i) held[i] = fetch(i);
   Moments m;
   if constexpr (Rows) m = moments_of_rows<W>(sets, count, lds, lds_d);
   else m = moments_of_parts<W>(sets, (int)count, lds_d);
   const Scale s = scale_of(a, m, blockIdx.x == 0 && threadIdx.x == 0);
-  for (int k = 0; item_index<W>(a, k) < (uint32_t)a.items; ++k) {
-    Held nxt;
-    const bool more = item_index<W>(a, k + 1) < (uint32_t)a.items;
-    if (more) nxt = fetch(k + 1);
+  if constexpr (Hold > 0) {
 #pragma unroll
-    for (int q = 0; q < kWhQuads; ++q) store_quad(a.out + cur.at + quad_at(q), cur.g[q], (cur.in >> (4 * q)) & 0xfu, s);
-    if (more) cur = nxt;
+    for (int i = 0; i < Hold; ++i) store(held[i], s);
+  } else {
+    for (int k = 0; item_index<W>(a, k) < (uint32_t)a.items; ++k) {
+      Held nxt;
+      const bool more = item_index<W>(a, k + 1) < (uint32_t)a.items;
+      if (more) nxt = fetch(k + 1);
+      store(held[0], s);
+      if (more) held[0] = nxt;
+    }
   }
 }
 
@@ -409,16 +423,26 @@ __global__ __launch_bounds__(kWhSmallThreads) void whiten_small_kernel(WhArgs a)
 // Items of a row: one that starts between boundaries spans up to 3 positions more.
 int64_t items_per_row(int64_t T) { return (T + (T % 4 != 0 ? 3 : 0) + kWhItem - 1) / kWhItem; }
 
-int whiten_waves(int64_t items, bool rows) { return items <= (rows ? kWhEightWavesRowsTo : kWhEightWavesTo) ? 8 : 16; }
-
 // An item for every wave of the smaller workgroups, up to what the chip holds of the larger ones.
-int whiten_groups(int64_t items, int waves) {
-  const int64_t want = waves == 16 ? kWhMaxGroups : (items + waves - 1) / waves;
+int whiten_groups(int64_t items) {
+  const int64_t want = (items + 7) / 8;
   return (int)(want < 1 ? 1 : (want > kWhMaxGroups ? kWhMaxGroups : want));
 }
 
+// The rewrite of these arguments.
+template <bool Rows>
+int launch_apply(const WhArgs& a, const Sums* sets, int64_t count, hipStream_t stream) {
+  const int64_t waves = (int64_t)a.groups * 8;
+  static_assert(kWhHold == 4, "the three sizes below");
+  const bool eight = a.items <= kWhHold * waves;
+  const auto kernel = a.items <= waves ? whiten_apply_kernel<Rows, 8, 1> : a.items <= 2 * waves ? whiten_apply_kernel<Rows, 8, 2>
+                      : eight ? whiten_apply_kernel<Rows, 8, 4> : whiten_apply_kernel<Rows, 16, 0>;
+  hipLaunchKernelGGL(kernel, dim3(a.groups), dim3((eight ? 8 : 16) * kWave), 0, stream, a, sets, count);
+  return hipGetLastError() == hipSuccess ? ESPO_OK : ESPO_EHIP;
+}
+
 WhArgs whiten_args(const float* adv, const int32_t* lengths, int64_t B, int64_t T, float eps, int shift_mean, int unbiased,
-                   float* out, double* stats, bool rows) {
+                   float* out, double* stats) {
   WhArgs a;
   a.adv = adv;
   a.lengths = lengths;
@@ -426,8 +450,7 @@ WhArgs whiten_args(const float* adv, const int32_t* lengths, int64_t B, int64_t 
   a.T = T;
   a.nch = items_per_row(T);
   a.items = B * a.nch;
-  a.waves = whiten_waves(a.items, rows);
-  a.groups = whiten_groups(a.items, a.waves);
+  a.groups = whiten_groups(a.items);
   a.eps = eps;
   a.shift_mean = shift_mean;
   a.ddof = unbiased ? 1 : 0;
@@ -446,34 +469,26 @@ bool whiten_indexable(int64_t B, int64_t T) {
   return B * ((T + 3 + kWhItem - 1) / kWhItem) < (1ll << 32) - kRoom;
 }
 
-size_t whiten_workspace(int64_t B, int64_t T) {
-  const int64_t items = B * items_per_row(T);
-  return (size_t)whiten_groups(items, whiten_waves(items, false)) * sizeof(Sums);
-}
+size_t whiten_workspace(int64_t B, int64_t T) { return (size_t)whiten_groups(B * items_per_row(T)) * sizeof(Sums); }
 
 int launch_whiten(const float* adv, const int32_t* lengths, int64_t B, int64_t T, float eps, int shift_mean,
                   int unbiased, float* out, double* stats, void* workspace, hipStream_t stream) {
-  WhArgs a = whiten_args(adv, lengths, B, T, eps, shift_mean, unbiased, out, stats, false);
+  WhArgs a = whiten_args(adv, lengths, B, T, eps, shift_mean, unbiased, out, stats);
   if (T >= 4 && B * T <= kWhSmall) {
     hipLaunchKernelGGL(whiten_small_kernel, dim3(1), dim3(kWhSmallThreads), 0, stream, a);
     return hipGetLastError() == hipSuccess ? ESPO_OK : ESPO_EHIP;
   }
   a.part = (Sums*)workspace;
-  const dim3 grid(a.groups), block(a.waves * kWave);
-  const auto partial = a.waves == 16 ? whiten_partial_kernel<16> : whiten_partial_kernel<8>;
-  hipLaunchKernelGGL(partial, grid, block, 0, stream, a);
+  const bool eight = a.items <= kWhEightWavesTo;
+  hipLaunchKernelGGL(eight ? whiten_partial_kernel<8> : whiten_partial_kernel<16>, dim3(a.groups), dim3((eight ? 8 : 16) * kWave), 0, stream, a);
   if (hipGetLastError() != hipSuccess) return ESPO_EHIP;
-  const auto apply = a.waves == 16 ? whiten_apply_kernel<false, 16> : whiten_apply_kernel<false, 8>;
-  hipLaunchKernelGGL(apply, grid, block, 0, stream, a, (const Sums*)a.part, (int64_t)a.groups);
-  return hipGetLastError() == hipSuccess ? ESPO_OK : ESPO_EHIP;
+  return launch_apply<false>(a, a.part, a.groups, stream);
 }
 
 int launch_whiten_rows(const float* adv, const int32_t* lengths, int64_t B, int64_t T, float eps, int shift_mean,
                        int unbiased, float* out, double* stats, const AdvRowStats* rows, hipStream_t stream) {
-  const WhArgs a = whiten_args(adv, lengths, B, T, eps, shift_mean, unbiased, out, stats, true);
-  const auto apply = a.waves == 16 ? whiten_apply_kernel<true, 16> : whiten_apply_kernel<true, 8>;
-  hipLaunchKernelGGL(apply, dim3(a.groups), dim3(a.waves * kWave), 0, stream, a, rows, B);
-  return hipGetLastError() == hipSuccess ? ESPO_OK : ESPO_EHIP;
+  const WhArgs a = whiten_args(adv, lengths, B, T, eps, shift_mean, unbiased, out, stats);
+  return launch_apply<true>(a, rows, B, stream);
 }
 
 }  // namespace espo

@@ -131,7 +131,7 @@ def _run(r, v, L, s, r_fail=-1.0, gamma=1.0, lam=0.95, eps=1e-8, shift_mean=True
     return worst
 
 
-@pytest.mark.parametrize("B", [4096, 4097])                    # items of 1024 positions: the most for workgroups of 8 waves, and one more
+@pytest.mark.parametrize("B", [4096, 4097, 8193, 16385])       # items of 1024 positions: one, two, four held by a wave of 8, and more
 def test_whitening_from_the_rows_with_both_sizes_of_workgroups(B):
     _say(f"[case] whitening from the rows' sums, B={B}")
     r, v, L, s = _batch(B, 1021, seed=B)

@@ -88,10 +88,11 @@ def test_rows_that_start_anywhere_and_the_one_launch_form(B, T):
     _check(a, L, in_place=True)
 
 
-@pytest.mark.parametrize("B,T", [(4096, 1021), (4097, 1021), (8192, 1021), (8193, 1021), (1, 8192 * 1024), (1, 8192 * 1024 + 1)])
+@pytest.mark.parametrize("B,T", [(4096, 1021), (4097, 1021), (8192, 1021), (8193, 1021), (1, 8192 * 1024), (1, 8192 * 1024 + 1),
+                                 (16384, 1021), (16385, 1021)])
 def test_both_sizes_of_workgroups(B, T):
-    # 8192 items of 1024 positions are the most that workgroups of 8 waves take; the last row ends with the array, not at a
-    # multiple of four positions
+    # 8192 items of 1024 positions are the most that workgroups of 8 waves sum up, and 4096, 8192 and 16384 the most that their waves
+    # rewrite with one, two and four items held; the last row ends with the array, not at a multiple of four positions
     _say(f"[case] whiten, both sizes of workgroups, B={B} T={T}")
     a, L = _batch(B, T, seed=T, lengths=[T - b % 7 for b in range(B - 1)] + [T], mean=0.3)
     _check(a, L, in_place=True)
