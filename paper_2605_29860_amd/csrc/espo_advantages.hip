@@ -35,7 +35,8 @@
 namespace espo {
 namespace {
 
-// A workgroup has W wavefronts, 16 or 4 (a template parameter of what depends on it): tiles of 4096 or 1024 tokens.
+// A workgroup has W wavefronts (a template parameter of what depends on it): 16, or 8 with two spans of 256 tokens each, for tiles of
+// 4096 tokens; 4 for tiles of 1024.
 constexpr int kPerLane = 4;
 constexpr int kWaveTokens = kWave * kPerLane;
 constexpr int kPair = 2;                          // inner tiles of a workgroup of 4 waves that share a barrier
@@ -63,7 +64,7 @@ struct AdvArgs {
   const int32_t* order;    // optional [B]: the rows, longest first (padded forms)
   AdvRowStats* row_stats;  // optional [B]: sums of every row's advantages (padded forms)
   int32_t* sorted;         // optional [B - kAdvFirstRows]: the rows from kAdvFirstRows on, longest first, written by
-                           //   workgroup 0 of this launch (padded forms in workgroups of 16 waves, no `order` given)
+                           //   workgroup 0 of this launch (padded forms in workgroups of 8 or 16 waves, no `order` given)
   uint32_t* sync;          // with `sorted`: [0] set once `sorted` is complete, [32] readers so far; both 0 between launches
 };
 
@@ -85,6 +86,7 @@ constexpr int64_t kAdvSortTokens = 4608;
 // read-modify-writes of the other on the same line cost the readers 15 us per launch between them.
 constexpr int kAdvSyncStride = 32;       // words
 constexpr size_t kAdvSyncBytes = 256;
+constexpr int64_t kAdvOnePerUnit = 256;  // rows: one for every compute unit at most
 constexpr int kOrderClasses = 256;
 
 __device__ __forceinline__ int class_of_length(int64_t L, int64_t T) {  // class 0 is the longest
@@ -93,8 +95,9 @@ __device__ __forceinline__ int class_of_length(int64_t L, int64_t T) {  // class
 }
 
 // Writes the rows first .. B-1 to order[0 .. B-first), longest first: a counting sort of the clipped lengths into
-// 256 classes by one workgroup of 16 waves (rows of one class in no particular order; no result depends on it).  The entries
+// 256 classes by one workgroup of W waves, 4 at least (rows of one class in no particular order; no result depends on it).  The entries
 // are written past the caches that other parts of the chip do not see, and are complete when the call returns.
+template <int W>
 __device__ __forceinline__ void sort_rows_by_length(const int32_t* __restrict__ lengths, int32_t first, int32_t B, int64_t T,
                                                     int32_t* __restrict__ order) {
   __shared__ int count[kOrderClasses];
@@ -103,7 +106,7 @@ __device__ __forceinline__ void sort_rows_by_length(const int32_t* __restrict__ 
   auto class_of = [&](int32_t i) { return class_of_length(lengths[i], T); };
   if (tid < kOrderClasses) count[tid] = 0;
   __syncthreads();
-  for (int32_t i = first + tid; i < B; i += 16 * kWave) atomicAdd(&count[class_of(i)], 1);
+  for (int32_t i = first + tid; i < B; i += W * kWave) atomicAdd(&count[class_of(i)], 1);
   __syncthreads();
   int mine = 0, incl = 0;
   if (tid < kOrderClasses) {  // inclusive prefix over the classes: inside each wave, then over the four waves
@@ -123,7 +126,7 @@ __device__ __forceinline__ void sort_rows_by_length(const int32_t* __restrict__ 
     count[tid] = before + incl - mine;  // where the class starts
   }
   __syncthreads();
-  for (int32_t i = first + tid; i < B; i += 16 * kWave)
+  for (int32_t i = first + tid; i < B; i += W * kWave)
     __hip_atomic_store(order + atomicAdd(&count[class_of(i)], 1), i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
@@ -203,9 +206,10 @@ __device__ __forceinline__ float pow_from_table(const float* tab, int e) {
 
 // Loads the lane's 4 tokens starting at t0 and, in lane 0, the value at t0 + 4; tokens at or
 // beyond L are never read.
-template <bool Dense>
-__device__ __forceinline__ TileIn load_tile(const float* __restrict__ rrow, const float* __restrict__ vrow, int64_t t0,
-                                            int64_t L, bool want_halo) {
+// Positions are of type Pos: 64-bit ones of a row, or 32-bit ones of a tile.
+template <bool Dense, typename Pos>
+__device__ __forceinline__ TileIn load_tile(const float* __restrict__ rrow, const float* __restrict__ vrow, Pos t0,
+                                            Pos L, bool want_halo) {
   TileIn in;
 #pragma unroll
   for (int j = 0; j < kPerLane; ++j) { in.r[j] = 0.0f; in.v[j] = 0.0f; }
@@ -232,12 +236,14 @@ __device__ __forceinline__ TileIn load_tile(const float* __restrict__ rrow, cons
 }
 
 // Stores x at t0 .. t0 + 3 where the row goes on (T % 4 == 0 here).
-__device__ __forceinline__ void store4(float* __restrict__ row, int64_t t0, int64_t T, const float x[kPerLane]) {
+template <typename Pos>
+__device__ __forceinline__ void store4(float* __restrict__ row, Pos t0, Pos T, const float x[kPerLane]) {
   if (t0 < T) __builtin_nontemporal_store(f32x4{x[0], x[1], x[2], x[3]}, (f32x4*)(row + t0));
 }
 
 // Stores x[j] at t0 + j for lo <= t0 + j < hi (t0 a multiple of 4, the row 16-byte aligned).
-__device__ __forceinline__ void store_span(float* __restrict__ row, int64_t t0, int64_t lo, int64_t hi, const float x[kPerLane]) {
+template <typename Pos>
+__device__ __forceinline__ void store_span(float* __restrict__ row, Pos t0, Pos lo, Pos hi, const float x[kPerLane]) {
   if (t0 >= lo && t0 + kPerLane <= hi) {
     __builtin_nontemporal_store(f32x4{x[0], x[1], x[2], x[3]}, (f32x4*)(row + t0));
     return;
@@ -359,11 +365,19 @@ __device__ __forceinline__ float walk_inner(const AdvArgs& a, const float* __res
 // Layout of the rows: [B, T] with T a multiple of four, [B, T] with any T, or back to back.
 enum RowLayout { kAligned, kShifted, kPacked };
 
+// What a workgroup has to do: its row, where the row's tokens lie and what its last token's reward is.  False: nothing.
+struct Row {
+  bool fill_only;      // zeros beyond the trajectory, and nothing else
+  int32_t row;
+  int64_t T, L, head;  // from the row's 16-byte boundary on: its end, the end of its valid part, its start
+  bool last_given;     // the reward of the last token is r_last, wherever the others come from
+  float r_last;
+  const float *rewards, *values;
+  float *td, *adv, *returns;
+};
+
 template <bool Dense, RowLayout Layout, int W>
-__global__ __launch_bounds__(W * kWave, W == 4 ? (Dense && Layout == kPacked ? 5 : 6) : 8) void espo_advantages_kernel(AdvArgs a) {
-  constexpr bool Packed = Layout == kPacked, Span = Layout != kAligned;
-  constexpr int kTile = W * kWaveTokens;
-  __shared__ float s_tot[2][W];  // wave totals, double-buffered by tile parity
+__device__ __forceinline__ bool open_row(const AdvArgs& a, Row& r) {
   // With zero padding, the tiles wholly beyond a trajectory are filled by a workgroup of their
   // own (the second half of the grid): the two kinds of work of a row are then dispatched
   // separately, which evens out the rows (a row costs 16 bytes per valid and 8 per padded token):
@@ -371,27 +385,28 @@ __global__ __launch_bounds__(W * kWave, W == 4 ? (Dense && Layout == kPacked ? 5
   // when they come in random order.  (Ranking the rows by length inside every workgroup, 8 or 64
   // classes, cost 3 to 5 us per launch, as much as the order gains; only the order of the rows that do
   // not fit the chip at once matters, and only their scans look their row up: see below.)
-  constexpr bool kOrdered = W == 16;  // of the smaller workgroups, for short rows, the chip holds 2048, and rows differ little
+  constexpr bool Packed = Layout == kPacked, kOrdered = W != 4;  // of the smallest workgroups, for short rows, the chip holds 2048, and rows differ little
   int unit = (int)blockIdx.x;
   if (kOrdered && !Packed && a.sorted) {
     // No order was given and the later rows are to be scanned longest first: workgroup 0 of this launch
     // sorts them while the first kAdvFirstRows are being scanned, and tells the others when it is done.
     // It waits for nobody and is dispatched before every workgroup that waits for it.
     if (unit == 0) {
-      sort_rows_by_length(a.lengths, kAdvFirstRows, a.B, a.T, a.sorted);
+      sort_rows_by_length<W>(a.lengths, kAdvFirstRows, a.B, a.T, a.sorted);
       if (threadIdx.x == 0) __hip_atomic_store(a.sync, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      return;
+      return false;
     }
     unit -= 1;
   }
-  const bool fill_only = !Packed && unit >= a.B;
+  r.fill_only = !Packed && unit >= a.B;
+  const bool fill_only = r.fill_only;
   int row = fill_only ? unit - a.B : unit;
   // Rows in order of length: the long scans start first and the short ones fill the launch's end (the
   // workgroups that only fill take the rows the other way round: the shortest row has the most padding).
   // An entry that names no row makes its workgroup do nothing.
   if (!Packed && a.order) {
     row = a.order[fill_only ? a.B - 1 - row : row];
-    if ((unsigned)row >= (unsigned)a.B) return;
+    if ((unsigned)row >= (unsigned)a.B) return false;
   } else if (kOrdered && !Packed && a.sorted && !fill_only && row >= a.ordered_from) {
     // one of the later scans: its row comes from the sorted list.  The last reader clears the two words, so the
     // next launch finds them as this one did.
@@ -405,7 +420,7 @@ __global__ __launch_bounds__(W * kWave, W == 4 ? (Dense && Layout == kPacked ? 5
     }
     __syncthreads();
     row = s_row;
-    if ((unsigned)row >= (unsigned)a.B) return;
+    if ((unsigned)row >= (unsigned)a.B) return false;
   } else if (kOrdered && !fill_only && row >= a.ordered_from) {
     // No order and nowhere to keep one: each of the later scans finds its row for itself, the
     // (row - kAdvFirstRows)-th longest of the later rows (five barriers and a few hundred LDS operations
@@ -418,11 +433,8 @@ __global__ __launch_bounds__(W * kWave, W == 4 ? (Dense && Layout == kPacked ? 5
     } else {
       row = kth_row_by_length<W>([&](int32_t i) { return class_of_length(a.lengths[i], a.T); }, kAdvFirstRows, a.B, row - kAdvFirstRows);
     }
-    if ((unsigned)row >= (unsigned)a.B) return;
+    if ((unsigned)row >= (unsigned)a.B) return false;
   }
-  const int tid = threadIdx.x;
-  const int lane = tid & (kWave - 1);
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int64_t T = a.T;
   int64_t L, base = (int64_t)row * T, head = 0;
   if constexpr (Packed) {
@@ -430,7 +442,7 @@ __global__ __launch_bounds__(W * kWave, W == 4 ? (Dense && Layout == kPacked ? 5
     int64_t first = a.cu[row], end = a.cu[row + 1];
     first = first < 0 ? 0 : (first > a.N ? a.N : first);
     end = end > a.N ? a.N : end;
-    if (end <= first) return;
+    if (end <= first) return false;
     base = first & ~(int64_t)(kPerLane - 1);
     head = first - base;
     L = end - base;
@@ -451,11 +463,59 @@ __global__ __launch_bounds__(W * kWave, W == 4 ? (Dense && Layout == kPacked ? 5
   const bool last_given = stopped || !Dense;
   float r_last = a.r_fail;
   if (!Dense && !stopped) r_last = a.terminal_reward[row];
-  const float* rrow = Dense ? a.rewards + base : nullptr;
-  const float* vrow = a.values + base;
-  float* drow = a.td + base;
-  float* arow = a.adv + base;
-  float* trow = a.returns ? a.returns + base : nullptr;
+  r.row = row;
+  r.T = T;
+  r.L = L;
+  r.head = head;
+  r.last_given = last_given;
+  r.r_last = r_last;
+  r.rewards = Dense ? a.rewards + base : nullptr;
+  r.values = a.values + base;
+  r.td = a.td + base;
+  r.adv = a.adv + base;
+  r.returns = a.returns ? a.returns + base : nullptr;
+  return true;
+}
+
+
+// The sums of a row's n advantages from those of its threads: lanes, then waves, in a fixed order.
+template <int W>
+__device__ __forceinline__ void leave_row_stats(const AdvArgs& a, int32_t row, double s1, double s2, double shift, int64_t n) {
+  __shared__ double s_stats[2][W];
+  const int wave = threadIdx.x >> 6;
+  s1 = wave_sum_f64(s1);
+  s2 = wave_sum_f64(s2);
+  if ((threadIdx.x & (kWave - 1)) == 0) {
+    s_stats[0][wave] = s1;
+    s_stats[1][wave] = s2;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double t1 = 0.0, t2 = 0.0;
+    for (int w = 0; w < W; ++w) {
+      t1 += s_stats[0][w];
+      t2 += s_stats[1][w];
+    }
+    a.row_stats[row] = AdvRowStats{t1, t2, shift, (long long)n};
+  }
+}
+
+template <bool Dense, RowLayout Layout, int W>
+__global__ __launch_bounds__(W * kWave, W == 4 ? (Dense && Layout == kPacked ? 5 : 6) : 8) void espo_advantages_kernel(AdvArgs a) {
+  constexpr bool Packed = Layout == kPacked, Span = Layout != kAligned;
+  constexpr int kTile = W * kWaveTokens;
+  __shared__ float s_tot[2][W];  // wave totals, double-buffered by tile parity
+  Row r;
+  if (!open_row<Dense, Layout, W>(a, r)) return;
+  const int tid = threadIdx.x;
+  const int lane = tid & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int32_t row = r.row;
+  const int64_t T = r.T, L = r.L, head = r.head;
+  const bool fill_only = r.fill_only, last_given = r.last_given;
+  const float r_last = r.r_last;
+  const float *const rrow = r.rewards, *const vrow = r.values;
+  float *const drow = r.td, *const arow = r.adv, *const trow = r.returns;
 
   const int64_t ntiles = (T + kTile - 1) / kTile;
   const int64_t nvalid = (L + kTile - 1) / kTile;  // tiles that hold at least one valid token
@@ -591,34 +651,212 @@ __global__ __launch_bounds__(W * kWave, W == 4 ? (Dense && Layout == kPacked ? 5
       }
     }
   }
-  if (want_stats) {  // lanes, then waves, in a fixed order
-    __shared__ double s_stats[2][W];
-    st_s1 = wave_sum_f64(st_s1);
-    st_s2 = wave_sum_f64(st_s2);
-    if (lane == 0) {
-      s_stats[0][wave] = st_s1;
-      s_stats[1][wave] = st_s2;
+  if (want_stats) leave_row_stats<W>(a, row, st_s1, st_s2, st_shift, L - head);
+}
+
+// The same walk in workgroups of 8 waves, each of which has two of a tile's 16 spans of 256 tokens: the same scan over the same spans, so
+// td and adv are the same bits.  For batches that give every compute unit two rows: a launch's waves start over some 4 us
+// where 512 rows have 16 each, which is a third of what such a batch takes.  us per call, 16 waves -> 8, lengths U[64, T]: 512 rows, T = 8192:
+// dense 12.2 -> 10.3, with the rows' sums 14.2 -> 12.0, terminal rewards with targets 13.6 -> 12.4, without the fill 10.3 -> 9.1, back to back 11.7 -> 10.9;
+// 1024 rows, T = 6000: 20.2 -> 18.9; T = 16384: 39.3 -> 38.6, without the fill 27.3 -> 24.8.  (A wave's two spans next to each
+// other: 40 instead of 37.4 back to back.  Four spans and 4 waves: without the fill 8.0 and 25.7, padding filled 12.6 and 49.)
+template <bool Dense, RowLayout Layout>
+__global__ __launch_bounds__(8 * kWave, 4) void espo_advantages_spans_kernel(AdvArgs a) {
+  constexpr bool Packed = Layout == kPacked, Span = Layout != kAligned;
+  constexpr int W = 8, G = 2, kSpans = W * G;
+  constexpr int kTile = kSpans * kWaveTokens;
+  __shared__ float s_tot[2][kSpans];  // the spans' totals, double-buffered by tile parity
+  Row r;
+  if (!open_row<Dense, Layout, W>(a, r)) return;
+  const int tid = threadIdx.x;
+  const int lane = tid & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int32_t row = r.row;
+  const int64_t T = r.T, L = r.L, head = r.head;
+  const bool fill_only = r.fill_only, last_given = r.last_given;
+  const float r_last = r.r_last;
+  const float *const rrow = r.rewards, *const vrow = r.values;
+  float *const drow = r.td, *const arow = r.adv, *const trow = r.returns;
+
+  const int64_t ntiles = (T + kTile - 1) / kTile;
+  const int64_t nvalid = (L + kTile - 1) / kTile;  // tiles that hold at least one valid token
+  // Span g of a tile is the lane's tokens in its wave's g-th; positions count from the tile's first token, whose address
+  // is uniform (with 64-bit positions of the row the kernel did not fit its registers).
+  auto place = [&](int g) { return ((kSpans - g * W) * kWave - 1 - tid) * kPerLane; };  // backwards: thread 0 holds the last tokens
+  auto in_tile = [&](int64_t t, int64_t k) {  // position t of the row, a little beyond the tile's end at most if it lies farther on
+    const int64_t off = t - k * kTile;
+    return (int32_t)(off < 0 ? 0 : off < kTile + 8 ? off : kTile + 8);
+  };
+  auto put = [&](float* out, int64_t k, int g, const float x[kPerLane]) {  // what the row owns of four positions
+    if constexpr (Span) store_span(out + k * kTile, place(g), in_tile(head, k), in_tile(Packed ? L : T, k), x);
+    else store4(out + k * kTile, place(g), in_tile(T, k), x);
+  };
+  auto load = [&](int64_t k, int g) {
+    return load_tile<Dense>(Dense ? rrow + k * kTile : nullptr, vrow + k * kTile, place(g), in_tile(L, k), lane == 0);
+  };
+  // tiles wholly beyond the trajectory: outputs are exactly zero
+  const float zero[kPerLane] = {0, 0, 0, 0};
+  if (fill_only) {
+    for (int64_t k = ntiles - 1; k >= nvalid; --k) {
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        put(drow, k, g, zero);
+        put(arow, k, g, zero);
+        if (trow) put(trow, k, g, zero);
+      }
+    }
+    return;
+  }
+  if (nvalid == 0) {
+    if (!Packed && a.zero_padding && T <= kTile) {  // a row of one tile has no workgroup that only fills
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        put(drow, 0, g, zero);
+        put(arow, 0, g, zero);
+        if (trow) put(trow, 0, g, zero);
+      }
+    }
+    if (!Packed && a.row_stats && tid == 0) a.row_stats[row] = AdvRowStats{0.0, 0.0, 0.0, 0};
+    return;
+  }
+  // Sums of the row's advantages for the batch statistics, in double about the advantage of the row's
+  // last token (r - V there: nothing is bootstrapped beyond the end), which every thread can form.
+  const bool want_stats = !Packed && a.row_stats != nullptr;
+  double st_shift = 0.0, st_s1 = 0.0, st_s2 = 0.0;
+  if (want_stats) st_shift = (double)((last_given ? r_last : rrow[L - 1]) - vrow[L - 1]);
+
+  // per-lane weights of the cross-row scan steps and of the carry into this lane and this wave
+  const float w_b15 = pow_from_table<5>(a.clane, (lane & 15) + 1);  // from lane 15 of the row before
+  const float w_b31 = pow_from_table<6>(a.clane, (lane & 31) + 1);  // from lane 31
+  const float w_lane = pow_from_table<6>(a.clane, lane);            // c^(4 lane): the wave's carry-in seen from this lane
+  float w_wave[G];                                                  // c^(256 span): the tile's carry-in seen from this span
+#pragma unroll
+  for (int g = 0; g < G; ++g) w_wave[g] = pow_from_table<4>(a.cwave, g * W + wave);
+
+  float carry = 0.0f;  // A at the first token of the tile processed before (the later one)
+  TileIn cur[G];
+#pragma unroll
+  for (int g = 0; g < G; ++g) cur[g] = load(nvalid - 1, g);
+  for (int64_t k = nvalid - 1; k >= 0; --k) {
+    TileIn nxt[G];
+    if (k > 0) {  // the earlier tile, in flight during the scan
+#pragma unroll
+      for (int g = 0; g < G; ++g) nxt[g] = load(k - 1, g);
+    }
+
+    float d[G][kPerLane], loc[G][kPerLane], s[G];
+    const int par = (int)(k & 1);
+    const int32_t end = in_tile(L, k);
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const TileIn& in = cur[g];
+      // V_{t+1} of the lane's last token: first value of the lane that holds the following tokens
+      float vnext = dpp_f32<kDppWaveShr1, 0xf>(0.0f, in.v[0]);
+      if (lane == 0) vnext = in.halo;
+
+      // delta_t and the recurrence over the lane's 4 tokens, later tokens first
+      const int32_t rem = end - place(g);  // valid tokens from the lane's first on (may be <= 0 or large)
+      float acc = 0.0f;
+      if (__builtin_amdgcn_ballot_w64(rem <= kPerLane) == 0) {  // whole wave strictly inside the trajectory
+#pragma unroll
+        for (int j = kPerLane - 1; j >= 0; --j) {
+          const float vn = (j == kPerLane - 1) ? vnext : in.v[j + 1];
+          d[g][j] = (in.r[j] + a.gamma * vn) - in.v[j];
+          acc = d[g][j] + a.c * acc;
+          loc[g][j] = acc;
+        }
+      } else {
+#pragma unroll
+        for (int j = kPerLane - 1; j >= 0; --j) {
+          float vn = (j == kPerLane - 1) ? vnext : in.v[j + 1];
+          if (j + 1 >= rem) vn = 0.0f;                        // no bootstrap beyond the last token
+          float r = in.r[j];
+          if (last_given && j + 1 == rem) r = r_last;
+          float dj = (r + a.gamma * vn) - in.v[j];
+          if (j >= rem) dj = 0.0f;
+          d[g][j] = dj;
+          acc = dj + a.c * acc;
+          loc[g][j] = acc;
+        }
+      }
+      s[g] = acc;
+    }
+    // inclusive prefix over the lanes: s_i = sum_{i' <= i} c^(4 (i - i')) acc_i', step by step for all spans
+#pragma unroll
+    for (int g = 0; g < G; ++g) s[g] = scan_step<kDppRowShr1, 0xf>(s[g], a.clane[0]);
+#pragma unroll
+    for (int g = 0; g < G; ++g) s[g] = scan_step<kDppRowShr2, 0xf>(s[g], a.clane[1]);
+#pragma unroll
+    for (int g = 0; g < G; ++g) s[g] = scan_step<kDppRowShr4, 0xf>(s[g], a.clane[2]);
+#pragma unroll
+    for (int g = 0; g < G; ++g) s[g] = scan_step<kDppRowShr8, 0xf>(s[g], a.clane[3]);
+#pragma unroll
+    for (int g = 0; g < G; ++g) s[g] = scan_step<kDppBcast15, 0xa>(s[g], w_b15);
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      s[g] = scan_step<kDppBcast31, 0xc>(s[g], w_b31);
+      if (lane == kWave - 1) s_tot[par][g * W + wave] = s[g];
     }
     __syncthreads();
-    if (tid == 0) {
-      double t1 = 0.0, t2 = 0.0;
-      for (int w = 0; w < W; ++w) {
-        t1 += s_stats[0][w];
-        t2 += s_stats[1][w];
+    // the same scan over the spans' totals, one per lane of the first row
+    float p = lane < kSpans ? s_tot[par][lane] : 0.0f;
+    p = scan_step<kDppRowShr1, 0xf>(p, a.cwave[0]);
+    p = scan_step<kDppRowShr2, 0xf>(p, a.cwave[1]);
+    p = scan_step<kDppRowShr4, 0xf>(p, a.cwave[2]);
+    p = scan_step<kDppRowShr8, 0xf>(p, a.cwave[3]);
+    const float carry_in = carry;
+    carry = fmaf(a.cwave[4], carry, uniform_f32(p, kSpans - 1));  // A at the tile's first token
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      // A at the first token after this span
+      const int span = g * W + wave;
+      const float before = span > 0 ? uniform_f32(p, span - 1) : 0.0f;
+      const float wave_in = fmaf(w_wave[g], carry_in, before);
+      // A at the first token after this lane's tokens
+      const float s_prev = dpp_f32<kDppWaveShr1, 0xf>(0.0f, s[g]);
+      const float a_next = fmaf(w_lane, wave_in, s_prev);
+      const int32_t rem = end - place(g);
+
+      float outA[kPerLane];
+#pragma unroll
+      for (int j = 0; j < kPerLane; ++j) outA[j] = (j < rem) ? fmaf(a.cj[kPerLane - j], a_next, loc[g][j]) : 0.0f;
+      float outR[kPerLane] = {0, 0, 0, 0};  // value targets: the lambda-return A_t + V(s_t)
+      if (trow) {
+#pragma unroll
+        for (int j = 0; j < kPerLane; ++j) outR[j] = (j < rem) ? outA[j] + cur[g].v[j] : 0.0f;
       }
-      a.row_stats[row] = AdvRowStats{t1, t2, st_shift, (long long)(L - head)};
+      if ((!Packed && a.zero_padding) || rem > 0) {  // lanes wholly beyond L only ever hold zeros
+        put(drow, k, g, d[g]);
+        put(arow, k, g, outA);
+        if (trow) put(trow, k, g, outR);
+      }
+      if (want_stats) {
+#pragma unroll
+        for (int j = 0; j < kPerLane; ++j)
+          if (j < rem && (!Span || place(g) + j >= in_tile(head, k))) {
+            const double dd = (double)outA[j] - st_shift;
+            st_s1 += dd;
+            st_s2 += dd * dd;
+          }
+      }
+    }
+    if (k > 0) {
+#pragma unroll
+      for (int g = 0; g < G; ++g) cur[g] = nxt[g];
     }
   }
+  if (want_stats) leave_row_stats<W>(a, row, st_s1, st_s2, st_shift, L - head);
 }
 
 __global__ __launch_bounds__(16 * kWave) void length_order_kernel(const int32_t* __restrict__ lengths, int32_t B, int64_t T,
                                                                   int32_t* __restrict__ order) {
-  sort_rows_by_length(lengths, 0, B, T, order);
+  sort_rows_by_length<16>(lengths, 0, B, T, order);
 }
 
 template <RowLayout Layout>
-void (*pick_kernel(bool dense, bool shortrows))(AdvArgs) {
-  if (shortrows) return dense ? espo_advantages_kernel<true, Layout, 4> : espo_advantages_kernel<false, Layout, 4>;
+void (*pick_kernel(bool dense, int waves))(AdvArgs) {
+  if (waves == 4) return dense ? espo_advantages_kernel<true, Layout, 4> : espo_advantages_kernel<false, Layout, 4>;
+  if (waves == 8) return dense ? espo_advantages_spans_kernel<true, Layout> : espo_advantages_spans_kernel<false, Layout>;
   return dense ? espo_advantages_kernel<true, Layout, 16> : espo_advantages_kernel<false, Layout, 16>;
 }
 
@@ -663,13 +901,17 @@ int launch_advantages(const float* rewards, const float* terminal_reward, const 
   const bool sort_here = can_sort && a.ordered_from < B;
   a.sorted = sort_here ? sorted : nullptr;
   a.sync = sort_here ? sync : nullptr;
+  // Two spans a wave where every compute unit has more than one row, unless three arrays of long rows are written
+  // (targets, T = 16383: 512 rows back to back 23.0 us with 16 waves, 23.8 with 8; terminal rewards, padding filled 30.3, 30.6); fewer
+  // rows have the chip to themselves, and more waves walk each faster (8 rows of 16384: 7.7 us, with 8 waves 8.0).
+  const int waves = shortrows ? 4 : B <= kAdvOnePerUnit || (returns && longest > 3 * kAdvSortTokens) ? 16 : 8;
   const int64_t tile = (shortrows ? 4 : 16) * kWaveTokens;
   const bool fillers = cu == nullptr && zero_padding && longest > tile;
-  const dim3 grid((unsigned)((fillers ? 2 * B : B) + (sort_here ? 1 : 0))), block(shortrows ? 4 * kWave : 16 * kWave);
+  const dim3 grid((unsigned)((fillers ? 2 * B : B) + (sort_here ? 1 : 0))), block(waves * kWave);
   void (*kernel)(AdvArgs);
-  if (cu) kernel = pick_kernel<kPacked>(rewards != nullptr, shortrows);
-  else if (T % 4 == 0) kernel = pick_kernel<kAligned>(rewards != nullptr, shortrows);
-  else kernel = pick_kernel<kShifted>(rewards != nullptr, shortrows);
+  if (cu) kernel = pick_kernel<kPacked>(rewards != nullptr, waves);
+  else if (T % 4 == 0) kernel = pick_kernel<kAligned>(rewards != nullptr, waves);
+  else kernel = pick_kernel<kShifted>(rewards != nullptr, waves);
   hipLaunchKernelGGL(kernel, grid, block, 0, stream, a);
   return hipGetLastError() == hipSuccess ? ESPO_OK : ESPO_EHIP;
 }

@@ -364,6 +364,22 @@ def test_packed_config5_full_size():
     _say(f"  terminal form: worst scaled error {worst:.2e}")
 
 
+# From 257 rows on a workgroup of 8 waves walks a row, two spans of 256 tokens of a tile of 4096 to a wave (16 waves where three arrays
+# of rows beyond 13824 tokens are written): both sides of these lines, lengths at the edges of spans, of a wave's first and second one, and of tiles.
+@pytest.mark.parametrize("B,T", [(256, 8192), (257, 8192), (257, 8195), (513, 4612), (257, 4097), (257, 13824), (257, 13828)])
+@pytest.mark.parametrize("gamma,lam", [(1.0, 0.95), (0.999, 0.9995)])
+def test_rows_walked_by_two_spans_a_wave(B, T, gamma, lam):
+    _say(f"[case] two spans a wave B={B} T={T} gamma={gamma} lambda={lam}")
+    edges = [0, 1, 255, 256, 257, 2047, 2048, 2049, 2305, 4095, 4096, 4097, 6143, 6145, 8191, 8192, 8193, T - 1, T]
+    L = [min(edges[b % len(edges)], T) for b in range(B)]
+    r, v, Lt, s = _batch(B, T, seed=T + B, lengths=L)
+    H.check_advantages(r, v, Lt, s, -1.0, gamma, lam)
+    term = torch.randn(B, generator=torch.Generator().manual_seed(B)).cuda()
+    for fill, returns in ((True, True), (False, True), (False, False)):
+        H.check_advantages_terminal(v, Lt, s, term, -1.0, gamma, lam, zero_padding=fill, want_returns=returns)
+    _check_packed_both_forms([max(n - b % 3, 0) for b, n in enumerate(L)], seed=T, gamma=gamma, lam=lam)
+
+
 @pytest.mark.parametrize("part", range(4))
 def test_packed_seeded_sweep(part):
     _say(f"[case] packed advantages, seeded sweep, part {part} (100 cases, both reward forms each)")
