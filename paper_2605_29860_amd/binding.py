@@ -142,6 +142,29 @@ def _check(rc: int):
         raise EspoError(rc, load_library().espo_strerror(rc).decode())
 
 
+def _native():
+    """The module beside the library that checks tensors and calls the C functions (csrc/espo_tensor.cpp)."""
+    try:
+        from . import _espo_tensor
+    except ImportError as e:
+        raise FileNotFoundError(f"the tensor checker next to {_LIB_PATH} is missing or does not load ({e}): build it with "
+                                "`python -m paper_2605_29860_amd.build`") from e
+    return _espo_tensor
+
+
+_entries = {}  # the library's functions, by name, as native callables
+
+
+def _entry(lib, name: str):
+    """C function `name` of `lib`: called natively if `lib` is the loaded library, else whatever `lib` has under that name."""
+    if lib is not _lib:
+        return getattr(lib, name)
+    fn = _entries.get(name)
+    if fn is None:
+        fn = _entries[name] = _native().entry(name, C.cast(getattr(lib, name), C.c_void_p).value)
+    return fn
+
+
 def _on_gpu(t: torch.Tensor) -> bool:
     return t.is_cuda
 
@@ -149,13 +172,8 @@ def _on_gpu(t: torch.Tensor) -> bool:
 def _address(*args):
     """`address` of the tensor checker (csrc/espo_tensor.cpp), loaded by the first call that needs it."""
     global _address
-    try:
-        from ._espo_tensor import address
-    except ImportError as e:
-        raise FileNotFoundError(f"the tensor checker next to {_LIB_PATH} is missing or does not load ({e}): build it with "
-                                "`python -m paper_2605_29860_amd.build`") from e
-    _address = address
-    return address(*args)
+    _address = _native().address
+    return _address(*args)
 
 
 def _dev(t: torch.Tensor, dtype, name: str, numel: int | None = None, shape: tuple | None = None):
@@ -171,7 +189,23 @@ def _dev(t: torch.Tensor, dtype, name: str, numel: int | None = None, shape: tup
     return _address(t, dtype, name, numel, shape)
 
 
+def _checker(lib):
+    """What the entry points of `lib` look their tensors over with: `_dev` as one native call, arguments in order, if `lib` is the
+    loaded library (`_dev` itself where another stands in for it)."""
+    global _gpu_address
+    if lib is not _lib:
+        return _dev
+    if _gpu_address is None:
+        _gpu_address = _native().gpu_address
+    return _gpu_address
+
+
+_gpu_address = None
+
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)  # the handle alone, without a Stream object around it
+
+
+_current_device = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device  # (a tensor on the GPU has initialised it)
 
 
 def _stream(stream):
@@ -179,7 +213,7 @@ def _stream(stream):
         return stream.cuda_stream
     if _raw_stream is None:
         return torch.cuda.current_stream().cuda_stream
-    return _raw_stream(torch.cuda.current_device())
+    return _raw_stream(_current_device())
 
 
 def espo_debug_math_errors(out: torch.Tensor, stream=None) -> None:
@@ -228,11 +262,13 @@ def espo_batch_stats(regret: torch.Tensor, lengths: torch.Tensor, stopped: torch
         raise ValueError("regret must be [B, T]")
     B, T = regret.shape
     ctrl = _BatchCtrl(alpha_ema, eta_beta, target_rate, beta_min, beta_max)
-    _check(load_library().espo_batch_stats(
-        _dev(regret, torch.float32, "regret"), _dev(lengths, torch.int32, "lengths", numel=B),
-        _dev(stopped, torch.uint8, "stopped", numel=B),
-        B, T, float(mu_g), float(var_g), float(beta), ctrl, _dev(out, torch.uint8, "out", numel=BATCH_RESULT_BYTES),
-        _dev(workspace, torch.uint8, "workspace"), workspace.numel(), _stream(stream)))
+    lib = load_library()
+    dev = _checker(lib)
+    call = _entry(lib, "espo_batch_stats")
+    _check(call(dev(regret, torch.float32, "regret", None, None), dev(lengths, torch.int32, "lengths", B, None),
+                dev(stopped, torch.uint8, "stopped", B, None), B, T, float(mu_g), float(var_g), float(beta), ctrl,
+                dev(out, torch.uint8, "out", BATCH_RESULT_BYTES, None), dev(workspace, torch.uint8, "workspace", None, None),
+                workspace.numel(), _stream(stream)))
 
 
 def espo_batch_stats_static(regret: torch.Tensor, lengths: torch.Tensor, stopped: torch.Tensor, mu_g: float, var_g: float,
@@ -243,11 +279,12 @@ def espo_batch_stats_static(regret: torch.Tensor, lengths: torch.Tensor, stopped
         raise ValueError("regret must be [B, T]")
     B, T = regret.shape
     ctrl = _BatchCtrl(alpha_ema, eta_beta, target_rate, beta_min, beta_max)
-    _check(load_library().espo_batch_stats_static(
-        _dev(regret, torch.float32, "regret"), _dev(lengths, torch.int32, "lengths", numel=B),
-        _dev(stopped, torch.uint8, "stopped", numel=B),
-        B, T, float(mu_g), float(var_g), float(beta), ctrl, _dev(out, torch.uint8, "out", numel=BATCH_RESULT_BYTES),
-        _stream(stream)))
+    lib = load_library()
+    dev = _checker(lib)
+    call = _entry(lib, "espo_batch_stats_static")
+    _check(call(dev(regret, torch.float32, "regret", None, None), dev(lengths, torch.int32, "lengths", B, None),
+                dev(stopped, torch.uint8, "stopped", B, None), B, T, float(mu_g), float(var_g), float(beta), ctrl,
+                dev(out, torch.uint8, "out", BATCH_RESULT_BYTES, None), _stream(stream)))
 
 
 def read_batch_result(out: torch.Tensor) -> dict:
@@ -285,6 +322,7 @@ def espo_step(logits: torch.Tensor, temperature: float, seed: int, step: int, va
     workgroups) or None.  With any of `margin_scale`, `waves`, `chunks` the call goes through
     `espo_debug_step` (include/espo_debug.h), which exposes those choices for this call."""
     lib = load_library()
+    dev = _checker(lib)
     if logits.dtype == torch.bfloat16:
         dt = ESPO_BF16
     elif logits.dtype == torch.float32:
@@ -300,18 +338,18 @@ def espo_step(logits: torch.Tensor, temperature: float, seed: int, step: int, va
         raise EspoError(-1, "V exceeds the width of logits")
     ws_ptr, ws_bytes = None, 0
     if workspace is not None:
-        ws_ptr, ws_bytes = _dev(workspace, torch.uint8, "workspace"), workspace.numel()
+        ws_ptr, ws_bytes = dev(workspace, torch.uint8, "workspace", None, None), workspace.numel()
     p = params._c()
     args = [logits.data_ptr(), dt, B, V, row_stride, float(temperature), int(seed),
-            int(step), _dev(values, torch.float32, "values", numel=B), p,
-            _dev(z, torch.float32, "z", numel=B), _dev(alive, torch.uint8, "alive", numel=B),
-            _dev(stop_step, torch.int32, "stop_step", numel=B), _dev(tokens, torch.int32, "tokens", numel=B),
-            _dev(regret, torch.float32, "regret", numel=B), _dev(logprob, torch.float32, "logprob", numel=B),
-            _dev(entropy, torch.float32, "entropy", numel=B), ws_ptr, ws_bytes, _stream(stream)]
+            int(step), dev(values, torch.float32, "values", B, None), p,
+            dev(z, torch.float32, "z", B, None), dev(alive, torch.uint8, "alive", B, None),
+            dev(stop_step, torch.int32, "stop_step", B, None), dev(tokens, torch.int32, "tokens", B, None),
+            dev(regret, torch.float32, "regret", B, None), dev(logprob, torch.float32, "logprob", B, None),
+            dev(entropy, torch.float32, "entropy", B, None), ws_ptr, ws_bytes, _stream(stream)]
     if margin_scale is None and waves is None and chunks is None:
-        rc = lib.espo_step(*args)
+        rc = _entry(lib, "espo_step")(*args)
     else:
-        rc = lib.espo_debug_step(*args, 1.0 if margin_scale is None else float(margin_scale), int(waves or 0), int(chunks or 0))
+        rc = _entry(lib, "espo_debug_step")(*args, 1.0 if margin_scale is None else float(margin_scale), int(waves or 0), int(chunks or 0))
     _check(rc)
 
 
@@ -320,15 +358,15 @@ def espo_advantages(rewards: torch.Tensor, values: torch.Tensor, lengths: torch.
                     td: torch.Tensor, adv: torch.Tensor, stream=None) -> None:
     """TD errors and GAE on truncated trajectories; see `espo_advantages` in include/espo.h."""
     lib = load_library()
+    dev = _checker(lib)
     if rewards.dim() != 2:
         raise TypeError("rewards: need [B, T]")
     B, T = shape = rewards.shape
-    rc = lib.espo_advantages(_dev(rewards, torch.float32, "rewards"), _dev(values, torch.float32, "values", shape=shape),
-                             _dev(lengths, torch.int32, "lengths", numel=B), _dev(stopped, torch.uint8, "stopped", numel=B),
-                             B, T, float(r_fail), float(gamma), float(lam),
-                             _dev(td, torch.float32, "td", shape=shape), _dev(adv, torch.float32, "adv", shape=shape),
-                             _stream(stream))
-    _check(rc)
+    call = _entry(lib, "espo_advantages")
+    _check(call(dev(rewards, torch.float32, "rewards", None, None), dev(values, torch.float32, "values", None, shape),
+                dev(lengths, torch.int32, "lengths", B, None), dev(stopped, torch.uint8, "stopped", B, None), B, T, float(r_fail),
+                float(gamma), float(lam), dev(td, torch.float32, "td", None, shape), dev(adv, torch.float32, "adv", None, shape),
+                _stream(stream)))
 
 
 def espo_advantages_ws_bytes(B: int) -> int:
@@ -338,9 +376,11 @@ def espo_advantages_ws_bytes(B: int) -> int:
 def espo_length_order(lengths: torch.Tensor, T: int, order: torch.Tensor, stream=None) -> None:
     """The rows by length, longest first; see `espo_length_order` in include/espo.h."""
     lib = load_library()
+    dev = _checker(lib)
     B = lengths.numel()
-    _check(lib.espo_length_order(_dev(lengths, torch.int32, "lengths"), B, int(T), _dev(order, torch.int32, "order", numel=B),
-                                 _stream(stream)))
+    call = _entry(lib, "espo_length_order")
+    _check(call(dev(lengths, torch.int32, "lengths", None, None), B, int(T), dev(order, torch.int32, "order", B, None),
+                _stream(stream)))
 
 
 def espo_advantages_ws(rewards: torch.Tensor, values: torch.Tensor, lengths: torch.Tensor,
@@ -350,17 +390,16 @@ def espo_advantages_ws(rewards: torch.Tensor, values: torch.Tensor, lengths: tor
     """espo_advantages with the rows' sums left in `workspace` and, optionally, the rows taken in a
     given order; see `espo_advantages_ws` in include/espo.h."""
     lib = load_library()
+    dev = _checker(lib)
     if rewards.dim() != 2:
         raise TypeError("rewards: need [B, T]")
     B, T = shape = rewards.shape
-    rc = lib.espo_advantages_ws(_dev(rewards, torch.float32, "rewards"), _dev(values, torch.float32, "values", shape=shape),
-                                _dev(lengths, torch.int32, "lengths", numel=B), _dev(stopped, torch.uint8, "stopped", numel=B),
-                                B, T, float(r_fail), float(gamma), float(lam),
-                                _dev(td, torch.float32, "td", shape=shape), _dev(adv, torch.float32, "adv", shape=shape),
-                                _dev(order, torch.int32, "order", numel=B),
-                                _dev(workspace, torch.uint8, "workspace"), workspace.numel() if workspace is not None else 0,
-                                _stream(stream))
-    _check(rc)
+    call = _entry(lib, "espo_advantages_ws")
+    _check(call(dev(rewards, torch.float32, "rewards", None, None), dev(values, torch.float32, "values", None, shape),
+                dev(lengths, torch.int32, "lengths", B, None), dev(stopped, torch.uint8, "stopped", B, None), B, T, float(r_fail),
+                float(gamma), float(lam), dev(td, torch.float32, "td", None, shape), dev(adv, torch.float32, "adv", None, shape),
+                dev(order, torch.int32, "order", B, None), dev(workspace, torch.uint8, "workspace", None, None),
+                workspace.numel() if workspace is not None else 0, _stream(stream)))
 
 
 def espo_whiten_from_ws(adv: torch.Tensor, lengths: torch.Tensor, out: torch.Tensor, workspace: torch.Tensor,
@@ -369,6 +408,7 @@ def espo_whiten_from_ws(adv: torch.Tensor, lengths: torch.Tensor, out: torch.Ten
     """espo_whiten from the sums that espo_advantages_ws left in `workspace`; see
     `espo_whiten_from_ws` in include/espo.h."""
     lib = load_library()
+    dev = _checker(lib)
     if adv.dim() != 2:
         raise TypeError("adv: need [B, T]")
     B, T = adv.shape
@@ -376,11 +416,11 @@ def espo_whiten_from_ws(adv: torch.Tensor, lengths: torch.Tensor, out: torch.Ten
         raise TypeError("out: need the shape of adv; lengths: need [B]")
     if stats is not None and stats.numel() < 3:
         raise TypeError("stats: need 3 doubles")
-    rc = lib.espo_whiten_from_ws(_dev(adv, torch.float32, "adv"), _dev(lengths, torch.int32, "lengths", numel=B), B, T,
-                                 float(eps), int(bool(shift_mean)), int(bool(unbiased)), _dev(out, torch.float32, "out"),
-                                 _dev(stats, torch.float64, "stats", numel=3), _dev(workspace, torch.uint8, "workspace"),
-                                 workspace.numel() if workspace is not None else 0, _stream(stream))
-    _check(rc)
+    call = _entry(lib, "espo_whiten_from_ws")
+    _check(call(dev(adv, torch.float32, "adv", None, None), dev(lengths, torch.int32, "lengths", B, None), B, T, float(eps),
+                int(bool(shift_mean)), int(bool(unbiased)), dev(out, torch.float32, "out", None, None),
+                dev(stats, torch.float64, "stats", 3, None), dev(workspace, torch.uint8, "workspace", None, None),
+                workspace.numel() if workspace is not None else 0, _stream(stream)))
 
 
 def espo_whiten_workspace_bytes(B: int, T: int) -> int:
@@ -392,6 +432,7 @@ def espo_whiten(adv: torch.Tensor, lengths: torch.Tensor, out: torch.Tensor, wor
     """Whitening of the advantages over the valid tokens; see `espo_whiten` in include/espo.h.
     `adv` is [B, T] (or [N] with `lengths` = [N] for a packed batch); `out` may be `adv`."""
     lib = load_library()
+    dev = _checker(lib)
     if adv.dim() == 1:
         B, T = 1, adv.numel()
     elif adv.dim() == 2:
@@ -402,11 +443,11 @@ def espo_whiten(adv: torch.Tensor, lengths: torch.Tensor, out: torch.Tensor, wor
         raise TypeError("out: need the shape of adv; lengths: need [B]")
     if stats is not None and stats.numel() < 3:
         raise TypeError("stats: need 3 doubles")
-    rc = lib.espo_whiten(_dev(adv, torch.float32, "adv"), _dev(lengths, torch.int32, "lengths", numel=B), B, T, float(eps),
-                         int(bool(shift_mean)), int(bool(unbiased)), _dev(out, torch.float32, "out"),
-                         _dev(stats, torch.float64, "stats", numel=3), _dev(workspace, torch.uint8, "workspace"),
-                         workspace.numel() if workspace is not None else 0, _stream(stream))
-    _check(rc)
+    call = _entry(lib, "espo_whiten")
+    _check(call(dev(adv, torch.float32, "adv", None, None), dev(lengths, torch.int32, "lengths", B, None), B, T, float(eps),
+                int(bool(shift_mean)), int(bool(unbiased)), dev(out, torch.float32, "out", None, None),
+                dev(stats, torch.float64, "stats", 3, None), dev(workspace, torch.uint8, "workspace", None, None),
+                workspace.numel() if workspace is not None else 0, _stream(stream)))
 
 
 def espo_advantages_packed(values: torch.Tensor, cu_seqlens: torch.Tensor, stopped: torch.Tensor,
@@ -416,6 +457,7 @@ def espo_advantages_packed(values: torch.Tensor, cu_seqlens: torch.Tensor, stopp
     """The advantage pass over trajectories stored back to back; see `espo_advantages_packed`
     in include/espo.h.  Exactly one of `rewards` [N] and `terminal_reward` [B]."""
     lib = load_library()
+    dev = _checker(lib)
     if values.dim() != 1 or cu_seqlens.dim() != 1 or cu_seqlens.numel() != stopped.numel() + 1:
         raise TypeError("values: need [N]; cu_seqlens: need [B + 1]")
     N, B = values.numel(), stopped.numel()
@@ -424,13 +466,12 @@ def espo_advantages_packed(values: torch.Tensor, cu_seqlens: torch.Tensor, stopp
             raise TypeError(f"{name}: need [N]")
     if terminal_reward is not None and terminal_reward.numel() != B:
         raise TypeError("terminal_reward: need [B]")
-    rc = lib.espo_advantages_packed(_dev(rewards, torch.float32, "rewards"),
-                                    _dev(terminal_reward, torch.float32, "terminal_reward"),
-                                    _dev(values, torch.float32, "values"), _dev(cu_seqlens, torch.int64, "cu_seqlens"),
-                                    _dev(stopped, torch.uint8, "stopped"), B, N, float(r_fail), float(gamma), float(lam),
-                                    _dev(td, torch.float32, "td"), _dev(adv, torch.float32, "adv"),
-                                    _dev(returns, torch.float32, "returns"), _stream(stream))
-    _check(rc)
+    call = _entry(lib, "espo_advantages_packed")
+    _check(call(dev(rewards, torch.float32, "rewards", None, None), dev(terminal_reward, torch.float32, "terminal_reward", None, None),
+                dev(values, torch.float32, "values", None, None), dev(cu_seqlens, torch.int64, "cu_seqlens", None, None),
+                dev(stopped, torch.uint8, "stopped", None, None), B, N, float(r_fail), float(gamma), float(lam),
+                dev(td, torch.float32, "td", None, None), dev(adv, torch.float32, "adv", None, None),
+                dev(returns, torch.float32, "returns", None, None), _stream(stream)))
 
 
 def espo_advantages_terminal(values: torch.Tensor, lengths: torch.Tensor, stopped: torch.Tensor,
@@ -440,16 +481,15 @@ def espo_advantages_terminal(values: torch.Tensor, lengths: torch.Tensor, stoppe
     """The advantage pass when only the last reward of a row is non-zero; see
     `espo_advantages_terminal` in include/espo.h."""
     lib = load_library()
+    dev = _checker(lib)
     if values.dim() != 2:
         raise TypeError("values: need [B, T]")
     B, T = shape = values.shape
-    rc = lib.espo_advantages_terminal(_dev(values, torch.float32, "values"), _dev(lengths, torch.int32, "lengths", numel=B),
-                                      _dev(stopped, torch.uint8, "stopped", numel=B),
-                                      _dev(terminal_reward, torch.float32, "terminal_reward", numel=B), B, T,
-                                      float(r_fail), float(gamma), float(lam), int(bool(zero_padding)),
-                                      _dev(td, torch.float32, "td", shape=shape), _dev(adv, torch.float32, "adv", shape=shape),
-                                      _dev(returns, torch.float32, "returns", shape=shape), _stream(stream))
-    _check(rc)
+    call = _entry(lib, "espo_advantages_terminal")
+    _check(call(dev(values, torch.float32, "values", None, None), dev(lengths, torch.int32, "lengths", B, None),
+                dev(stopped, torch.uint8, "stopped", B, None), dev(terminal_reward, torch.float32, "terminal_reward", B, None), B, T,
+                float(r_fail), float(gamma), float(lam), int(bool(zero_padding)), dev(td, torch.float32, "td", None, shape),
+                dev(adv, torch.float32, "adv", None, shape), dev(returns, torch.float32, "returns", None, shape), _stream(stream)))
 
 
 def espo_advantages_terminal_ws(values: torch.Tensor, lengths: torch.Tensor, stopped: torch.Tensor,
@@ -460,16 +500,14 @@ def espo_advantages_terminal_ws(values: torch.Tensor, lengths: torch.Tensor, sto
     """espo_advantages_terminal with the later rows taken longest first and the rows' sums left in
     `workspace`; see `espo_advantages_terminal_ws` in include/espo.h."""
     lib = load_library()
+    dev = _checker(lib)
     if values.dim() != 2:
         raise TypeError("values: need [B, T]")
     B, T = shape = values.shape
-    rc = lib.espo_advantages_terminal_ws(_dev(values, torch.float32, "values"), _dev(lengths, torch.int32, "lengths", numel=B),
-                                         _dev(stopped, torch.uint8, "stopped", numel=B),
-                                         _dev(terminal_reward, torch.float32, "terminal_reward", numel=B), B, T,
-                                         float(r_fail), float(gamma), float(lam), int(bool(zero_padding)),
-                                         _dev(td, torch.float32, "td", shape=shape), _dev(adv, torch.float32, "adv", shape=shape),
-                                         _dev(returns, torch.float32, "returns", shape=shape),
-                                         _dev(order, torch.int32, "order", numel=B),
-                                         _dev(workspace, torch.uint8, "workspace"), workspace.numel() if workspace is not None else 0,
-                                         _stream(stream))
-    _check(rc)
+    call = _entry(lib, "espo_advantages_terminal_ws")
+    _check(call(dev(values, torch.float32, "values", None, None), dev(lengths, torch.int32, "lengths", B, None),
+                dev(stopped, torch.uint8, "stopped", B, None), dev(terminal_reward, torch.float32, "terminal_reward", B, None), B, T,
+                float(r_fail), float(gamma), float(lam), int(bool(zero_padding)), dev(td, torch.float32, "td", None, shape),
+                dev(adv, torch.float32, "adv", None, shape), dev(returns, torch.float32, "returns", None, shape),
+                dev(order, torch.int32, "order", B, None), dev(workspace, torch.uint8, "workspace", None, None),
+                workspace.numel() if workspace is not None else 0, _stream(stream)))

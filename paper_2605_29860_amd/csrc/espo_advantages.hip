@@ -884,9 +884,11 @@ int launch_advantages(const float* rewards, const float* terminal_reward, const 
   a.gamma = gamma;
   const double c = (double)gamma * (double)lambda;
   a.c = (float)c;
-  for (int j = 0; j <= kPerLane; ++j) a.cj[j] = (float)pow(c, (double)j);
-  for (int k = 0; k < 6; ++k) a.clane[k] = (float)pow(c, (double)(kPerLane << k));
-  for (int k = 0; k < 5; ++k) a.cwave[k] = (float)pow(c, (double)((kPerLane * kWave) << k));
+  double power = 1.0;
+  for (int j = 0; j <= kPerLane; ++j, power *= c) a.cj[j] = (float)power;
+  static_assert(kPerLane == 4 && kWave == 64, "the squares below");
+  power = (c * c) * (c * c);
+  for (int k = 0; k < 11; ++k, power *= power) (k < 6 ? a.clane[k] : a.cwave[k - 6]) = (float)power;  // c^(4 2^k)
   a.td = td;
   a.adv = adv;
   // Workgroups of 4 waves for short rows: more rows at once, fewer waves without work, no second round of workgroups
