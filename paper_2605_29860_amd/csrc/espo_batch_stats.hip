@@ -39,6 +39,8 @@ constexpr int kStatQuads = 4;                        // groups of four positions
 constexpr int kStatItem = kWave * 4 * kStatQuads;    // positions per item: 1024
 constexpr int kStatUnroll = 4;                       // items of a wave, their loads in flight together
 constexpr int kRowLoads = 4;                         // 16-byte loads of a lane in flight when a workgroup takes whole rows
+constexpr uint32_t kDeepLoads = 8;                   // the same in rows of more than kLongRow tokens
+constexpr int64_t kLongRow = 4096;
 constexpr int kShortUnroll = 2;                      // rows of a wave in flight when every row is one item
 constexpr int kMaxStatGroups = 1024;                 // partials the workspace has room for
 constexpr int kFinalThreads = 256, kFinalEach = kMaxStatGroups / kFinalThreads;  // partials per thread
@@ -181,8 +183,10 @@ __device__ __forceinline__ void write_partial(const PartialArgs& a, RowCounts& c
   if (threadIdx.x == 0) a.part[blockIdx.x] = Partial{v[0], v[1], (long long)v[2], (long long)v[3]};
 }
 
-// Aligned: T % 4 == 0, every row starts at a 16-byte boundary.
-template <bool Aligned>
+// Rows that start at 16-byte boundaries (T % 4 == 0), long ones of them, and rows that start anywhere.
+enum RowKind { kAlignedRows, kLongRows, kAnyRows };
+
+template <RowKind Kind>
 __global__ __launch_bounds__(kStatThreads) void batch_partial_kernel(PartialArgs a) {
   __shared__ double lds[4 * kStatWaves];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -192,10 +196,29 @@ __global__ __launch_bounds__(kStatThreads) void batch_partial_kernel(PartialArgs
   for (int64_t row = blockIdx.x; row < a.B; row += gridDim.x) {
     int64_t L;
     const RowSpan r = row_span(a, row, L);
-    if constexpr (Aligned) {  // 16.8 us at B = 1024, T = 16384, where the loop below takes 17.6
+    if constexpr (Kind == kLongRows) {
+      // Rounds of eight loads per lane, all on their way before the first is added: one at a time, as below, a row's loads
+      // wait for each other (us per call: B = 512, T = 8192: 9.6 -> 9.0; 1024, 16384: 16.5 -> 15.0; 8, 16384: 9.1 -> 8.4; but 300, 2000: 6.5 -> 6.6).
+      constexpr uint32_t kStride = kStatThreads * 4;
+      const uint32_t full = (uint32_t)L & ~3u;  // (T is below 2^31)
+      for (uint32_t base = 0; base < full; base += kDeepLoads * kStride) {
+        f32x4 g[kDeepLoads];
+#pragma unroll
+        for (uint32_t u = 0; u < kDeepLoads; ++u) {
+          const uint32_t t = base + u * kStride + threadIdx.x * 4;
+          if (t < full) g[u] = __builtin_nontemporal_load((const f32x4*)(r.src + t));
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < kDeepLoads; ++u)
+          if (base + u * kStride + threadIdx.x * 4 < full) add_tokens(g[u], shift, s1, s2);
+      }
+    } else if constexpr (Kind == kAlignedRows) {
       const int64_t full = L & ~(int64_t)3;
       for (int64_t t = (int64_t)threadIdx.x * 4; t < full; t += kStatThreads * 4)
         add_tokens(__builtin_nontemporal_load((const f32x4*)(r.src + t)), shift, s1, s2);
+    }
+    if constexpr (Kind != kAnyRows) {
+      const int64_t full = L & ~(int64_t)3;
       if (threadIdx.x < (unsigned)(L - full)) {  // the last one to three tokens
         const double d = (double)r.src[full + threadIdx.x] - shift;
         s1 += d;
@@ -363,9 +386,9 @@ int launch_batch_stats(const float* regret, const int32_t* lengths, const uint8_
   if (one_item)
     hipLaunchKernelGGL(batch_short_kernel, dim3(groups), dim3(kStatThreads), 0, stream, p);
   else if (T % 4 == 0)
-    hipLaunchKernelGGL(batch_partial_kernel<true>, dim3(groups), dim3(kStatThreads), 0, stream, p);
+    hipLaunchKernelGGL(T > kLongRow ? batch_partial_kernel<kLongRows> : batch_partial_kernel<kAlignedRows>, dim3(groups), dim3(kStatThreads), 0, stream, p);
   else
-    hipLaunchKernelGGL(batch_partial_kernel<false>, dim3(groups), dim3(kStatThreads), 0, stream, p);
+    hipLaunchKernelGGL(batch_partial_kernel<kAnyRows>, dim3(groups), dim3(kStatThreads), 0, stream, p);
   if (hipGetLastError() != hipSuccess) return ESPO_EHIP;
   hipLaunchKernelGGL(batch_final_kernel, dim3(1), dim3(kFinalThreads), 0, stream, p.part, groups, f);
   return hipGetLastError() == hipSuccess ? ESPO_OK : ESPO_EHIP;
