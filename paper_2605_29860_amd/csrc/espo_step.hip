@@ -1410,6 +1410,7 @@ __device__ __forceinline__ void step_row(const StepArgs& a, unsigned char* smem_
       // the shorter search included.)  A word without the mark is not there, so the workspace may hold anything before the launch; who
       // finishes a row leaves its words zero, so that nothing of this launch can pass for a result in a later one.
       const size_t unit = (size_t)row * nch + chunk;
+      asm volatile("" : "+v"(z_prev) : : "memory");  // z has arrived before this chunk's words let another one finish the row and write it
       {
         const uint32_t w = lane == 0 ? __builtin_bit_cast(uint32_t, m) : lane == 1 ? __builtin_bit_cast(uint32_t, S)
                            : lane == 2 ? __builtin_bit_cast(uint32_t, Sw) : lane == 3 ? __builtin_bit_cast(uint32_t, s_a)
