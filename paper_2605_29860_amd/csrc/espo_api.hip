@@ -132,7 +132,7 @@ int espo_debug_step(const void* logits, espo_dtype dt, int64_t B, int64_t V, int
 
 size_t espo_debug_step_workspace_bytes(int64_t B, int32_t chunks) {
   if (B <= 0 || chunks <= 1) return 0;
-  return espo::step_workspace_layout(B, chunks, nullptr, nullptr);
+  return espo::step_workspace_layout(B, chunks, nullptr);
 }
 
 int espo_debug_read(const void* src, size_t bytes, void* sink, void* stream) {

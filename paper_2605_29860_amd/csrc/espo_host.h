@@ -15,6 +15,7 @@ constexpr int64_t kMaxVocab = 400000;               // one workgroup per row: 96
 // workgroups in the launch, dynamic LDS per workgroup, and the bytes of workspace a split needs.
 struct StepPlan {
   int waves, chunks;
+  int places;  // of a row in the workspace, each with room for four chunks; its size follows from them
   size_t lds, workspace;
 };
 
@@ -23,8 +24,9 @@ struct StepPlan {
 // 256 rows on, and long rows of a batch that leaves compute units idle split, if `waves` is its choice too.
 StepPlan plan_step(int dt, int64_t B, int64_t V, bool filter, int waves, int chunks);
 
-// Bytes of workspace for B rows split `chunks` ways; where the two parts of the chunk results begin.
-size_t step_workspace_layout(int64_t B, int chunks, size_t* hi_offset, size_t* lo_offset);
+// Bytes of workspace for B rows with `places` places each (one per chunk where a split is forced); where the last of the
+// planes that hold the chunks' results begins.
+size_t step_workspace_layout(int64_t B, int places, size_t* last_plane);
 
 int launch_step(const void* logits, int dt, int64_t B, int64_t V, int64_t row_stride, float temperature,
                 uint64_t seed, int32_t step, const float* values, const espo_params& p, float margin_scale,

@@ -54,6 +54,8 @@ constexpr float kRescaleAt = 64.0f;               // advance a lane's softmax re
 // 64-bit word of its own with this mark above it, so that a word is either there as a whole or recognised as not there.
 constexpr uint32_t kMailMark = 0x4553504Fu;
 constexpr int kMailWords = 7;
+constexpr int kPartsShift = 2;                        // every place of a row's workspace has room for this power of two of chunks
+constexpr int kPlaneCount = 2 << kPartsShift;
 
 struct StepArgs {
   const void* logits;
@@ -80,7 +82,12 @@ struct StepArgs {
   // a row split over `nch` workgroups: workgroup (row, c) streams `chunk_tiles` tiles, one more for the first `chunk_extra` chunks
   int32_t nch, chunk_tiles, chunk_extra;
   unsigned long long* row_words;  // [B] 8 bytes per row at the head of the workspace, left zero for live rows
-  unsigned long long *mail_lo, *mail_hi;  // [B * nch][4] each: words 0 to 3 and 4 to 6 of what each chunk found; left zero
+  // Where the chunks of a row leave what they found, in kPlaneCount planes of [B][mail_row] words, all left zero: chunk c takes four
+  // words of plane 2 g and three of plane 2 g + 1 at place c >> part_shift, g being its low part_shift bits.  Plane 0, whose address
+  // this is, is the last in memory.
+  unsigned long long* mail;
+  size_t mail_plane;  // words of a plane
+  int32_t mail_row, part_shift;
 };
 
 
@@ -1409,13 +1416,14 @@ __device__ __forceinline__ void step_row(const StepArgs& a, unsigned char* smem_
       // to the outputs of B = 64, V = 152064 bf16, against 5000 now; B = 4, V = 150001 fp32 with the entropy, 8 chunks: 13.8 -> 11.3 us,
       // the shorter search included.)  A word without the mark is not there, so the workspace may hold anything before the launch; who
       // finishes a row leaves its words zero, so that nothing of this launch can pass for a result in a later one.
-      const size_t unit = (size_t)row * nch + chunk;
+      unsigned long long* const row_mail = a.mail + (size_t)row * a.mail_row;
+      auto mail_of = [&](int c) { return row_mail + (c >> a.part_shift) * 4 - (size_t)(c & ((1 << a.part_shift) - 1)) * 2 * a.mail_plane; };
       asm volatile("" : "+v"(z_prev) : : "memory");  // z has arrived before this chunk's words let another one finish the row and write it
       {
         const uint32_t w = lane == 0 ? __builtin_bit_cast(uint32_t, m) : lane == 1 ? __builtin_bit_cast(uint32_t, S)
                            : lane == 2 ? __builtin_bit_cast(uint32_t, Sw) : lane == 3 ? __builtin_bit_cast(uint32_t, s_a)
                            : lane == 4 ? __builtin_bit_cast(uint32_t, e_a) : lane == 5 ? __builtin_bit_cast(uint32_t, x_a) : (uint32_t)tok;
-        unsigned long long* const dst = lane < 4 ? a.mail_lo + unit * 4 + lane : a.mail_hi + unit * 4 + (lane - 4);
+        unsigned long long* const dst = mail_of(chunk) + (lane < 4 ? (ptrdiff_t)lane : (ptrdiff_t)(lane - 4) - (ptrdiff_t)a.mail_plane);
         if (lane < kMailWords) __hip_atomic_store(dst, (unsigned long long)kMailMark << 32 | w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // acknowledged before the others' words are read
       }
@@ -1424,8 +1432,8 @@ __device__ __forceinline__ void step_row(const StepArgs& a, unsigned char* smem_
       Best win = no_best();
       bool there = true;
       if (lane < nch) {
-        unsigned long long* const lo = a.mail_lo + ((size_t)row * nch + lane) * 4;
-        unsigned long long* const hi = a.mail_hi + ((size_t)row * nch + lane) * 4;
+        unsigned long long* const lo = mail_of(lane);
+        unsigned long long* const hi = lo - a.mail_plane;
         uint32_t w[kMailWords];
 #pragma unroll
         for (int j = 0; j < kMailWords; ++j) {
@@ -1443,12 +1451,14 @@ __device__ __forceinline__ void step_row(const StepArgs& a, unsigned char* smem_
         if (win.v < 0) win = no_best();
       }
       if (__builtin_amdgcn_ballot_w64(!there) != 0) return;
-      if (lane < nch) {
-        u32x4* const lo = (u32x4*)(a.mail_lo + ((size_t)row * nch + lane) * 4);
-        u32x4* const hi = (u32x4*)(a.mail_hi + ((size_t)row * nch + lane) * 4);
-        lo[0] = lo[1] = hi[0] = hi[1] = u32x4{0u, 0u, 0u, 0u};
-        if (lane == 0) a.row_words[row] = 0;
+      // all of the row's bytes of the workspace, whatever of them this launch has used; sixteen lanes a plane: two stores, unless a
+      // caller forces more than eight chunks (after the row's own results they would hold up the end of the launch: 0.2 us)
+#pragma unroll
+      for (int i = 0; i < kPlaneCount; i += 4) {
+        unsigned long long* const plane = row_mail - (size_t)(i + (lane >> 4)) * a.mail_plane;
+        for (int k = (lane & 15) * 2; k < a.mail_row; k += 32) *(u32x4*)(plane + k) = u32x4{0u, 0u, 0u, 0u};
       }
+      if (lane == 0) a.row_words[row] = 0;
       sums = merge_sums<Entropy, false>(a, m_c, S_c, Sw_c);  // the chunks' sums are relative to their own maxima
       m = sums.m;
       S = sums.S;
@@ -2233,7 +2243,7 @@ int launch_math_errors(float* out, hipStream_t stream) {
 // more than 8 us late); with 768 slots all have started within 4 us.  A filtered draw has the same two sizes, with
 // twice the registers per wave, so half as many workgroups to a compute unit.  The diagnostics
 // entry point can force the waves per workgroup and a split of every row into `chunks` runs of
-// tiles, each streamed by a workgroup of its own and combined by the last one to arrive.  Where all compute
+// tiles, each streamed by a workgroup of its own and combined by the one that finds all results there.  Where all compute
 // units have rows enough, no split pays (B = 512, V = 152064 bf16, all rows live): 34.7 us unsplit, 41 us in 2 chunks
 // of 16 waves, 39.6 us in 2 chunks of 8 waves, 53 us in 8 chunks of 4 waves: every chunk pays for a search of its
 // own and the row for two more trips through memory (a chunk's result written, then all of them read), which is
@@ -2242,16 +2252,16 @@ int launch_math_errors(float* out, hipStream_t stream) {
 // per row, meant to make rows that are done cost a claim instead of a workgroup: 512 device-scope
 // atomics on one address take 50 ns each, and a launch of B = 1024 live rows went from 56 to 82 us.)
 
-// 8 bytes per row first (256-byte aligned size), then words 4 to 6 of the chunk results, then words 0 to 3
-size_t step_workspace_layout(int64_t B, int chunks, size_t* hi_offset, size_t* lo_offset) {
+// 8 bytes per row first (256-byte aligned size), then the planes of the mail (StepArgs), the last one first
+size_t step_workspace_layout(int64_t B, int places, size_t* last_plane) {
   const size_t head = (((size_t)B * sizeof(unsigned long long)) + 255) & ~(size_t)255;
-  const size_t half = (size_t)B * (size_t)chunks * 4 * sizeof(unsigned long long);
-  if (hi_offset) *hi_offset = head;
-  if (lo_offset) *lo_offset = head + half;
-  return head + 2 * half;
+  const size_t plane = (size_t)B * (size_t)places * 4 * sizeof(unsigned long long);
+  if (last_plane) *last_plane = head + (kPlaneCount - 1) * plane;
+  return head + kPlaneCount * plane;
 }
 
 constexpr int64_t kEightWavesFrom = 256;
+constexpr int kComputeUnits = 256;
 
 // How the library itself splits the rows of a plain draw, given a workspace: chunks per row and waves per chunk.
 // A compute unit takes 4.9 to 8.3 us to stream a bf16 row of 152064 logits (its vector units are the limit: some 45
@@ -2277,27 +2287,45 @@ constexpr int64_t kEightWavesFrom = 256;
 //   401 to 512 rows: V = 140000, B = 480: 54.9 -> 57.2 in 2 chunks, 59.0 in 3; 512: 56.1 -> 59.1, 63.8: not split.
 //   513 to 640 rows of f32 from 512 KB on (more rows than two a compute unit), 2 chunks: V = 131500: B = 513: 66.5 -> 61.0,
 //     570: 76.0 -> 68.4; V = 150001, B = 640: 88.4 -> 81.7.  bf16 V = 150001, B = 320: 30.3 -> 29.8, 512: 34.9 -> 40.8: not split.
-// (The lines were drawn when the combine took a third trip; a split now gains 1 to 2 us more on either side of them.)
-// A chunk of bf16 is streamed by 16 waves, one of f32 by 8, which was the faster of the two at every one of these sizes.
+// These lines, and how many places a row has in the workspace for it (4 or 8 up to 64 rows, then 2 or 3, as the chunks above), were
+// drawn with a search and a combine that took twice as long.  Into how many chunks a row goes was measured again since (a place
+// has room for four): as many as give every compute unit one of 8 waves, as long as that is 3, 4, 8 or 16 to a row, or two
+// of them where that takes 5.  us per launch, chunks before -> now, with log-probabilities / without:
+//   16 of 8 waves up to 16 rows: f32 V = 150001: B = 1: 10.7 -> 9.3 / 9.9 -> 8.9, 4: 10.5 -> 9.7 / 9.8 -> 9.1, 16: 10.3 -> 9.8 / 9.7 -> 9.3 (32 of 4
+//     waves, B = 4: 10.1); bf16 V = 152064, B = 1: 10.8 -> 9.4 / 9.6 -> 8.9, 16: 11.4 -> 9.8 / 9.9 -> 9.1
+//   8 of 8 waves from 17 to 32: f32 V = 150001, B = 32: 13.2 -> 11.4 / 12.6 -> 10.7; bf16 V = 201000, B = 32: 12.3 -> 10.7
+//   33 to 64: 4 stay (B = 64: bf16 8 of 8 waves 11.6 -> 12.6, f32 14.6 -> 15.4).
+//   3 from 65 to 85: f32 V = 150001, B = 85: 20.6 -> 17.8; bf16 V = 201000, B = 85, 16 waves: 15.7 -> 14.2.  At 96 rows they lose: f32 20.5 -> 24.2.
+//   5 of f32 from 86 to 102: V = 150001, B = 102: 21.1 -> 19.9; V = 100000 at temperature 1.0 19.0 -> 16.8.  bf16 V = 152064: 14.2 -> 14.6: not.
+//   4 of f32 from 257 to 320 (five to a compute unit at most), from 576 KB on: V = 150001: B = 280: 42.2 -> 40.2, 320: 44.2 -> 42.9; but B = 340:
+//     44.5 -> 46.8, and V = 131072, B = 320: 37.3 -> 38.1.
+// A chunk of bf16 beyond 32 rows is streamed by 16 waves (at temperature 1.0, V = 152064, B = 64: 8 waves 7 % slower), every other by 8.
 struct RowSplit {
-  int chunks, waves;
+  int chunks, waves, places;
 };
 
 RowSplit own_split(int dt, int64_t B, int64_t V) {
   const bool bf16 = dt == ESPO_BF16;
   const int64_t row_bytes = V * (bf16 ? 2 : 4);
-  const int waves = bf16 ? 16 : 8;
   constexpr int64_t kKB = 1024, kVeryLong = 512 * kKB;
+  constexpr RowSplit whole{1, 0, 0};
   if (B <= 64) {
-    if (row_bytes < (!bf16 && B <= 32 ? 384 * kKB : 256 * kKB)) return RowSplit{1, 0};
-    return RowSplit{B <= 16 && row_bytes >= kVeryLong ? 8 : 4, waves};
+    if (row_bytes < (!bf16 && B <= 32 ? 384 * kKB : 256 * kKB)) return whole;
+    const int places = B <= 16 && row_bytes >= kVeryLong ? 8 : 4;
+    if (B <= 32) return RowSplit{B <= 16 ? 16 : 8, 8, places};
+    return RowSplit{4, bf16 ? 16 : 8, places};
   }
-  if (B <= 128) return bf16 ? (row_bytes >= 288 * kKB ? RowSplit{2, waves} : RowSplit{1, 0}) : (row_bytes > 256 * kKB ? RowSplit{2, waves} : RowSplit{1, 0});
+  if (B <= 128) {
+    if (bf16 ? row_bytes < 288 * kKB : row_bytes <= 256 * kKB) return whole;
+    if (B <= kComputeUnits / 3) return RowSplit{3, bf16 ? 16 : 8, 2};
+    if (!bf16 && B <= 2 * kComputeUnits / 5) return RowSplit{5, 8, 2};
+    return RowSplit{2, bf16 ? 16 : 8, 2};
+  }
   if (!bf16 && row_bytes >= kVeryLong) {
-    if (B > 256 && B <= 400) return RowSplit{3, waves};
-    if (B > 512 && B <= 640) return RowSplit{2, waves};
+    if (B > 256 && B <= 400) return RowSplit{B <= 5 * kComputeUnits / 4 && row_bytes >= 576 * kKB ? 4 : 3, 8, 3};
+    if (B > 512 && B <= 640) return RowSplit{2, 8, 2};
   }
-  return RowSplit{1, 0};
+  return whole;
 }
 
 StepPlan plan_step(int dt, int64_t B, int64_t V, bool filter, int waves, int chunks) {
@@ -2305,14 +2333,16 @@ StepPlan plan_step(int dt, int64_t B, int64_t V, bool filter, int waves, int chu
   const int ntiles = (int)((V + kTile - 1) / kTile);
   p.waves = waves > 0 ? waves : B >= kEightWavesFrom ? 8 : 16;
   int nch = filter || chunks <= 0 ? 1 : chunks;
+  p.places = 0;
   if (!filter && waves <= 0 && chunks <= 0) {
     const RowSplit own = own_split(dt, B, V);
     nch = own.chunks;
-    if (nch > 1) p.waves = own.waves;
+    if (nch > 1) p.waves = own.waves, p.places = own.places;  // (at least 128 tiles: as many chunks as it says)
   }
   if (nch > ntiles) nch = ntiles;
   if (nch > kMaxChunks) nch = kMaxChunks;
   p.chunks = nch;
+  if (p.places == 0) p.places = nch;
   const int ctiles = (ntiles + nch - 1) / nch;
   auto lds = [&](int w) {
     const size_t tables = step_lds_bytes(dt, ctiles, filter, w);
@@ -2323,7 +2353,7 @@ StepPlan plan_step(int dt, int64_t B, int64_t V, bool filter, int waves, int chu
   };
   p.lds = lds(p.waves);
   if (filter && waves <= 0 && p.lds > kMaxStepLds) p.lds = lds(p.waves = 8);  // the widest vocabularies: 8 waves need less
-  p.workspace = nch > 1 ? step_workspace_layout(B, nch, nullptr, nullptr) : 0;
+  p.workspace = nch > 1 ? step_workspace_layout(B, p.places, nullptr) : 0;
   return p;
 }
 
@@ -2369,13 +2399,17 @@ int launch_step(const void* logits, int dt, int64_t B, int64_t V, int64_t row_st
   a.nch = plan.chunks;
   a.chunk_tiles = a.ntiles / plan.chunks;
   a.chunk_extra = a.ntiles % plan.chunks;
-  a.row_words = a.mail_lo = a.mail_hi = nullptr;
+  a.row_words = a.mail = nullptr;
+  a.mail_plane = 0;
+  a.mail_row = a.part_shift = 0;
   if (plan.chunks > 1) {
-    size_t lo = 0, hi = 0;
-    step_workspace_layout(B, plan.chunks, &hi, &lo);
+    size_t last_plane = 0;
+    step_workspace_layout(B, plan.places, &last_plane);
     a.row_words = (unsigned long long*)workspace;
-    a.mail_lo = (unsigned long long*)((char*)workspace + lo);
-    a.mail_hi = (unsigned long long*)((char*)workspace + hi);
+    a.mail = (unsigned long long*)((char*)workspace + last_plane);
+    a.mail_row = plan.places * 4;
+    a.mail_plane = (size_t)B * (size_t)a.mail_row;
+    while ((plan.places << a.part_shift) < plan.chunks) ++a.part_shift;  // at most kPartsShift: plan_step
   }
 
   // the entropy output costs two more vector operations per logit: its own instantiation

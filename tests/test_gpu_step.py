@@ -705,6 +705,25 @@ def test_rows_the_library_splits_itself(B, V, dtype, chunks):
                     np.testing.assert_allclose(got, want, rtol=2e-6, atol=2e-6 * (np.log(V) if k == 6 else 1.0), err_msg=f"{name} step {step} output {k}")
 
 
+# Rows that go into more chunks than they have places in the workspace (three of two, five of two, four of three, eight of four, sixteen of four and of
+# eight): results as above, and all of a live row's bytes are zero afterwards, all of a row's that is done as before.
+@pytest.mark.parametrize("B,V,dtype,places", [(85, 66000, torch.float32, 2), (102, 65537, torch.float32, 2), (320, 147456, torch.float32, 3),
+                                              (17, 131072, torch.bfloat16, 4), (7, 131083, torch.bfloat16, 4), (2, 399999, torch.bfloat16, 8)])
+def test_rows_in_more_chunks_than_places(B, V, dtype, places):
+    test_rows_the_library_splits_itself(B, V, dtype, places)
+    logits = torch.randn(B, (V + 7) // 8 * 8, device="cuda", generator=torch.Generator("cuda").manual_seed(V)).to(dtype)
+    gp, op = H.params_pair(stop_enabled=0)
+    st = H.GpuState(B, alive=(torch.arange(B) % 3 != 1).to(torch.uint8), z=torch.zeros(B))
+    need = espo.espo_step_workspace_bytes(B, V, dtype)
+    planes = B * places * 32
+    ws = torch.randint(0, 256, (need,), dtype=torch.uint8, device="cuda")
+    before = ws.clone()
+    espo.espo_step(logits, 1.0, 3, 0, torch.zeros(B, device="cuda"), gp, st.z, st.alive, st.stop_step, st.tokens, st.regret, st.logprob, V=V, workspace=ws)
+    live = (torch.arange(B) % 3 != 1).cuda()
+    mail, was = (t[need - 8 * planes:].view(8, B, places * 32) for t in (ws, before))
+    assert not bool(mail[:, live].any()) and torch.equal(mail[:, ~live], was[:, ~live])
+
+
 @pytest.mark.parametrize("B", [513, 600, 1024, 1500, 2600])
 def test_more_rows_than_resident_workgroups(B):
     _say(f"[case] more rows than resident workgroups, B={B}")
