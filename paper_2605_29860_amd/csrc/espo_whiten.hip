@@ -469,7 +469,14 @@ bool whiten_indexable(int64_t B, int64_t T) {
   return B * ((T + 3 + kWhItem - 1) / kWhItem) < (1ll << 32) - kRoom;
 }
 
-size_t whiten_workspace(int64_t B, int64_t T) { return (size_t)whiten_groups(B * items_per_row(T)) * sizeof(Sums); }
+// Room for a partial for each 4096 positions of a row, up to the most a launch has: never more for fewer rows or steps, so that
+// a buffer sized for a program's largest call serves all its calls.  (Workgroups go by items, of which 65535 positions
+// have one more than 65536; 4096 positions are at most five items, five eighths of a workgroup, so there is always room.)
+size_t whiten_workspace(int64_t B, int64_t T) {
+  static_assert(kWhItem == 1024, "five items in 4096 positions");
+  const int64_t parts = B * ((T + 4095) / 4096);
+  return (size_t)(parts < 1 ? 1 : parts > kWhMaxGroups ? kWhMaxGroups : parts) * sizeof(Sums);
+}
 
 int launch_whiten(const float* adv, const int32_t* lengths, int64_t B, int64_t T, float eps, int shift_mean,
                   int unbiased, float* out, double* stats, void* workspace, hipStream_t stream) {

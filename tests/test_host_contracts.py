@@ -231,3 +231,16 @@ def test_tensor_checks_of_the_binding(monkeypatch, make, kw, err):
 def test_shapes_that_the_library_splits(dtype, B, V, chunks):
     import paper_2605_29860_amd as espo
     assert espo.espo_step_workspace_bytes(B, V, dtype) == espo.espo_debug_step_workspace_bytes(B, chunks)
+
+
+# A program that sizes the whitening's buffer for its largest call, or for its horizon rounded up, makes every smaller call with it.
+@pytest.mark.parametrize("B", [1, 3, 17, 64, 511, 512, 5000])
+def test_whiten_workspace_of_a_call_serves_every_smaller_one(B):
+    import paper_2605_29860_amd as espo
+    need = espo.espo_whiten_workspace_bytes
+    for T in (4, 1024, 1028, 4096, 4100, 8192, 16384, 65536, 1 << 20, 3_000_000):
+        assert 0 < need(B, T) <= 16384
+        for k in (1, 2, 3, 4, 5, T // 2):
+            if k < T:
+                assert need(B, T - k) <= need(B, T), (B, T, k)
+        assert need(max(B - 1, 1), T) <= need(B, T)
