@@ -28,6 +28,7 @@
 #include "../../include/espo.h"
 #include "espo_device.h"
 #include "espo_host.h"
+#include "espo_quad.h"
 
 namespace espo {
 namespace {
@@ -108,44 +109,44 @@ __device__ __forceinline__ uint32_t item_index(const WhArgs& a, int k) {
 
 __device__ __forceinline__ int quad_at(int q) { return q * kWave * 4 + (int)(threadIdx.x & (kWave - 1)) * 4; }
 
-// This lane's four tokens at position t of an item, and which of them are valid (bit j).  At a row's ends a lane of the smaller workgroups
-// loads all four where any is valid and the array goes on behind them (`end`: its positions from the item's start on), and drops the
-// others: with single loads there, a wave waits for memory twice (B = 1000, T = 300: 13.0 -> 8.9 us, the smaller workgroups
-// included).  The larger ones have no registers for that (B = 1024, T = 16384: 25.5 -> 27.4).
+// Where this lane's four tokens for position t of an item start, and which of them are its own.  Workgroups of 8 waves load four
+// tokens of the row at its ends too, from as far inside as it takes: with single loads there, a wave waits for memory
+// twice (B = 1000, T = 300: 13.0 -> 8.9 us, the smaller workgroups included).  The larger ones have no registers for that (whole quads there, B = 1024,
+// T = 16384: 25.5 -> 27.4).
 template <int W>
-__device__ __forceinline__ uint32_t load_quad(const float* __restrict__ src, int end, const Item& im, int t, f32x4& g) {
+__device__ __forceinline__ Quad lane_quad(const Item& im, int t) {
+  if constexpr (W == 16) {
+    const int lo = im.lo - t, hi = im.hi - t;  // its own: lo <= j < hi
+    return Quad{t, (hi >= 4 ? 0xfu : hi > 0 ? (1u << hi) - 1u : 0u) & (lo <= 0 ? 0xfu : lo < 4 ? 0xfu << lo : 0u)};
+  } else {
+    return quad_of(t, im.lo, im.hi);
+  }
+}
+
+using f32x4_any = float __attribute__((ext_vector_type(4), aligned(4)));  // at any element
+
+// Loads them; returns which of them are the lane's own.  Positions that are not of the row's valid ones are never read.
+template <int W>
+__device__ __forceinline__ uint32_t load_quad(const float* __restrict__ src, const Item& im, int t, f32x4& g) {
   g = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  uint32_t in = 0;
   if constexpr (W == 16) {
     if (t >= im.lo && t + 4 <= im.hi) {
       g = __builtin_nontemporal_load((const f32x4*)(src + im.start + t));
       return 0xfu;
     }
+  }
+  const Quad quad = lane_quad<W>(im, t);
+  if (quad.in != 0) {
+    const float* const from = src + im.start + quad.at;
+    if (W != 16 && im.hi - im.lo >= 4) {  // (wave-uniform)
+      g = __builtin_nontemporal_load((const f32x4_any*)from);
+    } else {
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      if (t + j >= im.lo && t + j < im.hi) {
-        g[j] = src[im.start + t + j];
-        in |= 1u << j;
-      }
-  } else {
-    const int lo = im.lo - t, hi = im.hi - t;  // valid: lo <= j < hi
-    in = (hi >= 4 ? 0xfu : hi > 0 ? (1u << hi) - 1u : 0u) & (lo <= 0 ? 0xfu : lo < 4 ? 0xfu << lo : 0u);
-    if (in != 0) {
-      if (t + 4 <= end) {
-        g = __builtin_nontemporal_load((const f32x4*)(src + im.start + t));
-      } else {
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          if ((in >> j) & 1u) g[j] = src[im.start + t + j];
-      }
+      for (int j = 0; j < 4; ++j)
+        if ((quad.in >> j) & 1u) g[j] = from[j];
     }
   }
-  return in;
-}
-
-__device__ __forceinline__ int item_end(const WhArgs& a, const Item& im) {
-  const int64_t left = a.B * a.T - im.start;
-  return (int)(left < kWhItem ? left : kWhItem);
+  return quad.in;
 }
 
 // ---------------------------------------------------------------- sums
@@ -222,9 +223,8 @@ __global__ __launch_bounds__(W * kWave, W == 16 ? 8 : 4) void whiten_partial_ker
 #pragma unroll
     for (int u = 0; u < kWhUnroll; ++u) {
       const Item im = item_of(a, item_index<W>(a, k + u));
-      const int end = item_end(a, im);
 #pragma unroll
-      for (int q = 0; q < kWhQuads; ++q) in[u][q] = load_quad<W>(a.adv, end, im, quad_at(q), g[u][q]);
+      for (int q = 0; q < kWhQuads; ++q) in[u][q] = load_quad<W>(a.adv, im, quad_at(q), g[u][q]);
     }
     if (W != 16 && k == 0) shift = batch_shift(a);  // two loads one after the other, behind those of the first items
 #pragma unroll
@@ -339,21 +339,20 @@ __global__ __launch_bounds__(W * kWave, W == 16 ? 8 : 4) void whiten_apply_kerne
   struct Held {
     f32x4 g[kWhQuads];
     uint32_t in;  // four bits per group of four
-    int64_t at;
+    Item im;
   };
   auto fetch = [&](int k) {
     Held h;
-    const Item im = item_of(a, item_index<W>(a, k));
-    const int end = item_end(a, im);
-    h.at = im.start;
+    h.im = item_of(a, item_index<W>(a, k));
     h.in = 0;
 #pragma unroll
-    for (int q = 0; q < kWhQuads; ++q) h.in |= load_quad<W>(a.adv, end, im, quad_at(q), h.g[q]) << (4 * q);
+    for (int q = 0; q < kWhQuads; ++q) h.in |= load_quad<W>(a.adv, h.im, quad_at(q), h.g[q]) << (4 * q);
     return h;
   };
   auto store = [&](const Held& h, const Scale& s) {
 #pragma unroll
-    for (int q = 0; q < kWhQuads; ++q) store_quad(a.out + h.at + quad_at(q), h.g[q], (h.in >> (4 * q)) & 0xfu, s);
+    for (int q = 0; q < kWhQuads; ++q)
+      store_quad(a.out + h.im.start + lane_quad<W>(h.im, quad_at(q)).at, h.g[q], (h.in >> (4 * q)) & 0xfu, s);
   };
   Held held[Hold > 0 ? Hold : 1];
 #pragma unroll
