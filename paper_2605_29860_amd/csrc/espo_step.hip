@@ -1528,13 +1528,21 @@ struct CollectLimits {  // packs of a wave's list: room, when it is compacted, w
   static constexpr int kKeep = (DT == ESPO_BF16 ? 160 : 112) * 8 / W;
 };
 
-// What a compaction keeps of a wave's list: half as many packs at the least.  A nucleus may need them all.  Of a top-k draw's
-// the waves together keep five times k at the least, so that fewer logits are binned and collected afterwards (us, V = 50003 bf16, top-k 50,
-// B = 100: 13.3 with what a nucleus gets, 12.7 so; V = 152064, B = 64: 19.3, 17.9; V = 60000, B = 300: 21.4, 18.8).
+// What a compaction leaves of a wave's list.  A nucleus may need all of it.  Of a top-k draw a wave keeps little more than k packs, so that
+// fewer logits are binned and collected afterwards, but no fewer than that: the row's largest logits may all be this wave's (common
+// tokens with neighbouring indices), and with fewer than k of them above T the row has to be read again.  us, what a nucleus gets / so /
+// a share of 10 k for each wave, k = 20: V = 50003 bf16, B = 100, synthetic rows 13.1 / 11.8 / 11.6, their largest logits within one tile 14.4 / 12.5 / 34.5;
+// V = 152064, B = 300: 30.7 / 26.6 / 26.2, 32.1 / 26.5 / 60.8; k = 50, V = 50003, B = 100: 13.4 / 12.9 / 11.9, 14.9 / 14.6 / 32.4.
+// From two thirds of kKeep on, k packs at the least make the lists longer than they have to be (k = 128, B = 300: 20.4 -> 21.1).
+struct Kept {
+  int least, most;
+};
 template <int DT, int W>
-__device__ __forceinline__ int packs_kept(const StepArgs& a) {
+__device__ __forceinline__ Kept packs_kept(const StepArgs& a) {
   constexpr int kAll = CollectLimits<DT, W>::kKeep;
-  return a.top_k > 0 && a.top_k < kAll * W / 10 ? max(10 * a.top_k / W, 16) : kAll;
+  if (a.top_k == 0 || a.top_k > kAll * 2 / 3) return Kept{kAll / 2, kAll};
+  const int most = min(max(a.top_k * 8 / 5, 16), kAll);
+  return Kept{max(a.top_k, most / 2), most};
 }
 
 template <int DT, int W>
@@ -1606,10 +1614,10 @@ __device__ __forceinline__ void pack_unpack(const Raw<DT>& r, int32_t v0, int32_
   }
 }
 
-// Raises a wave's threshold to a value that at most `keep` of the list's packs reach beyond and drops the
+// Raises a wave's threshold to a value that at most `keep.most` of the list's packs reach beyond and drops the
 // others.  (Packs that tie at the threshold are dropped as well: what is kept is everything above it.)
 template <int DT, int W>
-__device__ __forceinline__ void compact_list(uint32_t* raw, uint16_t* id, int32_t V, int keep, int& n, float& thr) {
+__device__ __forceinline__ void compact_list(uint32_t* raw, uint16_t* id, int32_t V, const Kept& keep, int& n, float& thr) {
   using Lim = CollectLimits<DT, W>;
   constexpr int kRounds = Lim::kRoom / kWave, kWords = Raw<DT>::kWords;
   const int lane = threadIdx.x & (kWave - 1);
@@ -1627,18 +1635,18 @@ __device__ __forceinline__ void compact_list(uint32_t* raw, uint16_t* id, int32_
     }
     top = fmaxf(top, pm[r]);
   }
-  float hi = wave_max(top), lo = -wave_max(bottom);  // none above hi; the search leaves at most `keep` above hi
+  float hi = wave_max(top), lo = -wave_max(bottom);  // none above hi; the search leaves at most `keep.most` above hi
 #pragma unroll 1
   for (int it = 0; it < 12; ++it) {
     const float mid = 0.5f * lo + 0.5f * hi;
     int c = 0;
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) c += (int)__builtin_popcountll(__builtin_amdgcn_ballot_w64(pm[r] > mid));
-    if (c > keep) {
+    if (c > keep.most) {
       lo = mid;
     } else {
       hi = mid;
-      if (2 * c >= keep) break;
+      if (c >= keep.least) break;
     }
   }
   thr = hi;
@@ -1948,7 +1956,7 @@ __device__ __forceinline__ bool filtered_row(const StepArgs& a, unsigned char* s
   int n = 0;                    // packs in this wave's list (wave-uniform)
   float thr = kMaskedBelow;     // every logit above it that the wave has seen is in the list
   float low = __builtin_huge_valf();  // the smallest pack maximum this lane has put there
-  const int keep = packs_kept<DT, W>(a);
+  const Kept keep = packs_kept<DT, W>(a);
   bool flooded = false;         // a compaction found most of the list tied at its threshold
   int dry = 0;                  // passes since then that have left the list next to empty
 
@@ -2017,7 +2025,7 @@ __device__ __forceinline__ bool filtered_row(const StepArgs& a, unsigned char* s
       ring[d] = load_tile(t + kRing * W);
     if ((d + 1) % Lim::kCheckTiles == 0 && n >= Lim::kCompactAt) {
       compact_list<DT, W>(my_raw, my_id, a.V, keep, n, thr);
-      flooded = flooded || 4 * n < keep;
+      flooded = flooded || 4 * n < keep.most;
     }
   };
   const int steady_end = my_tiles > 2 * kRing ? ((my_tiles - kRing - 1) / kRing) * kRing : 0;
@@ -2029,7 +2037,7 @@ __device__ __forceinline__ bool filtered_row(const StepArgs& a, unsigned char* s
     // Ties at the wave's largest logits: the kept set most likely reaches down to them, and they are not in the
     // list.  Given up early, such a row costs the general search and a few tiles (all logits equal, V = 152064, bf16 / fp32: B = 64: 23.6 / 35.1 us,
     // streamed to the end 26.2 / 38.6, the general search alone 22.9 / 31.0).
-    if (flooded && (n == 0 || (8 * n < keep && ++dry == 2))) {
+    if (flooded && (n == 0 || (8 * n < keep.most && ++dry == 2))) {
       thr = __builtin_huge_valf();  // nothing is above it: the row is handed on
       i0 = my_tiles;
       break;

@@ -1009,9 +1009,8 @@ def test_top_p_at_the_edge_with_logits_far_from_zero(tau, offset, ties):
                         raise AssertionError(f"p {p_val / pa - 1.0:+.1e} off the edge, {layout} step {step}: {err}")
 
 
-# What a wave's list is cut down to follows from k: both sides of its lower and of its upper end, with 8 and 16 waves and
-# for both types, on rows whose largest logits are spread, come last, or lie in the tiles of a single wave (whose threshold
-# then leaves fewer than k logits above it).
+# What a wave's list is cut down to follows from k: both sides of the lines of that rule, with 8 and 16 waves and for both types, on
+# rows whose largest logits are spread, come last, or lie in the tiles of a single wave (whose threshold then decides alone).
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("order", ["random", "ascending", "one wave"])
 def test_top_k_lists_cut_by_k(order, dtype):
@@ -1026,11 +1025,41 @@ def test_top_k_lists_cut_by_k(order, dtype):
     x[:, V:] = 1e4
     logits = x.to(dtype).cuda()
     vals = torch.zeros(B, device="cuda")
-    for k in (2, 12, 13, 25, 26, 88, 90, 127, 128, 700):
+    for k in (2, 10, 11, 25, 37, 38, 50, 53, 54, 74, 75, 106, 107, 128, 700):
         gp, op = H.params_pair(stop_enabled=0, top_k=k)
         for layout in FILTER_LAYOUTS:
             st = H.GpuState(B)
             H.compare_step(logits, 1.0, 43, 0, vals, gp, op, st, V=V, **layout)
+
+
+# Common tokens often have neighbouring indices: a row whose largest logits all lie in one tile, i.e. in a single wave's list, is drawn
+# from the lists like one that holds the same logits anywhere, not by reading it again (which takes two to three times as long).
+@pytest.mark.parametrize("B,V,k,dtype", [(100, 50003, 20, torch.bfloat16), (16, 152064, 50, torch.bfloat16), (300, 50003, 50, torch.bfloat16),
+                                         (100, 50003, 20, torch.float32), (300, 50003, 50, torch.float32)])
+def test_top_k_takes_no_longer_where_the_largest_logits_are_neighbours(B, V, k, dtype):
+    _say(f"[case] top-k of neighbours B={B} V={V} k={k} {dtype}")
+    stride = (V + 7) // 8 * 8
+    x = torch.randn(B, stride, device="cuda", generator=torch.Generator("cuda").manual_seed(3)) * 2.0
+    x[:, :512] += 12.0
+    apart = x.clone()
+    apart[:, :V] = x[:, :V][:, torch.randperm(V, device="cuda", generator=torch.Generator("cuda").manual_seed(4))]
+    vals = torch.zeros(B, device="cuda")
+    gp, _ = H.params_pair(stop_enabled=0, top_k=k)
+    st = H.GpuState(B)
+    took = []
+    for logits in (x.to(dtype), apart.to(dtype)):
+        best = float("inf")
+        for rep in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for step in range(40):
+                espo.espo_step(logits, 1.0, 3, step, vals, gp, st.z, st.alive, st.stop_step, st.tokens, st.regret, st.logprob, V=V)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) / 40)
+        took.append(best)
+    _say(f"  {took[0] * 1e3:.1f} us, spread {took[1] * 1e3:.1f}")
+    assert took[0] < 1.5 * took[1]
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
