@@ -196,9 +196,11 @@ __global__ __launch_bounds__(kStatThreads) void batch_partial_kernel(PartialArgs
   for (int64_t row = blockIdx.x; row < a.B; row += gridDim.x) {
     int64_t L;
     const RowSpan r = row_span(a, row, L);
-    if constexpr (Kind == kLongRows) {
+    if (Kind == kLongRows && __builtin_expect(L > kLongRow, 0)) {  // (wave-uniform; the shorter way stays in a straight line)
       // Rounds of eight loads per lane, all on their way before the first is added: one at a time, as below, a row's loads
       // wait for each other (us per call: B = 512, T = 8192: 9.6 -> 9.0; 1024, 16384: 16.5 -> 15.0; 8, 16384: 9.1 -> 8.4; but 300, 2000: 6.5 -> 6.6).
+      // Trajectories that end early in such rows are short ones (T = 4100, B = 4000, 256 tokens each: 8.5, in rounds 9.6; B = 1500, 3072: 8.6,
+      // 8.9; from 4096 tokens on both take the same).
       constexpr uint32_t kStride = kStatThreads * 4;
       const uint32_t full = (uint32_t)L & ~3u;  // (T is below 2^31)
       for (uint32_t base = 0; base < full; base += kDeepLoads * kStride) {
@@ -212,7 +214,7 @@ __global__ __launch_bounds__(kStatThreads) void batch_partial_kernel(PartialArgs
         for (uint32_t u = 0; u < kDeepLoads; ++u)
           if (base + u * kStride + threadIdx.x * 4 < full) add_tokens(g[u], shift, s1, s2);
       }
-    } else if constexpr (Kind == kAlignedRows) {
+    } else if constexpr (Kind != kAnyRows) {
       const int64_t full = L & ~(int64_t)3;
       for (int64_t t = (int64_t)threadIdx.x * 4; t < full; t += kStatThreads * 4)
         add_tokens(__builtin_nontemporal_load((const f32x4*)(r.src + t)), shift, s1, s2);

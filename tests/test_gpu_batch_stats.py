@@ -63,11 +63,12 @@ def test_items_at_every_boundary(B, T):
     assert got["tokens"] == B * T
 
 
-# Rows of more than 4096 tokens that start at 16-byte boundaries: rounds of eight loads of 1024 tokens, lengths at their edges.
+# Rows of more than 4096 steps that start at 16-byte boundaries: rounds of eight loads of 1024 tokens where a trajectory has more than
+# 4096, lengths at their edges and at that line.
 @pytest.mark.parametrize("T", [4096, 4100, 8192, 8196, 16384, 40964])
 def test_long_rows(T):
     print(f"[case] batch stats long rows T={T}", flush=True)
-    L = [0, 1, 3, 4, 1023, 1024, 1025, 4097, 7168, 7171, 8188, 8191, 8192, 8193, 9215, T - 1, T, T]
+    L = [0, 1, 3, 4, 1023, 1024, 1025, 4095, 4096, 4097, 7168, 7171, 8188, 8191, 8192, 8193, 9215, T - 1, T, T]
     regret, lengths, stopped = W.regret_batch(len(L), T, len_lo=0, seed=T, device="cuda")
     lengths[:] = torch.tensor([min(n, T) for n in L], dtype=torch.int32)
     regret[torch.arange(T, device="cuda")[None, :] >= lengths[:, None]] = float("nan")
