@@ -868,8 +868,10 @@ __device__ __forceinline__ Best fast_argmax(const StepArgs& a, const StepShared&
     const float u = sh.ub(b);
     return u > kMaskedBelow && b != skip && holds_eligible(sh, b) ? ub_rounded_up(u) : kNegInf;
   };
-  constexpr int kAhead = W == 16 ? 3 : 5;  // read before the barrier: all blocks of a wave for V up to 196608 (16 waves) or 163840
-  float ahead[kAhead];
+  // Read before the barrier: all blocks of a wave for V up to 196608 (16 waves) or 163840.  None in the general search of a filtered draw,
+  // which few rows need and which shares its registers with the draw from the lists.
+  constexpr int kAhead = Filter ? 0 : W == 16 ? 3 : 5;
+  float ahead[Filter ? 1 : kAhead];
 #pragma unroll
   for (int i = 0; i < kAhead; ++i) {
     ahead[i] = kNegInf;
@@ -1054,8 +1056,8 @@ __device__ __forceinline__ void step_row(const StepArgs& a, unsigned char* smem_
   const uint32_t last_group = (uint32_t)(a.V - 1) & ~7u;
   // the last 16-byte group of the chunk: where the first ring's loads of a wave with fewer tiles go
   const uint32_t chunk_last = tile1 == ntiles ? last_group : (uint32_t)tile1 * kTile - 8u;
-  const uint32_t lane_off = (uint32_t)lane * 8u;
-  const uint32_t lane_bytes = lane_off * (uint32_t)elem_bytes<DT>();
+  uint32_t lane_off = (uint32_t)lane * 8u;
+  uint32_t lane_bytes = lane_off * (uint32_t)elem_bytes<DT>();
   auto load_tile = [&](int t) {  // t is wave-uniform
     if (t != ntiles - 1) return load_raw_inner<DT>((const char*)rowp + (size_t)t * kTile * elem_bytes<DT>(), lane_bytes);
     const uint32_t e0 = (uint32_t)t * kTile + lane_off;  // last tile: may be ragged
@@ -1299,7 +1301,7 @@ __device__ __forceinline__ void step_row(const StepArgs& a, unsigned char* smem_
           acc_n += above ? 1.0f : 0.0f;  // counts stay exact in fp32: V < 2^24
         }
       };
-      constexpr int kLoads = 4, kDeep = 6;
+      constexpr int kLoads = 4, kDeep = DT == ESPO_F32 ? 5 : 6;  // (with 6 of fp32 two registers go to scratch)
       if (3 * nabove <= 2 * nslots) {
         // the listed blocks only, laid out as in phase 1: a lane group of 8 lanes per block, 16 bytes per lane
         const uint32_t sub = (uint32_t)(lane & 7) * 8u;
@@ -1351,6 +1353,7 @@ __device__ __forceinline__ void step_row(const StepArgs& a, unsigned char* smem_
       above.floor = m == 0.0f ? -1.401298464e-45f : __builtin_bit_cast(float, bits + (m > 0.0f ? -1 : 1));
     }
     while (m > kNegInf) {  // (a row without a finite logit has no winner)
+      asm volatile("" : "+v"(lane_off), "+v"(lane_bytes));  // no address that follows from them is kept in registers from round to round
       search(above);
       if (tok < 0 || a.top_k == 1) break;
       measure(x_a);
@@ -2157,7 +2160,9 @@ __device__ __forceinline__ bool filtered_row(const StepArgs& a, unsigned char* s
 }
 
 template <int DT, bool Entropy, int W>
-// Registers: 107 per lane, two workgroups of 8 waves on a compute unit or one of 16.
+// Registers: 120 per lane (fp32 127) of at most 128, none in scratch: two workgroups of 8 waves on a compute unit or one of 16.  With the
+// search's bounds read ahead, addresses kept over its rounds and six fp32 loads in flight it was 128 and 12 to 36 bytes of scratch
+// (us, fp32 normal logits, top-p 0.9, V = 152064, B = 64: 114 -> 99; 256: 139 -> 125; synthetic rows at temperature 1.3, B = 64: 115 -> 105).
 __global__ __launch_bounds__(W * kWave, 4) void espo_filtered_kernel(StepArgs a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int row = (int)blockIdx.x;
