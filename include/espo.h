@@ -203,7 +203,7 @@ typedef enum {
  *               Without it (NULL, too short or misaligned), and where that size is 0, one workgroup
  *               handles a whole row.  What it holds before the call does not matter, unless calls that overlapped
  *               in time have shared it: two such calls write into each other's rows, and what they leave can still be
- *               taken for an arrival by a later call, so the buffer has to be cleared before it is used again.
+ *               taken for a result by a later call, so the buffer has to be cleared before it is used again.
  *               Calls that may run at the same time need a workspace each (up to version 310 no call
  *               wrote to it).  After the call the bytes of live rows are zero, those of rows that are done are as before.
  *   stream      hipStream_t as void*.
@@ -215,7 +215,9 @@ int espo_step(const void* logits, espo_dtype dt, int64_t B, int64_t V, int64_t r
               int32_t* tokens, float* regret, float* logprob, float* entropy,
               void* workspace, size_t workspace_bytes, void* stream);
 
-/* Bytes of workspace with which espo_step splits the rows of this shape (0 where it does not). */
+/* Bytes of workspace with which espo_step splits the rows of this shape (0 where it does not): 64 for each workgroup of a
+ * row.  The figure belongs to the library that returns it: up to version 320 the same shapes were given from 36 to 520 bytes a row, and a
+ * buffer of another version's size may be too short, which leaves every row to one workgroup. */
 size_t espo_step_workspace_bytes(int64_t B, int64_t V, espo_dtype dt);
 
 /*

@@ -120,7 +120,7 @@ int step_checked(const void* logits, espo_dtype dt, int64_t B, int64_t V, int64_
 #pragma GCC visibility push(default)
 extern "C" {
 
-int espo_version(void) { return 320; }
+int espo_version(void) { return 330; }
 
 int espo_debug_step(const void* logits, espo_dtype dt, int64_t B, int64_t V, int64_t row_stride, float temperature,
                     uint64_t seed, int32_t step, const float* values, const espo_params* params, float* z, uint8_t* alive,
@@ -132,7 +132,7 @@ int espo_debug_step(const void* logits, espo_dtype dt, int64_t B, int64_t V, int
 
 size_t espo_debug_step_workspace_bytes(int64_t B, int32_t chunks) {
   if (B <= 0 || chunks <= 1) return 0;
-  return espo::step_workspace_layout(B, chunks, nullptr);
+  return espo::step_workspace(B, chunks);
 }
 
 int espo_debug_read(const void* src, size_t bytes, void* sink, void* stream) {

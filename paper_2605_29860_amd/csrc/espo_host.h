@@ -11,11 +11,9 @@ namespace espo {
 constexpr size_t kMaxStepLds = 128 * 1024;         // dynamic LDS a step workgroup may ask for (160 KB per CU)
 constexpr int64_t kMaxVocab = 400000;               // one workgroup per row: 96 bytes of LDS per 512-index tile plus 26-42 KB fixed
 
-// How one espo_step call is laid out: wavefronts per workgroup (16, 8 or 4), workgroups per row,
-// workgroups in the launch, dynamic LDS per workgroup, and the bytes of workspace a split needs.
+// How one espo_step call is laid out: wavefronts per workgroup (16, 8 or 4), workgroups per row, dynamic LDS per workgroup, and the bytes of workspace a split needs.
 struct StepPlan {
   int waves, chunks;
-  int places;  // of a row in the workspace, each with room for four chunks; its size follows from them
   size_t lds, workspace;
 };
 
@@ -24,9 +22,8 @@ struct StepPlan {
 // 256 rows on, and long rows of a batch that leaves compute units idle split, if `waves` is its choice too.
 StepPlan plan_step(int dt, int64_t B, int64_t V, bool filter, int waves, int chunks);
 
-// Bytes of workspace for B rows with `places` places each (one per chunk where a split is forced); where the last of the
-// planes that hold the chunks' results begins.
-size_t step_workspace_layout(int64_t B, int places, size_t* last_plane);
+// Bytes of workspace for B rows of `chunks` chunks each.
+size_t step_workspace(int64_t B, int chunks);
 
 int launch_step(const void* logits, int dt, int64_t B, int64_t V, int64_t row_stride, float temperature,
                 uint64_t seed, int32_t step, const float* values, const espo_params& p, float margin_scale,

@@ -53,9 +53,7 @@ constexpr float kRescaleAt = 64.0f;               // advance a lane's softmax re
 // and its exact local winner (score known to within +-e): m, sum, sumw, s, e, x, v.  Each goes into the workspace as a
 // 64-bit word of its own with this mark above it, so that a word is either there as a whole or recognised as not there.
 constexpr uint32_t kMailMark = 0x4553504Fu;
-constexpr int kMailWords = 7;
-constexpr int kPartsShift = 2;                        // every place of a row's workspace has room for this power of two of chunks
-constexpr int kPlaneCount = 2 << kPartsShift;
+constexpr int kMailWords = 7, kMailRoom = 8;  // words of a chunk, and what it has room for
 
 struct StepArgs {
   const void* logits;
@@ -81,13 +79,10 @@ struct StepArgs {
   float* entropy;
   // a row split over `nch` workgroups: workgroup (row, c) streams `chunk_tiles` tiles, one more for the first `chunk_extra` chunks
   int32_t nch, chunk_tiles, chunk_extra;
-  unsigned long long* row_words;  // [B] 8 bytes per row at the head of the workspace, left zero for live rows
-  // Where the chunks of a row leave what they found, in kPlaneCount planes of [B][mail_row] words, all left zero: chunk c takes four
-  // words of plane 2 g and three of plane 2 g + 1 at place c >> part_shift, g being its low part_shift bits.  Plane 0, whose address
-  // this is, is the last in memory.
+  // Where the chunks leave what they found, all left zero for live rows: [B][kMailRoom][nch] words.  A row's words are read by lanes that
+  // hold a chunk each, so word j of all chunks is one access (us per launch, eight planes with four words of every row each -> this:
+  // bf16 V = 152064, B = 1: 8.85 -> 8.48, 64: 11.02 -> 10.79; f32 V = 150001, B = 64: 14.1 -> 13.6, 320: 42.7 -> 41.7).
   unsigned long long* mail;
-  size_t mail_plane;  // words of a plane
-  int32_t mail_row, part_shift;
 };
 
 
@@ -1419,15 +1414,13 @@ __device__ __forceinline__ void step_row(const StepArgs& a, unsigned char* smem_
       // to the outputs of B = 64, V = 152064 bf16, against 5000 now; B = 4, V = 150001 fp32 with the entropy, 8 chunks: 13.8 -> 11.3 us,
       // the shorter search included.)  A word without the mark is not there, so the workspace may hold anything before the launch; who
       // finishes a row leaves its words zero, so that nothing of this launch can pass for a result in a later one.
-      unsigned long long* const row_mail = a.mail + (size_t)row * a.mail_row;
-      auto mail_of = [&](int c) { return row_mail + (c >> a.part_shift) * 4 - (size_t)(c & ((1 << a.part_shift) - 1)) * 2 * a.mail_plane; };
+      unsigned long long* const row_mail = a.mail + (size_t)row * (size_t)(nch * kMailRoom);
       asm volatile("" : "+v"(z_prev) : : "memory");  // z has arrived before this chunk's words let another one finish the row and write it
       {
         const uint32_t w = lane == 0 ? __builtin_bit_cast(uint32_t, m) : lane == 1 ? __builtin_bit_cast(uint32_t, S)
                            : lane == 2 ? __builtin_bit_cast(uint32_t, Sw) : lane == 3 ? __builtin_bit_cast(uint32_t, s_a)
                            : lane == 4 ? __builtin_bit_cast(uint32_t, e_a) : lane == 5 ? __builtin_bit_cast(uint32_t, x_a) : (uint32_t)tok;
-        unsigned long long* const dst = mail_of(chunk) + (lane < 4 ? (ptrdiff_t)lane : (ptrdiff_t)(lane - 4) - (ptrdiff_t)a.mail_plane);
-        if (lane < kMailWords) __hip_atomic_store(dst, (unsigned long long)kMailMark << 32 | w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (lane < kMailWords) __hip_atomic_store(row_mail + lane * nch + chunk, (unsigned long long)kMailMark << 32 | w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // acknowledged before the others' words are read
       }
       // lane c holds chunk c (nch <= 64); the other lanes hold a chunk without any finite logit
@@ -1435,12 +1428,10 @@ __device__ __forceinline__ void step_row(const StepArgs& a, unsigned char* smem_
       Best win = no_best();
       bool there = true;
       if (lane < nch) {
-        unsigned long long* const lo = mail_of(lane);
-        unsigned long long* const hi = lo - a.mail_plane;
         uint32_t w[kMailWords];
 #pragma unroll
         for (int j = 0; j < kMailWords; ++j) {
-          const unsigned long long word = __hip_atomic_load(j < 4 ? lo + j : hi + (j - 4), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          const unsigned long long word = __hip_atomic_load(row_mail + j * nch + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           w[j] = (uint32_t)word;
           there = there && (uint32_t)(word >> 32) == kMailMark;
         }
@@ -1454,14 +1445,9 @@ __device__ __forceinline__ void step_row(const StepArgs& a, unsigned char* smem_
         if (win.v < 0) win = no_best();
       }
       if (__builtin_amdgcn_ballot_w64(!there) != 0) return;
-      // all of the row's bytes of the workspace, whatever of them this launch has used; sixteen lanes a plane: two stores, unless a
-      // caller forces more than eight chunks (after the row's own results they would hold up the end of the launch: 0.2 us)
-#pragma unroll
-      for (int i = 0; i < kPlaneCount; i += 4) {
-        unsigned long long* const plane = row_mail - (size_t)(i + (lane >> 4)) * a.mail_plane;
-        for (int k = (lane & 15) * 2; k < a.mail_row; k += 32) *(u32x4*)(plane + k) = u32x4{0u, 0u, 0u, 0u};
-      }
-      if (lane == 0) a.row_words[row] = 0;
+      // all of the row's bytes of the workspace: sixteen to a lane, one store unless a caller forces more than sixteen chunks
+      // (behind the row's own results they would hold up the end of the launch: 0.2 us)
+      for (int k = lane * 2; k < nch * kMailRoom; k += 2 * kWave) *(u32x4*)(row_mail + k) = u32x4{0u, 0u, 0u, 0u};
       sums = merge_sums<Entropy, false>(a, m_c, S_c, Sw_c);  // the chunks' sums are relative to their own maxima
       m = sums.m;
       S = sums.S;
@@ -2265,13 +2251,7 @@ int launch_math_errors(float* out, hipStream_t stream) {
 // per row, meant to make rows that are done cost a claim instead of a workgroup: 512 device-scope
 // atomics on one address take 50 ns each, and a launch of B = 1024 live rows went from 56 to 82 us.)
 
-// 8 bytes per row first (256-byte aligned size), then the planes of the mail (StepArgs), the last one first
-size_t step_workspace_layout(int64_t B, int places, size_t* last_plane) {
-  const size_t head = (((size_t)B * sizeof(unsigned long long)) + 255) & ~(size_t)255;
-  const size_t plane = (size_t)B * (size_t)places * 4 * sizeof(unsigned long long);
-  if (last_plane) *last_plane = head + (kPlaneCount - 1) * plane;
-  return head + kPlaneCount * plane;
-}
+size_t step_workspace(int64_t B, int chunks) { return (size_t)B * (size_t)chunks * kMailRoom * sizeof(unsigned long long); }
 
 constexpr int64_t kEightWavesFrom = 256;
 constexpr int kComputeUnits = 256;
@@ -2300,10 +2280,9 @@ constexpr int kComputeUnits = 256;
 //   401 to 512 rows: V = 140000, B = 480: 54.9 -> 57.2 in 2 chunks, 59.0 in 3; 512: 56.1 -> 59.1, 63.8: not split.
 //   513 to 640 rows of f32 from 512 KB on (more rows than two a compute unit), 2 chunks: V = 131500: B = 513: 66.5 -> 61.0,
 //     570: 76.0 -> 68.4; V = 150001, B = 640: 88.4 -> 81.7.  bf16 V = 150001, B = 320: 30.3 -> 29.8, 512: 34.9 -> 40.8: not split.
-// These lines, and how many places a row has in the workspace for it (4 or 8 up to 64 rows, then 2 or 3, as the chunks above), were
-// drawn with a search and a combine that took twice as long.  Into how many chunks a row goes was measured again since (a place
-// has room for four): as many as give every compute unit one of 8 waves, as long as that is 3, 4, 8 or 16 to a row, or two
-// of them where that takes 5.  us per launch, chunks before -> now, with log-probabilities / without:
+// These lines were drawn with a search and a combine that took twice as long.  Into how many chunks a row goes was measured again
+// since: as many as give every compute unit one of 8 waves, as long as that is 3, 4, 8 or 16 to a row, or two of them where
+// that takes 5.  us per launch, chunks before -> now, with log-probabilities / without:
 //   16 of 8 waves up to 16 rows: f32 V = 150001: B = 1: 10.7 -> 9.3 / 9.9 -> 8.9, 4: 10.5 -> 9.7 / 9.8 -> 9.1, 16: 10.3 -> 9.8 / 9.7 -> 9.3 (32 of 4
 //     waves, B = 4: 10.1); bf16 V = 152064, B = 1: 10.8 -> 9.4 / 9.6 -> 8.9, 16: 11.4 -> 9.8 / 9.9 -> 9.1
 //   8 of 8 waves from 17 to 32: f32 V = 150001, B = 32: 13.2 -> 11.4 / 12.6 -> 10.7; bf16 V = 201000, B = 32: 12.3 -> 10.7
@@ -2314,29 +2293,28 @@ constexpr int kComputeUnits = 256;
 //     44.5 -> 46.8, and V = 131072, B = 320: 37.3 -> 38.1.
 // A chunk of bf16 beyond 32 rows is streamed by 16 waves (at temperature 1.0, V = 152064, B = 64: 8 waves 7 % slower), every other by 8.
 struct RowSplit {
-  int chunks, waves, places;
+  int chunks, waves;
 };
 
 RowSplit own_split(int dt, int64_t B, int64_t V) {
   const bool bf16 = dt == ESPO_BF16;
   const int64_t row_bytes = V * (bf16 ? 2 : 4);
   constexpr int64_t kKB = 1024, kVeryLong = 512 * kKB;
-  constexpr RowSplit whole{1, 0, 0};
+  constexpr RowSplit whole{1, 0};
   if (B <= 64) {
     if (row_bytes < (!bf16 && B <= 32 ? 384 * kKB : 256 * kKB)) return whole;
-    const int places = B <= 16 && row_bytes >= kVeryLong ? 8 : 4;
-    if (B <= 32) return RowSplit{B <= 16 ? 16 : 8, 8, places};
-    return RowSplit{4, bf16 ? 16 : 8, places};
+    if (B <= 32) return RowSplit{B <= 16 ? 16 : 8, 8};
+    return RowSplit{4, bf16 ? 16 : 8};
   }
   if (B <= 128) {
     if (bf16 ? row_bytes < 288 * kKB : row_bytes <= 256 * kKB) return whole;
-    if (B <= kComputeUnits / 3) return RowSplit{3, bf16 ? 16 : 8, 2};
-    if (!bf16 && B <= 2 * kComputeUnits / 5) return RowSplit{5, 8, 2};
-    return RowSplit{2, bf16 ? 16 : 8, 2};
+    if (B <= kComputeUnits / 3) return RowSplit{3, bf16 ? 16 : 8};
+    if (!bf16 && B <= 2 * kComputeUnits / 5) return RowSplit{5, 8};
+    return RowSplit{2, bf16 ? 16 : 8};
   }
   if (!bf16 && row_bytes >= kVeryLong) {
-    if (B > 256 && B <= 400) return RowSplit{B <= 5 * kComputeUnits / 4 && row_bytes >= 576 * kKB ? 4 : 3, 8, 3};
-    if (B > 512 && B <= 640) return RowSplit{2, 8, 2};
+    if (B > 256 && B <= 400) return RowSplit{B <= 5 * kComputeUnits / 4 && row_bytes >= 576 * kKB ? 4 : 3, 8};
+    if (B > 512 && B <= 640) return RowSplit{2, 8};
   }
   return whole;
 }
@@ -2346,16 +2324,14 @@ StepPlan plan_step(int dt, int64_t B, int64_t V, bool filter, int waves, int chu
   const int ntiles = (int)((V + kTile - 1) / kTile);
   p.waves = waves > 0 ? waves : B >= kEightWavesFrom ? 8 : 16;
   int nch = filter || chunks <= 0 ? 1 : chunks;
-  p.places = 0;
   if (!filter && waves <= 0 && chunks <= 0) {
     const RowSplit own = own_split(dt, B, V);
     nch = own.chunks;
-    if (nch > 1) p.waves = own.waves, p.places = own.places;  // (at least 128 tiles: as many chunks as it says)
+    if (nch > 1) p.waves = own.waves;
   }
   if (nch > ntiles) nch = ntiles;
   if (nch > kMaxChunks) nch = kMaxChunks;
   p.chunks = nch;
-  if (p.places == 0) p.places = nch;
   const int ctiles = (ntiles + nch - 1) / nch;
   auto lds = [&](int w) {
     const size_t tables = step_lds_bytes(dt, ctiles, filter, w);
@@ -2366,7 +2342,7 @@ StepPlan plan_step(int dt, int64_t B, int64_t V, bool filter, int waves, int chu
   };
   p.lds = lds(p.waves);
   if (filter && waves <= 0 && p.lds > kMaxStepLds) p.lds = lds(p.waves = 8);  // the widest vocabularies: 8 waves need less
-  p.workspace = nch > 1 ? step_workspace_layout(B, p.places, nullptr) : 0;
+  p.workspace = nch > 1 ? step_workspace(B, nch) : 0;
   return p;
 }
 
@@ -2412,18 +2388,7 @@ int launch_step(const void* logits, int dt, int64_t B, int64_t V, int64_t row_st
   a.nch = plan.chunks;
   a.chunk_tiles = a.ntiles / plan.chunks;
   a.chunk_extra = a.ntiles % plan.chunks;
-  a.row_words = a.mail = nullptr;
-  a.mail_plane = 0;
-  a.mail_row = a.part_shift = 0;
-  if (plan.chunks > 1) {
-    size_t last_plane = 0;
-    step_workspace_layout(B, plan.places, &last_plane);
-    a.row_words = (unsigned long long*)workspace;
-    a.mail = (unsigned long long*)((char*)workspace + last_plane);
-    a.mail_row = plan.places * 4;
-    a.mail_plane = (size_t)B * (size_t)a.mail_row;
-    while ((plan.places << a.part_shift) < plan.chunks) ++a.part_shift;  // at most kPartsShift: plan_step
-  }
+  a.mail = plan.chunks > 1 ? (unsigned long long*)workspace : nullptr;
 
   // the entropy output costs two more vector operations per logit: its own instantiation
   // and so does a filtered draw (more passes over the row)

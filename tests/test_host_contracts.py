@@ -216,18 +216,22 @@ def test_tensor_checks_of_the_binding(monkeypatch, make, kw, err):
             b._dev(t, torch.float32, "thing", **kw)
 
 
-# espo_step_workspace_bytes says where the library splits the rows of a plain draw itself: both sides of every line of that rule.
+# espo_step_workspace_bytes says where the library splits the rows of a plain draw itself, and into how many workgroups each: both
+# sides of every line of that rule.
 @pytest.mark.parametrize("dtype,B,V,chunks", [
-    (torch.bfloat16, 1, 131071, 1), (torch.bfloat16, 1, 131072, 4), (torch.bfloat16, 64, 131071, 1), (torch.bfloat16, 64, 131072, 4),
-    (torch.bfloat16, 16, 262143, 4), (torch.bfloat16, 16, 262144, 8), (torch.bfloat16, 17, 262144, 4), (torch.bfloat16, 65, 147455, 1),
-    (torch.bfloat16, 65, 147456, 2), (torch.bfloat16, 128, 400000, 2), (torch.bfloat16, 129, 400000, 1), (torch.bfloat16, 300, 400000, 1),
-    (torch.float32, 1, 98303, 1), (torch.float32, 1, 98304, 4), (torch.float32, 32, 98303, 1), (torch.float32, 32, 98304, 4),
-    (torch.float32, 33, 65535, 1), (torch.float32, 33, 65536, 4), (torch.float32, 16, 131071, 4), (torch.float32, 16, 131072, 8),
-    (torch.float32, 17, 131072, 4), (torch.float32, 64, 65536, 4), (torch.float32, 65, 65536, 1), (torch.float32, 65, 65537, 2),
-    (torch.float32, 128, 200000, 2), (torch.float32, 129, 200000, 1), (torch.float32, 256, 200000, 1), (torch.float32, 257, 131071, 1),
-    (torch.float32, 257, 131072, 3), (torch.float32, 400, 131072, 3), (torch.float32, 401, 200000, 1), (torch.float32, 512, 200000, 1),
-    (torch.float32, 513, 131071, 1), (torch.float32, 513, 131072, 2), (torch.float32, 640, 131072, 2), (torch.float32, 641, 200000, 1),
-    (torch.float32, 0, 131072, 1), (torch.float32, 4, 400001, 1)])
+    (torch.bfloat16, 1, 131071, 1), (torch.bfloat16, 1, 131072, 16), (torch.bfloat16, 16, 131072, 16), (torch.bfloat16, 17, 131072, 8),
+    (torch.bfloat16, 32, 131072, 8), (torch.bfloat16, 33, 131072, 4), (torch.bfloat16, 64, 131071, 1), (torch.bfloat16, 64, 131072, 4),
+    (torch.bfloat16, 16, 262144, 16), (torch.bfloat16, 17, 262144, 8), (torch.bfloat16, 65, 147455, 1), (torch.bfloat16, 65, 147456, 3),
+    (torch.bfloat16, 85, 147456, 3), (torch.bfloat16, 86, 147456, 2), (torch.bfloat16, 102, 147456, 2), (torch.bfloat16, 128, 400000, 2),
+    (torch.bfloat16, 129, 400000, 1), (torch.bfloat16, 300, 400000, 1),
+    (torch.float32, 1, 98303, 1), (torch.float32, 1, 98304, 16), (torch.float32, 32, 98303, 1), (torch.float32, 32, 98304, 8),
+    (torch.float32, 33, 65535, 1), (torch.float32, 33, 65536, 4), (torch.float32, 16, 131072, 16), (torch.float32, 17, 131072, 8),
+    (torch.float32, 64, 65536, 4), (torch.float32, 65, 65536, 1), (torch.float32, 65, 65537, 3), (torch.float32, 85, 65537, 3),
+    (torch.float32, 86, 65537, 5), (torch.float32, 102, 65537, 5), (torch.float32, 103, 65537, 2), (torch.float32, 128, 200000, 2),
+    (torch.float32, 129, 200000, 1), (torch.float32, 256, 200000, 1), (torch.float32, 257, 131071, 1), (torch.float32, 257, 131072, 3),
+    (torch.float32, 320, 147455, 3), (torch.float32, 320, 147456, 4), (torch.float32, 321, 147456, 3), (torch.float32, 400, 131072, 3),
+    (torch.float32, 401, 200000, 1), (torch.float32, 512, 200000, 1), (torch.float32, 513, 131071, 1), (torch.float32, 513, 131072, 2),
+    (torch.float32, 640, 131072, 2), (torch.float32, 641, 200000, 1), (torch.float32, 0, 131072, 1), (torch.float32, 4, 400001, 1)])
 def test_shapes_that_the_library_splits(dtype, B, V, chunks):
     import paper_2605_29860_amd as espo
     assert espo.espo_step_workspace_bytes(B, V, dtype) == espo.espo_debug_step_workspace_bytes(B, chunks)
