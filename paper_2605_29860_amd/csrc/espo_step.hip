@@ -380,7 +380,7 @@ __device__ __forceinline__ void finish_row(const StepArgs& a, int row, const voi
 }
 
 // ---------------------------------------------------------------- shared memory
-// Blocks are named by their index q in the row everywhere (survivor lists, own, visq); the
+// Blocks are named by their index q in the row everywhere (survivor lists, own); the
 // per-block tables only cover the workgroup's chunk and are reached through the accessors, which
 // subtract q0, the chunk's first block (a multiple of 8).
 struct StepShared {
@@ -403,7 +403,6 @@ struct StepShared {
   int* res_v;
   float* res_x;
   float* lo;        // [W] score each wave knows to be attained
-  int* visq;        // [W] block each wave scored before the first barrier of the search in double, or -1
   int* own;         // [W][8] blocks that a wave has to read again
   float* fres;      // [W][8] per-wave results of the fp32 search: s, e, x, hi2, v
   int32_t* cand_v;  // [kCandCap] long survivor lists: indices that can still win ...
@@ -433,7 +432,6 @@ __device__ __forceinline__ StepShared carve(unsigned char* base, int nslots, int
   s.res_v = (int*)take(kStepWaves * 4);
   s.res_x = (float*)take(kStepWaves * 4);
   s.lo = (float*)take(kStepWaves * 4);
-  s.visq = (int*)take(kStepWaves * 4);
   s.own = (int*)take(kSlots * 4);
   s.fres = (float*)take(8 * kStepWaves * 4);
   s.cand_v = (int32_t*)take(kCandCap * 4);
@@ -451,7 +449,7 @@ __device__ __forceinline__ StepShared carve(unsigned char* base, int nslots, int
 [[maybe_unused]] size_t step_lds_bytes(int dt, int ntiles, bool filter, int waves) {
   const size_t esz = dt == ESPO_BF16 ? 2 : 4;
   const size_t nslots = (size_t)ntiles * kGroups, slots = (size_t)waves * kGroups;
-  return 2 * (size_t)waves * 8 + slots * kDrawBlock * esz + slots * 4 + 16 * (size_t)waves * 4 + 16 + 2 * kCandCap * 4 +
+  return 2 * (size_t)waves * 8 + slots * kDrawBlock * esz + slots * 4 + 15 * (size_t)waves * 4 + 16 + 2 * kCandCap * 4 +
          ((nslots * 8 + 15) & ~(size_t)15) + (filter ? 2 : 1) * ((nslots * 4 + 15) & ~(size_t)15);
 }
 
@@ -463,9 +461,6 @@ __device__ __forceinline__ float ub_rounded_up(float u) { return fmaf(fabsf(u), 
 // filtered; then only if its largest logit is above the floor.
 __device__ __forceinline__ bool holds_eligible(const StepShared& sh, int q) { return sh.bmx == nullptr || sh.blockmax(q) > sh.floor; }
 
-// Wave that streamed block q in phase 1.
-template <int W>
-__device__ __forceinline__ int wave_of(const StepShared& sh, int q) { return ((q - sh.q0) >> 3) & (W - 1); }
 // ---------------------------------------------------------------- phase 2
 // Lanes below this one whose bit is set in `mask`.
 __device__ __forceinline__ int rank_below(uint64_t mask) {
@@ -513,57 +508,32 @@ __device__ __forceinline__ Search<F> combine_search(const StepShared& sh, Search
   return all;
 }
 
-// Finds the argmax over the row in precision F.  `bound0` is a score that is known to be
-// attained or exceeded (prunes from the start); `q_own` is the block this wave scores
-// first, without waiting for the others (or -1).  Every block whose bound reaches the best
-// score found that way is then scored, one block per wave visit.  Returns the winner, the same in every thread; all threads of
+// Finds the argmax over the row in double.  `bound` is a score that is known to be attained or exceeded: every block whose own bound
+// reaches it is scored, one block per wave visit.  Returns the winner, the same in every thread; all threads of
 // the workgroup must call it.
-template <int DT, typename F, int W>
-__device__ __forceinline__ Search<F> find_argmax(const StepArgs& a, const StepShared& sh, const void* rowp, int row,
-                                                 int nslots, int q_own, F bound0) {
-  constexpr int kStepWaves = W, kStepThreads = W * kWave;
+template <int DT, int W>
+__device__ __forceinline__ Search<double> find_argmax(const StepArgs& a, const StepShared& sh, const void* rowp, int row,
+                                                      int nslots, double bound) {
   const int tid = threadIdx.x;
-  const int lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  Search<F> st;
-  st.init();
-  F bound = bound0;
-  int q = q_own, k = wave, nsurv = 0;
-  bool first = true;
-#pragma unroll 1
-  while (true) {  // one visit site for the wave's own block and for the survivors
-    if (q >= 0) {
-      visit_block<DT, F>(a, row, q, (const char*)rowp + (size_t)q * kDrawBlock * elem_bytes<DT>(), bound, sh.floor, st);
-      const float lo = wave_max(round_down_f32(st.lower()));  // best score this wave has seen, rounded down
-      bound = bound > (F)lo ? bound : (F)lo;
-    }
-    if (first) {
-      first = false;
-      if (lane == 0) {
-        sh.lo[wave] = round_down_f32(bound);  // rounded down: a shared bound must never overshoot
-        sh.visq[wave] = q_own;
-      }
-      if (tid == 0) *sh.nsurv = 0;
-      __syncthreads();
-      float bound_f = sh.lo[0];
-#pragma unroll
-      for (int w = 1; w < kStepWaves; ++w) bound_f = fmaxf(bound_f, sh.lo[w]);
-      // blocks whose bound reaches the best score found so far
-      for (int b = sh.q0 + tid; b < sh.q0 + nslots; b += kStepThreads) {
-        const float u = sh.ub(b);
-        if (u > kMaskedBelow && ub_rounded_up(u) >= bound_f && sh.visq[wave_of<W>(sh, b)] != b && holds_eligible(sh, b))
-          sh.surv(atomicAdd(sh.nsurv, 1)) = b;
-      }
-      __syncthreads();
-      nsurv = *sh.nsurv;
-      bound = bound > (F)bound_f ? bound : (F)bound_f;
-    } else {
-      k += kStepWaves;
-    }
-    if (k >= nsurv) break;
-    q = sh.surv(k);
+  if (tid == 0) *sh.nsurv = 0;
+  __syncthreads();
+  const float bound_f = round_down_f32(bound);
+  for (int b = sh.q0 + tid; b < sh.q0 + nslots; b += W * kWave) {
+    const float u = sh.ub(b);
+    if (u > kMaskedBelow && ub_rounded_up(u) >= bound_f && holds_eligible(sh, b)) sh.surv(atomicAdd(sh.nsurv, 1)) = b;
   }
-  return combine_search<F, W>(sh, st);
+  __syncthreads();
+  const int nsurv = *sh.nsurv;
+  Search<double> st;
+  st.init();
+#pragma unroll 1
+  for (int k = wave; k < nsurv; k += W) {
+    const int q = sh.surv(k);
+    visit_block<DT, double>(a, row, q, (const char*)rowp + (size_t)q * kDrawBlock * elem_bytes<DT>(), bound, sh.floor, st);
+    bound = fmax(bound, (double)wave_max(round_down_f32(st.lower())));  // best score this wave has seen, rounded down
+  }
+  return combine_search<double, W>(sh, st);
 }
 
 // ---------------------------------------------------------------- phase 2 in fp32
@@ -1244,7 +1214,7 @@ __device__ __forceinline__ void step_row(const StepArgs& a, unsigned char* smem_
       Search<double> exact;
       if (!exact_among_candidates<DT, W>(a, shx, rowp, row, nslots, fast.s - fast.e, exact)) {
         __syncthreads();
-        exact = find_argmax<DT, double, W>(a, shx, rowp, row, nslots, -1, (double)fast.s - (double)fast.e);
+        exact = find_argmax<DT, W>(a, shx, rowp, row, nslots, (double)fast.s - (double)fast.e);
       }
       tok = exact.best.v;
       x_a = exact.best.x;
@@ -1296,7 +1266,7 @@ __device__ __forceinline__ void step_row(const StepArgs& a, unsigned char* smem_
           acc_n += above ? 1.0f : 0.0f;  // counts stay exact in fp32: V < 2^24
         }
       };
-      constexpr int kLoads = 4, kDeep = DT == ESPO_F32 ? 5 : 6;  // (with 6 of fp32 two registers go to scratch)
+      constexpr int kLoads = 4, kDeep = DT == ESPO_F32 ? 5 : 6;  // (with 6 of fp32 a register goes to scratch)
       if (3 * nabove <= 2 * nslots) {
         // the listed blocks only, laid out as in phase 1: a lane group of 8 lanes per block, 16 bytes per lane
         const uint32_t sub = (uint32_t)(lane & 7) * 8u;
@@ -1474,8 +1444,9 @@ __device__ __forceinline__ void step_row(const StepArgs& a, unsigned char* smem_
 }
 
 template <int DT, bool Entropy, bool Sum, int W>
-// Registers: workgroups of 8 waves get up to 80 (three of them fit on a compute unit, in registers and in LDS) and use 77
-// without spilling; one of 16 waves, which has a compute unit to itself (plan_step), up to 128.
+// Registers: workgroups of 8 waves get up to 80 (three of them fit on a compute unit, in registers and in LDS) and use 73;
+// one of 16 waves, which has a compute unit to itself (plan_step), may have 128 and uses 73 too.  Workgroups of 4 waves, which
+// the diagnostics entry point alone launches, are held to 64 and keep some 15 registers in scratch.
 __global__ __launch_bounds__(W * kWave, W == 8 ? 6 : W == 16 ? 4 : 8) void espo_step_kernel(StepArgs a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   step_row<DT, Entropy, false, Sum, W>(a, smem_raw);
@@ -2146,7 +2117,7 @@ __device__ __forceinline__ bool filtered_row(const StepArgs& a, unsigned char* s
 }
 
 template <int DT, bool Entropy, int W>
-// Registers: 120 per lane (fp32 127) of at most 128, none in scratch: two workgroups of 8 waves on a compute unit or one of 16.  With the
+// Registers: 118 per lane (fp32 125) of at most 128, none in scratch: two workgroups of 8 waves on a compute unit or one of 16.  With the
 // search's bounds read ahead, addresses kept over its rounds and six fp32 loads in flight it was 128 and 12 to 36 bytes of scratch
 // (us, fp32 normal logits, top-p 0.9, V = 152064, B = 64: 114 -> 99; 256: 139 -> 125; synthetic rows at temperature 1.3, B = 64: 115 -> 105).
 __global__ __launch_bounds__(W * kWave, 4) void espo_filtered_kernel(StepArgs a) {
