@@ -87,6 +87,7 @@ constexpr int64_t kAdvSortTokens = 4608;
 constexpr int kAdvSyncStride = 32;       // words
 constexpr size_t kAdvSyncBytes = 256;
 constexpr int64_t kAdvOnePerUnit = 256;  // rows: one for every compute unit at most
+constexpr int64_t kAdvFiveArrays = 13824;  // twice the mean length
 constexpr int kOrderClasses = 256;
 
 __device__ __forceinline__ int class_of_length(int64_t L, int64_t T) {  // class 0 is the longest
@@ -903,10 +904,13 @@ int launch_advantages(const float* rewards, const float* terminal_reward, const 
   const bool sort_here = can_sort && a.ordered_from < B;
   a.sorted = sort_here ? sorted : nullptr;
   a.sync = sort_here ? sync : nullptr;
-  // Two spans a wave where every compute unit has more than one row, unless three arrays of long rows are written
-  // (targets, T = 16383: 512 rows back to back 23.0 us with 16 waves, 23.8 with 8; terminal rewards, padding filled 30.3, 30.6); fewer
-  // rows have the chip to themselves, and more waves walk each faster (8 rows of 16384: 7.7 us, with 8 waves 8.0).
-  const int waves = shortrows ? 4 : B <= kAdvOnePerUnit || (returns && longest > 3 * kAdvSortTokens) ? 16 : 8;
+  // Two spans a wave where every compute unit has more than one row; fewer have the chip to themselves, and more waves walk each
+  // faster (8 rows of 16384: 7.7 us, with 8 waves 8.0).  Long rows back to back with rewards and targets, five arrays, are as fast or faster
+  // with 16 waves (us, 16 waves / 8, lengths U[T / 16, T]: T = 16384: 300 rows 19.5 / 20.3, 512 23.2 / 24.2, 1024 37.5 / 37.9; whole rows of
+  // 8192: 257 10.1 / 10.1, 320 10.9 / 11.2; but mean length 6144: 384 rows 11.4 / 10.4).  No other form is (targets of terminal rewards, U[1024, 16384],
+  // 512 rows: padded 21.7 / 19.0, filled 26.0 / 25.7, back to back 20.7 / 19.5).
+  const bool five = cu && rewards && returns;
+  const int waves = shortrows ? 4 : B <= kAdvOnePerUnit || (five && longest > kAdvFiveArrays) ? 16 : 8;
   const int64_t tile = (shortrows ? 4 : 16) * kWaveTokens;
   const bool fillers = cu == nullptr && zero_padding && longest > tile;
   const dim3 grid((unsigned)((fillers ? 2 * B : B) + (sort_here ? 1 : 0))), block(waves * kWave);

@@ -364,8 +364,8 @@ def test_packed_config5_full_size():
     _say(f"  terminal form: worst scaled error {worst:.2e}")
 
 
-# From 257 rows on a workgroup of 8 waves walks a row, two spans of 256 tokens of a tile of 4096 to a wave (16 waves where three arrays
-# of rows beyond 13824 tokens are written): both sides of these lines, lengths at the edges of spans, of a wave's first and second one, and of tiles.
+# From 257 rows on a workgroup of 8 waves walks a row, two spans of 256 tokens of a tile of 4096 to a wave: both sides of that line, with
+# and without targets, lengths at the edges of spans, of a wave's first and second one, and of tiles.
 @pytest.mark.parametrize("B,T", [(256, 8192), (257, 8192), (257, 8195), (513, 4612), (257, 4097), (257, 13824), (257, 13828)])
 @pytest.mark.parametrize("gamma,lam", [(1.0, 0.95), (0.999, 0.9995)])
 def test_rows_walked_by_two_spans_a_wave(B, T, gamma, lam):
@@ -378,6 +378,17 @@ def test_rows_walked_by_two_spans_a_wave(B, T, gamma, lam):
     for fill, returns in ((True, True), (False, True), (False, False)):
         H.check_advantages_terminal(v, Lt, s, term, -1.0, gamma, lam, zero_padding=fill, want_returns=returns)
     _check_packed_both_forms([max(n - b % 3, 0) for b, n in enumerate(L)], seed=T, gamma=gamma, lam=lam)
+
+
+# Back to back with rewards and targets, 16 waves walk a row again beyond a mean length of 6912: both sides of that line.
+@pytest.mark.parametrize("mean", [6912, 6913])
+def test_packed_rewards_and_targets_of_long_trajectories(mean):
+    _say(f"[case] packed advantages with rewards and targets, mean length {mean}")
+    lens = [mean + (-1) ** b * (b // 2 * 47) for b in range(256)] + [mean]
+    assert sum(lens) // len(lens) == mean
+    v, r, starts, s, term = _packed(lens, seed=mean)
+    cu = torch.tensor(starts + [starts[-1] + lens[-1]], dtype=torch.int64).cuda()
+    H.check_advantages_packed(v, cu, s, -1.0, 1.0, 0.95, rewards=r, want_returns=True)
 
 
 @pytest.mark.parametrize("part", range(4))
