@@ -20,7 +20,7 @@ extern "C" {
  *                       huge value sends every row through the double-precision search).  The
  *                       sampled token does not depend on it.  ESPO_EINVAL below 1 or for NaN.
  *   waves               wavefronts per workgroup: 4, 8 or 16, or 0 for the library's choice (16; 8 from
- *                       256 rows on, and for the chunks of split fp32 rows).
+ *                       256 rows on, and for the chunks of split rows, of bf16 rows up to a batch of 32).
  *   chunks              workgroups a row is split over, or 0 for the library's choice (1 if `waves` is
  *                       given; else as espo_step, workspace included).  With
  *                       more than one, every workgroup streams a run of 512-index tiles of its row,

@@ -40,8 +40,8 @@
 namespace espo {
 namespace {
 
-// A workgroup has W wavefronts (a template parameter of everything below that depends on it): 16 when
-// one workgroup owns a whole row, 4 when a row is split into chunks that several workgroups stream.
+// A workgroup has W wavefronts (a template parameter of everything below that depends on it): 16 or 8 (plan_step), or 4
+// where a caller of the diagnostics entry point forces them.
 constexpr int kTile = 512;                        // indices per wave iteration
 constexpr int kGroups = kTile / kDrawBlock;       // draw blocks per tile = lane groups per wave
 constexpr int kMaxChunks = 64;                    // a row is split over at most this many workgroups (one lane each in the combine)
@@ -785,6 +785,9 @@ __device__ __forceinline__ Best merge_waves(const float* fres) {
 // barrier, and the lane that holds a wave's best hands it on itself.  us per launch from a graph, before -> now, V = 152064 bf16,
 // all rows live: B = 1: 11.5 -> 10.2, 64: 14.0 -> 12.8 (both with the cheaper combine of step_row), 512: 34.5 -> 33.2,
 // 1024: 59.4 -> 57.5; at temperature 1.0 / 1.3, B = 512: 39.7 -> 36.5 / 65.3 -> 37.6; all logits equal, B = 512: 32.9 -> 32.3.
+// Short rows of flat logits pay for it, 0.3 to 0.6 us: their best block is looked at a second time, behind the barrier (means over 60 steps, all logits equal,
+// B = 1, V = 8000: 6.3 -> 6.7; 255, 32000: 8.2 -> 8.7; normal logits at temperature 3, 255, 32000: 8.4 -> 9.2).  (Leaving out there, or in the branch for several
+// indices a lane, what cannot beat the index that received M_q: 3 to 5 % slower on all other rows.)
 // Returns the wave-uniform result, the same in every wave; all threads of the workgroup must call it.
 template <int DT, bool Filter, int W>
 __device__ __forceinline__ Best fast_argmax(const StepArgs& a, const StepShared& sh, const void* rowp, int row, int my_tiles,
@@ -1474,8 +1477,8 @@ __global__ __launch_bounds__(W * kWave, W == 8 ? 6 : W == 16 ? 4 : 8) void espo_
 // Bound by the streaming like the plain draw: B = 512, V = 152064 bf16, us per launch, against a
 // search for the edge that read the row's blocks again after a trial floor: top-p 0.7 at temperature
 // 0.6 / 0.8 / 1.0: 35.0 / 34.8 / 35.6 (44.1 / 48.7 / 67.3), top-k 50 at 1.0: 35.3 (48.8), the plain
-// draw at 1.0: 36.4.  B = 100, V = 50003, top-k 50: 13.6 (24.9).  What is left after the last tile is
-// five barriers, 7 to 8 us of a workgroup.  The lists' room is what two workgroups of 8 waves on a
+// draw at 1.0: 36.4 (now 32.2 / 32.2 / 36.1, 32.5, the plain draw 33.7).  B = 100, V = 50003, top-k 50: 13.6 (24.9; now 12.3).  What is
+// left after the last tile is five barriers: sums, bins, edge, kept logits, scores.  The lists' room is what two workgroups of 8 waves on a
 // compute unit leave (73 KB of LDS each); 16 waves are used below 256 rows (13.6 against 16.0 us there).
 constexpr int kKeptCap2 = 3072, kEdgeBins = 256, kEdgeMembers = 256;
 constexpr int32_t kInDoubt = 1 << 30;  // on top of an index whose membership of the kept set fp32 cannot tell
@@ -2204,18 +2207,18 @@ int launch_math_errors(float* out, hipStream_t stream) {
 
 // ---------------------------------------------------------------- launch configuration
 // How a call is laid out on the GPU.  Unless it is split (own_split below), one workgroup streams a row: 8 waves, three
-// workgroups to a compute unit, from 256 rows on; 16 waves, two to a compute unit, for smaller batches, where a
-// compute unit has one row at most and more waves stream it faster (B = 128: 17.0 against 18.5 us).
-// With every row live the two are within 1 us of each other from B = 256 to 4096; with rows that are
-// done in the batch the smaller workgroups are 2 to 5 us faster (B = 1024 with 431 live rows: 36.8
-// against 41.7 us; B = 512 with 446: 30.6 against 32.9): workgroups are dispatched in order, and with
-// only 512 slots live rows further back in the batch wait for one (timestamps: a tenth of them start
-// more than 8 us late); with 768 slots all have started within 4 us.  A filtered draw has the same two sizes, with
-// twice the registers per wave, so half as many workgroups to a compute unit.  The diagnostics
+// workgroups to a compute unit, from 256 rows on; 16 waves for smaller batches, where a compute unit has one row at most and more
+// waves stream it faster.  A workgroup of 16 waves has a compute unit to itself, and by the library's choice a launch never has more of
+// them than there are compute units (255 whole rows, 64 in 4 chunks, 85 in 3, 128 in 2): from 257 on the others would be a second generation.
+// us, 16 waves / 8, V = 152064 bf16, at temperature 0.6 | with the entropy at 1.0: 128 rows 16.1 / 16.9 | 19.9 / 22.6, 200: 16.5 / 17.0 | 20.5 / 23.2, 255: 18.1 / 17.7 |
+// 21.1 / 23.5, 256: 19.2 / 17.5 | 20.9 / 23.2; 257: 28.1 / 23.2 | 32.4 / 28.2, 512: 36.3 / 29.3 | 38.3 / 34.0, 1024: 68.0 / 53.4 | 74.2 / 62.7; V = 32000: 200: 9.8 / 10.1 | 11.2 / 13.1,
+// 300: 16.0 / 11.9 | 18.2 / 14.9; fp32 V = 100000: 128: 21.4 / 21.8, 255: 24.2 / 24.1, 257: 37.3 / 33.0.  With half of the rows done it is the live ones that
+// count (300 rows: 15.9 / 23.5, 400: 28.0 / 23.9, 1024: 54.2 / 36.3), which the host does not know.  A filtered draw has the same two sizes,
+// with more registers per wave: two workgroups of 8 waves to a compute unit.  The diagnostics
 // entry point can force the waves per workgroup and a split of every row into `chunks` runs of
 // tiles, each streamed by a workgroup of its own and combined by the one that finds all results there.  Where all compute
-// units have rows enough, no split pays (B = 512, V = 152064 bf16, all rows live): 34.7 us unsplit, 41 us in 2 chunks
-// of 16 waves, 39.6 us in 2 chunks of 8 waves, 53 us in 8 chunks of 4 waves: every chunk pays for a search of its
+// units have rows enough, no split pays (B = 512, V = 152064 bf16, all rows live): 30.8 us unsplit, 45.7 us in 2 chunks
+// of 16 waves, 36.0 us in 2 chunks of 8 waves, 38.9 us in 8 chunks of 4 waves (which keep some registers in scratch): every chunk pays for a search of its
 // own and the row for two more trips through memory (a chunk's result written, then all of them read), which is
 // more than the finer grain gains.  (Also measured and left out:
 // 512 resident workgroups that claim rows from a counter in the workspace instead of one workgroup
@@ -2255,13 +2258,16 @@ constexpr int kComputeUnits = 256;
 // since: as many as give every compute unit one of 8 waves, as long as that is 3, 4, 8 or 16 to a row, or two of them where
 // that takes 5.  us per launch, chunks before -> now, with log-probabilities / without:
 //   16 of 8 waves up to 16 rows: f32 V = 150001: B = 1: 10.7 -> 9.3 / 9.9 -> 8.9, 4: 10.5 -> 9.7 / 9.8 -> 9.1, 16: 10.3 -> 9.8 / 9.7 -> 9.3 (32 of 4
-//     waves, B = 4: 10.1); bf16 V = 152064, B = 1: 10.8 -> 9.4 / 9.6 -> 8.9, 16: 11.4 -> 9.8 / 9.9 -> 9.1
+//     waves, with registers in scratch, B = 4: 10.1); bf16 V = 152064, B = 1: 10.8 -> 9.4 / 9.6 -> 8.9, 16: 11.4 -> 9.8 / 9.9 -> 9.1
 //   8 of 8 waves from 17 to 32: f32 V = 150001, B = 32: 13.2 -> 11.4 / 12.6 -> 10.7; bf16 V = 201000, B = 32: 12.3 -> 10.7
 //   33 to 64: 4 stay (B = 64: bf16 8 of 8 waves 11.6 -> 12.6, f32 14.6 -> 15.4).
-//   3 from 65 to 85: f32 V = 150001, B = 85: 20.6 -> 17.8; bf16 V = 201000, B = 85, 16 waves: 15.7 -> 14.2.  At 96 rows they lose: f32 20.5 -> 24.2.
-//   5 of f32 from 86 to 102: V = 150001, B = 102: 21.1 -> 19.9; V = 100000 at temperature 1.0 19.0 -> 16.8.  bf16 V = 152064: 14.2 -> 14.6: not.
-//   4 of f32 from 257 to 320 (five to a compute unit at most), from 576 KB on: V = 150001: B = 280: 42.2 -> 40.2, 320: 44.2 -> 42.9; but B = 340:
-//     44.5 -> 46.8, and V = 131072, B = 320: 37.3 -> 38.1.
+//   3 from 65 to 85: f32, 2 chunks / 3: V = 66000, B = 65: 13.0 / 11.2, 85: 13.4 / 11.8; 100000, 85: 16.0 / 14.1; 200000, 85: 23.7 / 19.5; but 88 rows: 13.7 / 14.5, 16.1 / 17.8,
+//     23.7 / 26.6.  bf16 V = 201000, B = 85, 16 waves: 15.7 -> 14.2.
+//   5 of f32 from 86 to 102, 2 chunks / 5: B = 102: V = 66000 14.0 / 13.6, 100000 16.4 / 15.8, 150001 20.9 / 19.7, 390000 42.9 / 37.2, with the entropy at temperature 1.0
+//     16.7 / 15.5, 19.4 / 17.9, 24.3 / 22.4, 45.9 / 40.0 (B = 94, V = 66000: 12.8 / 13.3, 16.0 / 15.1); but 104 rows: 13.8 / 14.9, 16.2 / 16.9, 20.7 / 22.6, 42.7 / 46.3.  bf16 V = 152064: 14.2 -> 14.6: not.
+//   4 of f32 from 257 to 320 (five to a compute unit at most), from 576 KB on, 3 chunks / 4: B = 288: V = 147456 39.0 / 37.9, 150001 42.6 / 40.5, 200000 50.5 / 48.5, 390000 104.1 / 100.5;
+//     320: 40.1 / 39.6, 44.1 / 42.6, 52.2 / 50.3, 108.1 / 103.9 (with half of the rows done 30.6 / 31.1, 32.7 / 33.4, 38.2 / 40.0, 78.4 / 72.3); but 336 rows: 40.9 / 43.1, 44.3 / 46.2, 53.0 / 55.7,
+//     and below, B = 320: V = 131072 36.9 / 37.1, with the entropy 39.5 / 40.9, 140000 39.0 / 39.3, 41.7 / 42.5.
 // A chunk of bf16 beyond 32 rows is streamed by 16 waves (at temperature 1.0, V = 152064, B = 64: 8 waves 7 % slower), every other by 8.
 struct RowSplit {
   int chunks, waves;

@@ -14,10 +14,9 @@
 // Positions at t >= L_b are neither read nor written.
 //
 // Bound by memory from some 10 MB on, below that by the two launches' latency (load lengths, load
-// tokens, reduce, store).  us per call, before -> now (before: items of 4096 positions and one
-// workgroup-wide access each, the sums merged before the first load, element-wise accesses for odd T):
-// B = 1024, T = 16384, lengths U[512, T]: 36.7 -> 27.2 (104 MB), from the rows' sums 23.9 -> 18.0 (69 MB,
-// 3.8 TB/s); B = 512, T = 8192: 18.1 -> 14.0; B = 4, T = 128: 9.8 -> 4.1.  The nontemporal accesses stay:
+// tokens, reduce, store).  us per call: B = 1024, T = 16384, lengths U[512, T]: 24.5 (104 MB), from the rows' sums 15.9 (69 MB,
+// 4.4 TB/s); B = 512, T = 8192: 11.6, 7.5; B = 4, T = 128: 4.1 (with items of 4096 positions and one workgroup-wide access each, the sums merged
+// before the first load, element-wise accesses for odd T: 36.7, 23.9, 18.1, 9.8).  The nontemporal accesses stay:
 // plain loads in the first launch take 3 us off the largest batch's second one, but leave the
 // next pass over other arrays 1.2 us slower on the B = 512 batch.  One workgroup against two launches:
 // 6.2 against 9.9 us for 8000 positions, 8.0 against 8.9 for 16384, so the line is there.
