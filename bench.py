@@ -558,7 +558,7 @@ def main() -> int:
     out.update({
         "advantages": {"workload": "B=1024, T=16384 fp32, lengths U[512,16384], 30% stopped, 8 rotated buffer sets",
                        "tokens_per_s": float(valid.sum() / adv_wall), "ms_per_call": adv_wall / args.adv_reps * 1e3,
-                       "roofline": {"kernel": "espo_advantages_kernel", "bound": "hbm", "achieved": adv_gbs,
+                       "roofline": {"kernel": "espo_advantages_spans_kernel", "bound": "hbm", "achieved": adv_gbs,
                                     "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": adv_gbs / HBM_PEAK_GBS,
                                     "avg_launch_us": adv_region_ms / args.adv_reps * 1e3,
                                     "avg_launch_us_event_pair_each": float(adv_ms.mean() * 1e3),
